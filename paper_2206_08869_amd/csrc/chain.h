@@ -1,0 +1,64 @@
+// Launch description of a whole narrow network that one workgroup per group of images runs out of LDS (see chain.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace iodf {
+
+constexpr size_t kChainMaxLds = 160 * 1024;
+constexpr int kChainMaxTiles = 8;  // 32-pixel tiles of a workgroup
+// A workgroup requests up to this many bytes past the end of a layer's weights.
+constexpr size_t kChainOverread = 12 * 1024;
+constexpr int kChainConstBytes = 4 * 128 * (int)sizeof(int32_t);
+
+// Bytes a pixel of a tensor with 32 * nc channels takes in LDS: 16 more than its channels, so that the 16-byte
+// reads of neighbouring pixels touch different banks.
+constexpr unsigned chain_pixel_bytes(int nc) { return nc ? nc * 32 + 16 : 0; }
+// A row of w pixels and two of padding, and an image of hw pixels in `rows` such rows: stretched so that the first
+// pixel of a row (image) lies, modulo the 64 LDS banks, where the pixel behind the last one of the row (image)
+// before would. A read of 32 consecutive pixels then has the banks of one unbroken run, however often it wraps.
+__host__ __device__ constexpr unsigned chain_row_bytes(int w, unsigned ps) { return (w + 2) * ps + ((0u - 2 * ps) & 255u); }
+__host__ __device__ constexpr unsigned chain_image_bytes(int h, int w, unsigned ps) {
+    return ps ? (h + 2) * chain_row_bytes(w, ps) + ((h * w * ps - (h + 2) * chain_row_bytes(w, ps)) & 255u) : 0u;
+}
+
+// Parameters of a network, one block: for every layer its weights and then its constants, in the order first layer,
+// (first, second convolution) of every residual block, last layer. Weights are fragments of 1 KB,
+// [n_blk][taps * nc][64 lanes][16 bytes]: lane l of fragment (blk, tap * nc + c) holds, for filter 32 * blk + l % 32,
+// the channels 32 * c + 16 * (l / 32) .. + 15 of that tap. Constants are int32 [4][128]: clamp bound, multiplier,
+// shift, bias; the shift is stored minus 32 except in the last layer.
+struct ChainArgs {
+    const uint8_t* params;
+    int32_t* state;      // int32 pixel-major [npix][state_c]
+    const int32_t* idx;  // physical channel of logical channel c; the translation channels begin at n_a
+    int8_t* codes;       // nullptr: the last layer adds into the state; else head codes as in conv.h
+    long long codes_img_stride, codes_off;
+    unsigned pf_bytes;   // size of the block, for the workgroups that fetch it ahead
+    int batch, mul_in;
+    unsigned short h, w;
+    unsigned short images;  // images of a workgroup
+    unsigned short state_c, n_a, n_out, blocks;
+    unsigned char nc_x, nc_t, nc_q;  // 32-channel chunks of the stream, the block-internal tensor (0: no blocks), the quantised input
+    unsigned char taps_two, taps_last, n_blk_last;  // 1 or 9; 32-filter blocks of the last layer
+    unsigned char shift_in, act_unsigned, relu_last, pf_blocks;
+    unsigned char last_fast;  // the last layer's shifts are all 33 or more and nothing in it requantises to half a code
+    signed char sign;
+};
+
+// One kernel: the kind of network it runs, and the 32-pixel tiles its workgroup takes. The tables, one to a kind, are
+// spread over several source files because compiling them takes a while.
+struct ChainKernel {
+    int nc_x, nc_t, taps_two, tiles, threads;
+    void (*kern)(const ChainArgs);
+};
+constexpr int kChainSizes = 4;  // 1, 2, 4 and 8 tiles
+extern const ChainKernel kChain443[], kChain423[], kChain223[], kChain441[], kChain421[], kChain221[], kChain40[], kChain20[];
+
+size_t chain_lds_bytes(const ChainArgs& a);
+// Whether a kernel exists for this network and this many images per workgroup.
+bool chain_args_ok(const ChainArgs& a);
+hipError_t launch_chain(const ChainArgs& a, hipStream_t stream);
+hipError_t chain_setup();
+
+}  // namespace iodf

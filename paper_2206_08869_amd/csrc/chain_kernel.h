@@ -1,0 +1,466 @@
+// Whole networks of at most 128 channels out of LDS (Sec. 4.1, App. B.1): input quantiser, first layer, residual
+// blocks, last layer and coupling add (or head codes) in one launch.
+//
+// A layer of 128 channels over the few pixels of a deep level is too little work for a launch of its own: it is
+// mostly launch, first operands and drain. Here a workgroup keeps the features of one or several whole images in
+// LDS and runs layer after layer on them; only the weights move, from the L2 straight into registers, in the order
+// the matrix cores take them (no LDS, no barrier, a stream that never stops between layers).
+//
+// Bound, per layer 128 -> 128 channels, 3x3, in clocks of a CU (measured in the kernel; 147 KB of weights at the
+// 57 bytes a clock that a CU gets from its L2 are 2600):
+//   4x4 maps, 1 tile of pixels:   products 2700, the weights; epilogue and barrier 950
+//   8x8 maps, 2 tiles:            products 3950 (matrix cores 2300, LDS reads 2300, weights 2600); 1350 to 1600
+//   16x16 maps, 8 tiles, 4 waves: products 11300 (matrix cores 9200); epilogue 4200, with a shortcut 5000
+#pragma once
+#include "chain.h"
+#include "conv_dev.h"
+
+namespace iodf {
+
+namespace {
+
+constexpr int kInvBits = 20;  // m / d = m * ceil(2^20 / d) >> 20 for m * d < 2^20
+
+// Global memory by type: a pointer rebuilt from scalar halves would otherwise be a generic one, whose loads also
+// count as LDS operations.
+typedef const uint8_t __attribute__((address_space(1)))* gbytes;
+typedef const v4i __attribute__((address_space(1)))* gv4i;
+
+__device__ __forceinline__ gbytes uniform(gbytes p) {
+    const unsigned long long v = (unsigned long long)p;
+    return (gbytes)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
+                    (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v));
+}
+
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// How NW waves divide n_blk blocks of 32 channels x `tiles` tiles of 32 pixels: TC blocks and TP tiles to a wave.
+template <int NW, int N_BLK, int TILES>
+struct Share {
+    static constexpr int TC = N_BLK == 4 && TILES == 8 ? 2 : 1;
+    static constexpr int WC = N_BLK / TC, WP = NW / WC;
+    static constexpr int TP = (TILES + WP - 1) / WP;
+};
+
+// The products of one layer. Weights come in fragments of 1 KB per channel block and step (a step: one tap, 32
+// channels). w holds those of the next 12 / TC steps, at most a kernel row: as soon as a step has used its
+// fragments their registers take those of a later step of the layer or, in the last kernel row, of the next layer,
+// so the stream runs on across layers. Pixels are read from LDS one step ahead, two where a step is only one or two
+// products long; the scheduling barriers keep the compiler from moving the reads next to their use.
+template <int TC, int NC, int NT>
+constexpr int chain_depth() { return NC * NT < 12 / TC ? NC * NT : 12 / TC; }
+
+template <int TC, int TP, int NC, int NT>
+__device__ __forceinline__ void chain_products(v16i (&acc)[TC][TP], v4i (&w)[12], const unsigned char* lds,
+                                               const unsigned (&at)[TP], const unsigned rowstep, const gbytes wcur,
+                                               const gbytes wnext, const unsigned tcs_next, const unsigned lane16) {
+    constexpr int S = NC * NT, PS = chain_pixel_bytes(NC), D = chain_depth<TC, NC, NT>();
+    constexpr unsigned tcs = TC == 2 ? S * NT * 1024 : 0;
+    static_assert(S % D == 0, "a kernel row is a whole number of rounds of the fragment registers");
+    constexpr int PD = S % 2 != 0 || (TP <= 2 && S % 3 == 0) ? 2 : 1;
+    static_assert(NT == 1 || S % (PD + 1) == 0, "and of the pixel registers");
+    v4i b[PD + 1][TP];
+    unsigned ba[TP];
+#pragma unroll
+    for (int tp = 0; tp < TP; ++tp) ba[tp] = at[tp];
+    auto read = [&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            b[i % (PD + 1)][tp] = *(const v4i*)(lds + ba[tp] + (i / NC) * PS + (i % NC) * 32);
+        });
+    };
+    static_for<PD>([&](auto i_) { read(i_); });
+#pragma unroll 1
+    for (int r = 0; r < NT; ++r) {
+        const bool last = r == NT - 1;
+        const gbytes wr = uniform(wcur + r * (S * 1024));
+        const gbytes wn = uniform(last ? wnext : wcur + (r + 1) * (S * 1024));
+        const unsigned ts = last ? tcs_next : tcs;
+        const unsigned adv = last ? 0u : rowstep;
+        static_for<S>([&](auto i_) {
+            constexpr int i = decltype(i_)::value;
+            if constexpr (i == S - PD) {
+#pragma unroll
+                for (int tp = 0; tp < TP; ++tp) ba[tp] += adv;
+            }
+            if constexpr (i + PD < S) read(std::integral_constant<int, i + PD>{});
+            else if constexpr (NT > 1) read(std::integral_constant<int, i + PD - S>{});
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<TC>([&](auto tc_) {
+                constexpr int tc = decltype(tc_)::value;
+                static_for<TP>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+                    acc[tc][tp] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[(i % D) * TC + tc], b[i % (PD + 1)][tp], acc[tc][tp], 0, 0, 0);
+                });
+            });
+            static_for<TC>([&](auto tc_) {
+                constexpr int tc = decltype(tc_)::value;
+                w[(i % D) * TC + tc] = i + D < S ? *(gv4i)(wr + tc * tcs + (i + D) * 1024 + lane16)
+                                                 : *(gv4i)(wn + tc * ts + (i + D - S) * 1024 + lane16);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    // what reads the accumulators next may be an opaque statement, which the compiler gives no wait states
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Fragments of the first steps of a layer, registers from FROM on.
+template <int TC, int NC, int NT, int FROM>
+__device__ __forceinline__ void chain_fetch(v4i (&w)[12], const gbytes p, const unsigned lane16) {
+    constexpr int n = chain_depth<TC, NC, NT>() * TC;
+    static_for<n>([&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        if constexpr (i >= FROM) w[i] = *(gv4i)(p + (i % TC) * (NC * NT * NT * 1024) + (i / TC) * 1024 + lane16);
+    });
+}
+
+// Hidden layer's epilogue: requantise, ReLU or shortcut, 16 channels of a pixel per lane and 32x32 block, into LDS.
+// at: where each tile's pixel lies in the output tensor.
+template <int TC, int TP, bool SHORTCUT>
+__device__ __forceinline__ void chain_store(const v16i (&acc)[TC][TP], unsigned char* lds, const unsigned (&at)[TP],
+                                            const int live, const int* cst, const int ch_base, const int half,
+                                            const bool act_unsigned) {
+    static_for<TC>([&](auto tc_) {
+        constexpr int tc = decltype(tc_)::value;
+        const int ch0 = ch_base + tc * 32;
+        v4i Bq[4], Mq[4], Sq[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int nl = ch0 + g * 8 + half * 4;
+            if (!SHORTCUT) Bq[g] = *(const v4i*)(cst + nl);
+            Mq[g] = *(const v4i*)(cst + 128 + nl);
+            Sq[g] = *(const v4i*)(cst + 256 + nl);
+        }
+        unsigned pk[TP][4];
+        if constexpr (SHORTCUT) {
+            // the shortcut's 16 bytes sit where the result's go; the regrouping below run backwards
+            v4i s4[TP];
+            static_for<TP>([&](auto tp_) { s4[decltype(tp_)::value] = *(const v4i*)(lds + at[decltype(tp_)::value] + ch0 + half * 16); });
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<TP>([&](auto tp_) {
+                constexpr int tp = decltype(tp_)::value;
+                auto x = __builtin_amdgcn_permlane32_swap((unsigned)s4[tp][0], (unsigned)s4[tp][2], false, false);
+                auto u = __builtin_amdgcn_permlane32_swap((unsigned)s4[tp][1], (unsigned)s4[tp][3], false, false);
+                auto q01 = __builtin_amdgcn_permlane32_swap(x[0], u[0], false, false);
+                auto q23 = __builtin_amdgcn_permlane32_swap(x[1], u[1], false, false);
+                pk[tp][0] = q01[0]; pk[tp][1] = q01[1]; pk[tp][2] = q23[0]; pk[tp][3] = q23[1];
+            });
+        }
+        static_for<4>([&](auto g_) {
+            constexpr int g = decltype(g_)::value;
+            unsigned Rq[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Rq[e] = 1u << (Sq[g][e] - 1);
+            static_for<TP>([&](auto tp_) {
+                constexpr int tp = decltype(tp_)::value;
+                if constexpr (SHORTCUT)
+                    pk[tp][g] = pack_signed_quad<true>(acc[tc][tp], std::integral_constant<int, g * 4>{}, Mq[g], Sq[g], Rq,
+                                                       (int)pk[tp][g], act_unsigned ? -128 : 0);
+                else
+                    pk[tp][g] = pack_relu_quad(acc[tc][tp], std::integral_constant<int, g * 4>{}, Bq[g], Mq[g], Sq[g], Rq, act_unsigned);
+            });
+        });
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            auto s01 = __builtin_amdgcn_permlane32_swap(pk[tp][0], pk[tp][1], false, false);
+            auto s23 = __builtin_amdgcn_permlane32_swap(pk[tp][2], pk[tp][3], false, false);
+            auto x = __builtin_amdgcn_permlane32_swap(s01[0], s23[0], false, false);
+            auto u = __builtin_amdgcn_permlane32_swap(s01[1], s23[1], false, false);
+            const v4i o4 = {(int)x[0], (int)u[0], (int)x[1], (int)u[1]};
+            if (live >> tp & 1) *(v4i*)(lds + at[tp] + ch0 + half * 16) = o4;
+        });
+    });
+}
+
+// NCX, NCT: 32-channel chunks of the stream x and of the tensor t inside a block (0: no blocks); NT2: kernel side of a
+// block's second convolution; TILES: 32-pixel tiles of the workgroup's images, rounded up to a power of two.
+template <int NW, int NCX, int NCT, int NT2, int TILES>
+__global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
+    constexpr int kThreads = NW * 64;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned lane16 = lane * 16;
+
+    const int groups = (a.batch + a.images - 1) / a.images;
+    if ((int)blockIdx.x >= groups) {
+        // workgroups beyond the groups bring the parameters into the L2 of an XCD that has groups (blocks go round the XCDs)
+        if ((int)(blockIdx.x & 7) >= groups) return;
+        const int base = (groups + 7) >> 3;  // first slot of an XCD that may hold such a block
+        const unsigned lines = a.pf_bytes >> 7, stride = a.pf_blocks * kThreads;
+        int sum = 0;
+        for (unsigned l = (((int)blockIdx.x >> 3) - base) * kThreads + tid; l < lines; l += 4 * stride) {
+#pragma unroll
+            for (unsigned u = 0; u < 4; ++u)
+                if (l + u * stride < lines) sum += *(const int*)(a.params + ((size_t)(l + u * stride) << 7));
+        }
+        asm volatile("" ::"v"(sum));  // the loads are the point: keep them
+        return;
+    }
+    const int img0 = blockIdx.x * a.images;
+    const int n_img = a.batch - img0 < a.images ? a.batch - img0 : a.images;
+    const int h = a.h, w = a.w, hw = h * w, M = n_img * hw;
+
+    // LDS: constants of the current and the next layer, then the three tensors, zero-bordered images each
+    constexpr unsigned psx = chain_pixel_bytes(NCX), pst = chain_pixel_bytes(NCT);
+    const unsigned psq = chain_pixel_bytes(a.nc_q);
+    const unsigned rpx = chain_row_bytes(w, psx), rpt = chain_row_bytes(w, pst), rpq = chain_row_bytes(w, psq);
+    const unsigned isx = chain_image_bytes(h, w, psx), ist = chain_image_bytes(h, w, pst), isq = chain_image_bytes(h, w, psq);
+    constexpr unsigned qb = 2 * kChainConstBytes;
+    const unsigned xb = qb + isq * n_img, tb = xb + isx * n_img, end = tb + ist * n_img;
+
+    // Parameter block: sizes of a layer's weights and constants
+    const unsigned bytes_in = NCX * 9 * a.nc_q * 1024 + kChainConstBytes;
+    constexpr unsigned w_one = NCT * 9 * NCX * 1024, w_two = NCX * NT2 * NT2 * NCT * 1024;
+    constexpr unsigned bytes_one = w_one + kChainConstBytes, bytes_block = bytes_one + w_two + kChainConstBytes;
+    const gbytes par = (gbytes)a.params;
+
+    using SX = Share<NW, NCX, TILES>;                 // layers that write the stream
+    using ST = Share<NW, NCT ? NCT : 1, TILES>;       // first convolution of a block
+    using S1 = Share<NW, 1, TILES>;                   // last layer, up to 32 filters
+    using S2 = Share<NW, 2, TILES>;                   // ... up to 64
+    const int xblk = wave % SX::WC * SX::TC, tblk = wave % ST::WC * ST::TC;
+
+    v4i wf[12];
+    static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+    const gbytes w_in = par + (size_t)(xblk * 9 * a.nc_q * 1024);
+    if (a.nc_q == 1) chain_fetch<SX::TC, 1, 3, 0>(wf, uniform(w_in), lane16);
+    else chain_fetch<SX::TC, 2, 3, 0>(wf, uniform(w_in), lane16);
+    auto fetch_const = [&](gbytes at) { return tid < kChainConstBytes / 16 ? *(gv4i)(at + tid * 16) : v4i{0, 0, 0, 0}; };
+    auto put_const = [&](int buf, const v4i& v) {
+        if (tid < kChainConstBytes / 16) *(v4i*)(lds + buf * kChainConstBytes + tid * 16) = v;
+    };
+    {
+        const v4i c0 = fetch_const(par + (bytes_in - kChainConstBytes));
+        // padding first: the quantised input's is byte 0, the features' the stored form of code 0
+        const int pad = a.act_unsigned ? (int)0x80808080 : 0;
+        for (unsigned o = qb + tid * 16; o < end; o += kThreads * 16) {
+            const int v = o < xb ? 0 : pad;
+            *(v4i*)(lds + o) = v4i{v, v, v, v};
+        }
+        put_const(0, c0);
+    }
+    lds_barrier();
+    {
+        // quantised input: channel c of pixel p is sat8(rq(S[p][idx[c]])). Four channels to a task, four tasks of a
+        // thread at a time: their loads, an index and a word behind it each, overlap.
+        const unsigned quads = (a.n_a + 3) >> 2, total = (unsigned)M * quads;
+        const int32_t* const s0 = a.state + (long long)img0 * hw * a.state_c;
+        for (unsigned t0 = tid; t0 < total; t0 += 4 * kThreads) {
+            int v[4][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned t = t0 + u * kThreads < total ? t0 + u * kThreads : t0, p = t / quads, g = t - p * quads;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e] = s0[p * a.state_c + a.idx[g * 4 + e < a.n_a ? g * 4 + e : 0]];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned t = t0 + u * kThreads, p = t / quads, g = t - p * quads;
+                if (t >= total) break;
+                unsigned packed = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if ((int)g * 4 + e < a.n_a) packed |= ((unsigned)sat8_dev(rq_dev(v[u][e], a.mul_in, a.shift_in)) & 0xffu) << (8 * e);
+                const unsigned im = p / hw, q = p - im * hw, row = q / w, col = q - row * w;
+                *(unsigned*)(lds + qb + im * isq + (row + 1) * rpq + (col + 1) * psq + g * 4) = packed;
+            }
+        }
+    }
+
+    // Where the pixels of this wave's tiles lie: image, row, column, as byte offsets of tap (0, 0) in each tensor.
+    // Lanes past the last pixel repeat it and store nothing.
+    const unsigned inv_w = ((1u << kInvBits) + w - 1) / w, inv_hw = ((1u << kInvBits) + hw - 1) / hw;
+    auto pixel_of = [&](int tile, int& im, int& row, int& col) {
+        int m = tile * 32 + l32;
+        const bool live = m < M;
+        m = live ? m : M - 1;
+        im = (int)(__umul24((unsigned)m, inv_hw) >> kInvBits);
+        const int q = m - im * hw;
+        row = (int)(__umul24((unsigned)q, inv_w) >> kInvBits);
+        col = q - row * w;
+        return live;
+    };
+    unsigned x_of_x[SX::TP], t_of_x[SX::TP], q_of_x[SX::TP], x_of_t[ST::TP], t_of_t[ST::TP];
+    int live_x = 0, live_t = 0;
+    static_for<SX::TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int im, row, col;
+        if (pixel_of(wave / SX::WC * SX::TP + tp, im, row, col)) live_x |= 1 << tp;
+        x_of_x[tp] = xb + im * isx + row * rpx + col * psx;
+        t_of_x[tp] = tb + im * ist + row * rpt + col * pst + half * 16;
+        q_of_x[tp] = qb + im * isq + row * rpq + col * psq + half * 16;
+    });
+    static_for<ST::TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int im, row, col;
+        if (pixel_of(wave / ST::WC * ST::TP + tp, im, row, col)) live_t |= 1 << tp;
+        x_of_t[tp] = xb + im * isx + row * rpx + col * psx + half * 16;
+        t_of_t[tp] = tb + im * ist + row * rpt + col * pst;
+    });
+    unsigned xo[SX::TP], to[ST::TP];  // the pixels themselves
+#pragma unroll
+    for (int i = 0; i < SX::TP; ++i) xo[i] = x_of_x[i] + rpx + psx;
+#pragma unroll
+    for (int i = 0; i < ST::TP; ++i) to[i] = t_of_t[i] + rpt + pst;
+    lds_barrier();
+
+    auto bias_to = [&](auto& acc, const int* cst, int blk) {
+        constexpr int TP = sizeof(acc[0]) / sizeof(v16i), TC = sizeof(acc) / sizeof(acc[0]);
+        static_for<TC>([&](auto tc_) {
+            constexpr int tc = decltype(tc_)::value;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4i b4 = *(const v4i*)(cst + 3 * 128 + (blk + tc) * 32 + g * 8 + half * 4);
+                static_for<TP>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[tc][tp][g * 4 + e] = b4[e];
+                });
+            }
+        });
+    };
+    const int* const cst0 = (const int*)lds;
+    const int* const cst1 = (const int*)(lds + kChainConstBytes);
+
+    // First layer. Behind it every layer's constants alternate between the two buffers: 1, 0, 1, ...
+    gbytes blockp = par + bytes_in;
+    constexpr bool carry_one = NCT != 0 && SX::TC == ST::TC;  // the stream of fragments runs on between x's layers and t's
+    constexpr unsigned tcs_one = ST::TC == 2 ? 9 * NCX * 1024 : 0, tcs_two = SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0;
+    {
+        const v4i cn = fetch_const(NCT ? blockp + w_one : blockp + a.n_blk_last * a.taps_last * NCX * 1024);
+        v16i acc[SX::TC][SX::TP];
+        bias_to(acc, cst0, xblk);
+        if (a.nc_q == 1) chain_products<SX::TC, SX::TP, 1, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
+        else chain_products<SX::TC, SX::TP, 2, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
+        if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
+        chain_store<SX::TC, SX::TP, false>(acc, lds, xo, live_x, cst0, xblk * 32, half, a.act_unsigned);
+        put_const(1, cn);
+    }
+    lds_barrier();
+    if constexpr (NCT != 0) {
+#pragma unroll 1
+        for (int b = 0; b < a.blocks; ++b) {
+            const bool last = b + 1 == a.blocks;
+            const gbytes p_one = blockp + tblk * 9 * NCX * 1024, p_two = blockp + bytes_one + xblk * NT2 * NT2 * NCT * 1024;
+            const gbytes next = last ? blockp : blockp + bytes_block;
+            {
+                const v4i cn = fetch_const(blockp + bytes_one + w_two);
+                v16i acc[ST::TC][ST::TP];
+                bias_to(acc, cst1, tblk);
+                chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_of_t, rpx, uniform(p_one), uniform(p_two), tcs_two, lane16);
+                constexpr int got = carry_one ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0;
+                chain_fetch<SX::TC, NCT, NT2, got>(wf, uniform(p_two), lane16);
+                chain_store<ST::TC, ST::TP, false>(acc, lds, to, live_t, cst1, tblk * 32, half, a.act_unsigned);
+                put_const(0, cn);
+            }
+            lds_barrier();
+            {
+                const v4i cn = fetch_const(last ? blockp + bytes_block + a.n_blk_last * a.taps_last * NCX * 1024 : next + w_one);
+                v16i acc[SX::TC][SX::TP];
+                bias_to(acc, cst0, xblk);
+                unsigned at[SX::TP];  // a 1x1 kernel begins at the pixel itself
+#pragma unroll
+                for (int i = 0; i < SX::TP; ++i) at[i] = NT2 == 1 ? t_of_x[i] + rpt + pst : t_of_x[i];
+                const gbytes p_next = next + tblk * 9 * NCX * 1024;
+                chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, at, rpt, uniform(p_two), uniform(p_next), tcs_one, lane16);
+                constexpr int got = carry_one ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0;
+                chain_fetch<ST::TC, NCX, 3, got>(wf, uniform(p_next), lane16);
+                chain_store<SX::TC, SX::TP, true>(acc, lds, xo, live_x, cst0, xblk * 32, half, a.act_unsigned);
+                put_const(1, cn);
+            }
+            lds_barrier();
+            blockp += bytes_block;
+        }
+    }
+
+    // Last layer: few filters, every wave takes some of the pixels.
+    auto last_layer = [&](auto share_, auto nt_) {
+        using S = decltype(share_);
+        constexpr int NT = decltype(nt_)::value, TP = S::TP;
+        const int blk = wave % S::WC;
+        const gbytes p = uniform(blockp + blk * NT * NT * NCX * 1024);
+        chain_fetch<1, NCX, NT, 0>(wf, p, lane16);
+        unsigned at[TP];
+        int gp[TP];  // image * hw + pixel, or -1
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int im, row, col;
+            const bool live = pixel_of(wave / S::WC * TP + tp, im, row, col);
+            at[tp] = xb + im * isx + (row + (NT == 1)) * rpx + (col + (NT == 1)) * psx + half * 16;
+            gp[tp] = live ? (img0 + im) * hw + row * w + col : -1;
+        });
+        int ix[16];  // physical channels of this lane's filters
+        static_for<16>([&](auto r_) {
+            constexpr int r = decltype(r_)::value;
+            const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+            ix[r] = a.codes ? 0 : a.idx[a.n_a + (n < a.n_out ? n : a.n_out - 1)];
+        });
+        auto result = [&](int acc, int n) {
+            int y;
+            if (a.last_fast) y = (__mulhi(acc, cst1[128 + n]) + (1 << (cst1[256 + n] - 33))) >> (cst1[256 + n] - 32);
+            else y = rq_dev(acc, cst1[128 + n], cst1[256 + n]);
+            if (a.relu_last) y = y < 0 ? 0 : y;
+            return sat8_dev(y);
+        };
+        v16i acc[1][TP];
+        bias_to(acc, cst1, blk);
+        chain_products<1, TP, NCX, NT>(acc, wf, lds, at, rpx, p, p, 0, lane16);
+        if (a.codes) {
+            static_for<TP>([&](auto tp_) {
+                constexpr int tp = decltype(tp_)::value;
+                if (gp[tp] < 0) return;
+                const int bi = gp[tp] / hw, qi = gp[tp] - bi * hw;
+                int8_t* const cp = a.codes + (long long)bi * a.codes_img_stride + a.codes_off + qi;
+                static_for<16>([&](auto r_) {
+                    constexpr int r = decltype(r_)::value;
+                    const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+                    if (n < a.n_out) cp[n * hw] = (int8_t)result(acc[0][tp][r], n);
+                });
+            });
+            return;
+        }
+        // The state words this lane updates: all on their way before the first is needed. Filters past the last one
+        // read its word and write nothing.
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int32_t* const sp = a.state + (long long)(gp[tp] < 0 ? img0 * hw : gp[tp]) * a.state_c;
+            int v[16];
+            static_for<16>([&](auto r_) { v[decltype(r_)::value] = sp[ix[decltype(r_)::value]]; });
+            if (gp[tp] < 0) return;
+            static_for<16>([&](auto r_) {
+                constexpr int r = decltype(r_)::value;
+                const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+                if (n < a.n_out) sp[ix[r]] = v[r] + a.sign * result(acc[0][tp][r], n);
+            });
+        });
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I3 = std::integral_constant<int, 3>;
+    if (a.taps_last == 9) {
+        if (a.n_blk_last == 1) last_layer(S1{}, I3{});
+        else last_layer(S2{}, I3{});
+    } else {
+        if (a.n_blk_last == 1) last_layer(S1{}, I1{});
+        else last_layer(S2{}, I1{});
+    }
+}
+
+}  // namespace
+
+template <int NW, int NCX, int NCT, int NT2, int TILES>
+constexpr ChainKernel chain_kernel() {
+    return ChainKernel{NCX, NCT, NCT ? NT2 * NT2 : 0, TILES, NW * 64, k_chain<NW, NCX, NCT, NT2, TILES>};
+}
+// The kernels of one kind of network, by tiles. Four waves read the fewest bytes for a product; over eight tiles
+// eight waves are ahead all the same (16x16 maps at batch 256: 147 us against 150), because two waves of a SIMD fill
+// each other's epilogue.
+#define IODF_CHAIN_TABLE(NAME, NCX, NCT, NT2)                                                         \
+    const ChainKernel NAME[kChainSizes] = {chain_kernel<4, NCX, NCT, NT2, 1>(), chain_kernel<4, NCX, NCT, NT2, 2>(), \
+                                           chain_kernel<4, NCX, NCT, NT2, 4>(), chain_kernel<8, NCX, NCT, NT2, 8>()};
+
+}  // namespace iodf

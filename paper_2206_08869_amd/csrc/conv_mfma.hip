@@ -14,45 +14,14 @@
 // through a ring of LDS stages (see conv_igemm). For 3x3 layers the activation tile of tap
 // (ky,kx) is the tile of the pixels shifted by (ky-1, kx-1) inside zero-bordered images.
 #include "conv.h"
-
-#include <type_traits>
+#include "conv_dev.h"
 
 namespace iodf {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
-
-// Compile-time loop: f(std::integral_constant<int, I>) for I = 0..N-1. Keeps every
-// accumulator index a constant so the accumulators stay in registers.
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for_impl(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for_impl<I + 1, N>(f);
-    }
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl<0, N>(f);
-}
 
 constexpr int KT = 64;    // bytes (= int8 values) of K per staged tile
 
 // Epilogue variants a kernel is compiled for.
 enum { EPI_ANY = 0, EPI_FAST = 1, EPI_FAST_RELU = 2 };
-
-// Round-half-away-from-zero of acc * M / 2^s, clamped far outside the 8-bit range
-// (the caller saturates to 8 bit after adding at most one 8-bit shortcut).
-__device__ __forceinline__ int rq_dev(int acc, int M, int s) {
-    long long v = (long long)acc * (long long)M;
-    long long half = s > 0 ? (1LL << (s - 1)) : 0LL;
-    long long r = v >= 0 ? ((v + half) >> s) : -((-v + half) >> s);
-    r = r > (1 << 20) ? (1 << 20) : r;
-    r = r < -(1 << 20) ? -(1 << 20) : r;
-    return (int)r;
-}
-
-__device__ __forceinline__ int sat8_dev(int v) { return v > 127 ? 127 : (v < -128 ? -128 : v); }
 
 // Pixel index m -> position of the pixel in the zero-bordered image stack, (b * PP + (i+1) * W2 + (j+1)).
 // Image sides that are powers of two (every benchmark shape) take shifts; others divide.
@@ -160,73 +129,12 @@ __device__ __forceinline__ void conv_epilogue_fast(const ConvArgs& a, v16i (&acc
             static_for<4>([&](auto g_) {
                 constexpr int g = decltype(g_)::value;
                 if constexpr (PURE_RELU) {
-                    // ReLU without shortcut. The accumulators already hold the bias. Clamping them to
-                    // [0, hi] first (hi = the smallest value that requantises to 127; the rescale is
-                    // monotone and steps by at most 1) replaces both the ReLU and the saturation, so
-                    // every result fits a byte and the last shift can drop it straight into its place
-                    // in the packed dword.
-                    unsigned q[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        int av;
-                        asm("v_med3_i32 %0, %1, 0, %2" : "=v"(av) : "v"(acc[tc][tp][g * 4 + e]), "v"(Bq[g][e]));
-                        q[e] = __umulhi((unsigned)av, (unsigned)Mq[g][e]) + Rq[g][e];
-                    }
-                    unsigned p4 = q[0] >> Sq[g][0];
-                    asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                        "src1_sel:DWORD" : "+v"(p4) : "v"(Sq[g][1]), "v"(q[1]));
-                    asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                        "src1_sel:DWORD" : "+v"(p4) : "v"(Sq[g][2]), "v"(q[2]));
-                    asm("v_lshrrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                        "src1_sel:DWORD" : "+v"(p4) : "v"(Sq[g][3]), "v"(q[3]));
-                    pk[g] = a.out_unsigned ? p4 ^ 0x80808080u : p4;  // code u is stored as u - 128
+                    pk[g] = pack_relu_quad(acc[tc][tp], std::integral_constant<int, g * 4>{}, Bq[g], Mq[g], Sq[g], Rq[g],
+                                           a.out_unsigned);
                     return;
                 } else {
-                    // Signed results: a shortcut and / or no ReLU. The accumulators hold the bias. In
-                    // stored bytes the result is clamp(rq(acc) + shortcut byte, lo, 127): for signed codes
-                    // lo is 0 with a ReLU and -128 without; for unsigned codes (stored as code - 128, which
-                    // only occur here together with a shortcut of the same format) the two offsets of 128
-                    // cancel and ReLU plus saturation to [0, 255] is the clamp to [-128, 127]. The shortcut
-                    // byte is added sign-extended straight out of its dword and the clamp's second half
-                    // drops the byte into the packed dword.
-                    const int sc = scq[tc][tp][g];
-                    const int lo2 = (a.relu && !a.out_unsigned) ? 0 : -128;
-                    unsigned p4 = 0;
-                    static_for<4>([&](auto e_) {
-                        constexpr int e = decltype(e_)::value;
-                        const int av = acc[tc][tp][g * 4 + e];
-                        const int sgn = av >> 31;
-                        const unsigned q = (__umulhi((unsigned)((av ^ sgn) - sgn), (unsigned)Mq[g][e]) + Rq[g][e]) >> Sq[g][e];
-                        const int r = ((int)q ^ sgn) - sgn;
-                        int t;
-                        if constexpr (e == 0)
-                            asm("v_add_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-                                "src1_sel:BYTE_0" : "=v"(t) : "v"(r), "v"(sc));
-                        else if constexpr (e == 1)
-                            asm("v_add_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-                                "src1_sel:BYTE_1" : "=v"(t) : "v"(r), "v"(sc));
-                        else if constexpr (e == 2)
-                            asm("v_add_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-                                "src1_sel:BYTE_2" : "=v"(t) : "v"(r), "v"(sc));
-                        else
-                            asm("v_add_u32_sdwa %0, %1, sext(%2) dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-                                "src1_sel:BYTE_3" : "=v"(t) : "v"(r), "v"(sc));
-                        t = t < lo2 ? lo2 : t;
-                        const int hi2 = 127;
-                        if constexpr (e == 0)
-                            asm("v_min_i32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                                "src1_sel:DWORD" : "+v"(p4) : "v"(t), "v"(hi2));
-                        else if constexpr (e == 1)
-                            asm("v_min_i32_sdwa %0, %1, %2 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                                "src1_sel:DWORD" : "+v"(p4) : "v"(t), "v"(hi2));
-                        else if constexpr (e == 2)
-                            asm("v_min_i32_sdwa %0, %1, %2 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                                "src1_sel:DWORD" : "+v"(p4) : "v"(t), "v"(hi2));
-                        else
-                            asm("v_min_i32_sdwa %0, %1, %2 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD "
-                                "src1_sel:DWORD" : "+v"(p4) : "v"(t), "v"(hi2));
-                    });
-                    pk[g] = p4;
+                    pk[g] = pack_signed_quad<false>(acc[tc][tp], std::integral_constant<int, g * 4>{}, Mq[g], Sq[g], Rq[g], scq[tc][tp][g],
+                                             (a.relu && !a.out_unsigned) ? 0 : -128);
                 }
             });
             // lower half holds channels {0-3, 8-11, 16-19, 24-27}, upper {4-7, 12-15, 20-23, 28-31}

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "chain.h"
 #include "codec_kernels.h"
 #include "conv.h"
 #include "flow_kernels.h"
@@ -221,6 +222,7 @@ struct DevLayer {
     int out_buf, out_off;  // output tensor (MODE_ACT)
     size_t wgt_off, bias_off, mul_off, shift_off;  // byte offsets into the parameter arena
     size_t hi_off = (size_t)-1;                    // rq_fast layers: clamp bound per channel
+    bool no_ties = false;                          // rq_fast layers: no accumulator requantises to exactly half a code
     // Unsigned format: a code u in 0..255 is stored as the byte u - 128 and planes are bordered with
     // -128, so that the int8 matrix cores see u - 128 everywhere; a layer reading such a tensor adds
     // 128 * (sum of its weights) to its bias, a layer writing one saturates to [0, 255] and stores u - 128.
@@ -235,8 +237,16 @@ struct DevLayer {
     bool wide;
 };
 
+// A network whose features can stay in one workgroup's LDS, as chain.hip reads it.
+struct DevChain {
+    bool ok = false;
+    size_t off = 0, bytes = 0;  // its parameters, one block of the arena
+    int nc_x = 0, nc_t = 0, nc_q = 0, blocks = 0, taps_two = 0, taps_last = 0, n_blk_last = 0;
+};
+
 struct DevNet {
     int kind, level, C, C_in, C_out, cin_pad0;
+    DevChain chain;
     int32_t M_in;
     int s_in;
     size_t phi_off;     // byte offset of this coupling's composed index map (int32[C]); heads: the level's last
@@ -341,6 +351,25 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
             if (a < (unsigned __int128)INT32_MAX) hi[n] = (int32_t)(uint64_t)a;
         }
     }
+    if (D.rq_fast) {
+        // acc * M / 2^s is half a code for acc an odd multiple of 2^(s - 1 - t) only, t = trailing zeros of M: compare
+        // with the largest accumulator the row's weights and bias allow (input bytes are at most 128 in magnitude).
+        D.no_ties = true;
+        mul = (int32_t*)(A.host.data() + D.mul_off);
+        sh = (int32_t*)(A.host.data() + D.shift_off);
+        for (size_t n = 0; n < rows.size(); ++n) {
+            if (mul[n] <= 0) continue;
+            const int8_t* src = L.W + (size_t)rows[n] * L.C_in * taps;
+            long long sum = 0;
+            for (int c = 0; c < L.C_in; ++c)
+                if (colpos[c] >= 0)
+                    for (int t = 0; t < taps; ++t) sum += src[(size_t)c * taps + t] < 0 ? -src[(size_t)c * taps + t] : src[(size_t)c * taps + t];
+            const long long b = ((const int32_t*)(A.host.data() + D.bias_off))[n];
+            const long long amax = 128 * sum + (b < 0 ? -b : b);
+            const int e = sh[n] + 31 - __builtin_ctz((unsigned)mul[n]);  // s - 1 - t
+            if (e < 0 || (e < 62 && amax >= (1LL << e))) D.no_ties = false;
+        }
+    }
     D.macs_per_pixel = (long long)kept * live * taps;
     D.bytes_per_pixel = (long long)live + (long long)kept;
     D.wgt_bytes = D.macs_per_pixel;
@@ -399,6 +428,65 @@ void pack_last_expanded(Arena& A, const HostLayer& L, const std::vector<int>& co
     D.wide = false;
 }
 
+// Second copy of a network's parameters in the order chain.hip reads them, if the network is one it can run: a
+// plain or residual network whose stream and inner tensors have at most 128 (padded) channels, whose hidden layers
+// take the short requantise with a ReLU, and whose last layer is a direct convolution.
+void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
+    const int nl = (int)D.layers.size();
+    if (m.family == FAM_DENSE || N.C_in > 64 || N.C_out > 64) return;
+    const int rw = D.layers[0].n_pad, tw = nl > 2 ? D.layers[1].n_pad : 0, taps2 = nl > 2 ? D.layers[2].taps : 0;
+    if (rw > 128 || tw > rw) return;
+    for (int l = 0; l < nl; ++l) {
+        const DevLayer& L = D.layers[l];
+        const bool last = l + 1 == nl, two = !last && l > 0 && l % 2 == 0;
+        if (last) {
+            if (L.mode != MODE_COUPLE && L.mode != MODE_CODES) return;
+            continue;
+        }
+        if (!L.rq_fast || !L.relu || L.hi_off == (size_t)-1 || L.n_store != L.n_pad || L.n_pad != (l % 2 ? tw : rw)) return;
+        if ((L.shortcut != 0) != two || (two && !L.no_ties) || L.taps != (two ? taps2 : 9)) return;
+    }
+    DevChain& C = D.chain;
+    C.nc_x = rw / 32;
+    C.nc_t = tw / 32;
+    C.nc_q = (N.C_in + 31) / 32;
+    C.blocks = (nl - 2) / 2;
+    C.taps_two = taps2;
+    C.taps_last = D.layers[nl - 1].taps;
+    C.n_blk_last = (N.C_out + 31) / 32;
+    std::vector<size_t> nw((size_t)nl);
+    size_t total = 0;
+    for (int l = 0; l < nl; ++l) {
+        const DevLayer& L = D.layers[l];
+        const int nc = l == 0 ? C.nc_q : L.cin_pad / 32, n_blk = l + 1 == nl ? C.n_blk_last : L.n_pad / 32;
+        total += (nw[l] = (size_t)n_blk * L.taps * nc * 1024) + kChainConstBytes;
+    }
+    C.bytes = total;
+    C.off = A.alloc(total + kChainOverread);
+    uint8_t* dst = A.host.data() + C.off;
+    for (int l = 0; l < nl; ++l) {
+        const DevLayer& L = D.layers[l];
+        const bool last = l + 1 == nl;
+        const int nc = l == 0 ? C.nc_q : L.cin_pad / 32, n_blk = (int)(nw[l] / ((size_t)L.taps * nc * 1024));
+        const int8_t* src = (const int8_t*)(A.host.data() + L.wgt_off);
+        for (int b = 0; b < n_blk; ++b)
+            for (int t = 0; t < L.taps; ++t)
+                for (int c = 0; c < nc; ++c)
+                    for (int lane = 0; lane < 64; ++lane, dst += 16)
+                        memcpy(dst, src + (((size_t)(c >> 1) * L.taps + t) * L.n_pad + 32 * b + lane % 32) * 64 +
+                                        32 * (c & 1) + 16 * (lane / 32), 16);
+        int32_t* k = (int32_t*)dst;
+        for (int n = 0; n < L.n_pad; ++n) {
+            if (L.hi_off != (size_t)-1) k[n] = ((const int32_t*)(A.host.data() + L.hi_off))[n];
+            k[128 + n] = ((const int32_t*)(A.host.data() + L.mul_off))[n];
+            k[256 + n] = ((const int32_t*)(A.host.data() + L.shift_off))[n] + (last && L.rq_fast ? 32 : 0);
+            k[384 + n] = ((const int32_t*)(A.host.data() + L.bias_off))[n];
+        }
+        dst += kChainConstBytes;
+    }
+    C.ok = true;
+}
+
 std::vector<int> identity_map(int n) {
     std::vector<int> v(n);
     for (int i = 0; i < n; ++i) v[i] = i;
@@ -444,6 +532,7 @@ void plan_net(Arena& A, const HostModel& m, const HostNet& N, DevNet& D, int buf
         plan_last(L[1], rank_map(L[0], 0), fw, D.layers[1]);
         D.layers[1].in_buf = BUF_A; D.layers[1].in_off = 0; D.layers[1].out_buf = -1; D.layers[1].out_off = 0;
         buf_w[BUF_A] = std::max(buf_w[BUF_A], fw);
+        pack_chain(A, m, N, D);
     } else if (m.family == FAM_RESNET) {
         // BUF_A: residual stream at full width; BUF_B: block-internal feature (compacted)
         const int Wd = L[0].C_out;
@@ -473,6 +562,7 @@ void plan_net(Arena& A, const HostModel& m, const HostNet& N, DevNet& D, int buf
         plan_last(L[nl - 1], identity_map(Wd), rw, D.layers[nl - 1]);
         D.layers[nl - 1].in_buf = BUF_A; D.layers[nl - 1].in_off = 0; D.layers[nl - 1].out_buf = -1;
         D.layers[nl - 1].out_off = 0;
+        pack_chain(A, m, N, D);
     } else {
         // BUF_A: concatenation of the compacted feature blocks f0..f_depth; BUF_B: bottleneck g
         const int depth = (nl - 2) / 2;
@@ -573,9 +663,9 @@ struct iodf_ctx {
 
 namespace {
 
-enum { CLS_QUANT_IN = 0, CLS_FILL_ZERO, CLS_INGEST, CLS_FACTOR_OUT, CLS_UNFACTOR, CLS_EMIT_X, CLS_TAPSUM,
+enum { CLS_QUANT_IN = 0, CLS_FILL_ZERO, CLS_CHAIN, CLS_INGEST, CLS_FACTOR_OUT, CLS_UNFACTOR, CLS_EMIT_X, CLS_TAPSUM,
        CLS_PRIOR_CF, CLS_RANS_ENCODE, CLS_RANS_PACK, CLS_RANS_DECODE, NUM_FLOW_CLS };
-const char* const kFlowClsName[NUM_FLOW_CLS] = {"k_quant_in", "k_fill_zero", "k_ingest_squeeze",
+const char* const kFlowClsName[NUM_FLOW_CLS] = {"k_quant_in", "k_fill_zero", "k_chain", "k_ingest_squeeze",
                                                 "k_factor_out", "k_unfactor", "k_emit_x", "conv_tapsum",
                                                 "k_prior_cf", "k_rans_encode", "k_rans_pack", "k_rans_decode_chunk"};
 
@@ -621,9 +711,82 @@ static void layer_param_span(const iodf_ctx* ctx, const DevLayer& L, const int8_
     *bytes = (unsigned)std::min<size_t>(end - L.wgt_off, 0xffffffffu);
 }
 
+static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int images, int mode_sign, int8_t* codes) {
+    const DevChain& C = N.chain;
+    const DevLayer& L = N.layers.back();
+    ChainArgs a;
+    memset(&a, 0, sizeof(a));
+    a.params = ctx->params + C.off;
+    a.pf_bytes = (unsigned)C.bytes;
+    a.state = ctx->state[N.level];
+    a.state_c = (unsigned short)N.C;
+    a.idx = (const int32_t*)(ctx->params + N.phi_off);
+    a.n_a = (unsigned short)N.C_in;
+    a.n_out = (unsigned short)N.C_out;
+    a.mul_in = N.M_in;
+    a.shift_in = (unsigned char)N.s_in;
+    a.batch = batch;
+    a.images = (unsigned short)images;
+    a.h = (unsigned short)(ctx->shape.H >> N.level);
+    a.w = (unsigned short)(ctx->shape.W >> N.level);
+    a.blocks = (unsigned short)C.blocks;
+    a.nc_x = (unsigned char)C.nc_x;
+    a.nc_t = (unsigned char)C.nc_t;
+    a.nc_q = (unsigned char)C.nc_q;
+    a.taps_two = (unsigned char)C.taps_two;
+    a.taps_last = (unsigned char)C.taps_last;
+    a.n_blk_last = (unsigned char)C.n_blk_last;
+    a.act_unsigned = (unsigned char)ctx->shape.act_unsigned;
+    a.relu_last = (unsigned char)L.relu;
+    a.last_fast = (unsigned char)(L.rq_fast && L.no_ties);
+    a.sign = (signed char)mode_sign;
+    if (L.mode == MODE_CODES) {
+        a.codes = codes;
+        a.codes_img_stride = ctx->d_codes;
+        a.codes_off = ctx->code_off[N.level];
+    }
+    // Over a single tile a step's weights take longer than its products, so that each miss in the L2 shows: eight
+    // workgroups per XCD read them ahead (4x4 maps: 36 -> 31 us a network at batch 16, 1 us at 256). Over more
+    // tiles they only compete with the first layers (8x8 maps at batch 256: 58 -> 59 us).
+    a.pf_blocks = (unsigned char)(images * a.h * a.w <= 32 ? 8 : 0);
+    return a;
+}
+
+// Images per workgroup with which a network runs as one launch (chain.hip); 0: layer by layer.
+//
+// Up to 128 pixels an image (deep levels) the one launch is always the shorter way: 128-wide residual networks of
+// eight blocks, 18 layers, batch 1 / 64 / 256: 4x4 maps 36 / 36 / 38 us against 92 / 105 / 130 us for a launch per
+// layer, 8x8 maps 47 / 47 / 58 us against 95 / 110 / 165 us. At 256 pixels a workgroup needs 150 us whatever the
+// batch, up to one image per compute unit, and a launch per layer needs 115 us at batch 1, 150 at 37 and 290 at 256.
+// Beyond an image per compute unit small images share a workgroup, which reads the weights once for all of them
+// (4x4 maps at batch 512: 82 us with two images, 103 with one).
+constexpr int kChainBatchFrom = 40;  // smallest batch at more than 128 pixels
+
+static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
+    if (!N.chain.ok) return 0;
+    const long long hw = (long long)(ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
+    if (hw > 32 * kChainMaxTiles || (hw > 128 && batch < kChainBatchFrom)) return 0;
+    int images = 1;
+    if (hw <= 64) images = std::min((batch + ctx->n_cu - 1) / ctx->n_cu, (int)(32 * kChainMaxTiles / hw));
+    for (; images > 0; --images)
+        if (chain_args_ok(chain_args(ctx, N, batch, images, 1, nullptr))) break;
+    return images;
+}
+
 // `next`: the network that runs after this one (its first layer's parameters are prefetched), or nullptr.
 int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st,
             const DevNet* next = nullptr) {
+    {
+        const int images = chain_images(ctx, N, batch);
+        if (images) {
+            long long macs = 0, bytes = 4LL * N.C_in + (N.layers.back().mode == MODE_CODES ? 1LL : 8LL) * N.C_out, wbytes = 0;
+            for (const DevLayer& L : N.layers) { macs += L.macs_per_pixel; wbytes += L.wgt_bytes; }
+            const long long px = (long long)batch * (ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
+            const ChainArgs ca = chain_args(ctx, N, batch, images, mode_sign, codes);
+            PROF_LAUNCH(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, launch_chain(ca, st));
+            return IODF_OK;
+        }
+    }
     const int lv = N.level;
     const int h = ctx->shape.H >> lv, w = ctx->shape.W >> lv;
     const int npix = batch * h * w;
@@ -828,6 +991,7 @@ int iodf_init(iodf_ctx** out, const void* model_blob, size_t blob_bytes, int dev
     // device side
     hipError_t e = hipSetDevice(device_ordinal);
     if (e == hipSuccess) e = conv_setup();
+    if (e == hipSuccess) e = chain_setup();
     if (e == hipSuccess) e = conv_device_cus(&ctx->n_cu);
     if (e != hipSuccess) { g_last_hip = (int)e; delete ctx; return IODF_E_HIP; }
     rc = scratch_setup(device_ordinal);

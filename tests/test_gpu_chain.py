@@ -1,0 +1,76 @@
+"""Networks that run as one launch out of LDS, against the oracle, bit-exact: every kind of kernel (stream and
+block-internal widths of one or two 64-channel planes, 1x1 and 3x3 second convolutions, no blocks at all) at the edges
+of its pixel tiles, with groups of several images, and where the requantise has exact ties."""
+import numpy as np
+import pytest
+
+import paper_2206_08869_amd as iodf
+from synth import make_blob, make_images
+from synth.configs import PLAIN, RESNET, FlowConfig
+from util import to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(cfg, batch, blob=None):
+    import oracle
+    import torch
+    blob = make_blob(cfg) if blob is None else blob
+    x = make_images(cfg, batch=batch)
+    print("chain", cfg, "batch", batch, flush=True)
+    z_ref, c_ref = oracle.Model(blob).forward(x)
+    flow = iodf.Flow(blob, max_batch=batch, device=0)
+    for _rep in range(2):
+        z, codes = flow.forward(to_gpu(x))
+        torch.cuda.synchronize()
+        assert np.array_equal(z.cpu().numpy(), z_ref)
+        if cfg.heads:
+            assert np.array_equal(codes.cpu().numpy(), c_ref)
+        x2 = flow.inverse(z)
+        torch.cuda.synchronize()
+        assert np.array_equal(x2.cpu().numpy(), x)
+    flow.close()
+
+
+# level-1 maps H/2 x W/2: 1, 2, 3..4 and 5..8 tiles of 32 pixels, full and ragged; images of 128 pixels and more run
+# as one launch from batch 40 on
+@pytest.mark.parametrize("H,W,batch", [(8, 8, 1), (8, 16, 1), (12, 12, 2), (16, 16, 1), (16, 20, 3), (16, 32, 2),
+                                       (24, 40, 41), (32, 32, 40)])
+@pytest.mark.parametrize("width,keep,k2", [(128, 1.0, 3), (128, 0.4, 3), (128, 0.4, 1), (64, 1.0, 3), (40, 0.8, 1)])
+def test_tiles_and_widths(H, W, batch, width, keep, k2):
+    _check(FlowConfig("chain", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=41, block_k2=k2), batch)
+
+
+@pytest.mark.parametrize("width,unsigned", [(128, False), (128, True), (48, True)])
+def test_plain_and_unsigned(width, unsigned):
+    _check(FlowConfig("plain", 16, 16, 3, 2, 2, PLAIN, width, 0, True, seed_id=42, act_unsigned=unsigned), 3)
+    _check(FlowConfig("res_u", 16, 16, 3, 3, 1, RESNET, width, 1, True, seed_id=43, act_unsigned=unsigned, block_k2=3), 3)
+
+
+# 4x4 and 2x2 maps: more images than compute units share workgroups, the last group is short
+@pytest.mark.parametrize("batch", [257, 515])
+def test_groups_of_images(batch):
+    _check(FlowConfig("groups", 8, 8, batch, 2, 1, RESNET, 32, 1, True, seed_id=44), batch)
+
+
+def test_ties_and_last_layers():
+    """Multipliers that are powers of two reach exact halves (away from zero, not up); a 1x1 last layer; a last layer
+    with a ReLU."""
+    from synth.model import pack_blob, parse_blob
+    cfg = FlowConfig("ties", 16, 16, 2, 2, 2, RESNET, 32, 2, True, seed_id=45)
+    m = parse_blob(make_blob(cfg).copy())
+    for n, net in enumerate(m["nets"]):
+        for l, L in enumerate(net["layers"]):
+            if n % 2 == 0:   # small weights and a coarse scale: many accumulators are odd multiples of half a code
+                L["M"][:] = 1 << 30
+                L["shift"][:] = 33
+                L["W"] //= 32
+                L["bias"] //= 256
+            elif l + 1 == len(net["layers"]):   # ties in the last layer only: the hidden ones keep the short form
+                L["M"][:] = 1 << 30
+                L["shift"][:] = 37
+        if n % 3 == 1:
+            net["layers"][-1]["W"] = np.ascontiguousarray(net["layers"][-1]["W"][:, :, 1:2, 1:2])
+        if n % 3 == 2:
+            net["layers"][-1]["flags"] |= 1
+    _check(cfg, 2, pack_blob(m))
