@@ -55,10 +55,44 @@ struct ChainKernel {
 constexpr int kChainSizes = 4;  // 1, 2, 4 and 8 tiles
 extern const ChainKernel kChain443[], kChain423[], kChain223[], kChain441[], kChain421[], kChain221[], kChain40[], kChain20[];
 
+// A network of the same kinds whose images are too large for one workgroup, or too few to fill the chip with whole
+// ones: strips of `rows` rows of an image. The stream x lives in planes as in conv.h and every launch below takes it from
+// one buffer to another: first layer (input quantiser included), one residual block, last layer.
+struct StripArgs {
+    const uint8_t* params;  // the layer's (block's) weights and constants, laid out as for ChainArgs
+    const int8_t* in;
+    int8_t* out;
+    int32_t* state;
+    const int32_t* idx;
+    int8_t* codes;
+    long long codes_img_stride, codes_off;
+    unsigned plane;
+    int batch, mul_in;
+    unsigned short h, w, rows, chunk;  // chunk: strips per XCD
+    unsigned short state_c, n_a, n_out;
+    unsigned char shift_in, act_unsigned, relu_last, last_fast, n_blk_last, taps_last, nc_q;
+    signed char sign;
+};
+struct StripKernel {
+    int nc_x, nc_t, taps_two;
+    int tiles_one, tiles_two;  // 32-pixel tiles of the block's first and second convolution (first and last layer: the same)
+    void (*kern)(const StripArgs);
+};
+constexpr int kStripThreads = 256;
+constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
+constexpr int kStripSizes = 5, kStripEnds = 2;
+extern const StripKernel kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
+extern const StripKernel kStripIn4[], kStripIn2[], kStripLast4[], kStripLast2[];
+
 size_t chain_lds_bytes(const ChainArgs& a);
 // Whether a kernel exists for this network and this many images per workgroup.
 bool chain_args_ok(const ChainArgs& a);
 hipError_t launch_chain(const ChainArgs& a, hipStream_t stream);
+// The kernel for strips of `rows` rows of h x w images, or nullptr: `block` of the residual networks with these widths,
+// or one of the ends (nc_t and taps_two unused).
+enum StripPart { STRIP_IN, STRIP_BLOCK, STRIP_LAST };
+const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int h, int w, int rows);
+hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a, hipStream_t stream);
 hipError_t chain_setup();
 
 }  // namespace iodf

@@ -7,6 +7,17 @@ namespace {
 
 const ChainKernel* const kChains[] = {kChain443, kChain423, kChain223, kChain441, kChain421, kChain221, kChain40, kChain20};
 
+const StripKernel* const kStrips[] = {kStrip443, kStrip423, kStrip223, kStrip441, kStrip421, kStrip221};
+const StripKernel* const kEnds[] = {kStripIn4, kStripIn2, kStripLast4, kStripLast2};
+
+size_t strip_lds_bytes(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int w, int rows) {
+    const int ext = taps_two == 9 ? 1 : 0;
+    const size_t px = chain_row_bytes(w, chain_pixel_bytes(nc_x));
+    if (part == STRIP_IN) return kChainConstBytes + chain_row_bytes(w, chain_pixel_bytes(nc_q)) * (size_t)(rows + 2);
+    if (part == STRIP_LAST) return kChainConstBytes + px * (rows + 2);
+    return 2 * kChainConstBytes + px * (rows + 2 + 2 * ext) + chain_row_bytes(w, chain_pixel_bytes(nc_t)) * (size_t)(rows + 2 * ext);
+}
+
 const ChainKernel* kernel_for(const ChainArgs& a) {
     const int need = (a.images * a.h * a.w + 31) / 32;
     for (const ChainKernel* t : kChains) {
@@ -38,7 +49,52 @@ hipError_t chain_setup() {
             const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainMaxLds);
             if (e != hipSuccess) return e;
         }
+    for (const StripKernel* t : kStrips)
+        for (int i = 0; i < kStripSizes; ++i) {
+            const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
+            if (e != hipSuccess) return e;
+        }
+    for (const StripKernel* t : kEnds)
+        for (int i = 0; i < kStripEnds; ++i) {
+            const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
+}
+
+const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int h, int w, int rows) {
+    if ((long long)(rows + 4) * 16 * (w + 2) * (w + 2) >= 1 << 20) return nullptr;  // the kernel's divisions by multiplication
+    if (rows < 1 || rows > h || strip_lds_bytes(part, nc_x, nc_t, taps_two, nc_q, w, rows) > kStripMaxLds) return nullptr;
+    if (part != STRIP_BLOCK) {
+        for (const StripKernel* t : kEnds) {
+            if (t->nc_x != nc_x || (part == STRIP_IN) != (t == kStripIn4 || t == kStripIn2)) continue;
+            for (int i = 0; i < kStripEnds; ++i)
+                if (rows * w <= 32 * t[i].tiles_two) return t + i;
+        }
+        return nullptr;
+    }
+    const int one = rows + (taps_two == 9 ? 2 : 0);
+    for (const StripKernel* t : kStrips) {
+        if (t->nc_x != nc_x || t->nc_t != nc_t || t->taps_two != taps_two) continue;
+        for (int i = 0; i < kStripSizes; ++i)
+            if (rows * w <= 32 * t[i].tiles_two && (one < h ? one : h) * w <= 32 * t[i].tiles_one) return t + i;
+    }
+    return nullptr;
+}
+
+hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a, hipStream_t st) {
+    if (a.batch <= 0) return hipSuccess;
+    if (!k || !a.params || (part == STRIP_IN ? !a.out || !a.state || !a.idx : !a.in) || (part == STRIP_BLOCK && !a.out) ||
+        (part == STRIP_LAST && (!a.state || !a.idx)) ||
+        k != strip_kernel_for(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.h, a.w, a.rows))
+        return hipErrorInvalidValue;
+    const int units = (a.h + a.rows - 1) / a.rows * a.batch;
+    StripArgs b = a;
+    b.chunk = (unsigned short)((units + 7) / 8);
+    if (units > 8 * 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k->kern, dim3(8 * b.chunk), dim3(kStripThreads),
+                       strip_lds_bytes(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.w, a.rows), st, b);
+    return hipGetLastError();
 }
 
 hipError_t launch_chain(const ChainArgs& a, hipStream_t st) {

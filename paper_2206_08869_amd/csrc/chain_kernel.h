@@ -37,7 +37,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // How NW waves divide n_blk blocks of 32 channels x `tiles` tiles of 32 pixels: TC blocks and TP tiles to a wave.
 template <int NW, int N_BLK, int TILES>
 struct Share {
-    static constexpr int TC = N_BLK == 4 && TILES == 8 ? 2 : 1;
+    static constexpr int TC = N_BLK == 4 && TILES > 4 ? 2 : 1;
     static constexpr int WC = N_BLK / TC, WP = NW / WC;
     static constexpr int TP = (TILES + WP - 1) / WP;
 };
@@ -118,11 +118,13 @@ __device__ __forceinline__ void chain_fetch(v4i (&w)[12], const gbytes p, const 
 }
 
 // Hidden layer's epilogue: requantise, ReLU or shortcut, 16 channels of a pixel per lane and 32x32 block, into LDS.
-// at: where each tile's pixel lies in the output tensor.
-template <int TC, int TP, bool SHORTCUT>
+// at: where each tile's pixel lies in the output tensor. With OUT the result goes there instead, to out[pixel * 64 ..]
+// of 64-channel planes, go = pixel * 64 (the shortcut still comes from LDS).
+template <int TC, int TP, bool SHORTCUT, bool OUT = false>
 __device__ __forceinline__ void chain_store(const v16i (&acc)[TC][TP], unsigned char* lds, const unsigned (&at)[TP],
                                             const int live, const int* cst, const int ch_base, const int half,
-                                            const bool act_unsigned) {
+                                            const bool act_unsigned, int8_t* out = nullptr, const unsigned plane = 0,
+                                            const unsigned* go = nullptr) {
     static_for<TC>([&](auto tc_) {
         constexpr int tc = decltype(tc_)::value;
         const int ch0 = ch_base + tc * 32;
@@ -170,7 +172,114 @@ __device__ __forceinline__ void chain_store(const v16i (&acc)[TC][TP], unsigned 
             auto x = __builtin_amdgcn_permlane32_swap(s01[0], s23[0], false, false);
             auto u = __builtin_amdgcn_permlane32_swap(s01[1], s23[1], false, false);
             const v4i o4 = {(int)x[0], (int)u[0], (int)x[1], (int)u[1]};
-            if (live >> tp & 1) *(v4i*)(lds + at[tp] + ch0 + half * 16) = o4;
+            if (live >> tp & 1) {
+                if constexpr (OUT) *(v4i*)(out + (size_t)(ch0 >> 6) * plane + go[tp] + (ch0 & 63) + half * 16) = o4;
+                else *(v4i*)(lds + at[tp] + ch0 + half * 16) = o4;
+            }
+        });
+    });
+}
+
+// Accumulators start at the bias.
+template <int TC, int TP>
+__device__ __forceinline__ void chain_bias(v16i (&acc)[TC][TP], const int* cst, const int blk, const int half) {
+    static_for<TC>([&](auto tc_) {
+        constexpr int tc = decltype(tc_)::value;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const v4i b4 = *(const v4i*)(cst + 3 * 128 + (blk + tc) * 32 + g * 8 + half * 4);
+            static_for<TP>([&](auto tp_) {
+                constexpr int tp = decltype(tp_)::value;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[tc][tp][g * 4 + e] = b4[e];
+            });
+        }
+    });
+}
+
+// Quantised input of rows [ya, yb) of some images: channel c of pixel p is sat8(rq(S[p][idx[c]])). q: the tensor, whose
+// first kept row is image row `org`. Four channels to a task, four tasks of a thread at a time: their loads, an index
+// and a word behind it each, overlap.
+template <int THREADS, class Args>
+__device__ __forceinline__ void chain_quant(const Args& a, unsigned char* q, const int img0, const int n_img, const int ya,
+                                            const int yb, const int org, const unsigned image, const unsigned row_bytes,
+                                            const unsigned pixel, const int tid) {
+    const unsigned w = a.w, hw = a.h * a.w, per = (yb - ya) * w;
+    const unsigned quads = (a.n_a + 3) >> 2, total = per * n_img * quads;
+    const int32_t* const s0 = a.state + ((long long)img0 * hw + ya * w) * a.state_c;
+    for (unsigned t0 = tid; t0 < total; t0 += 4 * THREADS) {
+        int v[4][4];
+        unsigned at[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned t = t0 + u * THREADS < total ? t0 + u * THREADS : t0, p = t / quads, g = t - p * quads;
+            const unsigned im = p / per, k = p - im * per, row = k / w, col = k - row * w;
+            const int32_t* const s = s0 + (im * hw + k) * a.state_c;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = s[a.idx[g * 4 + e < a.n_a ? g * 4 + e : 0]];
+            at[u] = im * image + (ya + row - org) * row_bytes + (col + 1) * pixel + g * 4;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (t0 + u * THREADS >= total) break;
+            const unsigned g = (t0 + u * THREADS) % quads;
+            unsigned packed = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (g * 4 + e < a.n_a) packed |= ((unsigned)sat8_dev(rq_dev(v[u][e], a.mul_in, a.shift_in)) & 0xffu) << (8 * e);
+            *(unsigned*)(q + at[u]) = packed;
+        }
+    }
+}
+
+// Epilogue of the last layer: requantise, then add into the state or write head codes. ix: physical channels of this
+// lane's sixteen filters (see chain_last_channels); gp: each tile's pixel, image * hw + q, or -1.
+template <class Args>
+__device__ __forceinline__ void chain_last_channels(const Args& a, int (&ix)[16], const int blk, const int half) {
+    static_for<16>([&](auto r_) {
+        constexpr int r = decltype(r_)::value;
+        const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        ix[r] = a.codes ? 0 : a.idx[a.n_a + (n < a.n_out ? n : a.n_out - 1)];
+    });
+}
+
+template <int TP, class Args>
+__device__ __forceinline__ void chain_last_store(const Args& a, const v16i (&acc)[1][TP], const int (&gp)[TP], const int (&ix)[16],
+                                                 const int* cst, const int blk, const int half) {
+    const int hw = a.h * a.w;
+    auto result = [&](int acc, int n) {
+        int y;
+        if (a.last_fast) y = (__mulhi(acc, cst[128 + n]) + (1 << (cst[256 + n] - 33))) >> (cst[256 + n] - 32);
+        else y = rq_dev(acc, cst[128 + n], cst[256 + n]);
+        if (a.relu_last) y = y < 0 ? 0 : y;
+        return sat8_dev(y);
+    };
+    if (a.codes) {
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            if (gp[tp] < 0) return;
+            const int bi = gp[tp] / hw, qi = gp[tp] - bi * hw;
+            int8_t* const cp = a.codes + (long long)bi * a.codes_img_stride + a.codes_off + qi;
+            static_for<16>([&](auto r_) {
+                constexpr int r = decltype(r_)::value;
+                const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+                if (n < a.n_out) cp[n * hw] = (int8_t)result(acc[0][tp][r], n);
+            });
+        });
+        return;
+    }
+    // The state words this lane updates: all on their way before the first is needed. Lanes past the last pixel
+    // and filters past the last one read a word that exists and write nothing.
+    static_for<TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int32_t* const sp = a.state + (long long)(gp[tp] < 0 ? 0 : gp[tp]) * a.state_c;
+        int v[16];
+        static_for<16>([&](auto r_) { v[decltype(r_)::value] = sp[ix[decltype(r_)::value]]; });
+        if (gp[tp] < 0) return;
+        static_for<16>([&](auto r_) {
+            constexpr int r = decltype(r_)::value;
+            const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+            if (n < a.n_out) sp[ix[r]] = v[r] + a.sign * result(acc[0][tp][r], n);
         });
     });
 }
@@ -245,32 +354,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         put_const(0, c0);
     }
     lds_barrier();
-    {
-        // quantised input: channel c of pixel p is sat8(rq(S[p][idx[c]])). Four channels to a task, four tasks of a
-        // thread at a time: their loads, an index and a word behind it each, overlap.
-        const unsigned quads = (a.n_a + 3) >> 2, total = (unsigned)M * quads;
-        const int32_t* const s0 = a.state + (long long)img0 * hw * a.state_c;
-        for (unsigned t0 = tid; t0 < total; t0 += 4 * kThreads) {
-            int v[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const unsigned t = t0 + u * kThreads < total ? t0 + u * kThreads : t0, p = t / quads, g = t - p * quads;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[u][e] = s0[p * a.state_c + a.idx[g * 4 + e < a.n_a ? g * 4 + e : 0]];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const unsigned t = t0 + u * kThreads, p = t / quads, g = t - p * quads;
-                if (t >= total) break;
-                unsigned packed = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if ((int)g * 4 + e < a.n_a) packed |= ((unsigned)sat8_dev(rq_dev(v[u][e], a.mul_in, a.shift_in)) & 0xffu) << (8 * e);
-                const unsigned im = p / hw, q = p - im * hw, row = q / w, col = q - row * w;
-                *(unsigned*)(lds + qb + im * isq + (row + 1) * rpq + (col + 1) * psq + g * 4) = packed;
-            }
-        }
-    }
+    chain_quant<kThreads>(a, lds + qb, img0, n_img, 0, h, -1, isq, rpq, psq, tid);
 
     // Where the pixels of this wave's tiles lie: image, row, column, as byte offsets of tap (0, 0) in each tensor.
     // Lanes past the last pixel repeat it and store nothing.
@@ -309,21 +393,6 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     for (int i = 0; i < ST::TP; ++i) to[i] = t_of_t[i] + rpt + pst;
     lds_barrier();
 
-    auto bias_to = [&](auto& acc, const int* cst, int blk) {
-        constexpr int TP = sizeof(acc[0]) / sizeof(v16i), TC = sizeof(acc) / sizeof(acc[0]);
-        static_for<TC>([&](auto tc_) {
-            constexpr int tc = decltype(tc_)::value;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const v4i b4 = *(const v4i*)(cst + 3 * 128 + (blk + tc) * 32 + g * 8 + half * 4);
-                static_for<TP>([&](auto tp_) {
-                    constexpr int tp = decltype(tp_)::value;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[tc][tp][g * 4 + e] = b4[e];
-                });
-            }
-        });
-    };
     const int* const cst0 = (const int*)lds;
     const int* const cst1 = (const int*)(lds + kChainConstBytes);
 
@@ -334,7 +403,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     {
         const v4i cn = fetch_const(NCT ? blockp + w_one : blockp + a.n_blk_last * a.taps_last * NCX * 1024);
         v16i acc[SX::TC][SX::TP];
-        bias_to(acc, cst0, xblk);
+        chain_bias(acc, cst0, xblk, half);
         if (a.nc_q == 1) chain_products<SX::TC, SX::TP, 1, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
         else chain_products<SX::TC, SX::TP, 2, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
         if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
@@ -351,7 +420,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
             {
                 const v4i cn = fetch_const(blockp + bytes_one + w_two);
                 v16i acc[ST::TC][ST::TP];
-                bias_to(acc, cst1, tblk);
+                chain_bias(acc, cst1, tblk, half);
                 chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_of_t, rpx, uniform(p_one), uniform(p_two), tcs_two, lane16);
                 constexpr int got = carry_one ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0;
                 chain_fetch<SX::TC, NCT, NT2, got>(wf, uniform(p_two), lane16);
@@ -362,7 +431,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
             {
                 const v4i cn = fetch_const(last ? blockp + bytes_block + a.n_blk_last * a.taps_last * NCX * 1024 : next + w_one);
                 v16i acc[SX::TC][SX::TP];
-                bias_to(acc, cst0, xblk);
+                chain_bias(acc, cst0, xblk, half);
                 unsigned at[SX::TP];  // a 1x1 kernel begins at the pixel itself
 #pragma unroll
                 for (int i = 0; i < SX::TP; ++i) at[i] = NT2 == 1 ? t_of_x[i] + rpt + pst : t_of_x[i];
@@ -394,50 +463,12 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
             at[tp] = xb + im * isx + (row + (NT == 1)) * rpx + (col + (NT == 1)) * psx + half * 16;
             gp[tp] = live ? (img0 + im) * hw + row * w + col : -1;
         });
-        int ix[16];  // physical channels of this lane's filters
-        static_for<16>([&](auto r_) {
-            constexpr int r = decltype(r_)::value;
-            const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-            ix[r] = a.codes ? 0 : a.idx[a.n_a + (n < a.n_out ? n : a.n_out - 1)];
-        });
-        auto result = [&](int acc, int n) {
-            int y;
-            if (a.last_fast) y = (__mulhi(acc, cst1[128 + n]) + (1 << (cst1[256 + n] - 33))) >> (cst1[256 + n] - 32);
-            else y = rq_dev(acc, cst1[128 + n], cst1[256 + n]);
-            if (a.relu_last) y = y < 0 ? 0 : y;
-            return sat8_dev(y);
-        };
+        int ix[16];
+        chain_last_channels(a, ix, blk, half);
         v16i acc[1][TP];
-        bias_to(acc, cst1, blk);
+        chain_bias(acc, cst1, blk, half);
         chain_products<1, TP, NCX, NT>(acc, wf, lds, at, rpx, p, p, 0, lane16);
-        if (a.codes) {
-            static_for<TP>([&](auto tp_) {
-                constexpr int tp = decltype(tp_)::value;
-                if (gp[tp] < 0) return;
-                const int bi = gp[tp] / hw, qi = gp[tp] - bi * hw;
-                int8_t* const cp = a.codes + (long long)bi * a.codes_img_stride + a.codes_off + qi;
-                static_for<16>([&](auto r_) {
-                    constexpr int r = decltype(r_)::value;
-                    const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-                    if (n < a.n_out) cp[n * hw] = (int8_t)result(acc[0][tp][r], n);
-                });
-            });
-            return;
-        }
-        // The state words this lane updates: all on their way before the first is needed. Filters past the last one
-        // read its word and write nothing.
-        static_for<TP>([&](auto tp_) {
-            constexpr int tp = decltype(tp_)::value;
-            int32_t* const sp = a.state + (long long)(gp[tp] < 0 ? img0 * hw : gp[tp]) * a.state_c;
-            int v[16];
-            static_for<16>([&](auto r_) { v[decltype(r_)::value] = sp[ix[decltype(r_)::value]]; });
-            if (gp[tp] < 0) return;
-            static_for<16>([&](auto r_) {
-                constexpr int r = decltype(r_)::value;
-                const int n = blk * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-                if (n < a.n_out) sp[ix[r]] = v[r] + a.sign * result(acc[0][tp][r], n);
-            });
-        });
+        chain_last_store<TP>(a, acc, gp, ix, cst1, blk, half);
     };
     using I1 = std::integral_constant<int, 1>;
     using I3 = std::integral_constant<int, 3>;

@@ -241,6 +241,7 @@ struct DevLayer {
 struct DevChain {
     bool ok = false;
     size_t off = 0, bytes = 0;  // its parameters, one block of the arena
+    size_t in_bytes = 0, block_bytes = 0;  // of these the first layer's and a residual block's
     int nc_x = 0, nc_t = 0, nc_q = 0, blocks = 0, taps_two = 0, taps_last = 0, n_blk_last = 0;
 };
 
@@ -460,6 +461,8 @@ void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
         const DevLayer& L = D.layers[l];
         const int nc = l == 0 ? C.nc_q : L.cin_pad / 32, n_blk = l + 1 == nl ? C.n_blk_last : L.n_pad / 32;
         total += (nw[l] = (size_t)n_blk * L.taps * nc * 1024) + kChainConstBytes;
+        if (l == 0) C.in_bytes = total;
+        if (l == 2 && l + 1 < nl) C.block_bytes = total - C.in_bytes;
     }
     C.bytes = total;
     C.off = A.alloc(total + kChainOverread);
@@ -563,6 +566,7 @@ void plan_net(Arena& A, const HostModel& m, const HostNet& N, DevNet& D, int buf
         D.layers[nl - 1].in_buf = BUF_A; D.layers[nl - 1].in_off = 0; D.layers[nl - 1].out_buf = -1;
         D.layers[nl - 1].out_off = 0;
         pack_chain(A, m, N, D);
+        if (D.chain.ok) buf_w[BUF_B] = std::max(buf_w[BUF_B], rw);  // strips pass the stream between the two buffers
     } else {
         // BUF_A: concatenation of the compacted feature blocks f0..f_depth; BUF_B: bottleneck g
         const int depth = (nl - 2) / 2;
@@ -663,9 +667,9 @@ struct iodf_ctx {
 
 namespace {
 
-enum { CLS_QUANT_IN = 0, CLS_FILL_ZERO, CLS_CHAIN, CLS_INGEST, CLS_FACTOR_OUT, CLS_UNFACTOR, CLS_EMIT_X, CLS_TAPSUM,
+enum { CLS_QUANT_IN = 0, CLS_FILL_ZERO, CLS_CHAIN, CLS_STRIP_IN, CLS_STRIP_BLOCK, CLS_STRIP_LAST, CLS_INGEST, CLS_FACTOR_OUT, CLS_UNFACTOR, CLS_EMIT_X, CLS_TAPSUM,
        CLS_PRIOR_CF, CLS_RANS_ENCODE, CLS_RANS_PACK, CLS_RANS_DECODE, NUM_FLOW_CLS };
-const char* const kFlowClsName[NUM_FLOW_CLS] = {"k_quant_in", "k_fill_zero", "k_chain", "k_ingest_squeeze",
+const char* const kFlowClsName[NUM_FLOW_CLS] = {"k_quant_in", "k_fill_zero", "k_chain", "k_strip_in", "k_strip_block", "k_strip_last", "k_ingest_squeeze",
                                                 "k_factor_out", "k_unfactor", "k_emit_x", "conv_tapsum",
                                                 "k_prior_cf", "k_rans_encode", "k_rans_pack", "k_rans_decode_chunk"};
 
@@ -756,16 +760,16 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
 //
 // Up to 128 pixels an image (deep levels) the one launch is always the shorter way: 128-wide residual networks of
 // eight blocks, 18 layers, batch 1 / 64 / 256: 4x4 maps 36 / 36 / 38 us against 92 / 105 / 130 us for a launch per
-// layer, 8x8 maps 47 / 47 / 58 us against 95 / 110 / 165 us. At 256 pixels a workgroup needs 150 us whatever the
-// batch, up to one image per compute unit, and a launch per layer needs 115 us at batch 1, 150 at 37 and 290 at 256.
+// layer, 8x8 maps 47 / 47 / 58 us against 95 / 110 / 165 us. At 256 pixels a workgroup needs 147 us whatever the
+// batch, up to one image per compute unit, and strips (strip_plan) 100 us at batch 1, 119 at 64, 158 at 128.
 // Beyond an image per compute unit small images share a workgroup, which reads the weights once for all of them
 // (4x4 maps at batch 512: 82 us with two images, 103 with one).
-constexpr int kChainBatchFrom = 40;  // smallest batch at more than 128 pixels
+static int chain_batch_from(const iodf_ctx* ctx) { return ctx->n_cu * 2 / 5; }  // smallest batch at more than 128 pixels
 
 static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
     if (!N.chain.ok) return 0;
     const long long hw = (long long)(ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
-    if (hw > 32 * kChainMaxTiles || (hw > 128 && batch < kChainBatchFrom)) return 0;
+    if (hw > 32 * kChainMaxTiles || (hw > 128 && N.chain.blocks && batch < chain_batch_from(ctx))) return 0;
     int images = 1;
     if (hw <= 64) images = std::min((batch + ctx->n_cu - 1) / ctx->n_cu, (int)(32 * kChainMaxTiles / hw));
     for (; images > 0; --images)
@@ -773,12 +777,108 @@ static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
     return images;
 }
 
+// Rows per strip for the three kinds of launch; rows[STRIP_BLOCK] = 0: not this way.
+//
+// The most rows that still give a strip to every compute unit, up to what the kernels hold: more rows mean fewer rows
+// computed twice and weights read less often, fewer rows a shorter way through a launch. 32x32 maps, whole call of
+// paper_res64 against a launch per layer, rows 4 / 2 / 1: batch 1 +209 / -66 / -133 us, batch 16 -187 / -422 / -104,
+// batch 64 -568 / +11 / +1502, batch 256 -234 / +1622 / +7283.
+struct StripPlan { int rows[3]; };
+
+static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
+    StripPlan p = {{0, 0, 0}};
+    const DevChain& C = N.chain;
+    if (!C.ok || !C.blocks) return p;
+    const int h = ctx->shape.H >> N.level, w = ctx->shape.W >> N.level;
+    auto rows_for = [&](StripPart part) {
+        int best = 0;
+        for (int r = 1; r <= h; ++r) {
+            if (!strip_kernel_for(part, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, r)) continue;
+            const int strips = (h + r - 1) / r;
+            if (best && (long long)batch * strips < ctx->n_cu) break;
+            if (best && strips == (h + best - 1) / best) continue;  // the same strips, less evenly cut
+            best = r;
+        }
+        return best;
+    };
+    const int in = rows_for(STRIP_IN), block = rows_for(STRIP_BLOCK), last = rows_for(STRIP_LAST);
+    if (in && block && last) {
+        p.rows[STRIP_IN] = in;
+        p.rows[STRIP_BLOCK] = block;
+        p.rows[STRIP_LAST] = last;
+    }
+    return p;
+}
+
+static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st, const StripPlan& p) {
+    const DevChain& C = N.chain;
+    const DevLayer& last = N.layers.back();
+    const int lv = N.level, h = ctx->shape.H >> lv, w = ctx->shape.W >> lv;
+    const long long px = (long long)batch * h * w;
+    StripArgs a;
+    memset(&a, 0, sizeof(a));
+    a.state = ctx->state[lv];
+    a.state_c = (unsigned short)N.C;
+    a.idx = (const int32_t*)(ctx->params + N.phi_off);
+    a.n_a = (unsigned short)N.C_in;
+    a.n_out = (unsigned short)N.C_out;
+    a.mul_in = N.M_in;
+    a.shift_in = (unsigned char)N.s_in;
+    a.plane = (unsigned)ctx->plane[lv];
+    a.batch = batch;
+    a.h = (unsigned short)h;
+    a.w = (unsigned short)w;
+    a.nc_q = (unsigned char)C.nc_q;
+    a.act_unsigned = (unsigned char)ctx->shape.act_unsigned;
+    a.relu_last = (unsigned char)last.relu;
+    a.last_fast = (unsigned char)(last.rq_fast && last.no_ties);
+    a.n_blk_last = (unsigned char)C.n_blk_last;
+    a.taps_last = (unsigned char)C.taps_last;
+    a.sign = (signed char)mode_sign;
+    if (last.mode == MODE_CODES) {
+        a.codes = codes;
+        a.codes_img_stride = ctx->d_codes;
+        a.codes_off = ctx->code_off[lv];
+    }
+    auto kernel = [&](StripPart part) {
+        a.rows = (unsigned short)p.rows[part];
+        return strip_kernel_for(part, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, p.rows[part]);
+    };
+    const long long xbytes = 32LL * C.nc_x;  // stream bytes of a pixel
+    auto macs = [&](int l) { return N.layers[(size_t)l].macs_per_pixel * px; };
+    auto wbytes = [&](int l) { return N.layers[(size_t)l].wgt_bytes; };
+    int cur = BUF_A;
+    a.params = ctx->params + C.off;
+    a.out = ctx->buf[lv][cur];
+    const StripKernel* k = kernel(STRIP_IN);
+    PROF_LAUNCH(ctx, st, CLS_STRIP_IN, macs(0), (4LL * N.C_in + xbytes) * px + wbytes(0), launch_strip(STRIP_IN, k, a, st));
+    k = kernel(STRIP_BLOCK);
+    for (int b = 0; b < C.blocks; ++b) {
+        a.params = ctx->params + C.off + C.in_bytes + (size_t)b * C.block_bytes;
+        a.in = ctx->buf[lv][cur];
+        cur = BUF_A + BUF_B - cur;
+        a.out = ctx->buf[lv][cur];
+        PROF_LAUNCH(ctx, st, CLS_STRIP_BLOCK, macs(1 + 2 * b) + macs(2 + 2 * b),
+                    2 * xbytes * px + wbytes(1 + 2 * b) + wbytes(2 + 2 * b), launch_strip(STRIP_BLOCK, k, a, st));
+    }
+    a.params = ctx->params + C.off + C.in_bytes + (size_t)C.blocks * C.block_bytes;
+    a.in = ctx->buf[lv][cur];
+    const int nl = (int)N.layers.size();
+    k = kernel(STRIP_LAST);
+    PROF_LAUNCH(ctx, st, CLS_STRIP_LAST, macs(nl - 1), (xbytes + (codes ? 1LL : 8LL) * N.C_out) * px + wbytes(nl - 1),
+                launch_strip(STRIP_LAST, k, a, st));
+    return IODF_OK;
+}
+
 // `next`: the network that runs after this one (its first layer's parameters are prefetched), or nullptr.
 int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st,
             const DevNet* next = nullptr) {
     {
         const int images = chain_images(ctx, N, batch);
-        if (images) {
+        if (!images) {
+            const StripPlan p = strip_plan(ctx, N, batch);
+            if (p.rows[STRIP_BLOCK]) return run_strips(ctx, N, batch, mode_sign, codes, st, p);
+        } else {
             long long macs = 0, bytes = 4LL * N.C_in + (N.layers.back().mode == MODE_CODES ? 1LL : 8LL) * N.C_out, wbytes = 0;
             for (const DevLayer& L : N.layers) { macs += L.macs_per_pixel; wbytes += L.wgt_bytes; }
             const long long px = (long long)batch * (ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);

@@ -1,0 +1,301 @@
+// Strips of images through the layers of a narrow network (see chain.h): the same products and epilogues as
+// chain_kernel.h, with the stream x in global memory between launches.
+//
+// A launch per layer fetches its activations nine times from the L2 (once per tap) and a block's inner tensor goes out
+// and comes back. Here a workgroup loads its strip and the rows around it once, runs both convolutions of a block on
+// it, the first one on one row more on either side, and writes the result.
+//
+// Bound. Blocks of two 3x3 layers, 128 wide, strips of four rows of 32 pixels, in clocks of a CU: request to LDS 5000,
+// products 9000 + 6800 (matrix cores 6900 + 4600, a quarter of it for the rows that two strips both compute), epilogues
+// 3500 + 3100. Two workgroups share a CU, so that the loads and epilogues of one run under the other's products: a pair
+// takes 41000. With a
+// strip or less per CU the length of that chain is what counts, hence strips down to a single row.
+#pragma once
+#include "chain_kernel.h"
+
+namespace iodf {
+
+namespace {
+
+struct StripGeom {
+    int img, r0, r1;
+};
+
+__device__ __forceinline__ bool strip_of(const StripArgs& a, StripGeom& g) {
+    const int strips = (a.h + a.rows - 1) / a.rows;
+    const int unit = (int)(blockIdx.x & 7) * a.chunk + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= a.chunk || unit >= strips * a.batch) return false;
+    g.img = unit / strips;
+    g.r0 = (unit - g.img * strips) * a.rows;
+    g.r1 = g.r0 + a.rows < a.h ? g.r0 + a.rows : a.h;
+    return true;
+}
+
+// Rows [y0, y1) of the stream (padding rows and columns included) into LDS, 16 bytes per thread and step, consecutive
+// threads on consecutive parts of a 64-channel plane. The first kStripLoads steps' loads are all requested by
+// strip_request, before anything else the kernel asks for, so that strip_put waits for one memory latency only.
+constexpr int kStripLoads = 9;
+
+template <int NCX>
+__device__ __forceinline__ const int8_t* strip_source(const StripArgs& a, const int img, const int y0, const int y1, const int t,
+                                                      unsigned& pl, unsigned& k) {
+    const unsigned W2 = a.w + 2, per = W2 * 4 * (y1 - y0);
+    pl = NCX == 4 && (unsigned)t >= per ? 1u : 0u;
+    k = t - pl * per;
+    return a.in + ((size_t)img * (a.h + 2) * W2 + (size_t)(y0 + 1) * W2) * 64 + (size_t)pl * a.plane + (size_t)k * 16;
+}
+
+template <int NCX>
+__device__ __forceinline__ void strip_request(const StripArgs& a, v4i (&v)[kStripLoads], const int img, const int y0, const int y1,
+                                              const int tid) {
+    const int total = (a.w + 2) * 4 * (y1 - y0) * (NCX / 2);
+#pragma unroll
+    for (int u = 0; u < kStripLoads; ++u) {
+        const int t = tid + u * kStripThreads;
+        unsigned pl, k;
+        v[u] = *(const v4i*)strip_source<NCX>(a, img, y0, y1, t < total ? t : 0, pl, k);
+    }
+}
+
+template <int NCX>
+__device__ __forceinline__ void strip_put(const StripArgs& a, const v4i (&v)[kStripLoads], unsigned char* x, const int img,
+                                          const int y0, const int y1, const unsigned rp, const int tid) {
+    constexpr unsigned ps = chain_pixel_bytes(NCX);
+    const unsigned per_row = (a.w + 2) * 4, inv = ((1u << kInvBits) + per_row - 1) / per_row;
+    const int total = per_row * (y1 - y0) * (NCX / 2);
+    auto put = [&](const v4i& d, unsigned pl, unsigned k) {
+        const unsigned row = __umul24(k, inv) >> kInvBits, c = k - row * per_row;
+        *(v4i*)(x + row * rp + (c >> 2) * ps + pl * 64 + (c & 3) * 16) = d;
+    };
+#pragma unroll
+    for (int u = 0; u < kStripLoads; ++u) {
+        const int t = tid + u * kStripThreads;
+        unsigned pl, k;
+        (void)strip_source<NCX>(a, img, y0, y1, t, pl, k);
+        if (t < total) put(v[u], pl, k);
+    }
+    for (int t = tid + kStripLoads * kStripThreads; t < total; t += kStripThreads) {
+        unsigned pl, k;
+        const v4i d = *(const v4i*)strip_source<NCX>(a, img, y0, y1, t, pl, k);
+        put(d, pl, k);
+    }
+}
+
+// 16 bytes per thread of a layer's constants; the first half of the threads hold them.
+__device__ __forceinline__ v4i strip_consts(const gbytes at, const int tid) {
+    return *(gv4i)(at + (tid & (kChainConstBytes / 16 - 1)) * 16);
+}
+__device__ __forceinline__ void strip_put_consts(unsigned char* lds, const v4i& v, const int buf, const int tid) {
+    if (tid < kChainConstBytes / 16) *(v4i*)(lds + buf * kChainConstBytes + tid * 16) = v;
+}
+
+// Pixel of lane l32 in a tile of rows [y0, y1): row, column; false past the last one (which is repeated).
+__device__ __forceinline__ bool strip_pixel(int tile, int l32, int w, unsigned inv_w, int y0, int y1, int& row, int& col) {
+    const int M = (y1 - y0) * w;
+    int m = tile * 32 + l32;
+    const bool live = m < M;
+    m = live ? m : M - 1;
+    const int q = (int)(__umul24((unsigned)m, inv_w) >> kInvBits);
+    row = y0 + q;
+    col = m - q * w;
+    return live;
+}
+
+// One residual block. T1, T2: tiles of the first and second convolution.
+template <int NCX, int NCT, int NT2, int T1, int T2>
+__global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned lane16 = lane * 16;
+    StripGeom g;
+    if (!strip_of(a, g)) return;
+    constexpr int EXT = NT2 == 3 ? 1 : 0;  // rows of the inner tensor beyond the strip
+    const int h = a.h, w = a.w, W2 = w + 2;
+    const int xo = g.r0 - 1 - EXT > -1 ? g.r0 - 1 - EXT : -1, xe = g.r1 + 1 + EXT < h + 1 ? g.r1 + 1 + EXT : h + 1;
+    const int to = g.r0 - EXT, te = g.r1 + EXT;                          // kept rows of t, and of these the image's
+    const int ty0 = to > 0 ? to : 0, ty1 = te < h ? te : h;
+    constexpr unsigned psx = chain_pixel_bytes(NCX), pst = chain_pixel_bytes(NCT);
+    const unsigned rpx = chain_row_bytes(w, psx), rpt = chain_row_bytes(w, pst);
+    constexpr unsigned xb = 2 * kChainConstBytes;
+    const unsigned tb = xb + rpx * (xe - xo), end = tb + rpt * (te - to);
+
+    using ST = Share<4, NCT, T1>;
+    using SX = Share<4, NCX, T2>;
+    const int tblk = wave % ST::WC * ST::TC, xblk = wave % SX::WC * SX::TC;
+    constexpr unsigned w_one = NCT * 9 * NCX * 1024, w_two = NCX * NT2 * NT2 * NCT * 1024;
+    const gbytes par = (gbytes)a.params;
+    const gbytes p_one = uniform(par + tblk * 9 * NCX * 1024);
+    const gbytes p_two = uniform(par + w_one + kChainConstBytes + xblk * NT2 * NT2 * NCT * 1024);
+    v4i xv[kStripLoads];
+    strip_request<NCX>(a, xv, g.img, xo, xe, tid);
+    const v4i c1 = strip_consts(par + w_one, tid), c0 = strip_consts(par + w_one + kChainConstBytes + w_two, tid);
+    v4i wf[12];
+    static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+    chain_fetch<ST::TC, NCX, 3, 0>(wf, p_one, lane16);
+    __builtin_amdgcn_sched_barrier(0);
+    const int pad = a.act_unsigned ? (int)0x80808080 : 0;
+    for (unsigned o = tb + tid * 16; o < end; o += kStripThreads * 16) *(v4i*)(lds + o) = v4i{pad, pad, pad, pad};
+    const unsigned inv_w = ((1u << kInvBits) + w - 1) / w;
+    unsigned x_in[ST::TP], t_out[ST::TP], t_in[SX::TP], x_sc[SX::TP], go[SX::TP];
+    int live_t = 0, live_x = 0;
+    static_for<ST::TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int row, col;
+        if (strip_pixel(wave / ST::WC * ST::TP + tp, l32, w, inv_w, ty0, ty1, row, col)) live_t |= 1 << tp;
+        x_in[tp] = xb + (row - 1 - xo) * rpx + col * psx + half * 16;
+        t_out[tp] = tb + (row - to) * rpt + (col + 1) * pst;
+    });
+    static_for<SX::TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int row, col;
+        if (strip_pixel(wave / SX::WC * SX::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col)) live_x |= 1 << tp;
+        t_in[tp] = tb + (row - EXT - to) * rpt + (col + 1 - EXT) * pst + half * 16;
+        x_sc[tp] = xb + (row - xo) * rpx + (col + 1) * psx;
+        go[tp] = (unsigned)(((g.img * (h + 2) + row + 1) * W2 + col + 1) * 64);
+    });
+    strip_put<NCX>(a, xv, lds + xb, g.img, xo, xe, rpx, tid);
+    strip_put_consts(lds, c1, 1, tid);
+    strip_put_consts(lds, c0, 0, tid);
+    lds_barrier();
+    const int* const cst0 = (const int*)lds;
+    const int* const cst1 = (const int*)(lds + kChainConstBytes);
+    {
+        v16i acc[ST::TC][ST::TP];
+        chain_bias(acc, cst1, tblk, half);
+        constexpr bool carry = ST::TC == SX::TC;
+        constexpr unsigned tcs_two = SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0;
+        chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_in, rpx, p_one, carry ? p_two : p_one,
+                                               carry ? tcs_two : (ST::TC == 2 ? 9 * NCX * 1024 : 0), lane16);
+        chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0>(wf, p_two, lane16);
+        chain_store<ST::TC, ST::TP, false>(acc, lds, t_out, live_t, cst1, tblk * 32, half, a.act_unsigned);
+    }
+    lds_barrier();
+    {
+        v16i acc[SX::TC][SX::TP];
+        chain_bias(acc, cst0, xblk, half);
+        chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, t_in, rpt, p_two, p_two, SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0, lane16);
+        chain_store<SX::TC, SX::TP, true, true>(acc, lds, x_sc, live_x, cst0, xblk * 32, half, a.act_unsigned, a.out, a.plane, go);
+    }
+}
+
+// Input quantiser and first layer.
+template <int NCX, int T>
+__global__ __launch_bounds__(kStripThreads, 2) void k_strip_in(const StripArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned lane16 = lane * 16;
+    StripGeom g;
+    if (!strip_of(a, g)) return;
+    const int h = a.h, w = a.w, W2 = w + 2;
+    const int qo = g.r0 - 1, qe = g.r1 + 1, ya = qo > 0 ? qo : 0, yb = qe < h ? qe : h;
+    const unsigned psq = chain_pixel_bytes(a.nc_q), rpq = chain_row_bytes(w, psq);
+    constexpr unsigned qb = kChainConstBytes;
+    const unsigned end = qb + rpq * (qe - qo);
+    using S = Share<4, NCX, T>;
+    const int blk = wave % S::WC * S::TC;
+    const gbytes par = (gbytes)a.params;
+    const gbytes p = uniform(par + blk * 9 * a.nc_q * 1024);
+    v4i wf[12];
+    static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+    if (a.nc_q == 1) chain_fetch<S::TC, 1, 3, 0>(wf, p, lane16);
+    else chain_fetch<S::TC, 2, 3, 0>(wf, p, lane16);
+    const v4i c0 = strip_consts(par + NCX * 9 * a.nc_q * 1024, tid);
+    for (unsigned o = qb + tid * 16; o < end; o += kStripThreads * 16) *(v4i*)(lds + o) = v4i{0, 0, 0, 0};
+    lds_barrier();
+    strip_put_consts(lds, c0, 0, tid);
+    chain_quant<kStripThreads>(a, lds + qb, g.img, 1, ya, yb, qo, 0, rpq, psq, tid);
+    const unsigned inv_w = ((1u << kInvBits) + w - 1) / w;
+    unsigned q_in[S::TP], go[S::TP];
+    int live = 0;
+    static_for<S::TP>([&](auto tp_) {
+        constexpr int tp = decltype(tp_)::value;
+        int row, col;
+        if (strip_pixel(wave / S::WC * S::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col)) live |= 1 << tp;
+        q_in[tp] = qb + (row - 1 - qo) * rpq + col * psq + half * 16;
+        go[tp] = (unsigned)(((g.img * (h + 2) + row + 1) * W2 + col + 1) * 64);
+    });
+    lds_barrier();
+    const int* const cst = (const int*)lds;
+    v16i acc[S::TC][S::TP];
+    chain_bias(acc, cst, blk, half);
+    const unsigned tcs = S::TC == 2 ? 9 * a.nc_q * 1024 : 0;
+    if (a.nc_q == 1) chain_products<S::TC, S::TP, 1, 3>(acc, wf, lds, q_in, rpq, p, p, tcs, lane16);
+    else chain_products<S::TC, S::TP, 2, 3>(acc, wf, lds, q_in, rpq, p, p, tcs, lane16);
+    chain_store<S::TC, S::TP, false, true>(acc, lds, q_in, live, cst, blk * 32, half, a.act_unsigned, a.out, a.plane, go);
+}
+
+// Last layer.
+template <int NCX, int T>
+__global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const unsigned lane16 = lane * 16;
+    StripGeom g;
+    if (!strip_of(a, g)) return;
+    const int h = a.h, w = a.w;
+    const int xo = g.r0 - 1, xe = g.r1 + 1;
+    constexpr unsigned psx = chain_pixel_bytes(NCX), xb = kChainConstBytes;
+    const unsigned rpx = chain_row_bytes(w, psx), inv_w = ((1u << kInvBits) + w - 1) / w;
+    const gbytes par = (gbytes)a.params;
+    v4i xv[kStripLoads];
+    strip_request<NCX>(a, xv, g.img, xo, xe, tid);
+    const v4i c0 = strip_consts(par + a.n_blk_last * a.taps_last * NCX * 1024, tid);
+    const int* const cst = (const int*)lds;
+    auto run = [&](auto n_blk_, auto nt_) {
+        constexpr int NT = decltype(nt_)::value;
+        using S = Share<4, decltype(n_blk_)::value, T>;
+        const int blk = wave % S::WC;
+        const gbytes p = uniform(par + blk * NT * NT * NCX * 1024);
+        v4i wf[12];
+        static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+        chain_fetch<1, NCX, NT, 0>(wf, p, lane16);
+        int ix[16];
+        chain_last_channels(a, ix, blk, half);
+        unsigned at[S::TP];
+        int gp[S::TP];
+        static_for<S::TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int row, col;
+            const bool live = strip_pixel(wave / S::WC * S::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col);
+            at[tp] = xb + (row - (NT == 3) - xo) * rpx + (col + (NT == 1)) * psx + half * 16;
+            gp[tp] = live ? (g.img * h + row) * w + col : -1;
+        });
+        strip_put<NCX>(a, xv, lds + xb, g.img, xo, xe, rpx, tid);
+        strip_put_consts(lds, c0, 0, tid);
+        lds_barrier();
+        v16i acc[1][S::TP];
+        chain_bias(acc, cst, blk, half);
+        chain_products<1, S::TP, NCX, NT>(acc, wf, lds, at, rpx, p, p, 0, lane16);
+        chain_last_store<S::TP>(a, acc, gp, ix, cst, blk, half);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    if (a.taps_last == 9) {
+        if (a.n_blk_last == 1) run(I1{}, I3{});
+        else run(I2{}, I3{});
+    } else {
+        if (a.n_blk_last == 1) run(I1{}, I1{});
+        else run(I2{}, I1{});
+    }
+}
+
+}  // namespace
+
+template <int NCX, int NCT, int NT2, int T1, int T2>
+constexpr StripKernel strip_kernel() {
+    return StripKernel{NCX, NCT, NT2 * NT2, T1, T2, k_strip_block<NCX, NCT, NT2, T1, T2>};
+}
+// Every wave's work is fixed by the tiles a kernel is compiled for, so the small ones are worth their own.
+#define IODF_STRIP_TABLE(NAME, NCX, NCT, NT2)                                                                       \
+    const StripKernel NAME[kStripSizes] = {strip_kernel<NCX, NCT, NT2, 2, 1>(), strip_kernel<NCX, NCT, NT2, 3, 1>(), \
+                                           strip_kernel<NCX, NCT, NT2, 3, 2>(), strip_kernel<NCX, NCT, NT2, 4, 2>(), \
+                                           strip_kernel<NCX, NCT, NT2, 6, 4>()};
+
+}  // namespace iodf

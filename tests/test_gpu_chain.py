@@ -74,3 +74,14 @@ def test_ties_and_last_layers():
         if n % 3 == 2:
             net["layers"][-1]["flags"] |= 1
     _check(cfg, 2, pack_blob(m))
+
+
+# strips: 24x40, 16x16 and 32x32 maps at batches that give one row, a few rows and the most rows a strip (the last
+# strip of an image short), images one strip high, and widths that are no multiple of a tile
+@pytest.mark.parametrize("H,W,batch", [(48, 80, 1), (32, 32, 1), (32, 32, 13), (64, 64, 3), (64, 64, 17), (64, 64, 66),
+                                       (2, 128, 2), (34, 70, 9)])
+@pytest.mark.parametrize("width,keep,k2,unsigned", [(128, 1.0, 3, False), (128, 0.4, 1, True), (64, 1.0, 3, True),
+                                                    (128, 0.4, 3, False)])
+def test_strips(H, W, batch, width, keep, k2, unsigned):
+    _check(FlowConfig("strips", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=46, block_k2=k2,
+                      act_unsigned=unsigned), batch)
