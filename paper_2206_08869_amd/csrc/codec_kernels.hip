@@ -43,25 +43,29 @@ constexpr long long kMass = 1LL << kMassBits;
 constexpr unsigned long long kStateLow = 1ULL << 31;
 constexpr int TPB = 256;
 
+// The table in LDS has one entry more than its kSigEntries points, so that the last point has a neighbour too.
+constexpr int kSigLds = kSigEntries + 1;
+
 __device__ __forceinline__ void load_sig(int* s_sig, const int32_t* sig) {
-    for (int i = threadIdx.x; i < kSigEntries; i += blockDim.x) s_sig[i] = sig[i];
+    for (int i = threadIdx.x; i < kSigLds; i += blockDim.x) s_sig[i] = sig[i < kSigEntries ? i : kSigEntries - 1];
     __syncthreads();
 }
 
-__device__ __forceinline__ long long sigm(const int* s_sig, long long T) {
-    constexpr long long tmax = 24LL << 24;
-    if (T <= -tmax) return 0;
-    if (T >= tmax) return 1LL << kSigBits;
-    const long long u = T + tmax;
-    const int j = (int)(u >> 18);
-    const long long frac = u & ((1LL << 18) - 1);
-    const long long a = s_sig[j], b = s_sig[j + 1];
-    return a + (((b - a) * frac) >> 18);
-}
-
-__device__ __forceinline__ int cdf(const int* s_sig, int r, long long inv) {
-    const long long T = (2LL * r - 1) * inv;
-    return (r + kAlphaR) + (int)(((kMass - 2 * kAlphaR) * sigm(s_sig, T)) >> kSigBits);
+// G(r) = (r + 8192) + floor((M - 16384) * S((2r - 1) * inv) / 2^30), S interpolated between the table's points with
+// floor. Everything fits 32-bit products: the argument saturates at +-24 (24 << 24 in its units), where S is 0 and
+// 2^30 exactly as the table's ends are; the interpolation's and the mass's shifts are folded into a factor so that the
+// result is a product's high word.
+__device__ __forceinline__ int cdf(const int* s_sig, int r, unsigned inv) {
+    constexpr unsigned tmax = 24u << 24;
+    const int t = 2 * r - 1;
+    const unsigned a = (unsigned)(t < 0 ? -t : t), lo = a * inv;
+    unsigned T = __umulhi(a, inv) ? tmax : lo;
+    T = T < tmax ? T : tmax;
+    const unsigned u = t < 0 ? tmax - T : tmax + T;
+    const unsigned j = u >> 18, frac = u & ((1u << 18) - 1);
+    const unsigned s0 = (unsigned)s_sig[j], s1 = (unsigned)s_sig[j + 1];
+    const unsigned S = s0 + __umulhi(s1 - s0, frac << 14);
+    return (r + kAlphaR) + (int)__umulhi((unsigned)(kMass - 2 * kAlphaR) << 2, S);
 }
 
 // codes of latent e of chunk c of one image
@@ -86,7 +90,7 @@ __global__ __launch_bounds__(TPB) void k_prior_cf(const CodecTables t, const Chu
                                                   long long d, const int8_t* __restrict__ codes, long long d_codes,
                                                   int batch, int32_t* __restrict__ c_out, int32_t* __restrict__ f_out,
                                                   unsigned long long* errs) {
-    __shared__ int s_sig[kSigEntries];
+    __shared__ int s_sig[kSigLds];
     load_sig(s_sig, t.sig);
     unsigned clamped = 0;
     const long long total = (long long)batch * d;
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(TPB) void k_prior_cf(const CodecTables t, const Chu
         int m, l;
         codes_of(ct, c, codes ? codes + (long long)b * d_codes : nullptr, e, m, l);
         const int r = residual(z[i], m, clamped);
-        const long long inv = t.inv[l + 128];
+        const unsigned inv = (unsigned)t.inv[l + 128];
         const int C = cdf(s_sig, r, inv);
         c_out[i] = C;
         f_out[i] = cdf(s_sig, r + 1, inv) - C;
@@ -107,46 +111,89 @@ __global__ __launch_bounds__(TPB) void k_prior_cf(const CodecTables t, const Chu
     if (clamped) atomicAdd(errs, (unsigned long long)clamped);
 }
 
-__global__ __launch_bounds__(TPB) void k_rans_encode(const CodecTables t, const ChunkTable ct,
-                                                     const int32_t* __restrict__ z, long long d,
-                                                     const int8_t* __restrict__ codes, long long d_codes, int batch,
-                                                     uint32_t* __restrict__ lane_words, long long lwpi,
-                                                     uint32_t* __restrict__ lane_meta, unsigned long long* errs) {
-    __shared__ int s_sig[kSigEntries];
+// One workgroup per (image, chunk). A lane's coder is a serial chain (shed a word, divide, multiply, add), but what it
+// is fed, the masses of its symbols, depends on nothing in it: the first wave runs the sixteen chains, one to a
+// thread, and the other four work out the masses and reciprocals of the next kEncBlock symbols of every lane
+// meanwhile. The chain's division X / F (63 by 24 bits, the quotient below 2^39) is a product with 1 / F in double
+// precision, off by less than 1.01 in either direction, and one correction.
+// Bound: the chain, about 110 ns a symbol (1150 ns with a thread per lane that also fetched, looked up and divided;
+// paper_res64 at batch 256, 1024 chunks of up to 384 symbols a lane: 443 us before).
+constexpr int kEncBlock = 32;
+constexpr int kEncThreads = 320;
+
+struct EncSymbol {
+    unsigned c, f;  // f = 0: no symbol here
+    double rcp;     // 1 / f
+};
+
+__global__ __launch_bounds__(kEncThreads) void k_rans_encode(const CodecTables t, const ChunkTable ct,
+                                                             const int32_t* __restrict__ z, long long d,
+                                                             const int8_t* __restrict__ codes, long long d_codes,
+                                                             uint32_t* __restrict__ lane_words, long long lwpi,
+                                                             uint32_t* __restrict__ lane_meta, unsigned long long* errs) {
+    __shared__ int s_sig[kSigLds];
+    __shared__ EncSymbol s_sym[2][kEncBlock * kLanes];
     load_sig(s_sig, t.sig);
     const int nslots = ct.n_chunks * kLanes;
-    const long long tid = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (tid >= (long long)batch * nslots) return;
-    const int b = (int)(tid / nslots), s = (int)(tid - (long long)b * nslots);
-    const int c = s / kLanes, j = s % kLanes;
+    const int b = blockIdx.x / ct.n_chunks, c = blockIdx.x - b * ct.n_chunks;
     const int n = ct.n[c];
-    const int k = j < n ? (n - j + kLanes - 1) / kLanes : 0;
+    const int kmax = (n + kLanes - 1) / kLanes, rounds = (kmax + kEncBlock - 1) / kEncBlock;
     const int32_t* zc = z + (long long)b * d + ct.z_off[c];
     const int8_t* ci = codes ? codes + (long long)b * d_codes : nullptr;
-    uint32_t* w = lane_words + (long long)b * lwpi + ct.lane_off[c] + (long long)j * ct.lane_cap[c];
+    const int j = threadIdx.x;  // the coder's lane (first wave, below kLanes)
+    uint32_t* w = lane_words + (long long)b * lwpi + ct.lane_off[c] + (long long)(j & (kLanes - 1)) * ct.lane_cap[c];
     unsigned long long X = kStateLow;
-    unsigned clamped = 0;
     int nw = 0;
-    for (int p = k - 1; p >= 0; --p) {
-        const int e = p * kLanes + j;
-        int m, l;
-        codes_of(ct, c, ci, e, m, l);
-        const int r = residual(zc[e], m, clamped);
-        const long long inv = t.inv[l + 128];
-        const unsigned C = (unsigned)cdf(s_sig, r, inv);
-        const unsigned F = (unsigned)cdf(s_sig, r + 1, inv) - C;
-        if (X >= ((unsigned long long)F << 39)) {  // at most once per symbol, so nw <= k < lane_cap
-            w[nw++] = (uint32_t)X;
-            X >>= 32;
+    unsigned clamped = 0;
+    // round r holds the symbols at positions kmax - 1 - r * kEncBlock and below, in coding order
+    auto produce = [&](int r) {
+        for (int s = (int)threadIdx.x - 64; s < kEncBlock * kLanes; s += kEncThreads - 64) {
+            const int p = kmax - 1 - r * kEncBlock - s / kLanes, e = p * kLanes + s % kLanes;
+            EncSymbol y = {0u, 0u, 0.0};
+            if (p >= 0 && e < n) {
+                int m, l;
+                codes_of(ct, c, ci, e, m, l);
+                const int res = residual(zc[e], m, clamped);
+                const unsigned inv = (unsigned)t.inv[l + 128];
+                y.c = (unsigned)cdf(s_sig, res, inv);
+                y.f = (unsigned)cdf(s_sig, res + 1, inv) - y.c;
+                y.rcp = 1.0 / (double)y.f;
+            }
+            s_sym[r & 1][s] = y;
         }
-        const unsigned long long q = X / F;
-        X = q * (unsigned long long)kMass + C + (X - q * F);
+    };
+    if (threadIdx.x >= 64 && rounds > 0) produce(0);
+    __syncthreads();
+    for (int r = 0; r < rounds; ++r) {
+        if (threadIdx.x >= 64) {
+            if (r + 1 < rounds) produce(r + 1);
+        } else if (threadIdx.x < kLanes) {
+            EncSymbol y = s_sym[r & 1][j];
+            for (int i = 0; i < kEncBlock; ++i) {
+                const EncSymbol next = s_sym[r & 1][(i + 1 < kEncBlock ? i + 1 : i) * kLanes + j];
+                if (y.f) {
+                    if (X >= ((unsigned long long)y.f << 39)) {  // at most once per symbol, so nw <= k < lane_cap
+                        w[nw++] = (uint32_t)X;
+                        X >>= 32;
+                    }
+                    unsigned long long q = (unsigned long long)((double)X * y.rcp);
+                    long long rem = (long long)(X - q * y.f);
+                    if (rem < 0) { --q; rem += y.f; }
+                    if (rem >= (long long)y.f) { ++q; rem -= y.f; }
+                    X = q * (unsigned long long)kMass + y.c + (unsigned long long)rem;
+                }
+                y = next;
+            }
+        }
+        __syncthreads();
     }
-    uint32_t* mt = lane_meta + ((long long)b * nslots + s) * 4;
-    mt[0] = (uint32_t)nw;
-    mt[1] = (uint32_t)X;
-    mt[2] = (uint32_t)(X >> 32);
-    mt[3] = 0;
+    if (threadIdx.x < kLanes) {
+        uint32_t* mt = lane_meta + ((long long)b * nslots + c * kLanes + j) * 4;
+        mt[0] = (uint32_t)nw;
+        mt[1] = (uint32_t)X;
+        mt[2] = (uint32_t)(X >> 32);
+        mt[3] = 0;
+    }
     if (clamped) atomicAdd(errs, (unsigned long long)clamped);
 }
 
@@ -158,15 +205,21 @@ __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const ui
                                                    uint32_t* __restrict__ out, long long cap,
                                                    uint32_t* __restrict__ sizes, unsigned long long* errs) {
     __shared__ long long s_off[kMaxChunks * kLanes + 1];
+    static_assert(kMaxChunks * kLanes <= TPB, "a thread per slot");
     const int b = blockIdx.x;
     const int nslots = ct.n_chunks * kLanes;
     const long long header = 1 + 3LL * nslots;
     const uint32_t* mt = lane_meta + (long long)b * nslots * 4;
-    if (threadIdx.x == 0) {
-        long long o = 0;
-        for (int s = 0; s < nslots; ++s) { s_off[s] = o; o += mt[4 * s]; }
-        s_off[nslots] = o;
+    // s_off[s] = words of the slots before s: an inclusive sum over at most 128 slots, one to a thread
+    long long sum = (int)threadIdx.x < nslots ? (long long)mt[4 * threadIdx.x] : 0;
+    for (int step = 1; step < nslots; step *= 2) {
+        if ((int)threadIdx.x < nslots) s_off[threadIdx.x + 1] = sum;
+        __syncthreads();
+        if ((int)threadIdx.x < nslots && (int)threadIdx.x >= step) sum += s_off[threadIdx.x + 1 - step];
+        __syncthreads();
     }
+    if ((int)threadIdx.x < nslots) s_off[threadIdx.x + 1] = sum;
+    if (threadIdx.x == 0) s_off[0] = 0;
     __syncthreads();
     const long long total = header + s_off[nslots];
     uint32_t* ob = out + (long long)b * cap;
@@ -192,21 +245,33 @@ __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const ui
     }
 }
 
-// Sixteen threads serve one lane: each bisection round they test sixteen cut points of the current
-// interval at once (a ballot counts how many lie at or below the slot), so the 2^14 residuals are
-// isolated in four rounds (16 * 16 * 16 * 4) instead of fourteen. All sixteen keep the same coder
-// state; thread 0 of the group writes the latent. A workgroup of 256 threads holds the 16 lanes of
-// one image's chunk.
-__global__ __launch_bounds__(256) void k_rans_decode_chunk(const CodecTables t, const ChunkTable ct, const int c,
-                                                           const uint32_t* __restrict__ cont, long long cap, int batch,
-                                                           const int8_t* __restrict__ codes, long long d_codes,
-                                                           int32_t* __restrict__ z, long long d,
-                                                           unsigned long long* errs) {
-    __shared__ int s_sig[kSigEntries];
+// Half a wave serves one lane, a workgroup eight of the sixteen lanes of one image's chunk, a wave to a SIMD.
+// The 2^14 residuals are isolated in
+// three rounds (32 * 32 * 16): in each the 32 threads work out G at 32 cut points of the current interval and a ballot
+// counts how many lie at or below the slot; the last round works out G at every residual left, so the symbol's mass
+// is two of its values. All threads keep the same coder state; the first of a half writes the latent.
+//
+// Bound: the chain from one state to the next. What does not hang on the state is kept off it: the first round's G
+// (its cut points are the same for every symbol, only the scale differs) is worked out a symbol ahead, and the codes
+// and words of 32 symbols and of the following 32 sit in the half wave's registers, one to a thread. That
+// leaves two table interpolations, three ballots and the update on the chain. (Sixteen threads, four dependent rounds
+// and two more interpolations, codes and words fetched as needed: 1270 ns a symbol.)
+constexpr int kDecLanes = 8, kDecThreads = 32 * kDecLanes;
+
+__global__ __launch_bounds__(kDecThreads) void k_rans_decode_chunk(const CodecTables t, const ChunkTable ct, const int c,
+                                                                   const uint32_t* __restrict__ cont, long long cap, int batch,
+                                                                   const int8_t* __restrict__ codes, long long d_codes,
+                                                                   int32_t* __restrict__ z, long long d,
+                                                                   unsigned long long* errs) {
+    __shared__ int s_sig[kSigLds];
+    __shared__ unsigned s_inv[256];
+    for (int i = threadIdx.x; i < 256; i += kDecThreads) s_inv[i] = (unsigned)t.inv[i];
     load_sig(s_sig, t.sig);
-    const int b = blockIdx.x;  // grid = batch
-    const int j = threadIdx.x >> 4, helper = threadIdx.x & 15;
-    const int grp_shift = (threadIdx.x & 63) & ~15;  // this group's first bit in the wave's ballot
+    constexpr int kParts = kLanes / kDecLanes;
+    const int b = blockIdx.x / kParts;  // grid = batch * kParts
+    const int j = blockIdx.x % kParts * kDecLanes + (threadIdx.x >> 5), helper = threadIdx.x & 31;
+    const int half_shift = threadIdx.x & 32;  // this half's first bit in the wave's ballot, its first lane
+    auto of_half = [&](int v, int i) { return __builtin_amdgcn_ds_bpermute((half_shift + i) << 2, v); };
     const int nslots = ct.n_chunks * kLanes;
     const long long header = 1 + 3LL * nslots;  // the host has checked cap >= header
     const uint32_t* cb = cont + (long long)b * cap;
@@ -217,43 +282,70 @@ __global__ __launch_bounds__(256) void k_rans_decode_chunk(const CodecTables t, 
     const int8_t* ci = codes ? codes + (long long)b * d_codes : nullptr;
     const long long total = cb[0];
     bool bad = total > cap || total < header;
-    long long pos = header;
     const int slot = c * kLanes + j;
-    for (int s = 0; s < slot; ++s) pos += cb[1 + s];
-    long long nw = cb[1 + slot];
-    if (bad || pos + nw > total) { bad = true; nw = 0; pos = header; }
+    // words of the lanes before this one: the half adds them up together
+    long long before = 0;
+    for (int s = helper; s < slot; s += 32) before += cb[1 + s];
+    for (int x = 16; x; x >>= 1) before += __shfl_xor(before, x, 32);
+    long long pos = header + before;
+    unsigned nw = cb[1 + slot];
+    if (bad || pos + (long long)nw > total) { bad = true; nw = 0; pos = header; }
     const uint32_t* w = cb + pos;  // reads stay below pos + nw <= total <= cap
-    long long used = 0;
+    unsigned used = 0;
+    auto words_at = [&](unsigned i) { return (long long)i + helper < nw ? w[i + helper] : 0u; };
+    unsigned w_cur = words_at(0), w_next = words_at(32);
     unsigned long long X = (unsigned long long)cb[1 + nslots + 2 * slot] |
                            ((unsigned long long)cb[1 + nslots + 2 * slot + 1] << 32);
-    for (int p = 0; p < kmax; ++p) {
-        const bool active = p < k;
-        const int e = active ? p * kLanes + j : 0;
+    // codes of 32 positions, one to a thread: mean code in the low half, log-scale code above it
+    auto codes_at = [&](int p) {
         int m = kDefaultM, l = kDefaultL;
-        if (active) codes_of(ct, c, ci, e, m, l);
-        const long long inv = t.inv[l + 128];
-        const int v = (int)(X & (unsigned long long)(kMass - 1));
-        // G(-8192) = 0 <= v < M = G(8192); cut points lo + (helper + 1) * step, the last one of the
-        // first three rounds is the interval's end (known to lie above the slot)
-        int lo = -kAlphaR;
-#pragma unroll
-        for (int round = 0; round < 4; ++round) {
-            const int step = round == 0 ? 1024 : round == 1 ? 64 : round == 2 ? 4 : 1;
-            const int cut = lo + (helper + 1) * step;
-            const bool below = (step == 1 ? helper < 3 : helper < 15) && cdf(s_sig, cut, inv) <= v;
-            const unsigned long long mask = __ballot(below);
-            lo += __popc((unsigned)(mask >> grp_shift) & 0xffffu) * step;
-        }
-        const int C = cdf(s_sig, lo, inv);
-        const int F = cdf(s_sig, lo + 1, inv) - C;
-        if (active) {
-            if (helper == 0) zc[e] = lo + 2 * m;
-            X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
-            if (X < kStateLow) {
-                if (used < nw) X = (X << 32) | w[used++];
-                else { X <<= 32; bad = true; }
+        if (p + helper < k) codes_of(ct, c, ci, (p + helper) * kLanes + j, m, l);
+        return (l << 16) | (m & 0xffff);
+    };
+    int ml_cur = codes_at(0), ml_next = codes_at(32);
+    // first round: cut points -8192 + (helper + 1) * 512; the last one is the interval's end, above every slot
+    const int cut1 = -kAlphaR + (helper < 31 ? helper + 1 : 31) * 512;
+    int ml = of_half(ml_cur, 0);
+    unsigned inv = s_inv[(ml >> 16) + 128];
+    int g1 = cdf(s_sig, cut1, inv);
+    for (int p0 = 0; p0 < kmax; p0 += 32) {
+        const int n_here = kmax - p0 < 32 ? kmax - p0 : 32;
+        int out = 0;  // this thread's latent of the 32
+        for (int i = 0; i < n_here; ++i) {
+            const int ml_after = of_half(i < 31 ? ml_cur : ml_next, (i + 1) & 31);
+            const unsigned word = (unsigned)of_half((int)w_cur, (int)(used & 31));
+            const unsigned inv_after = s_inv[(ml_after >> 16) + 128];
+            const int v = (int)(X & (unsigned long long)(kMass - 1));
+            // G(-8192) = 0 <= v < M = G(8192)
+            unsigned below = (unsigned)(__ballot(helper < 31 && g1 <= v) >> half_shift);
+            int lo = -kAlphaR + __popc(below) * 512;
+            below = (unsigned)(__ballot(helper < 31 && cdf(s_sig, lo + (helper + 1) * 16, inv) <= v) >> half_shift);
+            lo += __popc(below) * 16;
+            const int g3 = cdf(s_sig, lo + (helper < 16 ? helper : 16), inv);
+            below = (unsigned)(__ballot(helper >= 1 && helper < 16 && g3 <= v) >> half_shift);
+            const int idx = __popc(below);
+            const int C = of_half(g3, idx);
+            const int F = of_half(g3, idx + 1) - C;
+            g1 = cdf(s_sig, cut1, inv_after);
+            if (helper == i) out = lo + idx + 2 * (int)(int16_t)(ml & 0xffff);
+            if (p0 + i < k) {
+                X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
+                if (X < kStateLow) {
+                    if (used < nw) {
+                        X = (X << 32) | word;
+                        if ((++used & 31) == 0) {
+                            w_cur = w_next;
+                            w_next = words_at(used + 32);
+                        }
+                    } else { X <<= 32; bad = true; }
+                }
             }
+            inv = inv_after;
+            ml = ml_after;
         }
+        if (p0 + helper < k) zc[(p0 + helper) * kLanes + j] = out;
+        ml_cur = ml_next;
+        ml_next = codes_at(p0 + 64);
     }
     if (X != kStateLow || used != nw) bad = true;
     if (bad && helper == 0) atomicAdd(errs + 2, 1ULL);
@@ -285,9 +377,8 @@ hipError_t launch_rans_encode(const CodecTables& t, const ChunkTable& ct, const 
                               hipStream_t st) {
     if (batch <= 0) return hipSuccess;
     if (!table_ok(ct) || !z || !lane_words || !lane_meta || !errs || !t.sig || !t.inv) return hipErrorInvalidValue;
-    const long long threads = (long long)batch * ct.n_chunks * kLanes;
-    hipLaunchKernelGGL(k_rans_encode, dim3((unsigned)((threads + TPB - 1) / TPB)), dim3(TPB), 0, st, t, ct, z, d, codes,
-                       d_codes, batch, lane_words, lane_words_per_image, lane_meta, errs);
+    hipLaunchKernelGGL(k_rans_encode, dim3((unsigned)batch * ct.n_chunks), dim3(kEncThreads), 0, st, t, ct, z, d, codes,
+                       d_codes, lane_words, lane_words_per_image, lane_meta, errs);
     return hipGetLastError();
 }
 
@@ -308,7 +399,7 @@ hipError_t launch_rans_decode_chunk(const CodecTables& t, const ChunkTable& ct, 
     if (!table_ok(ct) || c < 0 || c >= ct.n_chunks || !cont || !z || !errs || !t.sig || !t.inv ||
         cap < 1 + 3LL * ct.n_chunks * kLanes)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rans_decode_chunk, dim3(batch), dim3(256), 0, st, t, ct, c, cont, cap, batch, codes, d_codes, z,
+    hipLaunchKernelGGL(k_rans_decode_chunk, dim3((unsigned)batch * (kLanes / kDecLanes)), dim3(kDecThreads), 0, st, t, ct, c, cont, cap, batch, codes, d_codes, z,
                        d, errs);
     return hipGetLastError();
 }
