@@ -80,9 +80,9 @@ struct StripKernel {
 };
 constexpr int kStripThreads = 256;
 constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
-constexpr int kStripSizes = 5, kStripEnds = 2;
+constexpr int kStripSizes = 5, kStripIns = 8, kStripLasts = 4;
 extern const StripKernel kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
-extern const StripKernel kStripIn4[], kStripIn2[], kStripLast4[], kStripLast2[];
+extern const StripKernel kStripIn[], kStripLast[];  // (nc_t of a first layer's kernel: chunks of the quantised input)
 
 size_t chain_lds_bytes(const ChainArgs& a);
 // Whether a kernel exists for this network and this many images per workgroup.

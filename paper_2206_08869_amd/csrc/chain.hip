@@ -8,7 +8,6 @@ namespace {
 const ChainKernel* const kChains[] = {kChain443, kChain423, kChain223, kChain441, kChain421, kChain221, kChain40, kChain20};
 
 const StripKernel* const kStrips[] = {kStrip443, kStrip423, kStrip223, kStrip441, kStrip421, kStrip221};
-const StripKernel* const kEnds[] = {kStripIn4, kStripIn2, kStripLast4, kStripLast2};
 
 size_t strip_lds_bytes(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int w, int rows) {
     const int ext = taps_two == 9 ? 1 : 0;
@@ -54,11 +53,11 @@ hipError_t chain_setup() {
             const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
             if (e != hipSuccess) return e;
         }
-    for (const StripKernel* t : kEnds)
-        for (int i = 0; i < kStripEnds; ++i) {
-            const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
-            if (e != hipSuccess) return e;
-        }
+    for (int i = 0; i < kStripIns + kStripLasts; ++i) {
+        const StripKernel& k = i < kStripIns ? kStripIn[i] : kStripLast[i - kStripIns];
+        const hipError_t e = hipFuncSetAttribute((const void*)k.kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
+        if (e != hipSuccess) return e;
+    }
     return hipSuccess;
 }
 
@@ -66,11 +65,9 @@ const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps
     if ((long long)(rows + 4) * 16 * (w + 2) * (w + 2) >= 1 << 20) return nullptr;  // the kernel's divisions by multiplication
     if (rows < 1 || rows > h || strip_lds_bytes(part, nc_x, nc_t, taps_two, nc_q, w, rows) > kStripMaxLds) return nullptr;
     if (part != STRIP_BLOCK) {
-        for (const StripKernel* t : kEnds) {
-            if (t->nc_x != nc_x || (part == STRIP_IN) != (t == kStripIn4 || t == kStripIn2)) continue;
-            for (int i = 0; i < kStripEnds; ++i)
-                if (rows * w <= 32 * t[i].tiles_two) return t + i;
-        }
+        const StripKernel* const t = part == STRIP_IN ? kStripIn : kStripLast;
+        for (int i = 0; i < (part == STRIP_IN ? kStripIns : kStripLasts); ++i)
+            if (t[i].nc_x == nc_x && (part == STRIP_LAST || t[i].nc_t == nc_q) && rows * w <= 32 * t[i].tiles_two) return t + i;
         return nullptr;
     }
     const int one = rows + (taps_two == 9 ? 2 : 0);

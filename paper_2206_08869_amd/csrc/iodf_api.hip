@@ -761,10 +761,11 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
 // Up to 128 pixels an image (deep levels) the one launch is always the shorter way: 128-wide residual networks of
 // eight blocks, 18 layers, batch 1 / 64 / 256: 4x4 maps 36 / 36 / 38 us against 92 / 105 / 130 us for a launch per
 // layer, 8x8 maps 47 / 47 / 58 us against 95 / 110 / 165 us. At 256 pixels a workgroup needs 147 us whatever the
-// batch, up to one image per compute unit, and strips (strip_plan) 100 us at batch 1, 119 at 64, 158 at 128.
+// batch, up to one image per compute unit; strips (strip_plan) need 100 us at batch 1 and 119 at 64, while there is
+// one for every compute unit at most, and 180 at 100.
 // Beyond an image per compute unit small images share a workgroup, which reads the weights once for all of them
 // (4x4 maps at batch 512: 82 us with two images, 103 with one).
-static int chain_batch_from(const iodf_ctx* ctx) { return ctx->n_cu * 2 / 5; }  // smallest batch at more than 128 pixels
+static int chain_batch_from(const iodf_ctx* ctx) { return ctx->n_cu / 4 + 1; }  // smallest batch at more than 128 pixels (four strips an image)
 
 static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
     if (!N.chain.ok) return 0;

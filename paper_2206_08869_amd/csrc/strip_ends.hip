@@ -2,8 +2,9 @@
 #include "strip_kernel.h"
 
 namespace iodf {
-const StripKernel kStripIn4[kStripEnds] = {{4, 0, 0, 2, 2, k_strip_in<4, 2>}, {4, 0, 0, 4, 4, k_strip_in<4, 4>}};
-const StripKernel kStripIn2[kStripEnds] = {{2, 0, 0, 2, 2, k_strip_in<2, 2>}, {2, 0, 0, 4, 4, k_strip_in<2, 4>}};
-const StripKernel kStripLast4[kStripEnds] = {{4, 0, 0, 2, 2, k_strip_last<4, 2>}, {4, 0, 0, 4, 4, k_strip_last<4, 4>}};
-const StripKernel kStripLast2[kStripEnds] = {{2, 0, 0, 2, 2, k_strip_last<2, 2>}, {2, 0, 0, 4, 4, k_strip_last<2, 4>}};
+#define IODF_STRIP_IN(NCX, NCQ, T) StripKernel{NCX, NCQ, 0, T, T, k_strip_in<NCX, NCQ, T>}
+#define IODF_STRIP_LAST(NCX, T) StripKernel{NCX, 0, 0, T, T, k_strip_last<NCX, T>}
+const StripKernel kStripIn[kStripIns] = {IODF_STRIP_IN(4, 1, 2), IODF_STRIP_IN(4, 1, 4), IODF_STRIP_IN(4, 2, 2), IODF_STRIP_IN(4, 2, 4),
+                                         IODF_STRIP_IN(2, 1, 2), IODF_STRIP_IN(2, 1, 4), IODF_STRIP_IN(2, 2, 2), IODF_STRIP_IN(2, 2, 4)};
+const StripKernel kStripLast[kStripLasts] = {IODF_STRIP_LAST(4, 2), IODF_STRIP_LAST(4, 4), IODF_STRIP_LAST(2, 2), IODF_STRIP_LAST(2, 4)};
 }  // namespace iodf

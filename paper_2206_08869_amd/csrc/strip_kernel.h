@@ -6,9 +6,9 @@
 // it, the first one on one row more on either side, and writes the result.
 //
 // Bound. Blocks of two 3x3 layers, 128 wide, strips of four rows of 32 pixels, in clocks of a CU: request to LDS 5000,
-// products 9000 + 6800 (matrix cores 6900 + 4600, a quarter of it for the rows that two strips both compute), epilogues
+// products 9000 + 6000 (matrix cores 6900 + 4600, a quarter of it for the rows that two strips both compute), epilogues
 // 3500 + 3100. Two workgroups share a CU, so that the loads and epilogues of one run under the other's products: a pair
-// takes 41000. With a
+// takes 39000 (87 us for the 2048 strips of 256 images; 94 us as two launches layer by layer). With a
 // strip or less per CU the length of that chain is what counts, hence strips down to a single row.
 #pragma once
 #include "chain_kernel.h"
@@ -180,9 +180,10 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     }
 }
 
-// Input quantiser and first layer.
-template <int NCX, int T>
-__global__ __launch_bounds__(kStripThreads, 2) void k_strip_in(const StripArgs a) {
+// Input quantiser and first layer. Little arithmetic behind a chain of latencies, so three workgroups to a CU
+// (32x32 maps at batch 256: 33 -> 29 us).
+template <int NCX, int NCQ, int T>
+__global__ __launch_bounds__(kStripThreads, 3) void k_strip_in(const StripArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -192,18 +193,18 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_in(const StripArgs a
     if (!strip_of(a, g)) return;
     const int h = a.h, w = a.w, W2 = w + 2;
     const int qo = g.r0 - 1, qe = g.r1 + 1, ya = qo > 0 ? qo : 0, yb = qe < h ? qe : h;
-    const unsigned psq = chain_pixel_bytes(a.nc_q), rpq = chain_row_bytes(w, psq);
+    constexpr unsigned psq = chain_pixel_bytes(NCQ);
+    const unsigned rpq = chain_row_bytes(w, psq);
     constexpr unsigned qb = kChainConstBytes;
     const unsigned end = qb + rpq * (qe - qo);
     using S = Share<4, NCX, T>;
     const int blk = wave % S::WC * S::TC;
     const gbytes par = (gbytes)a.params;
-    const gbytes p = uniform(par + blk * 9 * a.nc_q * 1024);
+    const gbytes p = uniform(par + blk * 9 * NCQ * 1024);
     v4i wf[12];
     static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
-    if (a.nc_q == 1) chain_fetch<S::TC, 1, 3, 0>(wf, p, lane16);
-    else chain_fetch<S::TC, 2, 3, 0>(wf, p, lane16);
-    const v4i c0 = strip_consts(par + NCX * 9 * a.nc_q * 1024, tid);
+    chain_fetch<S::TC, NCQ, 3, 0>(wf, p, lane16);
+    const v4i c0 = strip_consts(par + NCX * 9 * NCQ * 1024, tid);
     for (unsigned o = qb + tid * 16; o < end; o += kStripThreads * 16) *(v4i*)(lds + o) = v4i{0, 0, 0, 0};
     lds_barrier();
     strip_put_consts(lds, c0, 0, tid);
@@ -222,13 +223,11 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_in(const StripArgs a
     const int* const cst = (const int*)lds;
     v16i acc[S::TC][S::TP];
     chain_bias(acc, cst, blk, half);
-    const unsigned tcs = S::TC == 2 ? 9 * a.nc_q * 1024 : 0;
-    if (a.nc_q == 1) chain_products<S::TC, S::TP, 1, 3>(acc, wf, lds, q_in, rpq, p, p, tcs, lane16);
-    else chain_products<S::TC, S::TP, 2, 3>(acc, wf, lds, q_in, rpq, p, p, tcs, lane16);
+    chain_products<S::TC, S::TP, NCQ, 3>(acc, wf, lds, q_in, rpq, p, p, S::TC == 2 ? 9 * NCQ * 1024 : 0, lane16);
     chain_store<S::TC, S::TP, false, true>(acc, lds, q_in, live, cst, blk * 32, half, a.act_unsigned, a.out, a.plane, go);
 }
 
-// Last layer.
+// Last layer. (Three workgroups to a CU would spill: 33 -> 35 us at batch 256.)
 template <int NCX, int T>
 __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
