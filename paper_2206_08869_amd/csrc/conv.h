@@ -104,6 +104,7 @@ struct ConvArgs {
     unsigned mode : 3;
     unsigned has_trace : 1;
     int sign : 2;        // +1 encode, -1 decode
+    unsigned no_ties : 1;  // rq_fast: no accumulator requantises to exactly half a code (see pack_signed_quad)
     int log2_w : 6, log2_hw : 8;  // filled by launch_conv: log2 of w and of h*w when both are powers of two, else -1
 };
 static_assert(sizeof(ConvArgs) == 120, "argument block");

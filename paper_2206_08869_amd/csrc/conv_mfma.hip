@@ -133,8 +133,10 @@ __device__ __forceinline__ void conv_epilogue_fast(const ConvArgs& a, v16i (&acc
                                            a.out_unsigned);
                     return;
                 } else {
-                    pk[g] = pack_signed_quad<false>(acc[tc][tp], std::integral_constant<int, g * 4>{}, Mq[g], Sq[g], Rq[g], scq[tc][tp][g],
-                                             (a.relu && !a.out_unsigned) ? 0 : -128);
+                    const int lo2 = (a.relu && !a.out_unsigned) ? 0 : -128;
+                    using I = std::integral_constant<int, g * 4>;
+                    pk[g] = a.no_ties ? pack_signed_quad<true>(acc[tc][tp], I{}, Mq[g], Sq[g], Rq[g], scq[tc][tp][g], lo2)
+                                      : pack_signed_quad<false>(acc[tc][tp], I{}, Mq[g], Sq[g], Rq[g], scq[tc][tp][g], lo2);
                 }
             });
             // lower half holds channels {0-3, 8-11, 16-19, 24-27}, upper {4-7, 12-15, 20-23, 28-31}

@@ -920,6 +920,7 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
         a.shift = (const int32_t*)(ctx->params + L.shift_off);
         a.n_store = L.n_store;
         a.rq_fast = L.rq_fast;
+        a.no_ties = L.no_ties;
         a.out_unsigned = L.out_unsigned && L.mode == MODE_ACT;
         a.sc_unsigned = L.sc_unsigned;
         a.clamp_hi = L.hi_off == (size_t)-1 ? nullptr : (const int32_t*)(ctx->params + L.hi_off);
