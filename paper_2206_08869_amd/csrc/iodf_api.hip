@@ -803,7 +803,8 @@ static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
         return best;
     };
     const int in = rows_for(STRIP_IN), block = rows_for(STRIP_BLOCK), last = rows_for(STRIP_LAST);
-    if (in && block && last) {
+    const int least = std::min(in, std::min(block, last));
+    if (least && (long long)batch * ((h + least - 1) / least) <= kStripMaxUnits) {
         p.rows[STRIP_IN] = in;
         p.rows[STRIP_BLOCK] = block;
         p.rows[STRIP_LAST] = last;
