@@ -81,6 +81,7 @@ struct StripKernel {
 constexpr int kStripThreads = 256;
 constexpr int kStripMaxUnits = 8 * 65535;  // strips of a launch: StripArgs::chunk has 16 bits
 constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
+constexpr int kStripMaxTiles = 6;  // tiles_one of the largest block kernel
 constexpr int kStripSizes = 5, kStripIns = 8, kStripLasts = 4;
 extern const StripKernel kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
 extern const StripKernel kStripIn[], kStripLast[];  // (nc_t of a first layer's kernel: chunks of the quantised input)

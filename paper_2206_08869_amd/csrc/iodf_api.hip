@@ -786,6 +786,27 @@ static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
 // batch 64 -568 / +11 / +1502, batch 256 -234 / +1622 / +7283.
 struct StripPlan { int rows[3]; };
 
+// Whether strips are the shorter way. Up to two strips per compute unit all run at once and a launch is as long as one
+// of them; beyond, it is the matrix work that counts, and a strip does more of it than a launch per layer: the rows next
+// to it twice, and whole kernels' tiles where its rows fill them in part. The largest ratio of that work to the layers'
+// own at which strips still win, over maps 4 to 64 wide at batch 1 to 512 (networks of four blocks, times of a launch
+// per layer over those of strips):
+//   128 wide inside, 3x3 second layer: ratio 1.25 -> 1.07 to 1.3, 1.48 -> 0.98 to 1.3, 1.67 -> 0.92 to 1.04,
+//     2.0 -> 0.79 to 1.1, 2.5 to 3.2 -> 0.54 to 0.85 (maps of 56 to 64 columns, where a single row takes the largest kernel)
+//   64 of 128 kept inside, 3x3: 1.82 -> 0.97 to 1.02, 2.0 -> 0.97 to 1.4, 2.5 -> 0.73 to 0.98
+//   128 wide inside, 1x1: 1.93 -> 1.03 to 1.07, 2.11 -> 0.90 to 1.0
+//   64 wide, 3x3: 2.86 -> 1.04 and more, 3.08 -> 0.95 to 1.02; the two 1x1 forms with 64 channels inside: never below 1.08
+// Strips of a single row in the largest kernel lose 128 wide already while few of them run (0.88 to 0.99 up to half a
+// strip per compute unit), where they are a longer way than four layers of small tiles.
+static bool strips_pay(const iodf_ctx* ctx, const DevChain& C, const StripKernel& k, int h, int w, int rows, int batch) {
+    const bool k3 = C.taps_two == 9, heavy = k3 && C.nc_t == 4;
+    const long long units = (long long)batch * ((h + rows - 1) / rows);
+    if (units <= 2LL * ctx->n_cu) return !(heavy && rows == 1 && k.tiles_one == kStripMaxTiles);
+    const int most = k3 ? (heavy ? 160 : C.nc_x == 4 ? 190 : 300) : C.nc_t == 4 ? 200 : 0;  // hundredths
+    const long long done = units * 32 * (9 * k.tiles_one + C.taps_two * k.tiles_two);
+    return !most || 100 * done <= (long long)batch * h * w * (9 + C.taps_two) * most;
+}
+
 static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     StripPlan p = {{0, 0, 0}};
     const DevChain& C = N.chain;
@@ -794,7 +815,7 @@ static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     auto rows_for = [&](StripPart part) {
         int best = 0;
         for (int r = 1; r <= h; ++r) {
-            if (!strip_kernel_for(part, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, r)) continue;
+            if (!strip_kernel_for(part, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, r)) break;  // nor for more rows
             const int strips = (h + r - 1) / r;
             if (best && (long long)batch * strips < ctx->n_cu) break;
             if (best && strips == (h + best - 1) / best) continue;  // the same strips, less evenly cut
@@ -804,11 +825,11 @@ static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     };
     const int in = rows_for(STRIP_IN), block = rows_for(STRIP_BLOCK), last = rows_for(STRIP_LAST);
     const int least = std::min(in, std::min(block, last));
-    if (least && (long long)batch * ((h + least - 1) / least) <= kStripMaxUnits) {
-        p.rows[STRIP_IN] = in;
-        p.rows[STRIP_BLOCK] = block;
-        p.rows[STRIP_LAST] = last;
-    }
+    if (!least || (long long)batch * ((h + least - 1) / least) > kStripMaxUnits) return p;
+    if (!strips_pay(ctx, C, *strip_kernel_for(STRIP_BLOCK, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, block), h, w, block, batch)) return p;
+    p.rows[STRIP_IN] = in;
+    p.rows[STRIP_BLOCK] = block;
+    p.rows[STRIP_LAST] = last;
     return p;
 }
 

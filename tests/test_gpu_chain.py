@@ -85,3 +85,34 @@ def test_ties_and_last_layers():
 def test_strips(H, W, batch, width, keep, k2, unsigned):
     _check(FlowConfig("strips", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=46, block_k2=k2,
                       act_unsigned=unsigned), batch)
+
+
+def _kernels(flow, x):
+    """Names of the kernels one forward call runs, and its latents."""
+    import torch
+    flow.profile_begin(4096)
+    z = flow.forward(x)[0]
+    torch.cuda.synchronize()
+    return {k["name"].split("<")[0] for k in flow.profile_end()}, z
+
+
+# Maps whose rows fill the largest strip kernel badly go layer by layer once more strips wait than run at once, or at
+# once where a single row already takes that kernel; the same images give the same latents either way.
+@pytest.mark.parametrize("H,batch,width,keep,k2,strips", [
+    (64, 64, 128, 1.0, 3, True), (80, 24, 128, 1.0, 3, True), (80, 96, 128, 1.0, 3, False), (96, 96, 128, 1.0, 3, False),
+    (128, 1, 128, 1.0, 3, False), (128, 48, 128, 1.0, 3, False), (128, 4, 128, 0.4, 3, True), (104, 48, 128, 0.4, 3, False),
+    (88, 128, 128, 1.0, 1, False), (96, 48, 128, 1.0, 1, True), (104, 96, 64, 1.0, 3, False), (128, 48, 64, 1.0, 3, True),
+    (128, 48, 128, 0.4, 1, True)])
+def test_strips_only_where_they_win(H, batch, width, keep, k2, strips):
+    import torch
+    cfg = FlowConfig("wide_maps", H, H, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=47, block_k2=k2)
+    print("strips or layers", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, H, H), generator=torch.Generator().manual_seed(5), dtype=torch.uint8).cuda()
+    names, z = _kernels(flow, x)
+    assert ("k_strip_block" in names) == strips and ("conv_igemm" in " ".join(names)) != strips, names
+    few = min(batch, 3)
+    _, z_few = _kernels(flow, x[-few:].contiguous())
+    assert torch.equal(z[-few:], z_few)
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
