@@ -87,8 +87,8 @@ extern const StripKernel kStrip443[], kStrip423[], kStrip223[], kStrip441[], kSt
 extern const StripKernel kStripIn[], kStripLast[];  // (nc_t of a first layer's kernel: chunks of the quantised input)
 
 size_t chain_lds_bytes(const ChainArgs& a);
-// Whether a kernel exists for this network and this many images per workgroup.
-bool chain_args_ok(const ChainArgs& a);
+// Tiles of the kernel for this network and this many images per workgroup; 0: there is none.
+int chain_tiles(const ChainArgs& a);
 hipError_t launch_chain(const ChainArgs& a, hipStream_t stream);
 // The kernel for strips of `rows` rows of h x w images, or nullptr: `block` of the residual networks with these widths,
 // or one of the ends (nc_t and taps_two unused).

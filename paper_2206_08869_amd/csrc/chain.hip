@@ -35,11 +35,13 @@ size_t chain_lds_bytes(const ChainArgs& a) {
     return 2 * kChainConstBytes + per * a.images;
 }
 
-bool chain_args_ok(const ChainArgs& a) {
-    return a.params && a.state && a.idx && a.batch >= 1 && a.h >= 1 && a.w >= 1 && a.images >= 1 && a.h * a.w <= 32 * kChainMaxTiles &&
+int chain_tiles(const ChainArgs& a) {
+    const bool ok = a.params && a.state && a.idx && a.batch >= 1 && a.h >= 1 && a.w >= 1 && a.images >= 1 && a.h * a.w <= 32 * kChainMaxTiles &&
            (a.nc_q == 1 || a.nc_q == 2) && a.n_a >= 1 && a.n_a <= 32 * a.nc_q && a.n_out >= 1 && a.n_out <= 32 * a.n_blk_last &&
            (a.n_blk_last == 1 || a.n_blk_last == 2) && (a.taps_last == 1 || a.taps_last == 9) && (a.nc_t != 0) == (a.blocks != 0) &&
-           kernel_for(a) && chain_lds_bytes(a) <= kChainMaxLds;
+           chain_lds_bytes(a) <= kChainMaxLds;
+    const ChainKernel* const k = ok ? kernel_for(a) : nullptr;
+    return k ? k->tiles : 0;
 }
 
 hipError_t chain_setup() {
@@ -96,7 +98,7 @@ hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a
 
 hipError_t launch_chain(const ChainArgs& a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
-    if (!chain_args_ok(a)) return hipErrorInvalidValue;
+    if (!chain_tiles(a)) return hipErrorInvalidValue;
     const ChainKernel* const k = kernel_for(a);
     const int groups = (a.batch + a.images - 1) / a.images;
     // blocks go round the XCDs, so those beyond the groups sit pf_blocks to an XCD

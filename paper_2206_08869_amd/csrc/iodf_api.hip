@@ -756,13 +756,38 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
     return a;
 }
 
-// Images per workgroup with which a network runs as one launch (chain.hip); 0: layer by layer.
+// Whether one launch for the whole network is the shorter way, with `images` to a workgroup and a kernel of `tiles`
+// tiles. A workgroup pays for whole kernels (1, 2, 4 and 8 tiles: 65 pixels as much as 128, 129 as much as 256) and one
+// to a compute unit runs at a time, or nearly so. Up to three workgroups per compute unit the launches that are saved
+// outweigh that; beyond, with `filled` hundredths computed for every one kept (times of a launch per layer over one
+// launch, networks of four blocks, 256 compute units):
+//   128 wide inside, 3x3 second layer: from 3.5 workgroups per unit on 0.79 to 1.2 at 178 and 197, 1.03 to 1.2 at 160 in
+//     eight tiles; past 8 per unit 0.87 to 0.98 at 160 in four tiles, 1.01 to 1.03 at 133
+//   128 wide inside, 1x1, or 64 of 128 kept inside, 3x3: past 8 per unit 0.85 to 0.96 at 160 to 197 in four tiles, above
+//     1.05 elsewhere; 64 of 128 kept and 1x1: 0.99 and more; 64 wide: 1.25 and more
+//   plain, 128 wide: past 5 per unit 0.80 to 0.98 at 133 to 197 in four tiles, 1.07 and more below
+// Two ends besides: plain networks of 128 channels over a few maps of more than 200 pixels are two layers that a chip
+// shares better than one compute unit each does it (16x16 maps: 0.94 at batch 1, 0.97 at 32, 1.04 at 48), and the 128
+// wide 3x3 kernel gains nothing from nine images of 10 to 28 pixels and more (4x4 maps: 0.95 at batch 2560, 0.99 at 4096).
+static bool chain_pays(const iodf_ctx* ctx, const DevChain& C, long long hw, int batch, int images, int tiles) {
+    if (C.nc_x < 4) return true;
+    const bool heavy = C.nc_t == 4 && C.taps_two == 9;
+    const long long n = ctx->n_cu, groups = (batch + images - 1) / images, filled = 100 * groups * tiles * 32 / (batch * hw);
+    if (!C.blocks && hw > 200 && batch <= n / 8) return false;
+    if (heavy && images > 8 && hw > 9 && tiles == kChainMaxTiles) return false;
+    if (heavy && groups > 3 * n && filled > 170) return false;
+    if (tiles != 4 || (C.nc_t == 2 && C.taps_two == 1)) return true;
+    return C.blocks ? groups <= 8 * n || filled <= 150 : groups <= 5 * n || filled <= 130;
+}
+
+// Images per workgroup with which a network runs as one launch (chain.hip); 0: strips or layer by layer.
 //
-// Up to 128 pixels an image (deep levels) the one launch is always the shorter way: 128-wide residual networks of
+// Up to 128 pixels an image (deep levels) the one launch is nearly always the shorter way: 128-wide residual networks of
 // eight blocks, 18 layers, batch 1 / 64 / 256: 4x4 maps 36 / 36 / 38 us against 92 / 105 / 130 us for a launch per
 // layer, 8x8 maps 47 / 47 / 58 us against 95 / 110 / 165 us. At 256 pixels a workgroup needs 147 us whatever the
 // batch, up to one image per compute unit; strips (strip_plan) need 100 us at batch 1 and 119 at 64, while there is
-// one for every compute unit at most, and 180 at 100.
+// one for every compute unit at most, and 180 at 100. The other widths and maps of 130 pixels on change over at the same
+// batch: strips are ahead of one launch up to 64 images, behind it from 96 on.
 // Beyond an image per compute unit small images share a workgroup, which reads the weights once for all of them
 // (4x4 maps at batch 512: 82 us with two images, 103 with one).
 static int chain_batch_from(const iodf_ctx* ctx) { return ctx->n_cu / 4 + 1; }  // smallest batch at more than 128 pixels (four strips an image)
@@ -774,8 +799,9 @@ static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
     int images = 1;
     if (hw <= 64) images = std::min((batch + ctx->n_cu - 1) / ctx->n_cu, (int)(32 * kChainMaxTiles / hw));
     for (; images > 0; --images)
-        if (chain_args_ok(chain_args(ctx, N, batch, images, 1, nullptr))) break;
-    return images;
+        if (const int tiles = chain_tiles(chain_args(ctx, N, batch, images, 1, nullptr)))
+            return chain_pays(ctx, N.chain, hw, batch, images, tiles) ? images : 0;
+    return 0;
 }
 
 // Rows per strip for the three kinds of launch; rows[STRIP_BLOCK] = 0: not this way.

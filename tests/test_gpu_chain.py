@@ -116,3 +116,26 @@ def test_strips_only_where_they_win(H, batch, width, keep, k2, strips):
     assert torch.equal(z[-few:], z_few)
     assert torch.equal(flow.inverse(z), x)
     flow.close()
+
+
+# Whole networks as one launch, but where kernels of whole tiles do too much padding for many images, and where two
+# plain layers over a few large maps keep more compute units busy.
+@pytest.mark.parametrize("H,W,batch,family,width,keep,k2,chain", [
+    (10, 26, 256, RESNET, 128, 1.0, 3, True), (10, 26, 900, RESNET, 128, 1.0, 3, False), (16, 16, 900, RESNET, 128, 1.0, 3, True),
+    (16, 20, 2560, RESNET, 128, 1.0, 3, False), (8, 8, 2560, RESNET, 128, 1.0, 3, False), (8, 8, 2048, RESNET, 128, 1.0, 3, True),
+    (20, 26, 900, RESNET, 128, 1.0, 3, False), (20, 26, 900, RESNET, 128, 0.4, 3, True), (10, 26, 2560, RESNET, 128, 0.4, 3, False),
+    (10, 26, 2560, RESNET, 128, 1.0, 1, False), (10, 26, 2560, RESNET, 128, 0.4, 1, True), (10, 26, 2560, RESNET, 64, 1.0, 3, True),
+    (32, 32, 1, PLAIN, 128, 1.0, 1, False), (32, 32, 64, PLAIN, 128, 1.0, 1, True), (10, 26, 2560, PLAIN, 128, 1.0, 1, False)])
+def test_one_launch_only_where_it_wins(H, W, batch, family, width, keep, k2, chain):
+    import torch
+    cfg = FlowConfig("ragged_maps", H, W, batch, 1, 1, family, width, 0 if family == PLAIN else 1, False, keep=keep, seed_id=48, block_k2=k2)
+    print("one launch or layers", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, H, W), generator=torch.Generator().manual_seed(6), dtype=torch.uint8).cuda()
+    names, z = _kernels(flow, x)
+    assert ("k_chain" in names) == chain and ("conv_igemm" in " ".join(names)) != chain, names
+    few = min(batch, 70)
+    _, z_few = _kernels(flow, x[-few:].contiguous())
+    assert torch.equal(z[-few:], z_few)
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
