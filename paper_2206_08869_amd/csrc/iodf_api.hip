@@ -823,11 +823,15 @@ struct StripPlan { int rows[3]; };
 //   128 wide inside, 1x1: 1.93 -> 1.03 to 1.07, 2.11 -> 0.90 to 1.0
 //   64 wide, 3x3: 2.86 -> 1.04 and more, 3.08 -> 0.95 to 1.02; the two 1x1 forms with 64 channels inside: never below 1.08
 // Strips of a single row in the largest kernel lose 128 wide already while few of them run (0.88 to 0.99 up to half a
-// strip per compute unit), where they are a longer way than four layers of small tiles.
+// strip per compute unit), where they are a longer way than four layers of small tiles; with 64 kept inside only where a
+// few units get a second one (0.94 to 0.98 between 1.03 and 1.4 strips per unit, 1.03 to 1.26 below, 1.08 and more above).
 static bool strips_pay(const iodf_ctx* ctx, const DevChain& C, const StripKernel& k, int h, int w, int rows, int batch) {
     const bool k3 = C.taps_two == 9, heavy = k3 && C.nc_t == 4;
     const long long units = (long long)batch * ((h + rows - 1) / rows);
-    if (units <= 2LL * ctx->n_cu) return !(heavy && rows == 1 && k.tiles_one == kStripMaxTiles);
+    if (units <= 2LL * ctx->n_cu) {
+        if (!k3 || C.nc_x != 4 || rows > 1 || k.tiles_one < kStripMaxTiles) return true;
+        return !heavy && (units <= ctx->n_cu || 2 * units > 3LL * ctx->n_cu);
+    }
     const int most = k3 ? (heavy ? 160 : C.nc_x == 4 ? 190 : 300) : C.nc_t == 4 ? 200 : 0;  // hundredths
     const long long done = units * 32 * (9 * k.tiles_one + C.taps_two * k.tiles_two);
     return !most || 100 * done <= (long long)batch * h * w * (9 + C.taps_two) * most;
