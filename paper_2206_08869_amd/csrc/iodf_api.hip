@@ -923,23 +923,40 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     return IODF_OK;
 }
 
+// How a network runs for a batch: `images` > 0: as one launch, that many to a workgroup; else strips.rows[STRIP_BLOCK] > 0:
+// as strips; else a launch per layer.
+struct Route {
+    int images;
+    StripPlan strips;
+    bool layers() const { return !images && !strips.rows[STRIP_BLOCK]; }
+};
+
+static Route route_of(const iodf_ctx* ctx, const DevNet& N, int batch) {
+    Route r = {chain_images(ctx, N, batch), {{0, 0, 0}}};
+    if (!r.images) r.strips = strip_plan(ctx, N, batch);
+    return r;
+}
+
+// What a network's first launch reads first, in the copy of the parameters that its route takes.
+static void net_param_span(const iodf_ctx* ctx, const DevNet& N, int batch, const int8_t** p, unsigned* bytes) {
+    if (route_of(ctx, N, batch).layers()) return layer_param_span(ctx, N.layers[0], p, bytes);
+    *p = (const int8_t*)(ctx->params + N.chain.off);
+    *bytes = (unsigned)N.chain.in_bytes;
+}
+
 // `next`: the network that runs after this one (its first layer's parameters are prefetched), or nullptr.
 int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st,
             const DevNet* next = nullptr) {
-    {
-        const int images = chain_images(ctx, N, batch);
-        if (!images) {
-            const StripPlan p = strip_plan(ctx, N, batch);
-            if (p.rows[STRIP_BLOCK]) return run_strips(ctx, N, batch, mode_sign, codes, st, p);
-        } else {
-            long long macs = 0, bytes = 4LL * N.C_in + (N.layers.back().mode == MODE_CODES ? 1LL : 8LL) * N.C_out, wbytes = 0;
-            for (const DevLayer& L : N.layers) { macs += L.macs_per_pixel; wbytes += L.wgt_bytes; }
-            const long long px = (long long)batch * (ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
-            const ChainArgs ca = chain_args(ctx, N, batch, images, mode_sign, codes);
-            PROF_LAUNCH(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, launch_chain(ca, st));
-            return IODF_OK;
-        }
+    const Route route = route_of(ctx, N, batch);
+    if (route.images) {
+        long long macs = 0, bytes = 4LL * N.C_in + (N.layers.back().mode == MODE_CODES ? 1LL : 8LL) * N.C_out, wbytes = 0;
+        for (const DevLayer& L : N.layers) { macs += L.macs_per_pixel; wbytes += L.wgt_bytes; }
+        const long long px = (long long)batch * (ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
+        const ChainArgs ca = chain_args(ctx, N, batch, route.images, mode_sign, codes);
+        PROF_LAUNCH(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, launch_chain(ca, st));
+        return IODF_OK;
     }
+    if (!route.layers()) return run_strips(ctx, N, batch, mode_sign, codes, st, route.strips);
     const int lv = N.level;
     const int h = ctx->shape.H >> lv, w = ctx->shape.W >> lv;
     const int npix = batch * h * w;
@@ -953,9 +970,9 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
         ConvArgs a;
         memset(&a, 0, sizeof(a));
         {
-            const DevLayer* Ln = li + 1 < N.layers.size() ? &N.layers[li + 1] : next && !next->layers.empty() ? &next->layers[0] : nullptr;
             unsigned pfb = 0;
-            if (Ln) layer_param_span(ctx, *Ln, &a.pf, &pfb);
+            if (li + 1 < N.layers.size()) layer_param_span(ctx, N.layers[li + 1], &a.pf, &pfb);
+            else if (next && !next->layers.empty()) net_param_span(ctx, *next, batch, &a.pf, &pfb);
             a.pf_bytes = pfb;
         }
         a.in = ctx->buf[lv][L.in_buf];
