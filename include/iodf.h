@@ -60,7 +60,7 @@ enum {
     IODF_Q_MAX_BATCH = 6,
     IODF_Q_IMAGE_H = 7,
     IODF_Q_IMAGE_W = 8,
-    IODF_Q_CONV_LAUNCHES = 9,    /* convolution kernels per forward call */
+    IODF_Q_CONV_LAUNCHES = 9,    /* convolution kernels of a forward call of max_batch images, heads included */
     IODF_Q_WIDE_MACS_FORWARD = 10, /* of IODF_Q_MACS_FORWARD, the part in layers whose C_in and C_out are both >= 128 */
     IODF_Q_CODEC_HEADER_WORDS = 11, /* 32-bit words of a container's header: 1 + 3 * 16 * levels */
     IODF_Q_CODEC_MAX_WORDS = 12,    /* capacity no container exceeds: header + d (a latent sheds at most one word) */

@@ -631,7 +631,6 @@ struct iodf_ctx {
     size_t raw_elems = 0;
     size_t workspace_bytes = 0;
     long long macs_fwd = 0, macs_inv = 0, macs_wide = 0;
-    int conv_launches = 0;
     // Launch-bound shapes (small batches: ~650 dependent kernels per call) are replayed from a
     // HIP graph. A graph is captured once per (direction, batch, codes) on an internal stream
     // against internal staging buffers for x, z and codes; a call then is: copy in, graph
@@ -937,6 +936,16 @@ static Route route_of(const iodf_ctx* ctx, const DevNet& N, int batch) {
     return r;
 }
 
+// Convolution kernels of a forward call with heads.
+static long long conv_launches(const iodf_ctx* ctx, int batch) {
+    long long n = 0;
+    for (const DevNet& N : ctx->nets) {
+        const Route r = route_of(ctx, N, batch);
+        n += r.images ? 1 : r.layers() ? (long long)N.layers.size() : N.chain.blocks + 2;
+    }
+    return n;
+}
+
 // What a network's first launch reads first, in the copy of the parameters that its route takes.
 static void net_param_span(const iodf_ctx* ctx, const DevNet& N, int batch, const int8_t** p, unsigned* bytes) {
     if (route_of(ctx, N, batch).layers()) return layer_param_span(ctx, N.layers[0], p, bytes);
@@ -1155,7 +1164,6 @@ int iodf_init(iodf_ctx** out, const void* model_blob, size_t blob_bytes, int dev
             ctx->macs_fwd += L.macs_per_pixel * hw;
             if (N.kind == 0) ctx->macs_inv += L.macs_per_pixel * hw;
             if (L.wide) ctx->macs_wide += L.macs_per_pixel * hw;
-            ++ctx->conv_launches;
         }
     }
 
@@ -1877,7 +1885,7 @@ int iodf_query(iodf_ctx* ctx, int what, int64_t* out) {
         case IODF_Q_MAX_BATCH: *out = ctx->max_batch; return IODF_OK;
         case IODF_Q_IMAGE_H: *out = ctx->shape.H; return IODF_OK;
         case IODF_Q_IMAGE_W: *out = ctx->shape.W; return IODF_OK;
-        case IODF_Q_CONV_LAUNCHES: *out = ctx->conv_launches; return IODF_OK;
+        case IODF_Q_CONV_LAUNCHES: *out = conv_launches(ctx, ctx->max_batch); return IODF_OK;
         case IODF_Q_RANGE_ERRORS: {
             HIP_TRY(hipSetDevice(ctx->device));
             HIP_TRY(hipDeviceSynchronize());

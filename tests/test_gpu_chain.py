@@ -140,3 +140,17 @@ def test_one_launch_only_where_it_wins(H, W, batch, family, width, keep, k2, cha
     assert torch.equal(z[-few:], z_few)
     assert torch.equal(flow.inverse(z), x)
     flow.close()
+
+
+@pytest.mark.parametrize("name,batch", [("cfg2", 64), ("cfg2", 3), ("paper_res32", 2), ("mini_dense", 5), ("deep6", 2), ("wide_resnet", 2)])
+def test_convolution_launches_of_a_call(name, batch):
+    """IODF_Q_CONV_LAUNCHES tells the launches that a call of max_batch images makes, whatever route its networks take."""
+    import torch
+    from util import gpu_flow, images
+    flow = gpu_flow(name, batch)
+    flow.profile_begin(4096)
+    flow.forward(to_gpu(images(name, batch)))
+    torch.cuda.synchronize()
+    ran = sum(k["launches"] for k in flow.profile_end() if k["name"].startswith(("conv_igemm", "k_chain", "k_strip")))
+    assert flow.query(iodf.IODF_Q_CONV_LAUNCHES) == ran
+    flow.close()
