@@ -225,7 +225,8 @@ int iodf_conv_probe_timeline(int device_ordinal, int c_in, int c_out, int k, int
 typedef struct iodf_kernel_stat {
     char name[48];      /* kernel, e.g. "k_quant_in"; a conv kernel's launches are listed per filter size:
                            "conv_igemm<256,256,2,4,4> 3x3" and "conv_igemm<256,256,2,4,4> 1x1"; entries whose
-                           name starts with "view:" sum conv launches already listed (the wide layers) */
+                           name starts with "view:" sum conv launches already listed (the wide layers, alone in their
+                           launch; "k_chain", a whole network in one, is in no view) */
     int64_t launches;
     double total_ms;    /* sum of event-measured durations */
     int64_t macs;       /* algorithmic multiply-accumulates of those launches (kept channels, true widths) */

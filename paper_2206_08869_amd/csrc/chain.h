@@ -23,6 +23,16 @@ __host__ __device__ constexpr unsigned chain_image_bytes(int h, int w, unsigned 
     return ps ? (h + 2) * chain_row_bytes(w, ps) + ((h * w * ps - (h + 2) * chain_row_bytes(w, ps)) & 255u) : 0u;
 }
 
+// How the waves of a workgroup divide n_blk blocks of 32 channels x `tiles` tiles of 32 pixels: share_blocks blocks to a
+// wave, and as many tiles as it takes; share_tiles is what all waves together then run, `tiles` or more. One block to a
+// wave reads the fewest weights but every pixel four times, which over four tiles and more is all that LDS delivers; two
+// blocks halve that (strips of 32x32 maps at batch 256, whole call: 8920 -> 8707 us for four tiles).
+__host__ __device__ constexpr int share_blocks(int n_blk, int tiles) { return n_blk == 4 && tiles >= 4 ? 2 : 1; }
+__host__ __device__ constexpr int share_tiles(int waves, int n_blk, int tiles) {
+    const int wp = waves / (n_blk / share_blocks(n_blk, tiles));
+    return (tiles + wp - 1) / wp * wp;
+}
+
 // Parameters of a network, one block: for every layer its weights and then its constants, in the order first layer,
 // (first, second convolution) of every residual block, last layer. Weights are fragments of 1 KB,
 // [n_blk][taps * nc][64 lanes][16 bytes]: lane l of fragment (blk, tap * nc + c) holds, for filter 32 * blk + l % 32,
@@ -90,11 +100,14 @@ size_t chain_lds_bytes(const ChainArgs& a);
 // Tiles of the kernel for this network and this many images per workgroup; 0: there is none.
 int chain_tiles(const ChainArgs& a);
 hipError_t launch_chain(const ChainArgs& a, hipStream_t stream);
+// Multiply-accumulates the matrix cores run for a launch: whole tiles, padded widths.
+long long chain_issued_macs(const ChainArgs& a);
 // The kernel for strips of `rows` rows of h x w images, or nullptr: `block` of the residual networks with these widths,
 // or one of the ends (nc_t and taps_two unused).
 enum StripPart { STRIP_IN, STRIP_BLOCK, STRIP_LAST };
 const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int h, int w, int rows);
 hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a, hipStream_t stream);
+long long strip_issued_macs(StripPart part, const StripKernel& k, const StripArgs& a);
 hipError_t chain_setup();
 
 }  // namespace iodf

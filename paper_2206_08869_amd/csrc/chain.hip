@@ -81,6 +81,29 @@ const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps
     return nullptr;
 }
 
+// One layer of a workgroup: n_blk blocks of 32 filters over `tiles` tiles, nc chunks of 32 input channels.
+static long long layer_macs(int waves, int n_blk, int tiles, int taps, int nc) {
+    return 32LL * share_tiles(waves, n_blk, tiles) * 32 * n_blk * taps * 32 * nc;
+}
+
+long long strip_issued_macs(StripPart part, const StripKernel& k, const StripArgs& a) {
+    const int waves = kStripThreads / 64;
+    long long per = 0;
+    if (part == STRIP_IN) per = layer_macs(waves, k.nc_x, k.tiles_two, 9, a.nc_q);
+    else if (part == STRIP_LAST) per = layer_macs(waves, a.n_blk_last, k.tiles_two, a.taps_last, k.nc_x);
+    else per = layer_macs(waves, k.nc_t, k.tiles_one, 9, k.nc_x) + layer_macs(waves, k.nc_x, k.tiles_two, k.taps_two, k.nc_t);
+    return per * ((a.h + a.rows - 1) / a.rows) * a.batch;
+}
+
+long long chain_issued_macs(const ChainArgs& a) {
+    if (!chain_tiles(a)) return 0;
+    const ChainKernel& k = *kernel_for(a);
+    const int waves = k.threads / 64;
+    long long per = layer_macs(waves, k.nc_x, k.tiles, 9, a.nc_q) + layer_macs(waves, a.n_blk_last, k.tiles, a.taps_last, k.nc_x);
+    if (a.blocks) per += a.blocks * (layer_macs(waves, k.nc_t, k.tiles, 9, k.nc_x) + layer_macs(waves, k.nc_x, k.tiles, k.taps_two, k.nc_t));
+    return per * ((a.batch + a.images - 1) / a.images);
+}
+
 hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a, hipStream_t st) {
     if (a.batch <= 0) return hipSuccess;
     if (!k || !a.params || (part == STRIP_IN ? !a.out || !a.state || !a.idx : !a.in) || (part == STRIP_BLOCK && !a.out) ||

@@ -34,14 +34,12 @@ __device__ __forceinline__ gbytes uniform(gbytes p) {
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// How NW waves divide n_blk blocks of 32 channels x `tiles` tiles of 32 pixels: TC blocks and TP tiles to a wave. One
-// block to a wave reads the fewest weights but every pixel four times, which over four tiles and more is all that LDS
-// delivers; two blocks halve that (strips of 32x32 maps at batch 256, whole call: 8920 -> 8707 us for four tiles).
+// share_blocks / share_tiles of chain.h as constants: TC blocks and TP tiles to a wave.
 template <int NW, int N_BLK, int TILES>
 struct Share {
-    static constexpr int TC = N_BLK == 4 && TILES >= 4 ? 2 : 1;
+    static constexpr int TC = share_blocks(N_BLK, TILES);
     static constexpr int WC = N_BLK / TC, WP = NW / WC;
-    static constexpr int TP = (TILES + WP - 1) / WP;
+    static constexpr int TP = share_tiles(NW, N_BLK, TILES) / WP;
 };
 
 // The products of one layer. Weights come in fragments of 1 KB per channel block and step (a step: one tap, 32

@@ -693,12 +693,13 @@ long long issued_macs(const ConvArgs& a) {
 }
 
 // Launch through `call`, bracketed by events when profiling is on.
-#define PROF_LAUNCH(ctx, st, cls, macs, bytes, call)        \
-    do {                                                    \
-        const bool p__ = prof_start(ctx, st);               \
-        HIP_TRY(call);                                      \
-        if (p__) prof_stop(ctx, st, cls, macs, bytes);      \
+#define PROF_LAUNCH_CONV(ctx, st, cls, macs, bytes, issued, wide, call)       \
+    do {                                                                      \
+        const bool p__ = prof_start(ctx, st);                                 \
+        HIP_TRY(call);                                                        \
+        if (p__) prof_stop(ctx, st, cls, macs, bytes, issued, wide);          \
     } while (0)
+#define PROF_LAUNCH(ctx, st, cls, macs, bytes, call) PROF_LAUNCH_CONV(ctx, st, cls, macs, bytes, 0, 0, call)
 
 static const int32_t* partial_of(const iodf_ctx* ctx);
 
@@ -903,22 +904,25 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     a.params = ctx->params + C.off;
     a.out = ctx->buf[lv][cur];
     const StripKernel* k = kernel(STRIP_IN);
-    PROF_LAUNCH(ctx, st, CLS_STRIP_IN, macs(0), (4LL * N.C_in + xbytes) * px + wbytes(0), launch_strip(STRIP_IN, k, a, st));
+    PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_IN, macs(0), (4LL * N.C_in + xbytes) * px + wbytes(0), strip_issued_macs(STRIP_IN, *k, a), 0,
+                     launch_strip(STRIP_IN, k, a, st));
     k = kernel(STRIP_BLOCK);
     for (int b = 0; b < C.blocks; ++b) {
         a.params = ctx->params + C.off + C.in_bytes + (size_t)b * C.block_bytes;
         a.in = ctx->buf[lv][cur];
         cur = BUF_A + BUF_B - cur;
         a.out = ctx->buf[lv][cur];
-        PROF_LAUNCH(ctx, st, CLS_STRIP_BLOCK, macs(1 + 2 * b) + macs(2 + 2 * b),
-                    2 * xbytes * px + wbytes(1 + 2 * b) + wbytes(2 + 2 * b), launch_strip(STRIP_BLOCK, k, a, st));
+        const bool wide = N.layers[1 + 2 * b].wide && N.layers[2 + 2 * b].wide;
+        PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_BLOCK, macs(1 + 2 * b) + macs(2 + 2 * b),
+                         2 * xbytes * px + wbytes(1 + 2 * b) + wbytes(2 + 2 * b), strip_issued_macs(STRIP_BLOCK, *k, a),
+                         wide ? (lv <= 2 ? 2 : 1) : 0, launch_strip(STRIP_BLOCK, k, a, st));
     }
     a.params = ctx->params + C.off + C.in_bytes + (size_t)C.blocks * C.block_bytes;
     a.in = ctx->buf[lv][cur];
     const int nl = (int)N.layers.size();
     k = kernel(STRIP_LAST);
-    PROF_LAUNCH(ctx, st, CLS_STRIP_LAST, macs(nl - 1), (xbytes + (codes ? 1LL : 8LL) * N.C_out) * px + wbytes(nl - 1),
-                launch_strip(STRIP_LAST, k, a, st));
+    PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_LAST, macs(nl - 1), (xbytes + (codes ? 1LL : 8LL) * N.C_out) * px + wbytes(nl - 1),
+                     strip_issued_macs(STRIP_LAST, *k, a), 0, launch_strip(STRIP_LAST, k, a, st));
     return IODF_OK;
 }
 
@@ -962,7 +966,7 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
         for (const DevLayer& L : N.layers) { macs += L.macs_per_pixel; wbytes += L.wgt_bytes; }
         const long long px = (long long)batch * (ctx->shape.H >> N.level) * (ctx->shape.W >> N.level);
         const ChainArgs ca = chain_args(ctx, N, batch, route.images, mode_sign, codes);
-        PROF_LAUNCH(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, launch_chain(ca, st));
+        PROF_LAUNCH_CONV(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, chain_issued_macs(ca), 0, launch_chain(ca, st));
         return IODF_OK;
     }
     if (!route.layers()) return run_strips(ctx, N, batch, mode_sign, codes, st, route.strips);

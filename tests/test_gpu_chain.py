@@ -154,3 +154,24 @@ def test_convolution_launches_of_a_call(name, batch):
     ran = sum(k["launches"] for k in flow.profile_end() if k["name"].startswith(("conv_igemm", "k_chain", "k_strip")))
     assert flow.query(iodf.IODF_Q_CONV_LAUNCHES) == ran
     flow.close()
+
+
+def test_profile_of_strips_and_whole_networks():
+    """Their launches report the matrix work that ran (no less than what the layers need, padding included), and blocks
+    of two wide layers are in the wide-layer view."""
+    import torch
+    from util import gpu_flow, images
+    flow = gpu_flow("cfg2", 4)   # level 1: strips of 16x16 maps, level 2: 8x8 maps as one launch
+    flow.profile_begin(4096)
+    flow.forward(to_gpu(images("cfg2", 4)))
+    torch.cuda.synchronize()
+    stats = {k["name"]: k for k in flow.profile_end()}
+    for name in ("k_strip_in", "k_strip_block", "k_strip_last", "k_chain"):
+        assert stats[name]["issued_macs"] >= stats[name]["macs"] > 0, stats[name]
+    blocks = stats["k_strip_block"]
+    for view in ("view: wide conv layers", "view: wide conv layers, levels 1-2"):
+        assert (stats[view]["launches"], stats[view]["macs"]) == (blocks["launches"], blocks["macs"])
+    # a workgroup takes one 8x8 map, two tiles of 32 pixels; its last layer, 12 filters of 32, runs over four
+    per_image = 64 * 128 * (9 * 32 + 2 * (9 + 1) * 128) + 128 * 32 * 9 * 128
+    assert stats["k_chain"]["issued_macs"] == 4 * stats["k_chain"]["launches"] * per_image
+    flow.close()
