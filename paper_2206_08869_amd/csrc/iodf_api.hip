@@ -222,7 +222,8 @@ struct DevLayer {
     int out_buf, out_off;  // output tensor (MODE_ACT)
     size_t wgt_off, bias_off, mul_off, shift_off;  // byte offsets into the parameter arena
     size_t hi_off = (size_t)-1;                    // rq_fast layers: clamp bound per channel
-    bool no_ties = false;                          // rq_fast layers: no accumulator requantises to exactly half a code
+    // rq_fast layers with a shortcut, without ReLU or last of their network: no accumulator requantises to exactly half a code
+    bool no_ties = false;
     // Unsigned format: a code u in 0..255 is stored as the byte u - 128 and planes are bordered with
     // -128, so that the int8 matrix cores see u - 128 everywhere; a layer reading such a tensor adds
     // 128 * (sum of its weights) to its bias, a layer writing one saturates to [0, 255] and stores u - 128.
@@ -302,8 +303,18 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
     int32_t* bias = (int32_t*)(A.host.data() + D.bias_off);
     int32_t* mul = (int32_t*)(A.host.data() + D.mul_off);
     int32_t* sh = (int32_t*)(A.host.data() + D.shift_off);
+    // live input columns as runs c .. c + len - 1 that lie together in a 64-channel plane, at pc .. pc + len - 1
+    struct Run { int c, pc, len; };
+    std::vector<Run> runs;
     int live = 0;
-    for (int c = 0; c < L.C_in; ++c) live += colpos[c] >= 0;
+    for (int c = 0; c < L.C_in; ++c) {
+        const int pc = colpos[c];
+        if (pc < 0) continue;
+        ++live;
+        Run* const r = runs.empty() ? nullptr : &runs.back();
+        if (r && c == r->c + r->len && pc == r->pc + r->len && (pc & 63)) ++r->len;
+        else runs.push_back({c, pc, 1});
+    }
     int kept = 0;
     for (size_t n = 0; n < rows.size(); ++n) {
         const int r = rows[n];
@@ -311,12 +322,12 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
         ++kept;
         const int8_t* src = L.W + (size_t)r * L.C_in * taps;
         // input column pc, tap t goes to k-tile (pc / 64) * taps + t, row n, byte pc % 64
-        for (int c = 0; c < L.C_in; ++c) {
-            const int pc = colpos[c];
-            if (pc < 0) continue;
-            for (int t = 0; t < taps; ++t)
-                w[(((size_t)(pc >> 6) * taps + t) * D.n_pad + n) * 64 + (pc & 63)] = src[(size_t)c * taps + t];
-        }
+        for (const Run& r : runs)
+            for (int t = 0; t < taps; ++t) {
+                int8_t* const d = w + (((size_t)(r.pc >> 6) * taps + t) * D.n_pad + n) * 64 + (r.pc & 63);
+                const int8_t* const s = src + (size_t)r.c * taps + t;
+                for (int i = 0; i < r.len; ++i) d[i] = s[(size_t)i * taps];
+            }
         long long fold = 0;  // sum of the row's kept weights
         if (D.in_unsigned)
             for (int c = 0; c < L.C_in; ++c)
@@ -352,7 +363,7 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
             if (a < (unsigned __int128)INT32_MAX) hi[n] = (int32_t)(uint64_t)a;
         }
     }
-    if (D.rq_fast) {
+    if (D.rq_fast && (D.shortcut || !D.relu || D.mode != MODE_ACT)) {  // no other epilogue asks
         // acc * M / 2^s is half a code for acc an odd multiple of 2^(s - 1 - t) only, t = trailing zeros of M: compare
         // with the largest accumulator the row's weights and bias allow (input bytes are at most 128 in magnitude).
         D.no_ties = true;
@@ -362,9 +373,11 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
             if (mul[n] <= 0) continue;
             const int8_t* src = L.W + (size_t)rows[n] * L.C_in * taps;
             long long sum = 0;
-            for (int c = 0; c < L.C_in; ++c)
-                if (colpos[c] >= 0)
-                    for (int t = 0; t < taps; ++t) sum += src[(size_t)c * taps + t] < 0 ? -src[(size_t)c * taps + t] : src[(size_t)c * taps + t];
+            for (const Run& r : runs) {
+                unsigned part = 0;  // at most 128 * 64 * 9
+                for (int i = 0; i < r.len * taps; ++i) part += (unsigned)abs((int)src[(size_t)r.c * taps + i]);
+                sum += part;
+            }
             const long long b = ((const int32_t*)(A.host.data() + D.bias_off))[n];
             const long long amax = 128 * sum + (b < 0 ? -b : b);
             const int e = sh[n] + 31 - __builtin_ctz((unsigned)mul[n]);  // s - 1 - t
@@ -516,8 +529,8 @@ void plan_net(Arena& A, const HostModel& m, const HostNet& N, DevNet& D, int buf
         if (H.k == 3 && cin_pad >= kExpandFromCin) {
             pack_last_expanded(A, H, cols, cin_pad, last_mode, d);
         } else {
-            pack_layer(A, H, kept_rows(H), cols, cin_pad, d);
             d.mode = last_mode;
+            pack_layer(A, H, kept_rows(H), cols, cin_pad, d);
             d.n_store = N.C_out;
         }
     };
@@ -1133,7 +1146,7 @@ int iodf_init(iodf_ctx** out, const void* model_blob, size_t blob_bytes, int dev
 
     // plan: pack weights (gate compaction), constants and composed permutations
     Arena A;
-    A.host.reserve(blob_bytes + blob_bytes / 2 + (1 << 20));
+    A.host.reserve((hm.family == FAM_DENSE ? blob_bytes + blob_bytes / 2 : 3 * blob_bytes) + (1 << 20));  // pack_chain: a second copy
     ctx->nets.resize(hm.nets.size());
     ctx->buf.assign(hm.levels + 2, std::array<int8_t*, NUM_BUFS>{nullptr, nullptr, nullptr});
     ctx->buf_w.assign(hm.levels + 2, std::array<int, NUM_BUFS>{0, 0, 0});
