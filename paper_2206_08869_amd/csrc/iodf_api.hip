@@ -1756,7 +1756,7 @@ static int conv_probe_impl(int device_ordinal, int c_in, int c_out, int k, int h
     a.n_cu = n_cu;
     a.wgt = (const int8_t*)(params + D.wgt_off); a.n_pad = n_pad;
     a.bias = (const int32_t*)(params + D.bias_off); a.mul = (const int32_t*)(params + D.mul_off);
-    a.shift = (const int32_t*)(params + D.shift_off); a.rq_fast = D.rq_fast;
+    a.shift = (const int32_t*)(params + D.shift_off); a.rq_fast = D.rq_fast; a.no_ties = D.no_ties;
     a.clamp_hi = D.hi_off == (size_t)-1 ? nullptr : (const int32_t*)(params + D.hi_off);
     a.n_store = n_pad; a.mode = MODE_ACT; a.relu = relu ? 1 : 0; a.out = dout; a.out_plane = plane;
     PROBE_TRY(hipEventCreate(&e0));

@@ -351,6 +351,33 @@ def test_epilogue_at_the_saturation_edges(relu, edge, b, side, c_in):
         assert 0 in seen
 
 
+@pytest.mark.parametrize("ties", [True, False])
+@pytest.mark.parametrize("b,side,c_in", [(2, 16, 64), (136, 32, 256)])
+def test_epilogue_without_relu_at_halves(ties, b, side, c_in):
+    """Layers without ReLU take a shorter epilogue where no accumulator requantises to exactly half a code. With
+    multipliers 2^30 and shifts 33 and 34 an accumulator a gives a / 8 and a / 16, so that the seven neighbouring
+    accumulators of a pixel include halves of either sign (rounded away from zero, not up); with odd multipliers just
+    below and above that, the nearest quotients on either side of a half."""
+    import oracle
+    c_out = 256
+    rng = np.random.default_rng(78 + b)
+    M = np.full(c_out, 1 << 30, np.int64) + (0 if ties else rng.choice([1, 3], c_out))
+    shift = (33 + np.arange(c_out) % 2).astype(np.uint8)
+    code = rng.integers(-130, 130, c_out)
+    bias = ((2 * code + 1) << (shift.astype(np.int64) - 31)).astype(np.int32)   # halfway between two codes
+    W = np.zeros((c_out, c_in, 1, 1), np.int8)
+    W[:, 0] = 1
+    W[:, 1] = -1
+    x = np.zeros((b, c_in, side, side), np.int8)
+    delta = (np.arange(b * side * side) % 7 - 3).reshape(b, side, side)
+    x[:, 0] = np.maximum(delta, 0)
+    x[:, 1] = np.maximum(-delta, 0)
+    y, _ = iodf.iodf_conv_probe(x, W, bias, M.astype(np.int32), shift, relu=False, iters=1)
+    for i in range(b):
+        ref = oracle.epilogue(oracle.conv_acc(x[i], W, bias), M.astype(np.int32), shift, relu=False)
+        assert np.array_equal(y[i], ref), "image %d" % i
+
+
 @pytest.mark.parametrize("c_in,k,b,side,tiles", [(64, 3, 2, 16, 32), (256, 1, 136, 32, 544)])
 def test_conv_probe_timeline(c_in, k, b, side, tiles):
     """The per-tile timeline is measurement support: it must not change the layer's result, report one
