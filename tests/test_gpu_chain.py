@@ -12,7 +12,17 @@ from util import to_gpu
 pytestmark = pytest.mark.gpu
 
 
-def _check(cfg, batch, blob=None):
+def _kernels(flow, x):
+    """Names of the kernels one forward call runs, and its latents."""
+    import torch
+    flow.profile_begin(4096)
+    z = flow.forward(x)[0]
+    torch.cuda.synchronize()
+    return {k["name"].split("<")[0] for k in flow.profile_end()}, z
+
+
+def _check(cfg, batch, blob=None, kernel="k_chain", alone=True):
+    """Forward and inverse against the oracle; `kernel` runs the networks (with `alone`: all of them)."""
     import oracle
     import torch
     blob = make_blob(cfg) if blob is None else blob
@@ -29,14 +39,17 @@ def _check(cfg, batch, blob=None):
         x2 = flow.inverse(z)
         torch.cuda.synchronize()
         assert np.array_equal(x2.cpu().numpy(), x)
+    names, _ = _kernels(flow, to_gpu(x))
+    ran = {n for n in names if n.startswith(("k_chain", "k_strip_block", "conv_igemm"))}
+    assert kernel in ran and (not alone or ran == {kernel}), names
     flow.close()
 
 
-# level-1 maps H/2 x W/2: 1, 2, 3..4 and 5..8 tiles of 32 pixels, full and ragged; images of 128 pixels and more run
-# as one launch from batch 40 on
+# level-1 maps H/2 x W/2: 1, 2, 3..4 and 5..8 tiles of 32 pixels, full and ragged; images of more than 128 pixels run
+# as one launch from an image for every fourth compute unit on (65), as strips below
 @pytest.mark.parametrize("H,W,batch", [(8, 8, 1), (8, 16, 1), (12, 12, 2), (16, 16, 1), (16, 20, 3), (16, 32, 2),
-                                       (24, 40, 41), (32, 32, 40)])
-@pytest.mark.parametrize("width,keep,k2", [(128, 1.0, 3), (128, 0.4, 3), (128, 0.4, 1), (64, 1.0, 3), (40, 0.8, 1)])
+                                       (2, 128, 2), (20, 26, 65), (24, 40, 67), (32, 32, 66)])
+@pytest.mark.parametrize("width,keep,k2", [(128, 1.0, 3), (128, 0.4, 3), (128, 1.0, 1), (128, 0.4, 1), (64, 1.0, 3), (40, 0.8, 1)])
 def test_tiles_and_widths(H, W, batch, width, keep, k2):
     _check(FlowConfig("chain", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=41, block_k2=k2), batch)
 
@@ -44,6 +57,7 @@ def test_tiles_and_widths(H, W, batch, width, keep, k2):
 @pytest.mark.parametrize("width,unsigned", [(128, False), (128, True), (48, True)])
 def test_plain_and_unsigned(width, unsigned):
     _check(FlowConfig("plain", 16, 16, 3, 2, 2, PLAIN, width, 0, True, seed_id=42, act_unsigned=unsigned), 3)
+    _check(FlowConfig("plain", 32, 32, 34, 1, 2, PLAIN, width, 0, False, seed_id=42, act_unsigned=unsigned), 34)
     _check(FlowConfig("res_u", 16, 16, 3, 3, 1, RESNET, width, 1, True, seed_id=43, act_unsigned=unsigned, block_k2=3), 3)
 
 
@@ -73,27 +87,17 @@ def test_ties_and_last_layers():
             net["layers"][-1]["W"] = np.ascontiguousarray(net["layers"][-1]["W"][:, :, 1:2, 1:2])
         if n % 3 == 2:
             net["layers"][-1]["flags"] |= 1
-    _check(cfg, 2, pack_blob(m))
+    _check(cfg, 2, pack_blob(m), alone=False)   # ties in a shortcut layer: layer by layer
 
 
-# strips: 24x40, 16x16 and 32x32 maps at batches that give one row, a few rows and the most rows a strip (the last
-# strip of an image short), images one strip high, and widths that are no multiple of a tile
-@pytest.mark.parametrize("H,W,batch", [(48, 80, 1), (32, 32, 1), (32, 32, 13), (64, 64, 3), (64, 64, 17), (64, 64, 66),
-                                       (2, 128, 2), (34, 70, 9)])
+# strips: 24x40, 16x16 and 32x32 maps at batches that give one row, a few rows and the most rows a strip XX that are no multiple of a tile
+@pytest.mark.parametrize("H,W,batch", [(48, 80, 1), (32, 32, 1), (32, 32, 13), (32, 32, 64), (64, 64, 3), (64, 64, 17), (64, 64, 66),
+                                       (10, 52, 2), (34, 70, 9)])
 @pytest.mark.parametrize("width,keep,k2,unsigned", [(128, 1.0, 3, False), (128, 0.4, 1, True), (64, 1.0, 3, True),
-                                                    (128, 0.4, 3, False)])
+                                                    (128, 0.4, 3, False), (128, 1.0, 1, False), (48, 1.0, 1, True)])
 def test_strips(H, W, batch, width, keep, k2, unsigned):
     _check(FlowConfig("strips", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=46, block_k2=k2,
-                      act_unsigned=unsigned), batch)
-
-
-def _kernels(flow, x):
-    """Names of the kernels one forward call runs, and its latents."""
-    import torch
-    flow.profile_begin(4096)
-    z = flow.forward(x)[0]
-    torch.cuda.synchronize()
-    return {k["name"].split("<")[0] for k in flow.profile_end()}, z
+                      act_unsigned=unsigned), batch, kernel="k_strip_block")
 
 
 # Maps whose rows fill the largest strip kernel badly go layer by layer once more strips wait than run at once, or at
