@@ -27,7 +27,14 @@ if ROOT not in sys.path:
 INT8_PEAK_TOPS = 5000.0   # MI355X dense int8 MFMA peak, TOP/s
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_PROFILE = os.path.join("profiles", "conv_hbm_traffic_cfg4.md")
-CONV_SOURCE = os.path.join("paper_2206_08869_amd", "csrc", "conv_mfma.hip")
+CONV_SOURCES = [os.path.join("paper_2206_08869_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_dev.h", "conv.h")]
+
+
+def conv_source_hash():
+    sha = hashlib.sha256()
+    for f in CONV_SOURCES:
+        sha.update(open(os.path.join(ROOT, f), "rb").read())
+    return sha.hexdigest()[:16]
 
 
 def recorded_traffic(workload_key, kernel):
@@ -44,11 +51,11 @@ def recorded_traffic(workload_key, kernel):
     if not m:
         return None, "%s has no machine-readable line" % TRAFFIC_PROFILE
     rec = json.loads(m.group(1))
-    sha = hashlib.sha256(open(os.path.join(ROOT, CONV_SOURCE), "rb").read()).hexdigest()[:16]
+    sha = conv_source_hash()
     if rec.get("workload") != workload_key:
         return None, "recorded for %s, not for %s" % (rec.get("workload"), workload_key)
     if rec.get("conv_source_sha16") != sha:
-        return None, "recorded with another build of %s (%s, now %s)" % (CONV_SOURCE, rec.get("conv_source_sha16"), sha)
+        return None, "recorded with another build of %s (%s, now %s)" % (", ".join(CONV_SOURCES), rec.get("conv_source_sha16"), sha)
     if kernel not in rec.get("bytes_per_launch", {}):
         return None, "kernel not in %s" % TRAFFIC_PROFILE
     return rec["bytes_per_launch"][kernel], "%s (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, scaled by a 1 GiB copy)" % TRAFFIC_PROFILE

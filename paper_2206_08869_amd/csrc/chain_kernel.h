@@ -10,7 +10,8 @@
 // 57 bytes a clock that a CU gets from its L2 are 2600):
 //   4x4 maps, 1 tile of pixels:   products 2700, the weights; epilogue and barrier 950
 //   8x8 maps, 2 tiles:            products 3950 (matrix cores 2300, LDS reads 2300, weights 2600); 1350 to 1600
-//   16x16 maps, 8 tiles, 4 waves: products 11300 (matrix cores 9200); epilogue 4200, with a shortcut 5000
+//   16x16 maps, 8 tiles:          products 11300 (matrix cores 9200); epilogue 4200, with a shortcut 5000, taken with four
+//                                 waves; the eight of the table run one's epilogue under the other's products
 #pragma once
 #include "chain.h"
 #include "conv_dev.h"

@@ -12,9 +12,9 @@
 // the slot X mod M, finds the symbol whose [C, C + F) holds it by bisection over r, restores
 // X <- F * floor(X / M) + (X mod M) - C and pulls a word back in when X < 2^31.
 // A chunk's latents are dealt round-robin to 16 lanes, each an independent stream encoded
-// last-to-first. The chains are serial (one thread per lane when encoding, sixteen when
-// decoding), so these kernels are bound by dependent integer latency, not by memory or the
-// vector units.
+// last-to-first. The chains are serial (encoding: one thread to a lane, what it is fed worked out
+// by other waves; decoding: half a wave to a lane), so these kernels are bound by dependent
+// integer latency, not by memory or the vector units.
 #include "codec_kernels.h"
 
 #include <cmath>
@@ -116,8 +116,9 @@ __global__ __launch_bounds__(TPB) void k_prior_cf(const CodecTables t, const Chu
 // thread, and the other four work out the masses and reciprocals of the next kEncBlock symbols of every lane
 // meanwhile. The chain's division X / F (63 by 24 bits, the quotient below 2^39) is a product with 1 / F in double
 // precision, off by less than 1.01 in either direction, and one correction.
-// Bound: the chain, about 110 ns a symbol (1150 ns with a thread per lane that also fetched, looked up and divided;
-// paper_res64 at batch 256, 1024 chunks of up to 384 symbols a lane: 443 us before).
+// Bound: the chain. paper_res64, up to 384 symbols a lane: 65 to 72 us at batch 1, 170 to 190 ns a symbol, the same
+// with eight producing waves instead of four; at batch 256, four workgroups to a compute unit, 94 us, 245 ns (eight
+// producing waves: 205 us, since two workgroups fit; a thread per lane that also fetched, looked up and divided: 443 us).
 constexpr int kEncBlock = 32;
 constexpr int kEncThreads = 320;
 

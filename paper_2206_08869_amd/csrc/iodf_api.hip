@@ -764,7 +764,8 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
     }
     // Over a single tile a step's weights take longer than its products, so that each miss in the L2 shows: eight
     // workgroups per XCD read them ahead (4x4 maps: 36 -> 31 us a network at batch 16, 1 us at 256). Over more
-    // tiles they only compete with the first layers (8x8 maps at batch 256: 58 -> 59 us).
+    // tiles they compete with the first layers where every compute unit has a workgroup (8x8 maps at batch 256:
+    // 58 -> 59 us; fewer images were not tried).
     a.pf_blocks = (unsigned char)(images * a.h * a.w <= 32 ? 8 : 0);
     return a;
 }

@@ -130,3 +130,18 @@ def test_codec_tables_of_the_library_are_the_correctly_rounded_ones():
     assert lib.iodf_conv_probe(0, 8, 8, 3, 8193, 4, 1, 1, buf, buf, buf, buf, buf, buf, 1, None) == -1
     assert lib.iodf_conv_probe(0, 8, 8, 3, 4, 70000, 1, 1, buf, buf, buf, buf, buf, buf, 1, None) == -1
     assert lib.iodf_tile_patches(None, None, 8, 8, 0, 1, None, None) == -1
+
+
+def test_recorded_traffic_is_tied_to_every_conv_source(tmp_path, monkeypatch):
+    """bench.py reports recorded HBM traffic only for the build it was recorded with: any of the conv kernels' sources
+    changes the hash."""
+    import bench
+    assert {os.path.basename(f) for f in bench.CONV_SOURCES} == {"conv_mfma.hip", "conv_dev.h", "conv.h"}
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "CONV_SOURCES", ["a", "b", "c"])
+    seen = set()
+    for changed in ("", "a", "b", "c"):
+        for f in "abc":
+            (tmp_path / f).write_text("1" if f == changed else "0")
+        seen.add(bench.conv_source_hash())
+    assert len(seen) == 4
