@@ -82,6 +82,9 @@ struct StripArgs {
     unsigned short state_c, n_a, n_out;
     unsigned char shift_in, act_unsigned, relu_last, last_fast, n_blk_last, taps_last, nc_q;
     signed char sign;
+    unsigned char pf_blocks;  // workgroups per XCD behind the strips that bring pf .. pf + pf_bytes into its L2
+    unsigned pf_bytes;        // what the next launch reads first
+    const uint8_t* pf;
 };
 struct StripKernel {
     int nc_x, nc_t, taps_two;

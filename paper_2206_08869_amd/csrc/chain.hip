@@ -114,7 +114,7 @@ hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a
     StripArgs b = a;
     b.chunk = (unsigned short)((units + 7) / 8);
     if (units > kStripMaxUnits) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k->kern, dim3(8 * b.chunk), dim3(kStripThreads),
+    hipLaunchKernelGGL(k->kern, dim3(8 * (b.chunk + b.pf_blocks)), dim3(kStripThreads),
                        strip_lds_bytes(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.w, a.rows), st, b);
     return hipGetLastError();
 }

@@ -301,14 +301,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         // workgroups beyond the groups bring the parameters into the L2 of an XCD that has groups (blocks go round the XCDs)
         if ((int)(blockIdx.x & 7) >= groups) return;
         const int base = (groups + 7) >> 3;  // first slot of an XCD that may hold such a block
-        const unsigned lines = a.pf_bytes >> 7, stride = a.pf_blocks * kThreads;
-        int sum = 0;
-        for (unsigned l = (((int)blockIdx.x >> 3) - base) * kThreads + tid; l < lines; l += 4 * stride) {
-#pragma unroll
-            for (unsigned u = 0; u < 4; ++u)
-                if (l + u * stride < lines) sum += *(const int*)(a.params + ((size_t)(l + u * stride) << 7));
-        }
-        asm volatile("" ::"v"(sum));  // the loads are the point: keep them
+        touch_lines(a.params, a.pf_bytes >> 7, (((int)blockIdx.x >> 3) - base) * kThreads + tid, a.pf_blocks * kThreads);
         return;
     }
     const int img0 = blockIdx.x * a.images;

@@ -25,6 +25,18 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl<0, N>(f);
 }
 
+// Reads one word of every 128-byte line of p, lines first, first + stride, ..., so that they sit in this XCD's L2. Four
+// independent loads at a time: a thread pays one memory latency a round and not one a line.
+__device__ __forceinline__ void touch_lines(const uint8_t* p, const unsigned lines, const unsigned first, const unsigned stride) {
+    int sum = 0;
+    for (unsigned l = first; l < lines; l += 4 * stride) {
+#pragma unroll
+        for (unsigned u = 0; u < 4; ++u)
+            if (l + u * stride < lines) sum += *(const int*)(p + ((size_t)(l + u * stride) << 7));
+    }
+    asm volatile("" ::"v"(sum));  // the loads are the point: keep them
+}
+
 // Round-half-away-from-zero of acc * M / 2^s, clamped far outside the 8-bit range
 // (the caller saturates to 8 bit after adding at most one 8-bit shortcut).
 __device__ __forceinline__ int rq_dev(int acc, int M, int s) {

@@ -764,9 +764,11 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
     }
     // Over a single tile a step's weights take longer than its products, so that each miss in the L2 shows: eight
     // workgroups per XCD read them ahead (4x4 maps: 36 -> 31 us a network at batch 16, 1 us at 256). Over more
-    // tiles they compete with the first layers where every compute unit has a workgroup (8x8 maps at batch 256:
-    // 58 -> 59 us; fewer images were not tried).
-    a.pf_blocks = (unsigned char)(images * a.h * a.w <= 32 ? 8 : 0);
+    // tiles that helps while most compute units have no images (8x8 maps, whole calls: paper_iodf64 at batch 1
+    // 2245 -> 2222 us, cfg2 at batch 64 197 -> 194.5); where all have, it competes with the first layers (batch 256: 58 -> 59 us
+    // a network).
+    const int groups = (batch + images - 1) / images;
+    a.pf_blocks = (unsigned char)(images * a.h * a.w <= 32 || 4 * groups <= ctx->n_cu ? 8 : 0);
     return a;
 }
 
@@ -877,7 +879,10 @@ static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     return p;
 }
 
-static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st, const StripPlan& p) {
+static void net_param_span(const iodf_ctx* ctx, const DevNet& N, int batch, const int8_t** p, unsigned* bytes);
+
+static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st, const StripPlan& p,
+                      const DevNet* next) {
     const DevChain& C = N.chain;
     const DevLayer& last = N.layers.back();
     const int lv = N.level, h = ctx->shape.H >> lv, w = ctx->shape.W >> lv;
@@ -907,6 +912,18 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
         a.codes_img_stride = ctx->d_codes;
         a.codes_off = ctx->code_off[lv];
     }
+    // What the launch behind this one reads first, fetched by workgroups of this one (eight per XCD) where there is room
+    // for them beside the strips, two workgroups to a compute unit (whole calls: paper_iodf64 at batch 1 2285 -> 2245 us,
+    // paper_res64 at batch 8 2030 -> 1993, cfg2 at batch 64 199.7 -> 196.7; four or sixteen per XCD the same).
+    auto ahead = [&](const uint8_t* at, size_t bytes) {
+        const long long units = (long long)batch * ((h + a.rows - 1) / a.rows);
+        a.pf = at;
+        a.pf_bytes = (unsigned)bytes;
+        a.pf_blocks = (unsigned char)(at && units + 8 * 8 <= 2LL * ctx->n_cu ? 8 : 0);
+    };
+    const uint8_t* const block0 = ctx->params + C.off + C.in_bytes;
+    const uint8_t* const last_at = block0 + (size_t)C.blocks * C.block_bytes;
+    const size_t last_bytes = C.bytes - (size_t)(last_at - (ctx->params + C.off));
     auto kernel = [&](StripPart part) {
         a.rows = (unsigned short)p.rows[part];
         return strip_kernel_for(part, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, p.rows[part]);
@@ -918,11 +935,14 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     a.params = ctx->params + C.off;
     a.out = ctx->buf[lv][cur];
     const StripKernel* k = kernel(STRIP_IN);
+    ahead(block0, C.block_bytes);
     PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_IN, macs(0), (4LL * N.C_in + xbytes) * px + wbytes(0), strip_issued_macs(STRIP_IN, *k, a), 0,
                      launch_strip(STRIP_IN, k, a, st));
     k = kernel(STRIP_BLOCK);
     for (int b = 0; b < C.blocks; ++b) {
-        a.params = ctx->params + C.off + C.in_bytes + (size_t)b * C.block_bytes;
+        a.params = block0 + (size_t)b * C.block_bytes;
+        if (b + 1 < C.blocks) ahead(a.params + C.block_bytes, C.block_bytes);
+        else ahead(last_at, last_bytes);
         a.in = ctx->buf[lv][cur];
         cur = BUF_A + BUF_B - cur;
         a.out = ctx->buf[lv][cur];
@@ -931,10 +951,14 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
                          2 * xbytes * px + wbytes(1 + 2 * b) + wbytes(2 + 2 * b), strip_issued_macs(STRIP_BLOCK, *k, a),
                          wide ? (lv <= 2 ? 2 : 1) : 0, launch_strip(STRIP_BLOCK, k, a, st));
     }
-    a.params = ctx->params + C.off + C.in_bytes + (size_t)C.blocks * C.block_bytes;
+    a.params = last_at;
     a.in = ctx->buf[lv][cur];
     const int nl = (int)N.layers.size();
     k = kernel(STRIP_LAST);
+    const int8_t* next_at = nullptr;
+    unsigned next_bytes = 0;
+    if (next && !next->layers.empty()) net_param_span(ctx, *next, batch, &next_at, &next_bytes);
+    ahead((const uint8_t*)next_at, next_bytes);
     PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_LAST, macs(nl - 1), (xbytes + (codes ? 1LL : 8LL) * N.C_out) * px + wbytes(nl - 1),
                      strip_issued_macs(STRIP_LAST, *k, a), 0, launch_strip(STRIP_LAST, k, a, st));
     return IODF_OK;
@@ -983,7 +1007,7 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
         PROF_LAUNCH_CONV(ctx, st, CLS_CHAIN, macs * px, bytes * px + wbytes, chain_issued_macs(ca), 0, launch_chain(ca, st));
         return IODF_OK;
     }
-    if (!route.layers()) return run_strips(ctx, N, batch, mode_sign, codes, st, route.strips);
+    if (!route.layers()) return run_strips(ctx, N, batch, mode_sign, codes, st, route.strips, next);
     const int lv = N.level;
     const int h = ctx->shape.H >> lv, w = ctx->shape.W >> lv;
     const int npix = batch * h * w;

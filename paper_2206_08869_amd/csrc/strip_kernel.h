@@ -31,6 +31,14 @@ __device__ __forceinline__ bool strip_of(const StripArgs& a, StripGeom& g) {
     return true;
 }
 
+// Workgroups behind the strips, pf_blocks to an XCD that holds strips (blocks go round the XCDs): what the next launch
+// reads first comes into the L2 while compute units would idle.
+__device__ __forceinline__ void strip_ahead(const StripArgs& a) {
+    const int slot = (int)(blockIdx.x >> 3) - a.chunk, units = (a.h + a.rows - 1) / a.rows * a.batch;
+    if (slot < 0 || (int)(blockIdx.x & 7) * a.chunk >= units) return;
+    touch_lines(a.pf, a.pf_bytes >> 7, slot * kStripThreads + threadIdx.x, a.pf_blocks * kStripThreads);
+}
+
 // Rows [y0, y1) of the stream (padding rows and columns included) into LDS, 16 bytes per thread and step, consecutive
 // threads on consecutive parts of a 64-channel plane. The first kStripLoads steps' loads are all requested by
 // strip_request, before anything else the kernel asks for, so that strip_put waits for one memory latency only.
@@ -110,7 +118,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
     StripGeom g;
-    if (!strip_of(a, g)) return;
+    if (!strip_of(a, g)) return strip_ahead(a);
     constexpr int EXT = NT2 == 3 ? 1 : 0;  // rows of the inner tensor beyond the strip
     const int h = a.h, w = a.w, W2 = w + 2;
     const int xo = g.r0 - 1 - EXT > -1 ? g.r0 - 1 - EXT : -1, xe = g.r1 + 1 + EXT < h + 1 ? g.r1 + 1 + EXT : h + 1;
@@ -190,7 +198,7 @@ __global__ __launch_bounds__(kStripThreads, 3) void k_strip_in(const StripArgs a
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
     StripGeom g;
-    if (!strip_of(a, g)) return;
+    if (!strip_of(a, g)) return strip_ahead(a);
     const int h = a.h, w = a.w, W2 = w + 2;
     const int qo = g.r0 - 1, qe = g.r1 + 1, ya = qo > 0 ? qo : 0, yb = qe < h ? qe : h;
     constexpr unsigned psq = chain_pixel_bytes(NCQ);
@@ -236,7 +244,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
     StripGeom g;
-    if (!strip_of(a, g)) return;
+    if (!strip_of(a, g)) return strip_ahead(a);
     const int h = a.h, w = a.w;
     const int xo = g.r0 - 1, xe = g.r1 + 1;
     constexpr unsigned psx = chain_pixel_bytes(NCX), xb = kChainConstBytes;
