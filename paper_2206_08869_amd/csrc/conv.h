@@ -56,17 +56,11 @@ struct ConvArgs {
     // (127, or 255 with out_unsigned), saturated to INT32_MAX; lets a ReLU layer clamp before the multiply instead of after it
     const int32_t* clamp_hi;
     int32_t* partial;  // optional split-K scratch: int32 [npix][n_pad], all zero between launches
-    union {
-        // Optional: memory the next launch will read first (its packed weights and constants, pf_bytes of
-        // them). A launch with a handful of tiles adds a few workgroups that touch it, one load per cache
-        // line, so that it sits in the L2 of the XCDs that hold tiles when that launch starts.
-        const int8_t* pf;
-        // Optional per-tile timeline (measurement support; has_trace = 1): the first wave of a workgroup writes,
-        // for the output tile in slot s, trace[8 s + 0..3] = the constant 100 MHz counter at tile start, after its
-        // first k-tile landed, after the k loop and after the epilogue; [4], [5] = the shader-clock counter at
-        // tile start and end. Slots are numbered as blockIdx.x of the plain kernel numbers them.
-        long long* trace;
-    };
+    // Optional per-tile timeline (measurement support; has_trace = 1): the first wave of a workgroup writes,
+    // for the output tile in slot s, trace[8 s + 0..3] = the constant 100 MHz counter at tile start, after its
+    // first k-tile landed, after the k loop and after the epilogue; [4], [5] = the shader-clock counter at
+    // tile start and end. Slots are numbered as blockIdx.x of the plain kernel numbers them.
+    long long* trace;
     // What the epilogue writes depends on the mode, and only that mode's fields are read: they share storage.
     union {
         struct {  // MODE_ACT
@@ -86,7 +80,6 @@ struct ConvArgs {
         };
     };
     unsigned in_plane;
-    unsigned pf_bytes;
     int npix;      // batch * h * w
     int cin_pad;   // channels read per tap, multiple of 64 (padding columns have zero weights)
     int n_pad;     // multiple of 64; rows n >= true C_out are zero
@@ -112,13 +105,12 @@ static_assert(sizeof(ConvArgs) == 120, "argument block");
 
 // Enqueue the layer on `stream`. Returns hipSuccess or the launch error.
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
-// Index of the kernel configuration launch_conv picks for `a` (-1: invalid arguments; the last index
-// stands for the persistent form of the first tile), the number of configurations, and a printable
-// name ("conv_igemm<256,256,2,4,4>").
+// Index of the kernel configuration launch_conv picks for `a` (-1: invalid arguments), the number of
+// configurations, and a printable name ("conv_igemm<256,256,2,4,4>").
 int conv_pick_tile(const ConvArgs& a);
 int conv_num_tiles();
 const char* conv_tile_name(int tile);
-// Timeline slots launch_conv would use for `a` (see ConvArgs::trace): 8 x int64 each; 0 for invalid arguments.
+// Timeline slots launch_conv uses for `a` with has_trace (see ConvArgs::trace): 8 x int64 each; 0 for invalid arguments.
 int conv_trace_slots(const ConvArgs& a);
 // Channels x pixels of a tile (0, 0 for an invalid index).
 void conv_tile_dims(int tile, int* bc, int* bp);

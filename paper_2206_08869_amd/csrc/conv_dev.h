@@ -6,6 +6,8 @@
 
 #include <type_traits>
 
+#include "conv.h"
+
 namespace iodf {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -52,8 +54,8 @@ __device__ __forceinline__ int sat8_dev(int v) { return v > 127 ? 127 : (v < -12
 
 // Four outputs of one lane, registers I .. I + 3 of its accumulators, requantised and packed into a dword of codes.
 // B: clamp bound, M: multiplier, S: shift - 32, R: rounding constant 2^(shift - 33) of the four channels.
-template <int I>
-__device__ __forceinline__ unsigned pack_relu_quad(const v16i& acc, std::integral_constant<int, I>, const v4i& Bq, const v4i& Mq,
+template <int I, class Acc>
+__device__ __forceinline__ unsigned pack_relu_quad(const Acc& acc, std::integral_constant<int, I>, const v4i& Bq, const v4i& Mq,
                                                    const v4i& Sq, const unsigned (&Rq)[4], const bool out_unsigned) {
     // ReLU without shortcut. The accumulators already hold the bias. Clamping them to
     // [0, hi] first (hi = the smallest value that requantises to 127; the rescale is
@@ -79,8 +81,8 @@ __device__ __forceinline__ unsigned pack_relu_quad(const v16i& acc, std::integra
 
 // NO_TIES: no accumulator of the layer lands exactly between two codes. Rounding half away from zero is then rounding
 // half up, one arithmetic shift of the (floored) high word, and the sign needs no handling of its own.
-template <bool NO_TIES, int I>
-__device__ __forceinline__ unsigned pack_signed_quad(const v16i& acc, std::integral_constant<int, I>, const v4i& Mq, const v4i& Sq,
+template <bool NO_TIES, int I, class Acc>
+__device__ __forceinline__ unsigned pack_signed_quad(const Acc& acc, std::integral_constant<int, I>, const v4i& Mq, const v4i& Sq,
                                                      const unsigned (&Rq)[4], const int sc, const int lo2) {
     // Signed results: a shortcut and / or no ReLU. The accumulators hold the bias. In
     // stored bytes the result is clamp(rq(acc) + shortcut byte, lo, 127): for signed codes
@@ -130,6 +132,36 @@ __device__ __forceinline__ unsigned pack_signed_quad(const v16i& acc, std::integ
                 "src1_sel:DWORD" : "+v"(p4) : "v"(t), "v"(hi2));
     });
     return p4;
+}
+
+// Epilogue variants a kernel is compiled for.
+enum { EPI_ANY = 0, EPI_FAST = 1, EPI_FAST_RELU = 2 };
+
+// Pixel index m -> position of the pixel in the zero-bordered image stack, (b * PP + (i+1) * W2 + (j+1)).
+// Image sides that are powers of two (every benchmark shape) take shifts; others divide.
+__device__ __forceinline__ int bordered_pos(const ConvArgs& a, int m, int hw, int W2, int PP) {
+    int b, i, j;
+    if (a.log2_w >= 0 && a.log2_hw >= 0) {
+        b = m >> a.log2_hw;
+        const int q = m & (hw - 1);
+        i = q >> a.log2_w;
+        j = q & (a.w - 1);
+    } else {
+        b = m / hw;
+        const int q = m - b * hw;
+        i = q / a.w;
+        j = q - i * a.w;
+    }
+    return b * PP + (i + 1) * W2 + (j + 1);
+}
+
+// Timeline of one output tile (see ConvArgs::trace): stamp `which` of slot `slot`.
+__device__ __forceinline__ void trace_stamp(const ConvArgs& a, int slot, int which, int tid) {
+    if (a.has_trace && tid == 0) {
+        a.trace[8LL * slot + which] = (long long)wall_clock64();
+        if (which == 0) a.trace[8LL * slot + 4] = (long long)clock64();
+        if (which == 3) a.trace[8LL * slot + 5] = (long long)clock64();
+    }
 }
 
 }  // namespace iodf

@@ -15,31 +15,11 @@
 // (ky,kx) is the tile of the pixels shifted by (ky-1, kx-1) inside zero-bordered images.
 #include "conv.h"
 #include "conv_dev.h"
+#include "conv_direct.h"
 
 namespace iodf {
 
 constexpr int KT = 64;    // bytes (= int8 values) of K per staged tile
-
-// Epilogue variants a kernel is compiled for.
-enum { EPI_ANY = 0, EPI_FAST = 1, EPI_FAST_RELU = 2 };
-
-// Pixel index m -> position of the pixel in the zero-bordered image stack, (b * PP + (i+1) * W2 + (j+1)).
-// Image sides that are powers of two (every benchmark shape) take shifts; others divide.
-__device__ __forceinline__ int bordered_pos(const ConvArgs& a, int m, int hw, int W2, int PP) {
-    int b, i, j;
-    if (a.log2_w >= 0 && a.log2_hw >= 0) {
-        b = m >> a.log2_hw;
-        const int q = m & (hw - 1);
-        i = q >> a.log2_w;
-        j = q & (a.w - 1);
-    } else {
-        b = m / hw;
-        const int q = m - b * hw;
-        i = q / a.w;
-        j = q - i * a.w;
-    }
-    return b * PP + (i + 1) * W2 + (j + 1);
-}
 
 // Fast exact requantise for shifts >= 33: with u = |acc| * M = hi * 2^32 + lo, the rounding
 // constant 2^(s-1) is a multiple of 2^32, so floor((u + 2^(s-1)) / 2^s) =
@@ -253,15 +233,6 @@ template <int N>
 __device__ __forceinline__ void wait_tiles_then_barrier() {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// Timeline of one output tile (see ConvArgs::trace): stamp `which` of slot `slot`.
-__device__ __forceinline__ void trace_stamp(const ConvArgs& a, int slot, int which, int tid) {
-    if (a.has_trace && tid == 0) {
-        a.trace[8LL * slot + which] = (long long)wall_clock64();
-        if (which == 0) a.trace[8LL * slot + 4] = (long long)clock64();
-        if (which == 3) a.trace[8LL * slot + 5] = (long long)clock64();
-    }
 }
 
 // Hand-placed LDS fragment reads (see conv_igemm_lean). The destination is an output of the read statement
@@ -693,25 +664,6 @@ __global__ __launch_bounds__(WC* WP* KS * 64, KS) void conv_igemm_lean(const Con
 
     const int bid = blockIdx.x;
     const int xcd = bid & 7, slot = bid >> 3;
-    const int tile_grid = ((npb + 7) / 8) * 8 * ncb;
-    if (bid >= tile_grid) {
-        // workgroups beyond the tiles (see ConvArgs::pf): those on an XCD that holds tiles share the lines
-        if (xcd >= npb) return;
-        const int j = (bid - tile_grid) >> 3, P = ((int)gridDim.x - tile_grid) >> 3;
-        const long long lines = (a.pf_bytes + 127) >> 7;
-        // four independent loads per round, so that a thread pays one memory latency and not one per line
-        const long long stride = (long long)P * blockDim.x;
-        int sum = 0;
-        for (long long l = (long long)j * blockDim.x + tid; l < lines; l += 4 * stride) {
-            const int v0 = *(const int*)(a.pf + (l << 7));
-            const int v1 = l + stride < lines ? *(const int*)(a.pf + ((l + stride) << 7)) : 0;
-            const int v2 = l + 2 * stride < lines ? *(const int*)(a.pf + ((l + 2 * stride) << 7)) : 0;
-            const int v3 = l + 3 * stride < lines ? *(const int*)(a.pf + ((l + 3 * stride) << 7)) : 0;
-            sum += v0 + v1 + v2 + v3;
-        }
-        asm volatile("" ::"v"(sum));  // the loads are the point: keep them
-        return;
-    }
     const int pb = (slot / ncb) * 8 + xcd, cb = slot % ncb;
     if (pb >= npb) return;
     const int p0 = pb * BP, c0 = cb * BC;
@@ -1270,6 +1222,8 @@ void (*const kPersist[3])(const ConvArgs) = {nullptr, conv_igemm_persist<256, 25
                                                         conv_igemm_persist<256, 256, 2, 4, 4, EPI_FAST_RELU>};
 constexpr size_t kPersistLds = (size_t)4 * (256 + 256) * KT + 2 * 4 * 256 * sizeof(int);
 constexpr int kPersistTile = kNumTiles;  // what conv_pick_tile answers for a persistent launch of tile 0
+constexpr int kDirect0 = kNumTiles + 1;  // the tiles of conv_igemm_direct
+bool is_direct(int tile) { return tile >= kDirect0 && tile < kDirect0 + kDirectTiles; }
 
 // Workgroups of a persistent launch: one per compute unit of the device the layer runs on, a
 // multiple of 8 so that a workgroup's tiles stay on its XCD.
@@ -1299,6 +1253,11 @@ hipError_t conv_setup() {
             if (e != hipSuccess) return e;
         }
     }
+    for (const DirectTile& t : kDirect)
+        for (int v = 0; v < 3; ++v) {
+            const hipError_t e = hipFuncSetAttribute((const void*)t.kern[v], hipFuncAttributeMaxDynamicSharedMemorySize, (int)t.lds);
+            if (e != hipSuccess) return e;
+        }
     for (int v = 1; v < 3; ++v) {
         hipError_t e = hipFuncSetAttribute((const void*)kPersist[v], hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)kPersistLds);
@@ -1314,13 +1273,19 @@ hipError_t conv_device_cus(int* n_cu) {
     return e;
 }
 
-int conv_num_tiles() { return kNumTiles + 1; }
+int conv_num_tiles() { return kDirect0 + kDirectTiles; }
 const char* conv_tile_name(int tile) {
     if (tile == kPersistTile) return "conv_igemm_persist<256,256,2,4,4>";
+    if (is_direct(tile)) return kDirect[tile - kDirect0].name;
     return tile >= 0 && tile < kNumTiles ? kTiles[tile].name : "?";
 }
 void conv_tile_dims(int tile, int* bc, int* bp) {
     if (tile == kPersistTile) tile = 0;
+    if (is_direct(tile)) {
+        *bc = kDirect[tile - kDirect0].bc;
+        *bp = kDirect[tile - kDirect0].bp;
+        return;
+    }
     const bool ok = tile >= 0 && tile < kNumTiles;
     *bc = ok ? kTiles[tile].bc : 0;
     *bp = ok ? kTiles[tile].bp : 0;
@@ -1379,8 +1344,23 @@ static int pick_tile_by_shape(const ConvArgs& a) {
     return best;
 }
 
+// The smallest tile of conv_igemm_direct that gives every compute unit one workgroup at most; 0: none does. A workgroup's time is
+// that of its operands, which half a tile's edge halves; a second workgroup on some units costs more than that saves
+// (16x16 tiles up to two a unit: cfg3 at batch 1 2455 -> 2555 us; 32x16: cfg5 2770 -> 2880; 32x32: cfg4 4255 -> 4410), and
+// 64x32 tiles, tried behind the three, lost as often as they won (cfg4 4255 -> 4225, mid_dense at batch 30 407 -> 418).
+// A launch whose timeline is asked for takes a kernel that stamps one.
+static int pick_direct(const ConvArgs& a, int tile) {
+    if (tile < 0 || a.has_trace || conv_pick_splits(a, tile) != 1) return 0;
+    for (int i = 0; i < kDirectTiles; ++i) {
+        const long long bp = kDirect[i].bp, bc = kDirect[i].bc;
+        if ((a.npix + bp - 1) / bp * ((a.n_store + bc - 1) / bc) <= a.n_cu) return kDirect0 + i;
+    }
+    return 0;
+}
+
 int conv_pick_tile(const ConvArgs& a) {
     const int t = pick_tile_by_shape(a);
+    if (const int d = pick_direct(a, t)) return d;
     // unsplit reductions on the 64x64 and 128x128 tiles take the lean kernel
     // (its load streams keep 32-bit positions)
     const long long nkt = (long long)a.taps * (a.cin_pad / KT);
@@ -1396,7 +1376,7 @@ int conv_pick_tile(const ConvArgs& a) {
 // K splits for a layer whose tiles alone cannot fill the chip (only the general epilogue
 // supports it, and only when the caller supplied the scratch).
 int conv_pick_splits(const ConvArgs& a, int tile) {
-    if (a.mode == MODE_RAW || tile == kPersistTile) return 1;  // raw: the scratch is written, not accumulated
+    if (a.mode == MODE_RAW || tile >= kPersistTile) return 1;  // raw: the scratch is written, not accumulated
     const bool fast = a.mode == MODE_ACT && a.rq_fast && a.n_store % 16 == 0;
     if (fast || !a.partial || tile < 0) return 1;
     const TileCfg& t = kTiles[tile];
@@ -1408,7 +1388,15 @@ int conv_pick_splits(const ConvArgs& a, int tile) {
     return s < 2 ? 1 : (int)s;
 }
 
-int conv_trace_slots(const ConvArgs& a) {
+// Workgroups of a conv_igemm_direct launch, numbered as the kernel numbers them.
+static int direct_grid(const DirectTile& t, const ConvArgs& a) {
+    const int npb = (a.npix + t.bp - 1) / t.bp, ncb = (a.n_store + t.bc - 1) / t.bc;
+    return (direct_by_pixels(a, t.bp) ? (npb + 7) / 8 * 8 : npb) * ncb;
+}
+
+int conv_trace_slots(const ConvArgs& a_in) {
+    ConvArgs a = a_in;
+    a.has_trace = 1;
     const int best = conv_pick_tile(a);
     if (best < 0) return 0;
     const TileCfg& t = kTiles[best == kPersistTile ? 0 : best];
@@ -1426,6 +1414,11 @@ hipError_t launch_conv(const ConvArgs& a_in, hipStream_t stream) {
     if (a.npix <= 0) return hipSuccess;
     const int best = conv_pick_tile(a);
     if (best < 0) return hipErrorInvalidValue;
+    if (is_direct(best)) {
+        const DirectTile& t = kDirect[best - kDirect0];
+        hipLaunchKernelGGL(t.kern[pick_epi(a)], dim3(direct_grid(t, a)), dim3(t.waves * 64), t.lds, stream, a);
+        return hipGetLastError();
+    }
     const bool persist = best == kPersistTile;
     const TileCfg& t = kTiles[persist ? 0 : best];
     const int npb = (a.npix + t.bp - 1) / t.bp, ncb = a.n_pad / t.bc;
@@ -1438,11 +1431,7 @@ hipError_t launch_conv(const ConvArgs& a_in, hipStream_t stream) {
         hipLaunchKernelGGL(kPersist[epi], dim3(persist_grid(a)), dim3(t.threads), kPersistLds, stream, a);
         return hipGetLastError();
     }
-    // few tiles, and the next launch's first reads known: eight more workgroups per XCD fetch them (lean kernel only;
-    // measured at batch 1 of the gate-pruned flow: 8, 16, 32, 64, 128 extra workgroups give 4.71, 3.77, 3.55, 3.51, 3.50 ms)
-    const bool lean_tile = best == kSmallLean || best == kMidLean;
-    const int pf_grid = lean_tile && !a.has_trace && a.pf && a.pf_bytes > 0 && (long long)npb * ncb <= 64 ? 64 : 0;
-    hipLaunchKernelGGL(t.kern[epi], dim3(grid + pf_grid, splits), dim3(t.threads), t.lds, stream, a);
+    hipLaunchKernelGGL(t.kern[epi], dim3(grid, splits), dim3(t.threads), t.lds, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     const long long n = (long long)a.npix * a.n_store;

@@ -995,7 +995,7 @@ static void net_param_span(const iodf_ctx* ctx, const DevNet& N, int batch, cons
     *bytes = (unsigned)N.chain.in_bytes;
 }
 
-// `next`: the network that runs after this one (its first layer's parameters are prefetched), or nullptr.
+// `next`: the network that runs after this one (strips fetch its first layer's parameters ahead), or nullptr.
 int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st,
             const DevNet* next = nullptr) {
     const Route route = route_of(ctx, N, batch);
@@ -1020,12 +1020,6 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
         const DevLayer& L = N.layers[li];
         ConvArgs a;
         memset(&a, 0, sizeof(a));
-        {
-            unsigned pfb = 0;
-            if (li + 1 < N.layers.size()) layer_param_span(ctx, N.layers[li + 1], &a.pf, &pfb);
-            else if (next && !next->layers.empty()) net_param_span(ctx, *next, batch, &a.pf, &pfb);
-            a.pf_bytes = pfb;
-        }
         a.in = ctx->buf[lv][L.in_buf];
         a.in_plane = plane;
         a.in_chunk0 = L.in_off / 64;

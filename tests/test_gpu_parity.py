@@ -280,6 +280,23 @@ def test_single_convolution_on_the_small_tile_kernel_matches_oracle(c_in, c_out,
     assert tl.shape[0] == tiles
 
 
+@pytest.mark.parametrize("c_in,c_out,k,relu,shift_lo,b,h,w", [
+    (64, 64, 1, True, 36, 1, 1, 1),        # one pixel, one k-tile: three of the four waves have none
+    (192, 64, 3, False, 36, 1, 1, 17),     # a second tile of one pixel, 27 k-tiles: shares of 6 and 7, depth 5
+    (1280, 64, 1, True, 36, 2, 3, 5),      # 20 k-tiles, 5 to a wave: exactly the depth
+    (1344, 64, 1, True, 20, 1, 4, 4),      # 21: a share of one more; general epilogue
+    (64, 64, 1, True, 36, 5, 5, 8),        # 200 pixels, more than weights: whole pixel blocks to an XCD, 13 of them
+    (128, 512, 3, True, 36, 9, 4, 4),      # 288 tiles of 16x16 would be too many: 32x16
+    (320, 512, 1, False, 36, 17, 4, 4),    # 272 of 32x16 too: 32x32, ragged
+    (128, 512, 3, True, 20, 32, 4, 4),     # 256 tiles of 32x32, general epilogue
+    (128, 512, 3, True, 36, 33, 4, 4),     # 272: back on the 64x64 tile
+    (640, 512, 1, False, 36, 50, 4, 4),    # 104 tiles of 64x64, ten k-tiles
+])
+def test_single_convolution_on_tiles_without_staging_matches_oracle(c_in, c_out, k, relu, shift_lo, b, h, w):
+    """Where the kernel for few pixels changes its tile, its share of the reduction or its order of tiles (256 compute units)."""
+    _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w)
+
+
 def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w):
     import oracle
     rng = np.random.default_rng(c_in * 1000 + c_out)
