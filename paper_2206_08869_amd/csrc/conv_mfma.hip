@@ -17,6 +17,8 @@
 #include "conv_dev.h"
 #include "conv_direct.h"
 
+#include <algorithm>
+
 namespace iodf {
 
 constexpr int KT = 64;    // bytes (= int8 values) of K per staged tile
@@ -1442,35 +1444,37 @@ hipError_t launch_conv(const ConvArgs& a_in, hipStream_t stream) {
 
 namespace {
 
-__global__ void conv_tapsum(const TapSumArgs a) {
-    const int hw = a.h * a.w;
-    const long long n = (long long)a.npix * a.c_out;
-    for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < n; t += (long long)gridDim.x * blockDim.x) {
-        const int m = (int)(t / a.c_out), c = (int)(t - (long long)m * a.c_out);
+// A workgroup takes `per` pixels, a thread one (pixel, channel) of them. All loads start together: the nine taps, outside
+// ones from an address that exists, and the state word with its index. (With a branch around each tap the loads waited
+// for one another, and 64-bit divisions found the pixel: 5.7 us a launch at batch 1, 2.9 to 4.1 now; 6 channels of 1M
+// pixels 99 -> 91 us.)
+__global__ __launch_bounds__(256) void conv_tapsum(const TapSumArgs a, const int per) {
+    const int hw = a.h * a.w, m0 = blockIdx.x * per, left = a.npix - m0 < per ? a.npix - m0 : per;
+    for (int t = threadIdx.x; t < left * a.c_out; t += 256) {
+        const int k = t / a.c_out, c = t - k * a.c_out, m = m0 + k;
         const int b = m / hw, q = m - b * hw, i = q / a.w, j = q - i * a.w;
-        // the state word this thread updates: its address hangs on the channel map, so both loads start
-        // before the taps are summed rather than behind them
-        int32_t* sp = nullptr;
-        int sv = 0;
+        const bool couple = a.mode == MODE_COUPLE;
+        const int ix = couple ? a.idx_b[c] : 0;
         const int mul = a.mul[c], shift = a.shift[c];
-        if (a.mode == MODE_COUPLE) {
-            sp = a.state + (long long)m * a.state_c + a.idx_b[c];
-            sv = *sp;
-        }
         int acc = a.bias[c];
+        const int32_t* const y = a.y + (long long)m * a.n_pad + c;
+        int v[9];
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
-            const int ii = i + tap / 3 - 1, jj = j + tap % 3 - 1;
-            if (ii >= 0 && ii < a.h && jj >= 0 && jj < a.w)
-                acc += a.y[((long long)b * hw + ii * a.w + jj) * a.n_pad + tap * a.c_out + c];
+            const int dy = tap / 3 - 1, dx = tap % 3 - 1;
+            const bool in = (unsigned)(i + dy) < (unsigned)a.h && (unsigned)(j + dx) < (unsigned)a.w;
+            const int r = y[in ? (long long)(dy * a.w + dx) * a.n_pad + tap * a.c_out : 0LL];
+            v[tap] = in ? r : 0;
         }
-        int y = rq_dev(acc, mul, shift);
-        if (a.relu) y = y < 0 ? 0 : y;
-        y = sat8_dev(y);
-        if (a.mode == MODE_COUPLE)
-            *sp = sv + a.sign * y;
-        else
-            a.codes[(long long)b * a.codes_img_stride + a.codes_off + (long long)c * hw + q] = (int8_t)y;
+        int32_t* const sp = couple ? a.state + (long long)m * a.state_c + ix : nullptr;
+        const int sv = couple ? *sp : 0;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) acc += v[tap];
+        int r = rq_dev(acc, mul, shift);
+        if (a.relu) r = r < 0 ? 0 : r;
+        r = sat8_dev(r);
+        if (couple) *sp = sv + a.sign * r;
+        else a.codes[(long long)b * a.codes_img_stride + a.codes_off + (long long)c * hw + q] = (int8_t)r;
     }
 }
 
@@ -1482,9 +1486,10 @@ hipError_t launch_tapsum(const TapSumArgs& a, hipStream_t stream) {
         a.npix % (a.h * a.w) || (a.mode == MODE_COUPLE && (!a.state || !a.idx_b)) ||
         (a.mode == MODE_CODES && !a.codes) || (a.mode != MODE_COUPLE && a.mode != MODE_CODES))
         return hipErrorInvalidValue;
-    const long long n = (long long)a.npix * a.c_out;
-    const int grid = (int)((n + 255) / 256 > 8192 ? 8192 : (n + 255) / 256);
-    hipLaunchKernelGGL(conv_tapsum, dim3(grid), dim3(256), 0, stream, a);
+    // one round of a workgroup while that gives fewer than 4096 of them, at most four
+    const long long items = std::min<long long>(1024, std::max<long long>(256, (long long)a.npix * a.c_out / 4096));
+    const int per = std::max(1, (int)items / a.c_out);
+    hipLaunchKernelGGL(conv_tapsum, dim3((a.npix + per - 1) / per), dim3(256), 0, stream, a, per);
     return hipGetLastError();
 }
 

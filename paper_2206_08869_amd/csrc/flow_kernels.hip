@@ -7,6 +7,8 @@
 // them into an index map phi (logical channel -> physical channel) per coupling.
 #include "flow_kernels.h"
 
+#include <algorithm>
+
 namespace iodf {
 
 namespace {
@@ -61,23 +63,25 @@ __device__ __forceinline__ int rq_in(int a, int M, int s) {
 // dwords that hold a real channel are written: the padding channels up to the next multiple of 64 were
 // zeroed when the buffer was allocated and nothing ever writes them (every network of a level reads the
 // same number of channels), which at the first level saves seven eighths of the pass's stores.
-__global__ void k_quant_in(const int32_t* __restrict__ S, int npix, int h, int w, int C, const int32_t* __restrict__ idx,
-                           int n_a, int M, int s, int8_t* __restrict__ xq, long long plane) {
+// A workgroup takes `per` pixels. The four indices of a thread, and then its four words, are loaded together (channels past
+// n_a repeat the last one).
+__global__ __launch_bounds__(TPB) void k_quant_in(const int32_t* __restrict__ S, int npix, int h, int w, int C,
+                                                  const int32_t* __restrict__ idx, int n_a, int M, int s, int8_t* __restrict__ xq,
+                                                  long long plane, int per) {
     const int groups = (n_a + 3) / 4;
-    const long long n = (long long)npix * groups;
     const int hw = h * w, W2 = w + 2, PP = (h + 2) * W2;
-    for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < n; t += (long long)gridDim.x * blockDim.x) {
-        const int g = (int)(t % groups);
-        const int p = (int)(t / groups);
+    const int p0 = blockIdx.x * per, left = npix - p0 < per ? npix - p0 : per;
+    for (int t = threadIdx.x; t < left * groups; t += TPB) {
+        const int k = t / groups, c0 = (t - k * groups) * 4, p = p0 + k;
+        const int32_t* const sp = S + (long long)p * C;
+        int v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = idx[c0 + e < n_a ? c0 + e : n_a - 1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = sp[v[e]];
         unsigned packed = 0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int c = g * 4 + e;
-            int v = 0;
-            if (c < n_a) v = rq_in(S[(long long)p * C + idx[c]], M, s);
-            packed |= ((unsigned)v & 0xffu) << (8 * e);
-        }
-        const int c0 = g * 4;
+        for (int e = 0; e < 4; ++e) packed |= (c0 + e < n_a ? (unsigned)rq_in(v[e], M, s) & 0xffu : 0u) << (8 * e);
         const int b = p / hw, q = p - b * hw, i = q / w, j = q - i * w;
         const long long pos = (long long)b * PP + (i + 1) * W2 + (j + 1);
         *(unsigned*)(xq + (long long)(c0 >> 6) * plane + pos * 64 + (c0 & 63)) = packed;
@@ -247,8 +251,11 @@ hipError_t launch_quant_in(const int32_t* S, int npix, int h, int w, int C, cons
     if (cpad % 64 || n_a > cpad || h < 1 || w < 1 || npix % (h * w) ||
         plane < (long long)(npix / (h * w)) * (h + 2) * (w + 2) * 64)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_quant_in, dim3(grid_for((long long)npix * ((n_a + 3) / 4))), dim3(TPB), 0, st, S, npix, h, w, C,
-                       idx, n_a, M, s, xq, plane);
+    // one round of a workgroup while that gives fewer than 4096 of them, at most four
+    const int groups = (n_a + 3) / 4;
+    const long long items = std::min<long long>(4 * TPB, std::max<long long>(TPB, (long long)npix * groups / 4096));
+    const int per = std::max(1, (int)items / groups);
+    hipLaunchKernelGGL(k_quant_in, dim3((npix + per - 1) / per), dim3(TPB), 0, st, S, npix, h, w, C, idx, n_a, M, s, xq, plane, per);
     return hipGetLastError();
 }
 
