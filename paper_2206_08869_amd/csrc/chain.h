@@ -63,7 +63,7 @@ struct ChainKernel {
     void (*kern)(const ChainArgs);
 };
 constexpr int kChainSizes = 4;  // 1, 2, 4 and 8 tiles
-extern const ChainKernel kChain443[], kChain423[], kChain223[], kChain441[], kChain421[], kChain221[], kChain40[], kChain20[];
+extern const ChainKernel kChain433[2], kChain443[], kChain423[], kChain223[], kChain441[], kChain421[], kChain221[], kChain40[], kChain20[];
 
 // A network of the same kinds whose images are too large for one workgroup, or too few to fill the chip with whole
 // ones: strips of `rows` rows of an image. The stream x lives in planes as in conv.h and every launch below takes it from
@@ -96,7 +96,7 @@ constexpr int kStripMaxUnits = 8 * 65535;  // strips of a launch: StripArgs::chu
 constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
 constexpr int kStripMaxTiles = 6;  // tiles_one of the largest block kernel
 constexpr int kStripSizes = 5, kStripIns = 8, kStripLasts = 4;
-extern const StripKernel kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
+extern const StripKernel kStrip433[], kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
 extern const StripKernel kStripIn[], kStripLast[];  // (nc_t of a first layer's kernel: chunks of the quantised input)
 
 size_t chain_lds_bytes(const ChainArgs& a);

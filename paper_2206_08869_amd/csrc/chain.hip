@@ -5,9 +5,11 @@ namespace iodf {
 
 namespace {
 
-const ChainKernel* const kChains[] = {kChain443, kChain423, kChain223, kChain441, kChain421, kChain221, kChain40, kChain20};
+const struct { const ChainKernel* of; int n; } kChains[] = {{kChain443, kChainSizes}, {kChain433, 2}, {kChain423, kChainSizes},
+                                                            {kChain223, kChainSizes}, {kChain441, kChainSizes}, {kChain421, kChainSizes},
+                                                            {kChain221, kChainSizes}, {kChain40, kChainSizes}, {kChain20, kChainSizes}};
 
-const StripKernel* const kStrips[] = {kStrip443, kStrip423, kStrip223, kStrip441, kStrip421, kStrip221};
+const StripKernel* const kStrips[] = {kStrip443, kStrip433, kStrip423, kStrip223, kStrip441, kStrip421, kStrip221};
 
 size_t strip_lds_bytes(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int w, int rows) {
     const int ext = taps_two == 9 ? 1 : 0;
@@ -19,10 +21,10 @@ size_t strip_lds_bytes(StripPart part, int nc_x, int nc_t, int taps_two, int nc_
 
 const ChainKernel* kernel_for(const ChainArgs& a) {
     const int need = (a.images * a.h * a.w + 31) / 32;
-    for (const ChainKernel* t : kChains) {
-        if (t->nc_x != a.nc_x || t->nc_t != a.nc_t || t->taps_two != a.taps_two) continue;
-        for (int i = 0; i < kChainSizes; ++i)
-            if (t[i].tiles >= need) return t + i;
+    for (const auto& t : kChains) {
+        if (t.of->nc_x != a.nc_x || t.of->nc_t != a.nc_t || t.of->taps_two != a.taps_two) continue;
+        for (int i = 0; i < t.n; ++i)
+            if (t.of[i].tiles >= need) return t.of + i;
     }
     return nullptr;
 }
@@ -45,9 +47,9 @@ int chain_tiles(const ChainArgs& a) {
 }
 
 hipError_t chain_setup() {
-    for (const ChainKernel* t : kChains)
-        for (int i = 0; i < kChainSizes; ++i) {
-            const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainMaxLds);
+    for (const auto& t : kChains)
+        for (int i = 0; i < t.n; ++i) {
+            const hipError_t e = hipFuncSetAttribute((const void*)t.of[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kChainMaxLds);
             if (e != hipSuccess) return e;
         }
     for (const StripKernel* t : kStrips)

@@ -49,15 +49,17 @@ struct Share {
 // so the stream runs on across layers. Pixels are read from LDS one step ahead, two where a step is only one or two
 // products long; the scheduling barriers keep the compiler from moving the reads next to their use.
 template <int TC, int NC, int NT>
-constexpr int chain_depth() { return NC * NT < 12 / TC ? NC * NT : 12 / TC; }
+constexpr int chain_depth() { return NC * NT == 9 || NC * NT < 12 / TC ? NC * NT : 12 / TC; }
 
-template <int TC, int TP, int NC, int NT>
-__device__ __forceinline__ void chain_products(v16i (&acc)[TC][TP], v4i (&w)[12], const unsigned char* lds,
+// With NEXT = false nothing follows: the last kernel row, unrolled by itself, requests no more than its own fragments (the
+// repeats that stood for a next layer's were a sixth to a third of a layer's stream).
+template <int TC, int TP, int NC, int NT, bool NEXT = true, int NW>
+__device__ __forceinline__ void chain_products(v16i (&acc)[TC][TP], v4i (&w)[NW], const unsigned char* lds,
                                                const unsigned (&at)[TP], const unsigned rowstep, const gbytes wcur,
                                                const gbytes wnext, const unsigned tcs_next, const unsigned lane16) {
     constexpr int S = NC * NT, PS = chain_pixel_bytes(NC), D = chain_depth<TC, NC, NT>();
     constexpr unsigned tcs = TC == 2 ? S * NT * 1024 : 0;
-    static_assert(S % D == 0, "a kernel row is a whole number of rounds of the fragment registers");
+    static_assert(S % D == 0 && D * TC <= NW, "a kernel row is a whole number of rounds of the fragment registers");
     constexpr int PD = S % 2 != 0 || (TP <= 2 && S % 3 == 0) ? 2 : 1;
     static_assert(NT == 1 || S % (PD + 1) == 0, "and of the pixel registers");
     v4i b[PD + 1][TP];
@@ -72,21 +74,17 @@ __device__ __forceinline__ void chain_products(v16i (&acc)[TC][TP], v4i (&w)[12]
         });
     };
     static_for<PD>([&](auto i_) { read(i_); });
-#pragma unroll 1
-    for (int r = 0; r < NT; ++r) {
-        const bool last = r == NT - 1;
-        const gbytes wr = uniform(wcur + r * (S * 1024));
-        const gbytes wn = uniform(last ? wnext : wcur + (r + 1) * (S * 1024));
-        const unsigned ts = last ? tcs_next : tcs;
-        const unsigned adv = last ? 0u : rowstep;
+    // fragments of this row at wr, of what comes behind it at wn
+    auto row = [&](auto end_, const gbytes wr, const gbytes wn, const unsigned ts, const unsigned adv) {
+        constexpr bool end = decltype(end_)::value;
         static_for<S>([&](auto i_) {
             constexpr int i = decltype(i_)::value;
-            if constexpr (i == S - PD) {
+            if constexpr (i == S - PD && !end) {
 #pragma unroll
                 for (int tp = 0; tp < TP; ++tp) ba[tp] += adv;
             }
             if constexpr (i + PD < S) read(std::integral_constant<int, i + PD>{});
-            else if constexpr (NT > 1) read(std::integral_constant<int, i + PD - S>{});
+            else if constexpr (NT > 1 && !end) read(std::integral_constant<int, i + PD - S>{});
             __builtin_amdgcn_sched_barrier(0);
             static_for<TC>([&](auto tc_) {
                 constexpr int tc = decltype(tc_)::value;
@@ -97,24 +95,199 @@ __device__ __forceinline__ void chain_products(v16i (&acc)[TC][TP], v4i (&w)[12]
             });
             static_for<TC>([&](auto tc_) {
                 constexpr int tc = decltype(tc_)::value;
-                w[(i % D) * TC + tc] = i + D < S ? *(gv4i)(wr + tc * tcs + (i + D) * 1024 + lane16)
-                                                 : *(gv4i)(wn + tc * ts + (i + D - S) * 1024 + lane16);
+                if constexpr (i + D < S) w[(i % D) * TC + tc] = *(gv4i)(wr + tc * tcs + (i + D) * 1024 + lane16);
+                else if constexpr (!end) w[(i % D) * TC + tc] = *(gv4i)(wn + tc * ts + (i + D - S) * 1024 + lane16);
             });
             __builtin_amdgcn_sched_barrier(0);
         });
+    };
+#pragma unroll 1
+    for (int r = 0; r < (NEXT ? NT : NT - 1); ++r) {
+        const bool last = NEXT && r == NT - 1;
+        row(std::false_type{}, uniform(wcur + r * (S * 1024)), uniform(last ? wnext : wcur + (r + 1) * (S * 1024)),
+            last ? tcs_next : tcs, last ? 0u : rowstep);
     }
+    if constexpr (!NEXT) row(std::true_type{}, uniform(wcur + (NT - 1) * (S * 1024)), wcur, 0, 0);
     // what reads the accumulators next may be an opaque statement, which the compiler gives no wait states
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The same for layers whose fragment registers hold one kernel row, in front of a layer of the 16-row form: next(i) loads
+// what register i holds for it.
+template <int TC, int TP, int NC, int NT, int NW, class Next>
+__device__ __forceinline__ void chain_products_then(v16i (&acc)[TC][TP], v4i (&w)[NW], const unsigned char* lds,
+                                                    const unsigned (&at)[TP], const unsigned rowstep, const gbytes wcur,
+                                                    const unsigned lane16, Next next) {
+    constexpr int S = NC * NT, PS = chain_pixel_bytes(NC);
+    constexpr unsigned tcs = TC == 2 ? S * NT * 1024 : 0;
+    static_assert(chain_depth<TC, NC, NT>() == S && S * TC <= NW && S % 3 == 0 && NT == 3, "one row of fragments, pixels two steps ahead");
+    v4i b[3][TP];
+    unsigned ba[TP];
+#pragma unroll
+    for (int tp = 0; tp < TP; ++tp) ba[tp] = at[tp];
+    auto read = [&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            b[i % 3][tp] = *(const v4i*)(lds + ba[tp] + (i / NC) * PS + (i % NC) * 32);
+        });
+    };
+    read(std::integral_constant<int, 0>{});
+    read(std::integral_constant<int, 1>{});
+    auto row = [&](auto last_, const gbytes wn) {
+        constexpr bool last = decltype(last_)::value;
+        static_for<S>([&](auto i_) {
+            constexpr int i = decltype(i_)::value;
+            if constexpr (i == S - 2 && !last) {
+#pragma unroll
+                for (int tp = 0; tp < TP; ++tp) ba[tp] += rowstep;
+            }
+            if constexpr (i + 2 < S) read(std::integral_constant<int, i + 2>{});
+            else if constexpr (!last) read(std::integral_constant<int, i + 2 - S>{});
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<TC>([&](auto tc_) {
+                constexpr int tc = decltype(tc_)::value;
+                static_for<TP>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+                    acc[tc][tp] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[i * TC + tc], b[i % 3][tp], acc[tc][tp], 0, 0, 0);
+                });
+            });
+            static_for<TC>([&](auto tc_) {
+                constexpr int tc = decltype(tc_)::value;
+                if constexpr (last) next(std::integral_constant<int, i * TC + tc>{});
+                else w[i * TC + tc] = *(gv4i)(wn + tc * tcs + i * 1024 + lane16);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#pragma unroll 1
+    for (int r = 1; r < NT; ++r) row(std::false_type{}, uniform(wcur + r * (S * 1024)));
+    row(std::true_type{}, wcur);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Fragments of the first steps of a layer, registers from FROM on.
-template <int TC, int NC, int NT, int FROM>
-__device__ __forceinline__ void chain_fetch(v4i (&w)[12], const gbytes p, const unsigned lane16) {
+template <int TC, int NC, int NT, int FROM, int NW>
+__device__ __forceinline__ void chain_fetch(v4i (&w)[NW], const gbytes p, const unsigned lane16) {
     constexpr int n = chain_depth<TC, NC, NT>() * TC;
     static_for<n>([&](auto i_) {
         constexpr int i = decltype(i_)::value;
         if constexpr (i >= FROM) w[i] = *(gv4i)(p + (i % TC) * (NC * NT * NT * 1024) + (i / TC) * 1024 + lane16);
+    });
+}
+
+// Three blocks of 32 filters do not divide over the waves. A layer of 96 filters over four tiles and more therefore runs
+// on v_mfma_i32_16x16x64_i8: a wave takes 48 filters, three blocks of 16, and half (a quarter) of the pixels in tiles of
+// 16; half a wave's lanes of a 32-filter fragment and of the one behind it are one operand of it. 96 of 128 filters kept,
+// against the kernels of 128: one residual block on 256 images of 32x32 85 -> 71 us, 18 layers on 256 of 16x16 146 -> 113.
+struct Wave48 {
+    unsigned at[3];  // a wave's three blocks of 16 filters: offsets in a layer's fragments
+    unsigned lane;   // and a lane's
+};
+
+template <int NC>
+__device__ __forceinline__ Wave48 wave48(const int col, const int lane) {
+    Wave48 f;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const int g = 3 * col + t;
+        f.at[t] = (unsigned)((g >> 1) * (9 * NC * 1024) + (g & 1) * 256);
+    }
+    const int quad = lane >> 4;
+    f.lane = (unsigned)((quad >> 1) * 1024 + (quad & 1) * 512 + (lane & 15) * 16);
+    return f;
+}
+
+// A step: one tap, 64 channels. w: the fragments of a kernel row's steps, three to a step.
+template <int NC>
+__device__ __forceinline__ void fetch48(v4i (&w)[18], const gbytes p, const Wave48& f) {
+    static_for<18>([&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        if constexpr (i < 3 * (NC / 2) * 3) w[i] = *(gv4i)(p + f.at[i % 3] + (i / 3) * 2048 + f.lane);
+    });
+}
+
+// The products of such a layer. next(i) loads what register i holds for the layer behind it.
+template <int TP, int NC, class Next>
+__device__ __forceinline__ void products48(v4i (&acc)[3][TP], v4i (&w)[18], const unsigned char* lds, const unsigned (&at)[TP],
+                                           const unsigned rowstep, const gbytes p, const Wave48& f, Next next) {
+    static_assert(NC == 4, "a step's three fragments and a row's six steps fill the registers");
+    constexpr int S = 6, PS = chain_pixel_bytes(NC);
+    v4i b[2][TP];
+    unsigned ba[TP];
+#pragma unroll
+    for (int tp = 0; tp < TP; ++tp) ba[tp] = at[tp];
+    auto read = [&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            b[i % 2][tp] = *(const v4i*)(lds + ba[tp] + (i / 2) * PS + (i % 2) * 64);
+        });
+    };
+    using I0 = std::integral_constant<int, 0>;
+    read(I0{});
+    auto row = [&](auto last_, const gbytes wn) {
+        constexpr bool last = decltype(last_)::value;
+        static_for<S>([&](auto i_) {
+            constexpr int i = decltype(i_)::value;
+            if constexpr (i + 1 < S) read(std::integral_constant<int, i + 1>{});
+            else if constexpr (!last) {
+#pragma unroll
+                for (int tp = 0; tp < TP; ++tp) ba[tp] += rowstep;
+                read(I0{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<3>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+                static_for<TP>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+                    acc[t][tp] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[i * 3 + t], b[i % 2][tp], acc[t][tp], 0, 0, 0);
+                });
+            });
+            static_for<3>([&](auto t_) {
+                constexpr int t = decltype(t_)::value;
+                if constexpr (last) next(std::integral_constant<int, i * 3 + t>{});
+                else w[i * 3 + t] = *(gv4i)(wn + f.at[t] + i * 2048 + f.lane);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#pragma unroll 1
+    for (int r = 1; r < 3; ++r) row(std::false_type{}, uniform(p + r * (S * 2048)));
+    row(std::true_type{}, p);
+    // what reads the accumulators next may be an opaque statement, which the compiler gives no wait states
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Its accumulators' start, and its epilogue: a lane holds four consecutive filters of a pixel for every block and tile.
+template <int TP>
+__device__ __forceinline__ void bias48(v4i (&acc)[3][TP], const int* cst, const int ch) {
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        const v4i b4 = *(const v4i*)(cst + 3 * 128 + ch + 16 * t);
+#pragma unroll
+        for (int tp = 0; tp < TP; ++tp) acc[t][tp] = b4;
+    }
+}
+
+template <int TP>
+__device__ __forceinline__ void store48(const v4i (&acc)[3][TP], unsigned char* lds, const unsigned (&at)[TP], const int live,
+                                        const int* cst, const int ch, const bool act_unsigned) {
+    static_for<3>([&](auto t_) {
+        constexpr int t = decltype(t_)::value;
+        const int n = ch + 16 * t;
+        const v4i B = *(const v4i*)(cst + n), M = *(const v4i*)(cst + 128 + n), S = *(const v4i*)(cst + 256 + n);
+        unsigned R[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) R[e] = 1u << (S[e] - 1);
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            const unsigned p4 = pack_relu_quad(acc[t][tp], std::integral_constant<int, 0>{}, B, M, S, R, act_unsigned);
+            if (live >> tp & 1) *(unsigned*)(lds + at[tp] + n) = p4;
+        });
     });
 }
 
@@ -328,8 +501,13 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     using S2 = Share<NW, 2, TILES>;                   // ... up to 64
     const int xblk = wave % SX::WC * SX::TC, tblk = wave % ST::WC * ST::TC;
 
-    v4i wf[12];
-    static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+    constexpr bool F48 = NCT == 3;  // a block's first convolution in the 16-row form: two columns of waves
+    static_assert(!F48 || (NCX == 4 && NT2 == 3 && TILES >= 4 && SX::TC == 2), "what the fragment registers are laid out for");
+    constexpr int TP48 = F48 ? 4 * TILES / NW : 1;
+    constexpr int NWF = F48 ? 18 : 12;
+    const Wave48 f48 = wave48<NCX>(wave & 1, lane);
+    v4i wf[NWF];
+    static_for<NWF>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
     const gbytes w_in = par + (size_t)(xblk * 9 * a.nc_q * 1024);
     if (a.nc_q == 1) chain_fetch<SX::TC, 1, 3, 0>(wf, uniform(w_in), lane16);
     else chain_fetch<SX::TC, 2, 3, 0>(wf, uniform(w_in), lane16);
@@ -353,8 +531,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     // Where the pixels of this wave's tiles lie: image, row, column, as byte offsets of tap (0, 0) in each tensor.
     // Lanes past the last pixel repeat it and store nothing.
     const unsigned inv_w = ((1u << kInvBits) + w - 1) / w, inv_hw = ((1u << kInvBits) + hw - 1) / hw;
-    auto pixel_of = [&](int tile, int& im, int& row, int& col) {
-        int m = tile * 32 + l32;
+    auto pixel_of = [&](int m, int& im, int& row, int& col) {
         const bool live = m < M;
         m = live ? m : M - 1;
         im = (int)(__umul24((unsigned)m, inv_hw) >> kInvBits);
@@ -368,7 +545,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     static_for<SX::TP>([&](auto tp_) {
         constexpr int tp = decltype(tp_)::value;
         int im, row, col;
-        if (pixel_of(wave / SX::WC * SX::TP + tp, im, row, col)) live_x |= 1 << tp;
+        if (pixel_of((wave / SX::WC * SX::TP + tp) * 32 + l32, im, row, col)) live_x |= 1 << tp;
         x_of_x[tp] = xb + im * isx + row * rpx + col * psx;
         t_of_x[tp] = tb + im * ist + row * rpt + col * pst + half * 16;
         q_of_x[tp] = qb + im * isq + row * rpq + col * psq + half * 16;
@@ -376,10 +553,21 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     static_for<ST::TP>([&](auto tp_) {
         constexpr int tp = decltype(tp_)::value;
         int im, row, col;
-        if (pixel_of(wave / ST::WC * ST::TP + tp, im, row, col)) live_t |= 1 << tp;
+        if (pixel_of((wave / ST::WC * ST::TP + tp) * 32 + l32, im, row, col)) live_t |= 1 << tp;
         x_of_t[tp] = xb + im * isx + row * rpx + col * psx + half * 16;
         t_of_t[tp] = tb + im * ist + row * rpt + col * pst;
     });
+    unsigned x_of_48[TP48], to_48[TP48];
+    int live_48 = 0;
+    if constexpr (F48) {
+        static_for<TP48>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int im, row, col;
+            if (pixel_of(((wave >> 1) * TP48 + tp) * 16 + (lane & 15), im, row, col)) live_48 |= 1 << tp;
+            x_of_48[tp] = xb + im * isx + row * rpx + col * psx + (lane >> 4) * 16;
+            to_48[tp] = tb + im * ist + (row + 1) * rpt + (col + 1) * pst;
+        });
+    }
     unsigned xo[SX::TP], to[ST::TP];  // the pixels themselves
 #pragma unroll
     for (int i = 0; i < SX::TP; ++i) xo[i] = x_of_x[i] + rpx + psx;
@@ -398,9 +586,10 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         const v4i cn = fetch_const(NCT ? blockp + w_one : blockp + a.n_blk_last * a.taps_last * NCX * 1024);
         v16i acc[SX::TC][SX::TP];
         chain_bias(acc, cst0, xblk, half);
-        if (a.nc_q == 1) chain_products<SX::TC, SX::TP, 1, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
-        else chain_products<SX::TC, SX::TP, 2, 3>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
-        if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
+        if (a.nc_q == 1) chain_products<SX::TC, SX::TP, 1, 3, false>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
+        else chain_products<SX::TC, SX::TP, 2, 3, false>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
+        if constexpr (F48) fetch48<NCX>(wf, uniform(blockp), f48);
+        else if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
         chain_store<SX::TC, SX::TP, false>(acc, lds, xo, live_x, cst0, xblk * 32, half, a.act_unsigned);
         put_const(1, cn);
     }
@@ -413,12 +602,24 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
             const gbytes next = last ? blockp : blockp + bytes_block;
             {
                 const v4i cn = fetch_const(blockp + bytes_one + w_two);
-                v16i acc[ST::TC][ST::TP];
-                chain_bias(acc, cst1, tblk, half);
-                chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_of_t, rpx, uniform(p_one), uniform(p_two), tcs_two, lane16);
-                constexpr int got = carry_one ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0;
-                chain_fetch<SX::TC, NCT, NT2, got>(wf, uniform(p_two), lane16);
-                chain_store<ST::TC, ST::TP, false>(acc, lds, to, live_t, cst1, tblk * 32, half, a.act_unsigned);
+                if constexpr (F48) {
+                    v4i acc[3][TP48];
+                    const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
+                    bias48(acc, cst1, ch);
+                    const gbytes pn = uniform(p_two);
+                    products48<TP48, NCX>(acc, wf, lds, x_of_48, rpx, uniform(blockp), f48, [&](auto i_) {
+                        constexpr int i = decltype(i_)::value;
+                        wf[i] = *(gv4i)(pn + i % 2 * tcs_two + (i / 2) * 1024 + lane16);
+                    });
+                    store48(acc, lds, to_48, live_48, cst1, ch, a.act_unsigned);
+                } else {
+                    v16i acc[ST::TC][ST::TP];
+                    chain_bias(acc, cst1, tblk, half);
+                    chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_of_t, rpx, uniform(p_one), uniform(p_two), tcs_two, lane16);
+                    constexpr int got = carry_one ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0;
+                    chain_fetch<SX::TC, NCT, NT2, got>(wf, uniform(p_two), lane16);
+                    chain_store<ST::TC, ST::TP, false>(acc, lds, to, live_t, cst1, tblk * 32, half, a.act_unsigned);
+                }
                 put_const(0, cn);
             }
             lds_barrier();
@@ -430,9 +631,17 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
 #pragma unroll
                 for (int i = 0; i < SX::TP; ++i) at[i] = NT2 == 1 ? t_of_x[i] + rpt + pst : t_of_x[i];
                 const gbytes p_next = next + tblk * 9 * NCX * 1024;
-                chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, at, rpt, uniform(p_two), uniform(p_next), tcs_one, lane16);
-                constexpr int got = carry_one ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0;
-                chain_fetch<ST::TC, NCX, 3, got>(wf, uniform(p_next), lane16);
+                if constexpr (F48) {
+                    const gbytes pn = uniform(next);
+                    chain_products_then<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, at, rpt, uniform(p_two), lane16, [&](auto i_) {
+                        constexpr int i = decltype(i_)::value;
+                        wf[i] = *(gv4i)(pn + f48.at[i % 3] + (i / 3) * 2048 + f48.lane);
+                    });
+                } else {
+                    chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, at, rpt, uniform(p_two), uniform(p_next), tcs_one, lane16);
+                    constexpr int got = carry_one ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0;
+                    chain_fetch<ST::TC, NCX, 3, got>(wf, uniform(p_next), lane16);
+                }
                 chain_store<SX::TC, SX::TP, true>(acc, lds, xo, live_x, cst0, xblk * 32, half, a.act_unsigned);
                 put_const(1, cn);
             }
@@ -453,7 +662,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         static_for<TP>([&](auto tp_) {
             constexpr int tp = decltype(tp_)::value;
             int im, row, col;
-            const bool live = pixel_of(wave / S::WC * TP + tp, im, row, col);
+            const bool live = pixel_of((wave / S::WC * TP + tp) * 32 + l32, im, row, col);
             at[tp] = xb + im * isx + (row + (NT == 1)) * rpx + (col + (NT == 1)) * psx + half * 16;
             gp[tp] = live ? (img0 + im) * hw + row * w + col : -1;
         });
@@ -461,7 +670,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         chain_last_channels(a, ix, blk, half);
         v16i acc[1][TP];
         chain_bias(acc, cst1, blk, half);
-        chain_products<1, TP, NCX, NT>(acc, wf, lds, at, rpx, p, p, 0, lane16);
+        chain_products<1, TP, NCX, NT, false>(acc, wf, lds, at, rpx, p, p, 0, lane16);
         chain_last_store<TP>(a, acc, gp, ix, cst1, blk, half);
     };
     using I1 = std::integral_constant<int, 1>;

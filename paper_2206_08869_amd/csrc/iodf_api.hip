@@ -218,6 +218,7 @@ int check_shapes(const HostModel& m) {
 
 struct DevLayer {
     int taps, cin_pad, n_pad, n_store, relu, shortcut, mode, rq_fast;
+    int rows;              // of n_pad
     int in_buf, in_off;    // input tensor: buffer and first channel (multiple of 64)
     int out_buf, out_off;  // output tensor (MODE_ACT)
     size_t wgt_off, bias_off, mul_off, shift_off;  // byte offsets into the parameter arena
@@ -291,7 +292,8 @@ void pack_layer(Arena& A, const HostLayer& L, const std::vector<int>& rows, cons
     const int taps = L.k * L.k;
     D.taps = taps;
     D.cin_pad = cin_pad;
-    D.n_pad = round64((int)rows.size());
+    D.rows = (int)rows.size();
+    D.n_pad = round64(D.rows);
     D.relu = L.relu;
     D.shortcut = L.shortcut;
     const size_t wbytes = (size_t)D.n_pad * taps * cin_pad;
@@ -463,6 +465,13 @@ void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
     DevChain& C = D.chain;
     C.nc_x = rw / 32;
     C.nc_t = tw / 32;
+    {
+        // 65 to 96 of 128 channels kept inside: kernels of their own, on maps of more than two tiles of pixels (smaller maps
+        // wait for weights and latencies, of which three waves out of four save little)
+        int most = 0;
+        for (int l = 1; l + 1 < nl; l += 2) most = std::max(most, D.layers[l].rows);
+        if (C.nc_t == 4 && most <= 96 && taps2 == 9 && (m.H >> N.level) * (m.W >> N.level) > 64) C.nc_t = 3;
+    }
     C.nc_q = (N.C_in + 31) / 32;
     C.blocks = (nl - 2) / 2;
     C.taps_two = taps2;
@@ -472,7 +481,8 @@ void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
     size_t total = 0;
     for (int l = 0; l < nl; ++l) {
         const DevLayer& L = D.layers[l];
-        const int nc = l == 0 ? C.nc_q : L.cin_pad / 32, n_blk = l + 1 == nl ? C.n_blk_last : L.n_pad / 32;
+        const bool two = l > 0 && l % 2 == 0 && l + 1 < nl;
+        const int nc = l == 0 ? C.nc_q : two ? C.nc_t : C.nc_x, n_blk = l + 1 == nl ? C.n_blk_last : l == 0 || two ? C.nc_x : C.nc_t;
         total += (nw[l] = (size_t)n_blk * L.taps * nc * 1024) + kChainConstBytes;
         if (l == 0) C.in_bytes = total;
         if (l == 2 && l + 1 < nl) C.block_bytes = total - C.in_bytes;
@@ -483,7 +493,7 @@ void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
     for (int l = 0; l < nl; ++l) {
         const DevLayer& L = D.layers[l];
         const bool last = l + 1 == nl;
-        const int nc = l == 0 ? C.nc_q : L.cin_pad / 32, n_blk = (int)(nw[l] / ((size_t)L.taps * nc * 1024));
+        const int nc = l == 0 ? C.nc_q : l % 2 == 0 && !last ? C.nc_t : C.nc_x, n_blk = (int)(nw[l] / ((size_t)L.taps * nc * 1024));
         const int8_t* src = (const int8_t*)(A.host.data() + L.wgt_off);
         for (int b = 0; b < n_blk; ++b)
             for (int t = 0; t < L.taps; ++t)
@@ -787,7 +797,7 @@ static ChainArgs chain_args(const iodf_ctx* ctx, const DevNet& N, int batch, int
 // wide 3x3 kernel gains nothing from nine images of 10 to 28 pixels and more (4x4 maps: 0.95 at batch 2560, 0.99 at 4096).
 static bool chain_pays(const iodf_ctx* ctx, const DevChain& C, long long hw, int batch, int images, int tiles) {
     if (C.nc_x < 4) return true;
-    const bool heavy = C.nc_t == 4 && C.taps_two == 9;
+    const bool heavy = C.nc_t >= 3 && C.taps_two == 9;
     const long long n = ctx->n_cu, groups = (batch + images - 1) / images, filled = 100 * groups * tiles * 32 / (batch * hw);
     if (!C.blocks && hw > 200 && batch <= n / 8) return false;
     if (heavy && images > 8 && hw > 9 && tiles == kChainMaxTiles) return false;
@@ -842,7 +852,7 @@ struct StripPlan { int rows[3]; };
 // strip per compute unit), where they are a longer way than four layers of small tiles; with 64 kept inside only where a
 // few units get a second one (0.94 to 0.98 between 1.03 and 1.4 strips per unit, 1.03 to 1.26 below, 1.08 and more above).
 static bool strips_pay(const iodf_ctx* ctx, const DevChain& C, const StripKernel& k, int h, int w, int rows, int batch) {
-    const bool k3 = C.taps_two == 9, heavy = k3 && C.nc_t == 4;
+    const bool k3 = C.taps_two == 9, heavy = k3 && C.nc_t >= 3;
     const long long units = (long long)batch * ((h + rows - 1) / rows);
     if (units <= 2LL * ctx->n_cu) {
         if (!k3 || C.nc_x != 4 || rows > 1 || k.tiles_one < kStripMaxTiles) return true;

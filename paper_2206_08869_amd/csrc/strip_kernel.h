@@ -97,10 +97,9 @@ __device__ __forceinline__ void strip_put_consts(unsigned char* lds, const v4i& 
     if (tid < kChainConstBytes / 16) *(v4i*)(lds + buf * kChainConstBytes + tid * 16) = v;
 }
 
-// Pixel of lane l32 in a tile of rows [y0, y1): row, column; false past the last one (which is repeated).
-__device__ __forceinline__ bool strip_pixel(int tile, int l32, int w, unsigned inv_w, int y0, int y1, int& row, int& col) {
+// Pixel m of rows [y0, y1): row, column; false past the last one (which is repeated).
+__device__ __forceinline__ bool strip_pixel(int m, int w, unsigned inv_w, int y0, int y1, int& row, int& col) {
     const int M = (y1 - y0) * w;
-    int m = tile * 32 + l32;
     const bool live = m < M;
     m = live ? m : M - 1;
     const int q = (int)(__umul24((unsigned)m, inv_w) >> kInvBits);
@@ -139,9 +138,16 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     v4i xv[kStripLoads];
     strip_request<NCX>(a, xv, g.img, xo, xe, tid);
     const v4i c1 = strip_consts(par + w_one, tid), c0 = strip_consts(par + w_one + kChainConstBytes + w_two, tid);
-    v4i wf[12];
-    static_for<12>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
-    chain_fetch<ST::TC, NCX, 3, 0>(wf, p_one, lane16);
+    // 96 filters: in the 16-row form over four tiles and more, else three of the waves take a block of 32 each
+    constexpr bool F48 = NCT == 3 && T1 >= 4;
+    static_assert(NCT != 3 || (NCX == 4 && NT2 == 3), "what the fragment registers are laid out for");
+    constexpr int NWF = NCT == 3 ? 18 : 12;
+    const Wave48 f48 = wave48<NCX>(wave & 1, lane);
+    const bool one = NCT != 3 || F48 || wave < 3;  // a wave with a share of the first convolution
+    v4i wf[NWF];
+    static_for<NWF>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
+    if constexpr (F48) fetch48<NCX>(wf, uniform(par), f48);
+    else if (one) chain_fetch<ST::TC, NCX, 3, 0>(wf, p_one, lane16);
     __builtin_amdgcn_sched_barrier(0);
     const int pad = a.act_unsigned ? (int)0x80808080 : 0;
     for (unsigned o = tb + tid * 16; o < end; o += kStripThreads * 16) *(v4i*)(lds + o) = v4i{pad, pad, pad, pad};
@@ -151,14 +157,28 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     static_for<ST::TP>([&](auto tp_) {
         constexpr int tp = decltype(tp_)::value;
         int row, col;
-        if (strip_pixel(wave / ST::WC * ST::TP + tp, l32, w, inv_w, ty0, ty1, row, col)) live_t |= 1 << tp;
+        if (strip_pixel((wave / ST::WC * ST::TP + tp) * 32 + l32, w, inv_w, ty0, ty1, row, col)) live_t |= 1 << tp;
         x_in[tp] = xb + (row - 1 - xo) * rpx + col * psx + half * 16;
         t_out[tp] = tb + (row - to) * rpt + (col + 1) * pst;
     });
+    // (F48) pixel of tile tp, out of l16 as if anew: what is only stored to need not stay in registers meanwhile
+    constexpr int TP48 = F48 ? T1 : 1;
+    auto pixel48 = [&](int tp, int l16, int& row, int& col) {
+        return strip_pixel(((wave >> 1) * TP48 + tp) * 16 + l16, w, inv_w, ty0, ty1, row, col);
+    };
+    unsigned x_48[TP48];
+    if constexpr (F48) {
+        static_for<TP48>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int row, col;
+            (void)pixel48(tp, lane & 15, row, col);
+            x_48[tp] = xb + (row - 1 - xo) * rpx + col * psx + (lane >> 4) * 16;
+        });
+    }
     static_for<SX::TP>([&](auto tp_) {
         constexpr int tp = decltype(tp_)::value;
         int row, col;
-        if (strip_pixel(wave / SX::WC * SX::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col)) live_x |= 1 << tp;
+        if (strip_pixel((wave / SX::WC * SX::TP + tp) * 32 + l32, w, inv_w, g.r0, g.r1, row, col)) live_x |= 1 << tp;
         t_in[tp] = tb + (row - EXT - to) * rpt + (col + 1 - EXT) * pst + half * 16;
         x_sc[tp] = xb + (row - xo) * rpx + (col + 1) * psx;
         go[tp] = (unsigned)(((g.img * (h + 2) + row + 1) * W2 + col + 1) * 64);
@@ -169,21 +189,41 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     lds_barrier();
     const int* const cst0 = (const int*)lds;
     const int* const cst1 = (const int*)(lds + kChainConstBytes);
-    {
+    constexpr bool carry = ST::TC == SX::TC;
+    constexpr unsigned tcs_two = SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0;
+    if constexpr (F48) {
+        v4i acc[3][TP48];
+        const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
+        bias48(acc, cst1, ch);
+        products48<TP48, NCX>(acc, wf, lds, x_48, rpx, uniform(par), f48, [&](auto i_) {
+            constexpr int i = decltype(i_)::value;
+            if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
+                wf[i] = *(gv4i)(p_two + i % SX::TC * tcs_two + (i / SX::TC) * 1024 + lane16);
+        });
+        unsigned t_48[TP48];
+        int live_48 = 0, l16 = lane & 15;
+        asm volatile("" : "+v"(l16));
+        static_for<TP48>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            int row, col;
+            if (pixel48(tp, l16, row, col)) live_48 |= 1 << tp;
+            t_48[tp] = tb + (row - to) * rpt + (col + 1) * pst;
+        });
+        store48(acc, lds, t_48, live_48, cst1, ch, a.act_unsigned);
+    } else if (one) {
         v16i acc[ST::TC][ST::TP];
         chain_bias(acc, cst1, tblk, half);
-        constexpr bool carry = ST::TC == SX::TC;
-        constexpr unsigned tcs_two = SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0;
-        chain_products<ST::TC, ST::TP, NCX, 3>(acc, wf, lds, x_in, rpx, p_one, carry ? p_two : p_one,
-                                               carry ? tcs_two : (ST::TC == 2 ? 9 * NCX * 1024 : 0), lane16);
+        chain_products<ST::TC, ST::TP, NCX, 3, carry>(acc, wf, lds, x_in, rpx, p_one, p_two, tcs_two, lane16);
         chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0>(wf, p_two, lane16);
         chain_store<ST::TC, ST::TP, false>(acc, lds, t_out, live_t, cst1, tblk * 32, half, a.act_unsigned);
+    } else {
+        chain_fetch<SX::TC, NCT, NT2, 0>(wf, p_two, lane16);
     }
     lds_barrier();
     {
         v16i acc[SX::TC][SX::TP];
         chain_bias(acc, cst0, xblk, half);
-        chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, t_in, rpt, p_two, p_two, SX::TC == 2 ? NT2 * NT2 * NCT * 1024 : 0, lane16);
+        chain_products<SX::TC, SX::TP, NCT, NT2, false>(acc, wf, lds, t_in, rpt, p_two, p_two, 0, lane16);
         chain_store<SX::TC, SX::TP, true, true>(acc, lds, x_sc, live_x, cst0, xblk * 32, half, a.act_unsigned, a.out, a.plane, go);
     }
 }
@@ -223,7 +263,7 @@ __global__ __launch_bounds__(kStripThreads, 3) void k_strip_in(const StripArgs a
     static_for<S::TP>([&](auto tp_) {
         constexpr int tp = decltype(tp_)::value;
         int row, col;
-        if (strip_pixel(wave / S::WC * S::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col)) live |= 1 << tp;
+        if (strip_pixel((wave / S::WC * S::TP + tp) * 32 + l32, w, inv_w, g.r0, g.r1, row, col)) live |= 1 << tp;
         q_in[tp] = qb + (row - 1 - qo) * rpq + col * psq + half * 16;
         go[tp] = (unsigned)(((g.img * (h + 2) + row + 1) * W2 + col + 1) * 64);
     });
@@ -231,7 +271,7 @@ __global__ __launch_bounds__(kStripThreads, 3) void k_strip_in(const StripArgs a
     const int* const cst = (const int*)lds;
     v16i acc[S::TC][S::TP];
     chain_bias(acc, cst, blk, half);
-    chain_products<S::TC, S::TP, NCQ, 3>(acc, wf, lds, q_in, rpq, p, p, S::TC == 2 ? 9 * NCQ * 1024 : 0, lane16);
+    chain_products<S::TC, S::TP, NCQ, 3, false>(acc, wf, lds, q_in, rpq, p, p, 0, lane16);
     chain_store<S::TC, S::TP, false, true>(acc, lds, q_in, live, cst, blk * 32, half, a.act_unsigned, a.out, a.plane, go);
 }
 
@@ -269,7 +309,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs
         static_for<S::TP>([&](auto tp_) {
             constexpr int tp = decltype(tp_)::value;
             int row, col;
-            const bool live = strip_pixel(wave / S::WC * S::TP + tp, l32, w, inv_w, g.r0, g.r1, row, col);
+            const bool live = strip_pixel((wave / S::WC * S::TP + tp) * 32 + l32, w, inv_w, g.r0, g.r1, row, col);
             at[tp] = xb + (row - (NT == 3) - xo) * rpx + (col + (NT == 1)) * psx + half * 16;
             gp[tp] = live ? (g.img * h + row) * w + col : -1;
         });
@@ -278,7 +318,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs
         lds_barrier();
         v16i acc[1][S::TP];
         chain_bias(acc, cst, blk, half);
-        chain_products<1, S::TP, NCX, NT>(acc, wf, lds, at, rpx, p, p, 0, lane16);
+        chain_products<1, S::TP, NCX, NT, false>(acc, wf, lds, at, rpx, p, p, 0, lane16);
         chain_last_store<S::TP>(a, acc, gp, ix, cst, blk, half);
     };
     using I1 = std::integral_constant<int, 1>;

@@ -100,6 +100,19 @@ def test_strips(H, W, batch, width, keep, k2, unsigned):
                       act_unsigned=unsigned), batch, kernel="k_strip_block")
 
 
+# 65 to 96 of 128 channels kept inside: blocks of 48 filters to a wave over four tiles and more, three waves of 32 below
+# (64, 80 and 128 pixel maps, 130 to 256 as one launch; strips at every tile count); 97 take the kernels of 128
+@pytest.mark.parametrize("H,W,batch,kernel", [(16, 16, 1, "k_chain"), (16, 20, 3, "k_chain"), (16, 32, 2, "k_chain"), (20, 26, 65, "k_chain"),
+                                              (24, 40, 67, "k_chain"), (32, 32, 66, "k_chain"), (48, 80, 1, "k_strip_block"),
+                                              (32, 32, 1, "k_strip_block"), (32, 32, 13, "k_strip_block"), (32, 32, 64, "k_strip_block"),
+                                              (64, 64, 3, "k_strip_block"), (64, 64, 17, "k_strip_block"), (64, 64, 66, "k_strip_block"),
+                                              (10, 52, 2, "k_strip_block"), (34, 70, 9, "k_strip_block")])
+@pytest.mark.parametrize("keep,unsigned", [(0.75, False), (0.625, True), (65 / 128, False), (97 / 128, False)])
+def test_three_quarters_kept(H, W, batch, kernel, keep, unsigned):
+    _check(FlowConfig("kept", H, W, batch, 1, 1, RESNET, 128, 2, False, keep=keep, seed_id=49, block_k2=3, act_unsigned=unsigned),
+           batch, kernel=kernel)
+
+
 # Maps whose rows fill the largest strip kernel badly go layer by layer once more strips wait than run at once, or at
 # once where a single row already takes that kernel; the same images give the same latents either way.
 @pytest.mark.parametrize("H,batch,width,keep,k2,strips", [
