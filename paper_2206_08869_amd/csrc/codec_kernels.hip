@@ -9,11 +9,11 @@
 //
 // Coder: 64-bit state X in [2^31, 2^63), initial 2^31. Encoding a symbol first sheds the low
 // 32 bits as a word if X >= F * 2^39, then X <- floor(X / F) * M + C + X mod F. Decoding reads
-// the slot X mod M, finds the symbol whose [C, C + F) holds it by bisection over r, restores
+// the slot X mod M, finds the symbol whose [C, C + F) holds it, restores
 // X <- F * floor(X / M) + (X mod M) - C and pulls a word back in when X < 2^31.
 // A chunk's latents are dealt round-robin to 16 lanes, each an independent stream encoded
 // last-to-first. The chains are serial (encoding: one thread to a lane, what it is fed worked out
-// by other waves; decoding: half a wave to a lane), so these kernels are bound by dependent
+// by other waves; decoding: a wave to a lane), so these kernels are bound by dependent
 // integer latency, not by memory or the vector units.
 #include "codec_kernels.h"
 
@@ -246,110 +246,150 @@ __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const ui
     }
 }
 
-// Half a wave serves one lane, a workgroup eight of the sixteen lanes of one image's chunk, a wave to a SIMD.
-// The 2^14 residuals are isolated in
-// three rounds (32 * 32 * 16): in each the 32 threads work out G at 32 cut points of the current interval and a ballot
-// counts how many lie at or below the slot; the last round works out G at every residual left, so the symbol's mass
-// is two of its values. All threads keep the same coder state; the first of a half writes the latent.
+// A whole wave serves one lane, a workgroup four. What hangs on the state is then the same for all 64 threads: the state lives in
+// scalar registers, counts come from whole ballots and picked values by v_readlane.
 //
-// Bound: the chain from one state to the next. What does not hang on the state is kept off it: the first round's G
-// (its cut points are the same for every symbol, only the scale differs) is worked out a symbol ahead, and the codes
-// and words of 32 symbols and of the following 32 sit in the half wave's registers, one to a thread. That
-// leaves two table interpolations, three ballots and the update on the chain. (Sixteen threads, four dependent rounds
-// and two more interpolations, codes and words fetched as needed: 1270 ns a symbol.)
-constexpr int kDecLanes = 8, kDecThreads = 32 * kDecLanes;
+// A symbol is found by a guess that is then proved. Where G is all floor mass (13.86 s and more from the mean, the
+// logistic's part below 16 of 2^24) the residual is the slot less a constant; elsewhere the logistic alone, inverted
+// in single precision, is close. The threads work out G at 64 residuals around the guess, and a ballot shows whether the
+// slot lies among them; if not (far from the mean, between the two regimes) the search over all residuals follows, 128
+// cut points and then 128 residuals, two to a thread. What a position's codes mean for all this is worked out 64 positions at
+// a time, one to a thread. Bound: the chain of some 60 instructions and one LDS read from one state to the next, 320 ns a
+// symbol at batch 1. (Half a wave to a lane, three rounds of 32, 32 and 16 cut points, the first a symbol ahead: 500 ns and more.
+// A whole wave with two rounds of 128: 440.) Whole calls, paper_iodf64 decode at batch 1 2150 -> 2025 us, cfg2 at batch 300
+// 520 -> 495.
+constexpr int kDecLanes = 4;
 
-__global__ __launch_bounds__(kDecThreads) void k_rans_decode_chunk(const CodecTables t, const ChunkTable ct, const int c,
-                                                                   const uint32_t* __restrict__ cont, long long cap, int batch,
-                                                                   const int8_t* __restrict__ codes, long long d_codes,
-                                                                   int32_t* __restrict__ z, long long d,
-                                                                   unsigned long long* errs) {
+// cdf() with its argument clamped before and after one signed product. inv: min(inv, kTMax), which gives the same G since
+// every argument is odd; cap: kTMax / inv + 1, from where on the argument saturates.
+constexpr int kTMax = 24 << 24;
+__device__ __forceinline__ int cdf_capped(const int* s_sig, int r, int inv, int cap) {
+    int t = 2 * r - 1;
+    t = t < -cap ? -cap : t > cap ? cap : t;
+    t *= inv;  // |t| <= kTMax + inv < 2^30
+    t = t < -kTMax ? -kTMax : t > kTMax ? kTMax : t;
+    const unsigned u = (unsigned)(t + kTMax), j = u >> 18;
+    const unsigned s0 = (unsigned)s_sig[j], s1 = (unsigned)s_sig[j + 1];
+    const unsigned S = s0 + __umulhi(s1 - s0, u << 14);
+    return (r + kAlphaR) + (int)__umulhi((unsigned)(kMass - 2 * kAlphaR) << 2, S);
+}
+
+__global__ __launch_bounds__(64 * kDecLanes) void k_rans_decode_chunk(const CodecTables t, const ChunkTable ct, const int c,
+                                                                      const uint32_t* __restrict__ cont, long long cap, int batch,
+                                                                      const int8_t* __restrict__ codes, long long d_codes,
+                                                                      int32_t* __restrict__ z, long long d,
+                                                                      unsigned long long* errs) {
     __shared__ int s_sig[kSigLds];
-    __shared__ unsigned s_inv[256];
-    for (int i = threadIdx.x; i < 256; i += kDecThreads) s_inv[i] = (unsigned)t.inv[i];
     load_sig(s_sig, t.sig);
     constexpr int kParts = kLanes / kDecLanes;
     const int b = blockIdx.x / kParts;  // grid = batch * kParts
-    const int j = blockIdx.x % kParts * kDecLanes + (threadIdx.x >> 5), helper = threadIdx.x & 31;
-    const int half_shift = threadIdx.x & 32;  // this half's first bit in the wave's ballot, its first lane
-    auto of_half = [&](int v, int i) { return __builtin_amdgcn_ds_bpermute((half_shift + i) << 2, v); };
+    const int lane = threadIdx.x & 63;
+    const int j = blockIdx.x % kParts * kDecLanes + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nslots = ct.n_chunks * kLanes;
     const long long header = 1 + 3LL * nslots;  // the host has checked cap >= header
     const uint32_t* cb = cont + (long long)b * cap;
     const int n = ct.n[c];
-    const int k = j < n ? (n - j + kLanes - 1) / kLanes : 0;
-    const int kmax = (n + kLanes - 1) / kLanes;  // the same for every thread: ballots stay convergent
+    const int k = __builtin_amdgcn_readfirstlane(j < n ? (n - j + kLanes - 1) / kLanes : 0);
     int32_t* zc = z + (long long)b * d + ct.z_off[c];
-    const int8_t* ci = codes ? codes + (long long)b * d_codes : nullptr;
+    const int8_t* const cm = codes && ct.code_off[c] >= 0 ? codes + (long long)b * d_codes + ct.code_off[c] : nullptr;
     const long long total = cb[0];
     bool bad = total > cap || total < header;
     const int slot = c * kLanes + j;
-    // words of the lanes before this one: the half adds them up together
-    long long before = 0;
-    for (int s = helper; s < slot; s += 32) before += cb[1 + s];
-    for (int x = 16; x; x >>= 1) before += __shfl_xor(before, x, 32);
+    // words of the lanes before this one: the wave adds them up together
+    unsigned long long sum = 0;
+    for (int s = lane; s < slot; s += 64) sum += cb[1 + s];
+    for (int x = 32; x; x >>= 1) sum += __shfl_xor(sum, x, 64);
+    const long long before = (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(sum >> 32)) << 32) |
+                                         (unsigned)__builtin_amdgcn_readfirstlane((int)sum));
     long long pos = header + before;
     unsigned nw = cb[1 + slot];
     if (bad || pos + (long long)nw > total) { bad = true; nw = 0; pos = header; }
-    const uint32_t* w = cb + pos;  // reads stay below pos + nw <= total <= cap
+    // 64 words or codes to a register, one to a thread, requested 64 words or positions before they are needed. Reads
+    // stay below pos + nw <= total <= cap and below k: threads past the end repeat the last one.
+    const uint32_t* const w = nw ? cb + pos : cb;
     unsigned used = 0;
-    auto words_at = [&](unsigned i) { return (long long)i + helper < nw ? w[i + helper] : 0u; };
-    unsigned w_cur = words_at(0), w_next = words_at(32);
+    auto words_at = [&](unsigned i) { return w[nw ? (i + lane < nw ? i + lane : nw - 1) : 0u]; };
+    unsigned w_cur = words_at(0), w_next = words_at(64);
     unsigned long long X = (unsigned long long)cb[1 + nslots + 2 * slot] |
                            ((unsigned long long)cb[1 + nslots + 2 * slot + 1] << 32);
-    // codes of 32 positions, one to a thread: mean code in the low half, log-scale code above it
-    auto codes_at = [&](int p) {
-        int m = kDefaultM, l = kDefaultL;
-        if (p + helper < k) codes_of(ct, c, ci, (p + helper) * kLanes + j, m, l);
-        return (l << 16) | (m & 0xffff);
+    auto code_at = [&](int p, int what) -> int {
+        if (!cm) return what ? kDefaultL : kDefaultM;
+        return cm[what * n + (p + lane < k ? p + lane : k - 1) * kLanes + j];
     };
-    int ml_cur = codes_at(0), ml_next = codes_at(32);
-    // first round: cut points -8192 + (helper + 1) * 512; the last one is the interval's end, above every slot
-    const int cut1 = -kAlphaR + (helper < 31 ? helper + 1 : 31) * 512;
-    int ml = of_half(ml_cur, 0);
-    unsigned inv = s_inv[(ml >> 16) + 128];
-    int g1 = cdf(s_sig, cut1, inv);
-    for (int p0 = 0; p0 < kmax; p0 += 32) {
-        const int n_here = kmax - p0 < 32 ? kmax - p0 : 32;
-        int out = 0;  // this thread's latent of the 32
-        for (int i = 0; i < n_here; ++i) {
-            const int ml_after = of_half(i < 31 ? ml_cur : ml_next, (i + 1) & 31);
-            const unsigned word = (unsigned)of_half((int)w_cur, (int)(used & 31));
-            const unsigned inv_after = s_inv[(ml_after >> 16) + 128];
-            const int v = (int)(X & (unsigned long long)(kMass - 1));
-            // G(-8192) = 0 <= v < M = G(8192)
-            unsigned below = (unsigned)(__ballot(helper < 31 && g1 <= v) >> half_shift);
-            int lo = -kAlphaR + __popc(below) * 512;
-            below = (unsigned)(__ballot(helper < 31 && cdf(s_sig, lo + (helper + 1) * 16, inv) <= v) >> half_shift);
-            lo += __popc(below) * 16;
-            const int g3 = cdf(s_sig, lo + (helper < 16 ? helper : 16), inv);
-            below = (unsigned)(__ballot(helper >= 1 && helper < 16 && g3 <= v) >> half_shift);
-            const int idx = __popc(below);
-            const int C = of_half(g3, idx);
-            const int F = of_half(g3, idx + 1) - C;
-            g1 = cdf(s_sig, cut1, inv_after);
-            if (helper == i) out = lo + idx + 2 * (int)(int16_t)(ml & 0xffff);
-            if (p0 + i < k) {
-                X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
-                if (X < kStateLow) {
+    // what a position's codes mean, one position to a thread
+    struct Scale { int m2, inv, cap, tail; float s; };
+    auto scale_of = [&](int m, int l) {
+        Scale q;
+        const int inv = t.inv[l + 128] < kTMax ? (int)t.inv[l + 128] : kTMax;  // 2^23 / scale, rounded
+        const float scale = 8388608.0f / (float)inv;
+        q.m2 = 2 * m;
+        q.inv = inv;
+        q.cap = kTMax / inv + 1;
+        q.tail = (int)(13.86f * scale) + 1;
+        q.s = 0.69314718f * scale;
+        return q;
+    };
+    auto pick = [&](const Scale& q, int i) {
+        return Scale{__builtin_amdgcn_readlane(q.m2, i), __builtin_amdgcn_readlane(q.inv, i), __builtin_amdgcn_readlane(q.cap, i),
+                     __builtin_amdgcn_readlane(q.tail, i), __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q.s), i))};
+    };
+    if (k > 0) {
+        Scale now = scale_of(code_at(0, 0), code_at(0, 1));
+        int m_next = code_at(64, 0), l_next = code_at(64, 1);
+        for (int p0 = 0; p0 < k; p0 += 64) {
+            const int n_here = k - p0 < 64 ? k - p0 : 64;
+            int out = 0;  // this thread's latent of the 64
+            Scale q = pick(now, 0);
+            for (int i = 0; i < n_here; ++i) {
+                const int v = (int)(X & (unsigned long long)(kMass - 1));
+                constexpr int A = (int)kMass - 2 * kAlphaR;  // mass of the logistic
+                const int u = v - kAlphaR, uh = A - u;       // u = r + A * sigma, about
+                // around the guess: 64 residuals from lo on, wholly inside the alphabet
+                const float g = q.s * (__log2f((float)(u > 1 ? u : 1)) - __log2f((float)(uh > 1 ? uh : 1)));
+                int lo = (int)fminf(fmaxf(g, -8192.0f), 8191.0f);
+                lo = u < -q.tail ? u : u - A > q.tail ? u - A : lo;
+                lo = (lo < -kAlphaR + 32 ? -kAlphaR + 32 : lo > kAlphaR - 32 ? kAlphaR - 32 : lo) - 32;
+                int g0 = cdf_capped(s_sig, lo + lane, q.inv, q.cap);
+                const Scale after = pick(now, (i + 1) & 63);
+                int idx = __popcll(__ballot(g0 <= v)) - 1;
+                int C, F;
+                if (__builtin_expect(idx >= 0 && idx < 63, 1)) {
+                    C = __builtin_amdgcn_readlane(g0, idx);
+                    F = __builtin_amdgcn_readlane(g0, idx + 1) - C;
+                } else {
+                    // cut points -8192 + 128 (i + 1), i = lane and lane + 64; G(-8192) = 0 <= v < M = G(8192)
+                    const int cut = -kAlphaR + (lane + 1) * 128;
+                    const int seg = __popcll(__ballot(cdf_capped(s_sig, cut, q.inv, q.cap) <= v)) +
+                                    __popcll(__ballot(cdf_capped(s_sig, cut + 64 * 128, q.inv, q.cap) <= v));
+                    lo = -kAlphaR + seg * 128;
+                    g0 = cdf_capped(s_sig, lo + lane, q.inv, q.cap);
+                    const int g1 = cdf_capped(s_sig, lo + 64 + lane, q.inv, q.cap);
+                    idx = __popcll(__ballot(g0 <= v)) + __popcll(__ballot(g1 <= v)) - 1;  // G(lo) <= v
+                    // both edges of the symbol, worked out by every thread alike
+                    C = __builtin_amdgcn_readfirstlane(cdf_capped(s_sig, lo + idx, q.inv, q.cap));
+                    F = __builtin_amdgcn_readfirstlane(cdf_capped(s_sig, lo + idx + 1, q.inv, q.cap)) - C;
+                }
+                if (lane == i) out = lo + idx + q.m2;
+                X = (unsigned long long)(unsigned)F * (X >> kMassBits) + (unsigned long long)(unsigned)(v - C);
+                if (X >> 31 == 0) {  // below kStateLow
                     if (used < nw) {
-                        X = (X << 32) | word;
-                        if ((++used & 31) == 0) {
+                        X = (X << 32) | (unsigned)__builtin_amdgcn_readlane((int)w_cur, (int)(used & 63));
+                        if ((++used & 63) == 0) {
                             w_cur = w_next;
-                            w_next = words_at(used + 32);
+                            w_next = words_at(used + 64);
                         }
                     } else { X <<= 32; bad = true; }
                 }
+                q = after;
             }
-            inv = inv_after;
-            ml = ml_after;
+            if (p0 + lane < k) zc[(p0 + lane) * kLanes + j] = out;
+            now = scale_of(m_next, l_next);
+            m_next = code_at(p0 + 128, 0);
+            l_next = code_at(p0 + 128, 1);
         }
-        if (p0 + helper < k) zc[(p0 + helper) * kLanes + j] = out;
-        ml_cur = ml_next;
-        ml_next = codes_at(p0 + 64);
     }
     if (X != kStateLow || used != nw) bad = true;
-    if (bad && helper == 0) atomicAdd(errs + 2, 1ULL);
+    if (bad && lane == 0) atomicAdd(errs + 2, 1ULL);
 }
 
 int grid_for(long long n, int tpb) {
@@ -400,8 +440,8 @@ hipError_t launch_rans_decode_chunk(const CodecTables& t, const ChunkTable& ct, 
     if (!table_ok(ct) || c < 0 || c >= ct.n_chunks || !cont || !z || !errs || !t.sig || !t.inv ||
         cap < 1 + 3LL * ct.n_chunks * kLanes)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rans_decode_chunk, dim3((unsigned)batch * (kLanes / kDecLanes)), dim3(kDecThreads), 0, st, t, ct, c, cont, cap, batch, codes, d_codes, z,
-                       d, errs);
+    hipLaunchKernelGGL(k_rans_decode_chunk, dim3((unsigned)batch * (kLanes / kDecLanes)), dim3(64 * kDecLanes), 0, st, t, ct, c, cont, cap,
+                       batch, codes, d_codes, z, d, errs);
     return hipGetLastError();
 }
 

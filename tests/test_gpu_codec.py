@@ -113,6 +113,33 @@ def test_containers_match_oracle_and_decode_everywhere(name, batch):
     flow.close()
 
 
+@pytest.mark.parametrize("name,batch", [("mid_dense", 3), ("mini_dense", 5)])
+def test_decoder_finds_symbols_in_the_tails_by_guess_and_by_search(name, batch):
+    """The decoder looks among 64 residuals around a guess (a tail's constant, or the logistic inverted) and searches all of
+    them where that misses, which happens between the two regimes: these latents have symbols of each kind."""
+    import torch
+    cfg = CONFIGS[name]
+    x = images(name, batch=batch)
+    z, codes = oracle_model(name).forward(x)
+    C, F, _ = _oracle_cf(cfg, z, codes)
+    n, z_off, code_off = _chunk_layout(cfg)
+    m, l = np.zeros(z.shape), np.full(z.shape, 96.0)
+    for k, zo, co in zip(n, z_off, code_off):
+        if co >= 0:
+            m[:, zo:zo + k], l[:, zo:zo + k] = codes[:, co:co + k], codes[:, co + k:co + 2 * k]
+    s, A = 2.0 ** (l / 16), (1 << 24) - 16384
+    u = C + F // 2 - 8192.0
+    tail = np.where(u < -13.86 * s - 2, u, np.where(u - A > 13.86 * s + 2, u - A, np.nan))
+    with np.errstate(over="ignore"):
+        guess = s * (np.log(np.maximum(u, 1)) - np.log(np.maximum(A - u, 1)))
+    off = np.abs(np.where(np.isnan(tail), guess, tail) - (z - 2 * m))
+    assert (~np.isnan(tail)).sum() > 100 and (np.isnan(tail) & (off < 20)).sum() > 100 and (off > 45).sum() > 0
+    flow = gpu_flow(name, max_batch=batch)
+    words, _ = flow.encode(to_gpu(x))
+    assert torch.equal(flow.decode(words), to_gpu(x))
+    flow.close()
+
+
 def test_capacity_and_malformed_containers():
     import torch
     name, batch = "mini_dense", 6
