@@ -1371,6 +1371,28 @@ static int enqueue_inverse(iodf_ctx* ctx, const int32_t* z_dev, int batch, uint8
     return IODF_OK;
 }
 
+// Whether a call is short enough to be launched kernel by kernel. A replay saves 0.8 us a launch where kernels are shorter
+// than the host takes to launch them, but costs copies into and out of the graph's own buffers and some 15 us of host work.
+// Direct against replayed: 4 launches (cfg1 at batch 1) 18.6 against 31 to 36 us, 23 (cfg2 at batch 1, 64, 512) 153 / 177 /
+// 392 against 163 / 192 / 407; 40 short ones (odd_dense_g at batch 1) 112 to 138 against 119, 90 (mid_dense at batch 1) 367
+// against 339.
+static bool launched_directly(const iodf_ctx* ctx, int dir, int batch, int codes) {
+    constexpr int kMost = 32;
+    const HostModel& m = ctx->shape;
+    int n = 1;  // pixels in or out
+    for (int lv = 1; lv <= m.levels; ++lv) {
+        ++n;  // split or un-split
+        const int nets = m.couplings + (dir == 0 && codes && m.has_heads && lv < m.levels ? 1 : 0);
+        for (int i = 0; i < nets; ++i) {
+            if (n + nets - i > kMost) return false;
+            const DevNet& N = ctx->nets[ctx->first_net[lv] + i];
+            const Route r = route_of(ctx, N, batch);
+            n += r.images ? 1 : r.layers() ? 1 + (int)N.layers.size() + (N.layers.back().mode == MODE_RAW) : N.chain.blocks + 2;
+        }
+    }
+    return n <= kMost;
+}
+
 // Find or capture the graph of one call shape. Returns nullptr (and *rc) when capture fails.
 static iodf_ctx::GraphEntry* get_graph(iodf_ctx* ctx, int dir, int batch, int codes, int* rc) {
     *rc = IODF_OK;
@@ -1421,8 +1443,9 @@ int iodf_forward(iodf_ctx* ctx, const uint8_t* x_dev, int batch, int32_t* z_dev,
     if (!x_dev || !z_dev) return IODF_E_ARG;
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(ctx->device));
-    if (!ctx->use_graphs || ctx->prof_on) return enqueue_forward(ctx, x_dev, batch, z_dev, codes_dev, st);
     const int codes = (codes_dev && ctx->d_codes) ? 1 : 0;
+    if (!ctx->use_graphs || ctx->prof_on || launched_directly(ctx, 0, batch, codes))
+        return enqueue_forward(ctx, x_dev, batch, z_dev, codes_dev, st);
     int rc;
     iodf_ctx::GraphEntry* g = get_graph(ctx, 0, batch, codes, &rc);
     if (!g) return rc;
@@ -1442,7 +1465,7 @@ int iodf_inverse(iodf_ctx* ctx, const int32_t* z_dev, int batch, uint8_t* x_dev,
     if (!x_dev || !z_dev) return IODF_E_ARG;
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(ctx->device));
-    if (!ctx->use_graphs || ctx->prof_on) return enqueue_inverse(ctx, z_dev, batch, x_dev, st);
+    if (!ctx->use_graphs || ctx->prof_on || launched_directly(ctx, 1, batch, 0)) return enqueue_inverse(ctx, z_dev, batch, x_dev, st);
     int rc;
     iodf_ctx::GraphEntry* g = get_graph(ctx, 1, batch, 0, &rc);
     if (!g) return rc;
