@@ -46,15 +46,21 @@ struct ChainArgs {
     long long codes_img_stride, codes_off;
     unsigned pf_bytes;   // size of the block, for the workgroups that fetch it ahead
     int batch, mul_in;
-    unsigned short h, w;
-    unsigned short images;  // images of a workgroup
-    unsigned short state_c, n_a, n_out, blocks;
-    unsigned char nc_x, nc_t, nc_q;  // 32-channel chunks of the stream, the block-internal tensor (0: no blocks), the quantised input
-    unsigned char taps_two, taps_last, n_blk_last;  // 1 or 9; 32-filter blocks of the last layer
-    unsigned char shift_in, act_unsigned, relu_last, pf_blocks;
-    unsigned char last_fast;  // the last layer's shifts are all 33 or more and nothing in it requantises to half a code
-    signed char sign;
+    // bit fields, so that they come out of whole words by scalar loads (bytes and halves took a vector load's latency)
+    unsigned h : 16, w : 16;
+    unsigned images : 16;  // images of a workgroup
+    unsigned blocks : 16;
+    unsigned n_a : 16, n_out : 16;
+    unsigned state_c : 16, shift_in : 8;
+    unsigned taps_two : 4, taps_last : 4;          // 1 or 9
+    unsigned nc_x : 4, nc_t : 4, nc_q : 4;         // 32-channel chunks of the stream, the block-internal tensor (0: no blocks), the quantised input
+    unsigned n_blk_last : 4;                       // 32-filter blocks of the last layer
+    unsigned pf_blocks : 8;
+    unsigned act_unsigned : 1, relu_last : 1;
+    unsigned last_fast : 1;  // the last layer's shifts are all 33 or more and nothing in it requantises to half a code
+    int sign : 2;
 };
+static_assert(sizeof(ChainArgs) == 80, "five words of fields");
 
 // One kernel: the kind of network it runs, and the 32-pixel tiles its workgroup takes. The tables, one to a kind, are
 // spread over several source files because compiling them takes a while.
@@ -76,16 +82,18 @@ struct StripArgs {
     const int32_t* idx;
     int8_t* codes;
     long long codes_img_stride, codes_off;
+    const uint8_t* pf;        // what the next launch reads first
+    unsigned pf_bytes;
     unsigned plane;
     int batch, mul_in;
-    unsigned short h, w, rows, chunk;  // chunk: strips per XCD
-    unsigned short state_c, n_a, n_out;
-    unsigned char shift_in, act_unsigned, relu_last, last_fast, n_blk_last, taps_last, nc_q;
-    signed char sign;
-    unsigned char pf_blocks;  // workgroups per XCD behind the strips that bring pf .. pf + pf_bytes into its L2
-    unsigned pf_bytes;        // what the next launch reads first
-    const uint8_t* pf;
+    unsigned h : 16, w : 16;
+    unsigned rows : 16, chunk : 16;  // chunk: strips per XCD
+    unsigned n_a : 16, n_out : 16;
+    unsigned state_c : 16, shift_in : 8, pf_blocks : 8;  // pf_blocks: workgroups per XCD behind the strips that bring pf .. pf + pf_bytes into its L2
+    unsigned taps_last : 4, nc_q : 4, n_blk_last : 4, act_unsigned : 1, relu_last : 1, last_fast : 1;
+    int sign : 2;
 };
+static_assert(sizeof(StripArgs) == 112, "five words of fields");
 struct StripKernel {
     int nc_x, nc_t, taps_two;
     int tiles_one, tiles_two;  // 32-pixel tiles of the block's first and second convolution (first and last layer: the same)

@@ -22,15 +22,16 @@ namespace {
 
 constexpr int kInvBits = 20;  // m / d = m * ceil(2^20 / d) >> 20 for m * d < 2^20
 
-// Global memory by type: a pointer rebuilt from scalar halves would otherwise be a generic one, whose loads also
-// count as LDS operations.
-typedef const uint8_t __attribute__((address_space(1)))* gbytes;
-typedef const v4i __attribute__((address_space(1)))* gv4i;
-
-__device__ __forceinline__ gbytes uniform(gbytes p) {
-    const unsigned long long v = (unsigned long long)p;
-    return (gbytes)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
-                    (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v));
+// See hold_args(const ConvArgs&).
+__device__ __forceinline__ void hold_args(const ChainArgs& a) {
+    asm volatile("" ::"s"(a.params), "s"(a.state), "s"(a.idx), "s"(a.codes), "s"(a.pf_bytes), "s"(a.batch), "s"(a.mul_in));
+    const unsigned* const raw = (const unsigned*)&a;
+    asm volatile("" ::"s"(raw[15]), "s"(raw[16]), "s"(raw[17]), "s"(raw[18]), "s"(raw[19]));
+}
+__device__ __forceinline__ void hold_args(const StripArgs& a) {
+    asm volatile("" ::"s"(a.params), "s"(a.in), "s"(a.out), "s"(a.state), "s"(a.idx), "s"(a.codes), "s"(a.plane), "s"(a.batch), "s"(a.mul_in));
+    const unsigned* const raw = (const unsigned*)&a;
+    asm volatile("" ::"s"(raw[22]), "s"(raw[23]), "s"(raw[24]), "s"(raw[25]), "s"(raw[26]));
 }
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -468,6 +469,7 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
+    hold_args(a);
 
     const int groups = (a.batch + a.images - 1) / a.images;
     if ((int)blockIdx.x >= groups) {

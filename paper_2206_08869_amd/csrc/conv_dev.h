@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "conv.h"
@@ -12,6 +14,17 @@ namespace iodf {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+
+// Global memory by type: a pointer rebuilt from scalar halves would otherwise be a generic one, whose loads also
+// count as LDS operations.
+typedef const uint8_t __attribute__((address_space(1)))* gbytes;
+typedef const v4i __attribute__((address_space(1)))* gv4i;
+
+__device__ __forceinline__ gbytes uniform(gbytes p) {
+    const unsigned long long v = (unsigned long long)p;
+    return (gbytes)(((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(v >> 32)) << 32) |
+                    (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v));
+}
 
 // Compile-time loop: f(std::integral_constant<int, I>) for I = 0..N-1. Keeps every
 // accumulator index a constant so the accumulators stay in registers.
@@ -136,6 +149,17 @@ __device__ __forceinline__ unsigned pack_signed_quad(const Acc& acc, std::integr
 
 // Epilogue variants a kernel is compiled for.
 enum { EPI_ANY = 0, EPI_FAST = 1, EPI_FAST_RELU = 2 };
+
+// Brings the arguments into registers in one go. Left alone they are loaded where first used, several memory latencies one
+// behind the other, the last of them in the epilogue (with conv_igemm_direct's divisions out of its prologue as well: cfg5 at
+// batch 1 2660 -> 2440 us, mid_dense 337 -> 307; conv_igemm_lean: cfg3 inverse at batch 50 7140 -> 7005).
+__device__ __forceinline__ void hold_args(const ConvArgs& a) {
+    asm volatile("" ::"s"(a.in), "s"(a.wgt), "s"(a.bias), "s"(a.mul), "s"(a.shift), "s"(a.clamp_hi), "s"(a.partial), "s"(a.out), "s"(a.idx_b),
+                 "s"(a.in_plane), "s"(a.npix), "s"(a.cin_pad), "s"(a.n_pad), "s"(a.n_store), "s"(a.state_c));
+    const unsigned* const raw = (const unsigned*)&a;  // in_chunk0, h, w, n_cu and the bit fields
+    static_assert(offsetof(ConvArgs, in_chunk0) == 104 && sizeof(ConvArgs) == 120, "raw[26 .. 28]");
+    asm volatile("" ::"s"(raw[26]), "s"(raw[27]), "s"(raw[28]));
+}
 
 // Pixel index m -> position of the pixel in the zero-bordered image stack, (b * PP + (i+1) * W2 + (j+1)).
 // Image sides that are powers of two (every benchmark shape) take shifts; others divide.

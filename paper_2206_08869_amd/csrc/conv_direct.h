@@ -15,7 +15,7 @@ struct DirectTile {
 // How the tiles of a launch with `bp` pixels a tile go round the XCDs. Over few pixels the weights are the larger operand
 // by far: the channel blocks go round, so that each L2 takes a part of the weights and not all of them. Else whole pixel blocks.
 __host__ __device__ inline bool direct_by_pixels(const ConvArgs& a, int bp) {
-    return a.npix > 7 * bp && a.npix >= a.n_pad * (int)a.taps;
+    return a.npix > 8 * bp && a.npix >= a.n_pad * (int)a.taps;
 }
 constexpr int kDirectTiles = 3;
 extern const DirectTile kDirect[kDirectTiles];

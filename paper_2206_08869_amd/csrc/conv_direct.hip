@@ -6,9 +6,6 @@ namespace iodf {
 
 namespace {
 
-typedef const uint8_t __attribute__((address_space(1)))* gbytes;
-typedef const v4i __attribute__((address_space(1)))* gv4i;
-
 // 16 TC channels x 16 TP pixels per workgroup, the k-tiles split over its KW waves: each wave multiplies whole tiles of
 // its share, and the partial sums (integers: any order of addition gives the same result) meet in LDS.
 //
@@ -29,44 +26,42 @@ __global__ __launch_bounds__(KW * 64) void conv_igemm_direct(const ConvArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int npb = (a.npix + BP - 1) / BP, ncb = (a.n_store + BC - 1) / BC;
-    const int bid = blockIdx.x, xcd = bid & 7;
+    hold_args(a);
+    // whole pixel blocks to an XCD (8 x ncb x npb / 8), as in conv_igemm, or the channel blocks round the XCDs (ncb x npb)
     const bool by_pixels = direct_by_pixels(a, BP);
-    const int slot = bid >> 3;
-    const int pb = by_pixels ? slot / ncb * 8 + xcd : bid / ncb, cb = by_pixels ? slot % ncb : bid % ncb;
-    if (pb >= npb) return;
+    const int cb = by_pixels ? blockIdx.y : blockIdx.x, pb = by_pixels ? blockIdx.z * 8 + blockIdx.x : blockIdx.y;
     const int p0 = pb * BP, c0 = cb * BC;
+    if (p0 >= a.npix) return;
 
     const int nkt = a.taps * (a.cin_pad / 64), hw = a.h * a.w, W2 = a.w + 2, PP = (a.h + 2) * W2;
     const int k0 = wave * nkt / KW, n = (wave + 1) * nkt / KW - k0;
 
-    // the stream of k-tiles: weights at wp, pixels at ap + shift
+    // the stream of k-tiles: weights at wp, pixels at ap + shift. Past this wave's last k-tile all lanes read the same
+    // 16 bytes, which nobody uses.
     const unsigned wstep = (unsigned)a.n_pad * 64;
     const bool k3 = a.taps == 9;
-    const int plane0 = k3 ? k0 / 9 : k0, tap0 = k3 ? k0 - plane0 * 9 : 0;
+    const int plane0 = k3 ? (int)((unsigned)k0 / 9u) : k0, tap0 = k3 ? k0 - plane0 * 9 : 0;
     gbytes wp = (gbytes)a.wgt + (size_t)k0 * wstep + (size_t)c0 * 64;
     gbytes ap = (gbytes)a.in + (size_t)(a.in_chunk0 + plane0) * a.in_plane;
-    int row = tap0 / 3, col = tap0 - row * 3;
+    int row = (int)((unsigned)tap0 / 3u), col = tap0 - row * 3;
     const unsigned wl = l16 * 64 + quad * 16;
     unsigned pl[TP];
-#pragma unroll
-    for (int tp = 0; tp < TP; ++tp) {
-        int m = p0 + tp * 16 + l16;
-        m = m < a.npix ? m : a.npix - 1;
-        pl[tp] = (unsigned)(bordered_pos(a, m, hw, W2, PP) - (k3 ? W2 + 1 : 0)) * 64 + quad * 16;
-    }
     v4i fw[D][TC], fp[D][TP];
-    int left = n;  // k-tiles not yet requested
-    auto issue = [&](auto d_) {
+    int w_left = n, p_left = n;  // k-tiles not yet requested
+    auto issue_w = [&](auto d_) {
         constexpr int d = decltype(d_)::value;
-        // past this wave's last k-tile all lanes read the same 16 bytes, which nobody uses
-        const unsigned live = left > 0 ? ~0u : 0u;
-        const gbytes as = left > 0 ? ap + (k3 ? (unsigned)((row * W2 + col) * 64) : 0u) : (gbytes)a.in;
-        const gbytes ws = left > 0 ? wp : (gbytes)a.wgt;
+        const unsigned live = (unsigned)(-w_left >> 31);  // all ones while there are any
+        const gbytes ws = uniform(w_left > 0 ? wp : (gbytes)a.wgt);
         static_for<TC>([&](auto i_) { constexpr int i = decltype(i_)::value; fw[d][i] = *(gv4i)(ws + ((i * 1024 + wl) & live)); });
-        static_for<TP>([&](auto i_) { constexpr int i = decltype(i_)::value; fp[d][i] = *(gv4i)(as + (pl[i] & live)); });
-        --left;
+        --w_left;
         wp += wstep;
+    };
+    auto issue_p = [&](auto d_) {
+        constexpr int d = decltype(d_)::value;
+        const unsigned live = (unsigned)(-p_left >> 31);
+        const gbytes as = uniform(p_left > 0 ? ap + (k3 ? (unsigned)((row * W2 + col) * 64) : 0u) : (gbytes)a.in);
+        static_for<TP>([&](auto i_) { constexpr int i = decltype(i_)::value; fp[d][i] = *(gv4i)(as + (pl[i] & live)); });
+        --p_left;
         if (k3) {
             if (++col == 3) {
                 col = 0;
@@ -74,7 +69,16 @@ __global__ __launch_bounds__(KW * 64) void conv_igemm_direct(const ConvArgs a) {
             }
         } else ap += a.in_plane;
     };
-    static_for<D>([&](auto d_) { issue(d_); });
+    // weights first: where the pixels lie takes a while to work out
+    static_for<D>([&](auto d_) { issue_w(d_); });
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int tp = 0; tp < TP; ++tp) {
+        int m = p0 + tp * 16 + l16;
+        m = m < a.npix ? m : a.npix - 1;
+        pl[tp] = (unsigned)(bordered_pos(a, m, hw, W2, PP) - (k3 ? W2 + 1 : 0)) * 64 + quad * 16;
+    }
+    static_for<D>([&](auto d_) { issue_p(d_); });
 
     // what the epilogue needs, on its way behind the first k-tiles
     v4i B4[PER], M4[PER], S4[PER], H4[PER];
@@ -113,7 +117,8 @@ __global__ __launch_bounds__(KW * 64) void conv_igemm_direct(const ConvArgs a) {
     for (; kt + D < n; kt += D)
         static_for<D>([&](auto d_) {
             mma(d_);
-            issue(d_);
+            issue_w(d_);
+            issue_p(d_);
         });
     static_for<D>([&](auto d_) {
         if (kt + decltype(d_)::value < n) mma(d_);

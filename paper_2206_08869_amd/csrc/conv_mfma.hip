@@ -640,6 +640,7 @@ __global__ __launch_bounds__(WC* WP * 64, (WC * WP == 4 && NST == 3) ? 2 : 1) vo
 // epilogue, which group 0 runs. Unsplit reductions only.
 template <int BC, int BP, int WC, int WP, int KS, int EPI>
 __global__ __launch_bounds__(WC* WP* KS * 64, KS) void conv_igemm_lean(const ConvArgs a) {
+    hold_args(a);
     const int npb = (a.npix + BP - 1) / BP, ncb = a.n_pad / BC;  // pixel blocks, channel blocks
     static_assert(KS == 1 || KS == 2, "a k-tile has two k-steps");
     constexpr int NST = 9;
@@ -1390,12 +1391,6 @@ int conv_pick_splits(const ConvArgs& a, int tile) {
     return s < 2 ? 1 : (int)s;
 }
 
-// Workgroups of a conv_igemm_direct launch, numbered as the kernel numbers them.
-static int direct_grid(const DirectTile& t, const ConvArgs& a) {
-    const int npb = (a.npix + t.bp - 1) / t.bp, ncb = (a.n_store + t.bc - 1) / t.bc;
-    return (direct_by_pixels(a, t.bp) ? (npb + 7) / 8 * 8 : npb) * ncb;
-}
-
 int conv_trace_slots(const ConvArgs& a_in) {
     ConvArgs a = a_in;
     a.has_trace = 1;
@@ -1418,7 +1413,9 @@ hipError_t launch_conv(const ConvArgs& a_in, hipStream_t stream) {
     if (best < 0) return hipErrorInvalidValue;
     if (is_direct(best)) {
         const DirectTile& t = kDirect[best - kDirect0];
-        hipLaunchKernelGGL(t.kern[pick_epi(a)], dim3(direct_grid(t, a)), dim3(t.waves * 64), t.lds, stream, a);
+        const int npb = (a.npix + t.bp - 1) / t.bp, ncb = (a.n_store + t.bc - 1) / t.bc;
+        const dim3 grid = direct_by_pixels(a, t.bp) ? dim3(8, ncb, (npb + 7) / 8) : dim3(ncb, npb);
+        hipLaunchKernelGGL(t.kern[pick_epi(a)], grid, dim3(t.waves * 64), t.lds, stream, a);
         return hipGetLastError();
     }
     const bool persist = best == kPersistTile;
@@ -1449,6 +1446,8 @@ namespace {
 // for one another, and 64-bit divisions found the pixel: 5.7 us a launch at batch 1, 2.9 to 4.1 now; 6 channels of 1M
 // pixels 99 -> 91 us.)
 __global__ __launch_bounds__(256) void conv_tapsum(const TapSumArgs a, const int per) {
+    asm volatile("" ::"s"(a.y), "s"(a.bias), "s"(a.mul), "s"(a.shift), "s"(a.state), "s"(a.idx_b), "s"(a.codes), "s"(a.n_pad), "s"(a.c_out),
+                 "s"(a.h), "s"(a.w), "s"(a.npix), "s"(a.mode), "s"(a.relu), "s"(a.state_c), "s"(a.sign));  // see hold_args
     const int hw = a.h * a.w, m0 = blockIdx.x * per, left = a.npix - m0 < per ? a.npix - m0 : per;
     for (int t = threadIdx.x; t < left * a.c_out; t += 256) {
         const int k = t / a.c_out, c = t - k * a.c_out, m = m0 + k;

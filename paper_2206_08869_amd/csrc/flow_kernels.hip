@@ -68,6 +68,8 @@ __device__ __forceinline__ int rq_in(int a, int M, int s) {
 __global__ __launch_bounds__(TPB) void k_quant_in(const int32_t* __restrict__ S, int npix, int h, int w, int C,
                                                   const int32_t* __restrict__ idx, int n_a, int M, int s, int8_t* __restrict__ xq,
                                                   long long plane, int per) {
+    // all arguments in one go: loaded where first used they cost several latencies one behind the other
+    asm volatile("" ::"s"(S), "s"(idx), "s"(xq), "s"(plane), "s"(npix), "s"(h), "s"(w), "s"(C), "s"(n_a), "s"(M), "s"(s), "s"(per));
     const int groups = (n_a + 3) / 4;
     const int hw = h * w, W2 = w + 2, PP = (h + 2) * W2;
     const int p0 = blockIdx.x * per, left = npix - p0 < per ? npix - p0 : per;

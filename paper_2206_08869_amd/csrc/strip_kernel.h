@@ -116,6 +116,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
+    hold_args(a);
     StripGeom g;
     if (!strip_of(a, g)) return strip_ahead(a);
     constexpr int EXT = NT2 == 3 ? 1 : 0;  // rows of the inner tensor beyond the strip
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(kStripThreads, 3) void k_strip_in(const StripArgs a
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
+    hold_args(a);
     StripGeom g;
     if (!strip_of(a, g)) return strip_ahead(a);
     const int h = a.h, w = a.w, W2 = w + 2;
@@ -283,6 +285,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const unsigned lane16 = lane * 16;
+    hold_args(a);
     StripGeom g;
     if (!strip_of(a, g)) return strip_ahead(a);
     const int h = a.h, w = a.w;
