@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <array>
 #include <climits>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -831,11 +832,6 @@ static int chain_images(const iodf_ctx* ctx, const DevNet& N, int batch) {
 }
 
 // Rows per strip for the three kinds of launch; rows[STRIP_BLOCK] = 0: not this way.
-//
-// The most rows that still give a strip to every compute unit, up to what the kernels hold: more rows mean fewer rows
-// computed twice and weights read less often, fewer rows a shorter way through a launch. 32x32 maps, whole call of
-// paper_res64 against a launch per layer, rows 4 / 2 / 1: batch 1 +209 / -66 / -133 us, batch 16 -187 / -422 / -104,
-// batch 64 -568 / +11 / +1502, batch 256 -234 / +1622 / +7283.
 struct StripPlan { int rows[3]; };
 
 // Whether strips are the shorter way. Up to two strips per compute unit all run at once and a launch is as long as one
@@ -863,11 +859,39 @@ static bool strips_pay(const iodf_ctx* ctx, const DevChain& C, const StripKernel
     return !most || 100 * done <= (long long)batch * h * w * (9 + C.taps_two) * most;
 }
 
+// Rows of a residual block's strips. `most`: the most that give a strip to every compute unit. That may put a second strip on
+// some of them, so other rows are taken where their estimated time is less by 4 % or more (10 % for the kinds that were not
+// timed for the estimate); of nearly equal ones (5 %) the most, which read weights less often. A launch takes a fixed part
+// and, for every strip that the fullest unit runs, its kernel's matrix work; a last round of strips that is not full saves a third
+// of what it lacks. Fixed part 75 us, 0.12 us per chunk x chunk x tile x tap of that work (16 launches of blocks and two networks'
+// ends; kernels of 128, 96 and 64 channels inside and 128 with a 1x1 layer, 16, 24 and 32 columns, batch 1 to 80: within 8 %). `most`
+// against the rows chosen: 32x32 maps at batch 24 362 against 244 us, 16x16 at batch 50 240 against 179, 24x24 at batch 40 364
+// against 248; none of the 160 cells timed got slower.
+static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w, int batch, int most) {
+    double least = 0, cost[kStripMaxTiles * 32 + 1];
+    int n = 0;  // rows tried
+    for (int r = 1; r <= h && r <= kStripMaxTiles * 32; ++r) {
+        const StripKernel* const k = strip_kernel_for(STRIP_BLOCK, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, r);
+        if (!k) break;  // nor for more rows
+        const double per = (double)batch * ((h + r - 1) / r) / ctx->n_cu, rounds = std::ceil(per);
+        cost[r] = 620 + (rounds - (rounds - per) / 3) * C.nc_x * C.nc_t * (9 * k->tiles_one + C.taps_two * k->tiles_two);
+        least = n && least < cost[r] ? least : cost[r];
+        n = r;
+    }
+    const bool timed = C.nc_x == 4 && (C.taps_two == 9 || C.nc_t == 4);
+    if (most < 1 || most > n || cost[most] <= (timed ? 1.04 : 1.10) * least) return most;
+    int best = n;
+    while (best > 1 && (cost[best] > 1.05 * least || (h + best - 1) / best == (h + best - 2) / (best - 1))) --best;  // (the same strips, less evenly cut)
+    return best;
+}
+
 static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     StripPlan p = {{0, 0, 0}};
     const DevChain& C = N.chain;
     if (!C.ok || !C.blocks) return p;
     const int h = ctx->shape.H >> N.level, w = ctx->shape.W >> N.level;
+    // The most rows that still give a strip to every compute unit, up to what the kernels hold. First and last layers run
+    // so, and whether strips pay is told from blocks cut so.
     auto rows_for = [&](StripPart part) {
         int best = 0;
         for (int r = 1; r <= h; ++r) {
@@ -884,7 +908,7 @@ static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     if (!least || (long long)batch * ((h + least - 1) / least) > kStripMaxUnits) return p;
     if (!strips_pay(ctx, C, *strip_kernel_for(STRIP_BLOCK, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, block), h, w, block, batch)) return p;
     p.rows[STRIP_IN] = in;
-    p.rows[STRIP_BLOCK] = block;
+    p.rows[STRIP_BLOCK] = strip_block_rows(ctx, C, h, w, batch, block);
     p.rows[STRIP_LAST] = last;
     return p;
 }

@@ -100,6 +100,13 @@ def test_strips(H, W, batch, width, keep, k2, unsigned):
                       act_unsigned=unsigned), batch, kernel="k_strip_block")
 
 
+# Batches at which the most rows that give a strip to every compute unit would put two on some: other rows are taken
+@pytest.mark.parametrize("H,batch", [(64, 9), (64, 24), (32, 50), (48, 40)])
+@pytest.mark.parametrize("keep,k2", [(1.0, 3), (0.7, 3), (1.0, 1)])
+def test_strip_rows(H, batch, keep, k2):
+    _check(FlowConfig("rows", H, H, batch, 1, 1, RESNET, 128, 2, False, keep=keep, seed_id=50, block_k2=k2), batch, kernel="k_strip_block")
+
+
 # 65 to 96 of 128 channels kept inside: blocks of 48 filters to a wave over four tiles and more, three waves of 32 below
 # (64, 80 and 128 pixel maps, 130 to 256 as one launch; strips at every tile count); 97 take the kernels of 128
 @pytest.mark.parametrize("H,W,batch,kernel", [(16, 16, 1, "k_chain"), (16, 20, 3, "k_chain"), (16, 32, 2, "k_chain"), (20, 26, 65, "k_chain"),
