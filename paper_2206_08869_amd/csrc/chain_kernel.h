@@ -169,6 +169,50 @@ __device__ __forceinline__ void chain_products_then(v16i (&acc)[TC][TP], v4i (&w
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The products of one layer, one block of filters to a wave, over one or two tiles, unrolled whole: the fragment registers are
+// a ring that holds R of the network's stream ahead, half a layer of 128 channels or one of 64. load(i) requests what follows R
+// behind fragment i. With few tiles the products take as long as the weights need to come, and with 12 ahead the stream
+// stood still during every epilogue. 18 layers 128 wide: on one 8x8 map 46.1 -> 40.1 us, on one 4x4 map 32.4 -> 31.4; 64 channels
+// inside 35.5 -> 32.1 and 30.1 -> 26.5. (36 ahead: the compiler no longer keeps the ring in place from block to block.)
+template <int TP, int NC, int NT, int R, class Load>
+__device__ __forceinline__ void chain_products_ring(v16i (&acc)[1][TP], v4i (&w)[R], const unsigned char* lds, const unsigned (&at)[TP],
+                                                    const unsigned rowstep, Load load) {
+    constexpr int S = NC * NT, F = S * NT, PS = chain_pixel_bytes(NC);
+    v4i b[3][TP];
+    unsigned ba[TP];
+#pragma unroll
+    for (int tp = 0; tp < TP; ++tp) ba[tp] = at[tp];
+    auto read = [&](auto i_) {
+        constexpr int i = decltype(i_)::value, j = i % S;
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            if constexpr (i > 0 && j == 0) ba[tp] += rowstep;
+            b[i % 3][tp] = *(const v4i*)(lds + ba[tp] + (j / NC) * PS + (j % NC) * 32);
+        });
+    };
+    read(std::integral_constant<int, 0>{});
+    read(std::integral_constant<int, 1>{});
+    static_for<F>([&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        if constexpr (i + 2 < F) read(std::integral_constant<int, i + 2>{});
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            acc[0][tp] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[i % R], b[i % 3][tp], acc[0][tp], 0, 0, 0);
+        });
+        load(i_);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    // what reads the accumulators next may be an opaque statement, which the compiler gives no wait states
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Fragment i of a layer at p: four to a base, so that the offsets fit a load's own field and take no registers.
+__device__ __forceinline__ v4i fragment(const gbytes p, const int i, const unsigned lane16) {
+    return *(gv4i)(uniform(p + (i & ~3) * 1024) + (i & 3) * 1024 + lane16);
+}
+
 // Fragments of the first steps of a layer, registers from FROM on.
 template <int TC, int NC, int NT, int FROM, int NW>
 __device__ __forceinline__ void chain_fetch(v4i (&w)[NW], const gbytes p, const unsigned lane16) {
@@ -461,8 +505,14 @@ __device__ __forceinline__ void chain_last_store(const Args& a, const v16i (&acc
 
 // NCX, NCT: 32-channel chunks of the stream x and of the tensor t inside a block (0: no blocks); NT2: kernel side of a
 // block's second convolution; TILES: 32-pixel tiles of the workgroup's images, rounded up to a power of two.
+// Networks of 3x3 blocks that hold their fragments in a ring (see chain_products_ring).
+template <int NCX, int NCT, int NT2, int TILES>
+constexpr bool chain_ring() { return NCX == 4 && (NCT == 2 || NCT == 4) && NT2 == 3 && TILES <= 2; }
+
+// (The ring is given 256 registers: with more, the compiler keeps part of it in accumulation registers and moves it back
+// every block, behind a wait for all loads.)
 template <int NW, int NCX, int NCT, int NT2, int TILES>
-__global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
+__global__ __launch_bounds__(NW * 64, (chain_ring<NCX, NCT, NT2, TILES>() ? 2 : 1)) void k_chain(const ChainArgs a) {
     constexpr int kThreads = NW * 64;
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -506,7 +556,10 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
     constexpr bool F48 = NCT == 3;  // a block's first convolution in the 16-row form: two columns of waves
     static_assert(!F48 || (NCX == 4 && NT2 == 3 && TILES >= 4 && SX::TC == 2), "what the fragment registers are laid out for");
     constexpr int TP48 = F48 ? 4 * TILES / NW : 1;
-    constexpr int NWF = F48 ? 18 : 12;
+    constexpr bool RING = chain_ring<NCX, NCT, NT2, TILES>();
+    constexpr int NWF = RING || F48 ? 18 : 12;
+    // one tile, 64 filters: two waves have the first convolution's, the other two go without
+    const bool one = !RING || NCT == 4 || TILES > 1 || wave < 2;
     const Wave48 f48 = wave48<NCX>(wave & 1, lane);
     v4i wf[NWF];
     static_for<NWF>([&](auto i_) { wf[decltype(i_)::value] = v4i{0, 0, 0, 0}; });
@@ -591,7 +644,10 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         if (a.nc_q == 1) chain_products<SX::TC, SX::TP, 1, 3, false>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
         else chain_products<SX::TC, SX::TP, 2, 3, false>(acc, wf, lds, q_of_x, rpq, uniform(w_in), uniform(w_in), 0, lane16);
         if constexpr (F48) fetch48<NCX>(wf, uniform(blockp), f48);
-        else if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
+        else if constexpr (RING) {
+            const gbytes p = uniform(one ? blockp + tblk * 9 * NCX * 1024 : blockp + bytes_one + xblk * 9 * NCT * 1024);
+            static_for<NWF>([&](auto i_) { wf[decltype(i_)::value] = fragment(p, decltype(i_)::value, lane16); });
+        } else if constexpr (NCT != 0) chain_fetch<ST::TC, NCX, 3, 0>(wf, uniform(blockp + tblk * 9 * NCX * 1024), lane16);
         chain_store<SX::TC, SX::TP, false>(acc, lds, xo, live_x, cst0, xblk * 32, half, a.act_unsigned);
         put_const(1, cn);
     }
@@ -614,6 +670,17 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
                         wf[i] = *(gv4i)(pn + i % 2 * tcs_two + (i / 2) * 1024 + lane16);
                     });
                     store48(acc, lds, to_48, live_48, cst1, ch, a.act_unsigned);
+                } else if constexpr (RING) {
+                    if (one) {
+                        v16i acc[1][ST::TP];
+                        chain_bias(acc, cst1, tblk, half);
+                        const gbytes p1 = uniform(p_one), p2 = uniform(p_two);
+                        chain_products_ring<ST::TP, NCX, 3>(acc, wf, lds, x_of_t, rpx, [&](auto i_) {
+                            constexpr int i = decltype(i_)::value, ahead = i + NWF;
+                            wf[i % NWF] = ahead < 36 ? fragment(p1, ahead, lane16) : fragment(p2, ahead - 36, lane16);
+                        });
+                        chain_store<1, ST::TP, false>(acc, lds, to, live_t, cst1, tblk * 32, half, a.act_unsigned);
+                    }
                 } else {
                     v16i acc[ST::TC][ST::TP];
                     chain_bias(acc, cst1, tblk, half);
@@ -639,6 +706,15 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
                         constexpr int i = decltype(i_)::value;
                         wf[i] = *(gv4i)(pn + f48.at[i % 3] + (i / 3) * 2048 + f48.lane);
                     });
+                } else if constexpr (RING) {
+                    // behind the last block: the last layer's first fragments, where it has as many
+                    const gbytes pn = uniform(last ? (a.taps_last == 9 ? blockp + bytes_block + wave % a.n_blk_last * (36 * 1024) : blockp)
+                                              : one ? p_next : next + bytes_one + xblk * 9 * NCT * 1024);
+                    const gbytes p2 = uniform(p_two);
+                    chain_products_ring<SX::TP, NCT, 3>(acc, wf, lds, at, rpt, [&](auto i_) {
+                        constexpr int i = decltype(i_)::value, ahead = i + NWF;
+                        wf[i % NWF] = ahead < 9 * NCT ? fragment(p2, ahead, lane16) : fragment(pn, ahead - 9 * NCT, lane16);
+                    });
                 } else {
                     chain_products<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, at, rpt, uniform(p_two), uniform(p_next), tcs_one, lane16);
                     constexpr int got = carry_one ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0;
@@ -658,7 +734,8 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         constexpr int NT = decltype(nt_)::value, TP = S::TP;
         const int blk = wave % S::WC;
         const gbytes p = uniform(blockp + blk * NT * NT * NCX * 1024);
-        chain_fetch<1, NCX, NT, 0>(wf, p, lane16);
+        constexpr bool carried = RING && NT == 3;
+        if constexpr (!carried) chain_fetch<1, NCX, NT, 0>(wf, p, lane16);
         unsigned at[TP];
         int gp[TP];  // image * hw + pixel, or -1
         static_for<TP>([&](auto tp_) {
@@ -672,7 +749,12 @@ __global__ __launch_bounds__(NW * 64) void k_chain(const ChainArgs a) {
         chain_last_channels(a, ix, blk, half);
         v16i acc[1][TP];
         chain_bias(acc, cst1, blk, half);
-        chain_products<1, TP, NCX, NT, false>(acc, wf, lds, at, rpx, p, p, 0, lane16);
+        if constexpr (carried)
+            chain_products_ring<TP, NCX, NT>(acc, wf, lds, at, rpx, [&](auto i_) {
+                constexpr int i = decltype(i_)::value;
+                if constexpr (i + NWF < 36) wf[i % NWF] = fragment(p, i + NWF, lane16);
+            });
+        else chain_products<1, TP, NCX, NT, false>(acc, wf, lds, at, rpx, p, p, 0, lane16);
         chain_last_store<TP>(a, acc, gp, ix, cst1, blk, half);
     };
     using I1 = std::integral_constant<int, 1>;
