@@ -198,16 +198,19 @@ __global__ __launch_bounds__(kEncThreads) void k_rans_encode(const CodecTables t
     if (clamped) atomicAdd(errs, (unsigned long long)clamped);
 }
 
-// One workgroup per image. Container: [0] total words; [1 .. 1 + S) words per lane slot;
+// kPackParts workgroups per image, each for some of the lanes (one for all of them took 12 to 25 us a launch, its lanes' words
+// one behind the other; 5 to 11 now). Container: [0] total words; [1 .. 1 + S) words per lane slot;
 // then S pairs (state low, state high); then every slot's words in the order the decoder
 // reads them (the reverse of the order they were shed). S = n_chunks * 16.
+constexpr int kPackParts = 4;
+
 __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const uint32_t* __restrict__ lane_words,
                                                    long long lwpi, const uint32_t* __restrict__ lane_meta,
                                                    uint32_t* __restrict__ out, long long cap,
                                                    uint32_t* __restrict__ sizes, unsigned long long* errs) {
     __shared__ long long s_off[kMaxChunks * kLanes + 1];
     static_assert(kMaxChunks * kLanes <= TPB, "a thread per slot");
-    const int b = blockIdx.x;
+    const int b = blockIdx.x / kPackParts, part = blockIdx.x % kPackParts;
     const int nslots = ct.n_chunks * kLanes;
     const long long header = 1 + 3LL * nslots;
     const uint32_t* mt = lane_meta + (long long)b * nslots * 4;
@@ -224,20 +227,20 @@ __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const ui
     __syncthreads();
     const long long total = header + s_off[nslots];
     uint32_t* ob = out + (long long)b * cap;
-    if (threadIdx.x == 0) {
+    if (part == 0 && threadIdx.x == 0) {
         sizes[b] = (uint32_t)total;
         if (cap > 0) ob[0] = (uint32_t)total;
         if (total > cap) atomicAdd(errs + 1, 1ULL);
     }
-    for (int s = threadIdx.x; s < nslots; s += blockDim.x) {
+    for (int s = threadIdx.x; part == 0 && s < nslots; s += blockDim.x) {
         if (1 + s < cap) ob[1 + s] = mt[4 * s];
         if (1 + nslots + 2 * s < cap) ob[1 + nslots + 2 * s] = mt[4 * s + 1];
         if (1 + nslots + 2 * s + 1 < cap) ob[1 + nslots + 2 * s + 1] = mt[4 * s + 2];
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-    for (int s = wave; s < nslots; s += nwaves) {
+    for (int s = part * nwaves + wave; s < nslots; s += kPackParts * nwaves) {
         const int c = s / kLanes, j = s % kLanes;
-        const long long nw = mt[4 * s];
+        const long long nw = s_off[s + 1] - s_off[s];
         const uint32_t* w = lane_words + (long long)b * lwpi + ct.lane_off[c] + (long long)j * ct.lane_cap[c];
         for (long long i = lane; i < nw; i += 64) {
             const long long dst = header + s_off[s] + i;
@@ -428,7 +431,7 @@ hipError_t launch_rans_pack(const ChunkTable& ct, const uint32_t* lane_words, lo
                             unsigned long long* errs, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
     if (!table_ok(ct) || !lane_words || !lane_meta || !out || !sizes || !errs || cap < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rans_pack, dim3(batch), dim3(TPB), 0, st, ct, lane_words, lane_words_per_image, lane_meta, out,
+    hipLaunchKernelGGL(k_rans_pack, dim3((unsigned)batch * kPackParts), dim3(TPB), 0, st, ct, lane_words, lane_words_per_image, lane_meta, out,
                        cap, sizes, errs);
     return hipGetLastError();
 }
