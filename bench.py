@@ -27,7 +27,7 @@ if ROOT not in sys.path:
 INT8_PEAK_TOPS = 5000.0   # MI355X dense int8 MFMA peak, TOP/s
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_PROFILE = os.path.join("profiles", "conv_hbm_traffic_cfg4.md")
-CONV_SOURCES = [os.path.join("paper_2206_08869_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_dev.h", "conv.h")]
+CONV_SOURCES = [os.path.join("paper_2206_08869_amd", "csrc", f) for f in ("conv_mfma.hip", "conv_direct.hip", "conv_direct.h", "conv_dev.h", "conv.h")]
 
 
 def conv_source_hash():

@@ -21,7 +21,8 @@
  * Calls of more than 32 kernels are replayed from HIP graphs kept per (direction, batch,
  * with/without codes): the first call of a shape captures its graph on an internal stream (host
  * work only, a few ms); inputs and outputs pass through internal staging buffers with
- * device-to-device copies on the caller's stream. Shorter calls launch their kernels directly. Setting IODF_NO_GRAPH=1 in the environment before iodf_init launches all kernels directly.
+ * device-to-device copies on the caller's stream. Shorter calls launch their kernels directly.
+ * Setting IODF_NO_GRAPH=1 in the environment before iodf_init launches all kernels directly.
  *
  * Every function returns IODF_OK (0) or a negative IODF_E_* code; nothing throws.
  */
