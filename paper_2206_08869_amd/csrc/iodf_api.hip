@@ -873,8 +873,10 @@ static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w
     for (int r = 1; r <= h && r <= kStripMaxTiles * 32; ++r) {
         const StripKernel* const k = strip_kernel_for(STRIP_BLOCK, C.nc_x, C.nc_t, C.taps_two, C.nc_q, h, w, r);
         if (!k) break;  // nor for more rows
-        const double per = (double)batch * ((h + r - 1) / r) / ctx->n_cu, rounds = std::ceil(per);
+        const long long strips = (long long)batch * ((h + r - 1) / r);
+        const double per = (double)strips / ctx->n_cu, rounds = std::ceil(per);
         cost[r] = 620 + (rounds - (rounds - per) / 3) * C.nc_x * C.nc_t * (9 * k->tiles_one + C.taps_two * k->tiles_two);
+        if (strips > kStripMaxUnits) cost[r] = HUGE_VAL;  // more than a launch counts; `most` gives fewer
         least = n && least < cost[r] ? least : cost[r];
         n = r;
     }

@@ -143,6 +143,22 @@ def test_strips_only_where_they_win(H, batch, width, keep, k2, strips):
     flow.close()
 
 
+# More images than a launch of strips of the cheapest rows could count (8 x 65535 of them): rows are taken with which it can
+@pytest.mark.parametrize("H,W,batch,width,keep,k2", [(110, 38, 27756, 128, 1.0, 3), (18, 96, 61008, 128, 0.4, 1), (14, 86, 82850, 64, 1.0, 1)])
+def test_strips_of_as_many_images_as_a_launch_counts(H, W, batch, width, keep, k2):
+    import torch
+    cfg = FlowConfig("many", H, W, batch, 1, 1, RESNET, width, 1, False, keep=keep, seed_id=53, block_k2=k2)
+    print("many strips", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, H, W), generator=torch.Generator(device="cuda").manual_seed(7), device="cuda", dtype=torch.uint8)
+    names, z = _kernels(flow, x)
+    assert "k_strip_block" in names, names
+    for part in (slice(0, 3), slice(batch - 3, batch)):
+        assert torch.equal(z[part], _kernels(flow, x[part].contiguous())[1])
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 # Whole networks as one launch, but where kernels of whole tiles do too much padding for many images, and where two
 # plain layers over a few large maps keep more compute units busy.
 @pytest.mark.parametrize("H,W,batch,family,width,keep,k2,chain", [
