@@ -866,7 +866,15 @@ static bool strips_pay(const iodf_ctx* ctx, const DevChain& C, const StripKernel
 // of what it lacks. Fixed part 75 us, 0.12 us per chunk x chunk x tile x tap of that work (16 launches of blocks and two networks'
 // ends; kernels of 128, 96 and 64 channels inside and 128 with a 1x1 layer, 16, 24 and 32 columns, batch 1 to 80: within 8 %). `most`
 // against the rows chosen: 32x32 maps at batch 24 362 against 244 us, 16x16 at batch 50 240 against 179, 24x24 at batch 40 364
-// against 248; none of the 160 cells timed got slower.
+// against 248.
+//
+// The estimate knows nothing of the rows that a strip fetches beside its own, of which more strips of fewer rows have more.
+// Fewer strips always do as well (more rows than `most`, time of `most` over theirs: 0.97 to 1.49, 230 networks of all kinds, maps 4
+// to 99 by 3 to 64, batch 2 to 200). More of them cost part of what is estimated (390 networks, batch 6 to 2048): with 96 and 128
+// channels inside 1.10 to 1.12 turns out 0.98 to 1.09 while `most` gives up to three strips a unit, 0.96 to 1.03 beyond, and 1.12 and
+// more 0.97 to 1.44; with 64 inside 1.16 and more is 1.00 to 1.27 up to four strips a unit, 0.84 to 0.99 beyond, 0.94 where the rows
+// fall to a third (17x16 maps at batch 111), and less than 1.16 is 0.86 to 1.04. `most` against fewer rows without these limits:
+// 26x19 maps, 64 wide, 1x1, batch 2048 1036 us against 1237; 64 of 128 kept, 32x19 at batch 384 509 against 590.
 static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w, int batch, int most) {
     double least = 0, cost[kStripMaxTiles * 32 + 1];
     int n = 0;  // rows tried
@@ -884,7 +892,10 @@ static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w
     if (most < 1 || most > n || cost[most] <= (timed ? 1.04 : 1.10) * least) return most;
     int best = n;
     while (best > 1 && (cost[best] > 1.05 * least || (h + best - 1) / best == (h + best - 2) / (best - 1))) --best;  // (the same strips, less evenly cut)
-    return best;
+    if (best >= most) return best;
+    const long long strips = (long long)batch * ((h + most - 1) / most);
+    if (C.nc_t >= 3) return cost[most] >= (strips <= 3LL * ctx->n_cu ? 1.10 : 1.12) * cost[best] ? best : most;
+    return cost[most] >= 1.16 * cost[best] && strips <= 4LL * ctx->n_cu && 3 * best > most ? best : most;
 }
 
 static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {

@@ -100,11 +100,54 @@ def test_strips(H, W, batch, width, keep, k2, unsigned):
                       act_unsigned=unsigned), batch, kernel="k_strip_block")
 
 
+def _issued_macs(batch, h, w, rows, nc_x, nc_t, k2):
+    """Multiply-accumulates that the matrix cores run for a residual block of nc_x (outside) and nc_t (inside) 32-channel chunks
+    in strips of `rows` rows: whole tiles of 32 pixels, as many as the smallest kernel that holds the strip takes."""
+    one = min(h, rows + 2 if k2 == 3 else rows)
+    t1, t2 = next(t for t in ((2, 1), (3, 1), (3, 2), (4, 2), (6, 4)) if one * w <= 32 * t[0] and rows * w <= 32 * t[1])
+
+    def layer(n_blk, tiles, taps, nc):
+        share = 4 // (n_blk // (2 if n_blk == 4 and tiles >= 4 else 1))   # waves beside each other over the pixels
+        return 32 * -(-tiles // share) * share * 32 * n_blk * taps * 32 * nc
+    return batch * -(-h // rows) * (layer(nc_t, t1, 9, nc_x) + layer(nc_x, t2, k2 * k2, nc_t))
+
+
+def _check_rows(cfg, batch, rows, nc_x, nc_t):
+    """The rows that a forward call's strips took (256 compute units), told from the matrix work of a block's launch; the same
+    images give the same latents in a small batch, and come back."""
+    import torch
+    print("rows", cfg, "batch", batch, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, cfg.H, cfg.W), generator=torch.Generator().manual_seed(8), dtype=torch.uint8).cuda()
+    flow.profile_begin(4096)
+    z = flow.forward(x)[0]
+    torch.cuda.synchronize()
+    blocks = {k["name"]: k for k in flow.profile_end()}["k_strip_block"]
+    h, w = cfg.H // 2, cfg.W // 2
+    assert blocks["issued_macs"] == blocks["launches"] * _issued_macs(batch, h, w, rows, nc_x, nc_t, cfg.block_k2)
+    assert torch.equal(z[-3:], flow.forward(x[-3:].contiguous())[0])
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 # Batches at which the most rows that give a strip to every compute unit would put two on some: other rows are taken
-@pytest.mark.parametrize("H,batch", [(64, 9), (64, 24), (32, 50), (48, 40)])
+@pytest.mark.parametrize("H,batch,rows", [(64, 9, 2), (64, 24, 4), (32, 50, 4), (48, 40, 5)])
 @pytest.mark.parametrize("keep,k2", [(1.0, 3), (0.7, 3), (1.0, 1)])
-def test_strip_rows(H, batch, keep, k2):
-    _check(FlowConfig("rows", H, H, batch, 1, 1, RESNET, 128, 2, False, keep=keep, seed_id=50, block_k2=k2), batch, kernel="k_strip_block")
+def test_strip_rows(H, batch, rows, keep, k2):
+    cfg = FlowConfig("rows", H, H, batch, 1, 1, RESNET, 128, 2, False, keep=keep, seed_id=50, block_k2=k2)
+    _check(cfg, batch, kernel="k_strip_block")
+    _check_rows(cfg, batch, rows, 4, 3 if keep < 1 else 4)
+
+
+# Fewer rows, more strips: where they save enough (five strips to two of seven rows), and not where many strips to a unit, or a
+# third of the rows, cost what the estimate leaves out
+@pytest.mark.parametrize("H,W,batch,width,keep,k2,rows", [
+    (40, 32, 200, 64, 1.0, 3, 4), (40, 32, 200, 128, 1.0, 3, 4), (40, 32, 2048, 128, 1.0, 1, 4),
+    (52, 38, 2048, 64, 1.0, 1, 6), (64, 38, 384, 128, 0.4, 3, 6), (110, 24, 1024, 128, 1.0, 3, 10), (34, 32, 111, 64, 1.0, 3, 6),
+    (64, 18, 256, 128, 0.4, 1, 11)])
+def test_strip_rows_where_more_strips_pay(H, W, batch, width, keep, k2, rows):
+    _check_rows(FlowConfig("more_strips", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=50, block_k2=k2),
+                batch, rows, width // 32, 2 if keep < 1 or width == 64 else 4)
 
 
 # 65 to 96 of 128 channels kept inside: blocks of 48 filters to a wave over four tiles and more, three waves of 32 below
