@@ -13,7 +13,7 @@
 // X <- F * floor(X / M) + (X mod M) - C and pulls a word back in when X < 2^31.
 // A chunk's latents are dealt round-robin to 16 lanes, each an independent stream encoded
 // last-to-first. The chains are serial (encoding: one thread to a lane, what it is fed worked out
-// by other waves; decoding: a wave to a lane), so these kernels are bound by dependent
+// by other waves; decoding: a wave to a lane, or half of one), so these kernels are bound by dependent
 // integer latency, not by memory or the vector units.
 #include "codec_kernels.h"
 
@@ -395,6 +395,110 @@ __global__ __launch_bounds__(64 * kDecLanes) void k_rans_decode_chunk(const Code
     if (bad && lane == 0) atomicAdd(errs + 2, 1ULL);
 }
 
+// The same with half a wave to a lane, a workgroup eight of the sixteen lanes of one image's chunk. The 2^14 residuals are isolated
+// in three rounds (32 * 32 * 16): in each the 32 threads work out G at 32 cut points of the current interval and a ballot counts how
+// many lie at or below the slot; the last round works out G at every residual left, so the symbol's mass is two of its values. The
+// first round's G (its cut points are the same for every symbol, only the scale differs) is worked out a symbol ahead.
+//
+// Its chain is longer (500 ns a symbol and more), but a wave brings two symbols on. With more images than fill the chip's wave slots
+// with a wave to a lane it is the issue of instructions that counts, and this one is ahead (us, a wave to a lane against half of one,
+// all chunks of a batch): 512 images of 8x8 20.0 against 20.0, 640 24.0 against 22.6, 2048 58.5 against 54.6; 4096 of 4x4 56 against
+// 39, of 16x16 360 against 330, of 32x32 1211 against 1192; 512 of 32x32 194 against 196, 640 of 64x64 863 against 851.
+constexpr int kHalfLanes = 8, kHalfThreads = 32 * kHalfLanes;
+
+__global__ __launch_bounds__(kHalfThreads) void k_rans_decode_half(const CodecTables t, const ChunkTable ct, const int c,
+                                                                   const uint32_t* __restrict__ cont, long long cap, int batch,
+                                                                   const int8_t* __restrict__ codes, long long d_codes,
+                                                                   int32_t* __restrict__ z, long long d,
+                                                                   unsigned long long* errs) {
+    __shared__ int s_sig[kSigLds];
+    __shared__ unsigned s_inv[256];
+    for (int i = threadIdx.x; i < 256; i += kHalfThreads) s_inv[i] = (unsigned)t.inv[i];
+    load_sig(s_sig, t.sig);
+    constexpr int kParts = kLanes / kHalfLanes;
+    const int b = blockIdx.x / kParts;  // grid = batch * kParts
+    const int j = blockIdx.x % kParts * kHalfLanes + (threadIdx.x >> 5), helper = threadIdx.x & 31;
+    const int half_shift = threadIdx.x & 32;  // this half's first bit in the wave's ballot, its first lane
+    auto of_half = [&](int v, int i) { return __builtin_amdgcn_ds_bpermute((half_shift + i) << 2, v); };
+    const int nslots = ct.n_chunks * kLanes;
+    const long long header = 1 + 3LL * nslots;  // the host has checked cap >= header
+    const uint32_t* cb = cont + (long long)b * cap;
+    const int n = ct.n[c];
+    const int k = j < n ? (n - j + kLanes - 1) / kLanes : 0;
+    const int kmax = (n + kLanes - 1) / kLanes;  // the same for every thread: ballots stay convergent
+    int32_t* zc = z + (long long)b * d + ct.z_off[c];
+    const int8_t* ci = codes ? codes + (long long)b * d_codes : nullptr;
+    const long long total = cb[0];
+    bool bad = total > cap || total < header;
+    const int slot = c * kLanes + j;
+    // words of the lanes before this one: the half adds them up together
+    long long before = 0;
+    for (int s = helper; s < slot; s += 32) before += cb[1 + s];
+    for (int x = 16; x; x >>= 1) before += __shfl_xor(before, x, 32);
+    long long pos = header + before;
+    unsigned nw = cb[1 + slot];
+    if (bad || pos + (long long)nw > total) { bad = true; nw = 0; pos = header; }
+    const uint32_t* w = cb + pos;  // reads stay below pos + nw <= total <= cap
+    unsigned used = 0;
+    auto words_at = [&](unsigned i) { return (long long)i + helper < nw ? w[i + helper] : 0u; };
+    unsigned w_cur = words_at(0), w_next = words_at(32);
+    unsigned long long X = (unsigned long long)cb[1 + nslots + 2 * slot] |
+                           ((unsigned long long)cb[1 + nslots + 2 * slot + 1] << 32);
+    // codes of 32 positions, one to a thread: mean code in the low half, log-scale code above it
+    auto codes_at = [&](int p) {
+        int m = kDefaultM, l = kDefaultL;
+        if (p + helper < k) codes_of(ct, c, ci, (p + helper) * kLanes + j, m, l);
+        return (l << 16) | (m & 0xffff);
+    };
+    int ml_cur = codes_at(0), ml_next = codes_at(32);
+    // first round: cut points -8192 + (helper + 1) * 512; the last one is the interval's end, above every slot
+    const int cut1 = -kAlphaR + (helper < 31 ? helper + 1 : 31) * 512;
+    int ml = of_half(ml_cur, 0);
+    unsigned inv = s_inv[(ml >> 16) + 128];
+    int g1 = cdf(s_sig, cut1, inv);
+    for (int p0 = 0; p0 < kmax; p0 += 32) {
+        const int n_here = kmax - p0 < 32 ? kmax - p0 : 32;
+        int out = 0;  // this thread's latent of the 32
+        for (int i = 0; i < n_here; ++i) {
+            const int ml_after = of_half(i < 31 ? ml_cur : ml_next, (i + 1) & 31);
+            const unsigned word = (unsigned)of_half((int)w_cur, (int)(used & 31));
+            const unsigned inv_after = s_inv[(ml_after >> 16) + 128];
+            const int v = (int)(X & (unsigned long long)(kMass - 1));
+            // G(-8192) = 0 <= v < M = G(8192)
+            unsigned below = (unsigned)(__ballot(helper < 31 && g1 <= v) >> half_shift);
+            int lo = -kAlphaR + __popc(below) * 512;
+            below = (unsigned)(__ballot(helper < 31 && cdf(s_sig, lo + (helper + 1) * 16, inv) <= v) >> half_shift);
+            lo += __popc(below) * 16;
+            const int g3 = cdf(s_sig, lo + (helper < 16 ? helper : 16), inv);
+            below = (unsigned)(__ballot(helper >= 1 && helper < 16 && g3 <= v) >> half_shift);
+            const int idx = __popc(below);
+            const int C = of_half(g3, idx);
+            const int F = of_half(g3, idx + 1) - C;
+            g1 = cdf(s_sig, cut1, inv_after);
+            if (helper == i) out = lo + idx + 2 * (int)(int16_t)(ml & 0xffff);
+            if (p0 + i < k) {
+                X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
+                if (X < kStateLow) {
+                    if (used < nw) {
+                        X = (X << 32) | word;
+                        if ((++used & 31) == 0) {
+                            w_cur = w_next;
+                            w_next = words_at(used + 32);
+                        }
+                    } else { X <<= 32; bad = true; }
+                }
+            }
+            inv = inv_after;
+            ml = ml_after;
+        }
+        if (p0 + helper < k) zc[(p0 + helper) * kLanes + j] = out;
+        ml_cur = ml_next;
+        ml_next = codes_at(p0 + 64);
+    }
+    if (X != kStateLow || used != nw) bad = true;
+    if (bad && helper == 0) atomicAdd(errs + 2, 1ULL);
+}
+
 int grid_for(long long n, int tpb) {
     long long g = (n + tpb - 1) / tpb;
     if (g > 256 * 16) g = 256 * 16;
@@ -438,13 +542,17 @@ hipError_t launch_rans_pack(const ChunkTable& ct, const uint32_t* lane_words, lo
 
 hipError_t launch_rans_decode_chunk(const CodecTables& t, const ChunkTable& ct, int c, const uint32_t* cont,
                                     long long cap, int batch, const int8_t* codes, long long d_codes, int32_t* z,
-                                    long long d, unsigned long long* errs, hipStream_t st) {
+                                    long long d, unsigned long long* errs, int n_cu, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
     if (!table_ok(ct) || c < 0 || c >= ct.n_chunks || !cont || !z || !errs || !t.sig || !t.inv ||
         cap < 1 + 3LL * ct.n_chunks * kLanes)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rans_decode_chunk, dim3((unsigned)batch * (kLanes / kDecLanes)), dim3(64 * kDecLanes), 0, st, t, ct, c, cont, cap,
-                       batch, codes, d_codes, z, d, errs);
+    if (rans_decode_by_halves(batch, n_cu))
+        hipLaunchKernelGGL(k_rans_decode_half, dim3((unsigned)batch * (kLanes / kHalfLanes)), dim3(kHalfThreads), 0, st, t, ct, c, cont, cap,
+                           batch, codes, d_codes, z, d, errs);
+    else
+        hipLaunchKernelGGL(k_rans_decode_chunk, dim3((unsigned)batch * (kLanes / kDecLanes)), dim3(64 * kDecLanes), 0, st, t, ct, c, cont, cap,
+                           batch, codes, d_codes, z, d, errs);
     return hipGetLastError();
 }
 

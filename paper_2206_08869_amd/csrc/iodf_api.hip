@@ -691,10 +691,10 @@ struct iodf_ctx {
 namespace {
 
 enum { CLS_QUANT_IN = 0, CLS_FILL_ZERO, CLS_CHAIN, CLS_STRIP_IN, CLS_STRIP_BLOCK, CLS_STRIP_LAST, CLS_INGEST, CLS_FACTOR_OUT, CLS_UNFACTOR, CLS_EMIT_X, CLS_TAPSUM,
-       CLS_PRIOR_CF, CLS_RANS_ENCODE, CLS_RANS_PACK, CLS_RANS_DECODE, NUM_FLOW_CLS };
+       CLS_PRIOR_CF, CLS_RANS_ENCODE, CLS_RANS_PACK, CLS_RANS_DECODE, CLS_RANS_DECODE_HALF, NUM_FLOW_CLS };
 const char* const kFlowClsName[NUM_FLOW_CLS] = {"k_quant_in", "k_fill_zero", "k_chain", "k_strip_in", "k_strip_block", "k_strip_last", "k_ingest_squeeze",
                                                 "k_factor_out", "k_unfactor", "k_emit_x", "conv_tapsum",
-                                                "k_prior_cf", "k_rans_encode", "k_rans_pack", "k_rans_decode_chunk"};
+                                                "k_prior_cf", "k_rans_encode", "k_rans_pack", "k_rans_decode_chunk", "k_rans_decode_half"};
 
 bool prof_start(iodf_ctx* ctx, hipStream_t st) {
     if (!ctx->prof_on || 2 * (ctx->prof_recs.size() + 1) > ctx->prof_ev.size()) return false;
@@ -1732,10 +1732,11 @@ int iodf_decode(iodf_ctx* ctx, const uint32_t* words_dev, int64_t cap_words, int
             rc = run_net(ctx, ctx->nets[n0 + m.couplings], batch, +1, ctx->codec_codes, st);
             if (rc != IODF_OK) return rc;
         }
-        PROF_LAUNCH(ctx, st, CLS_RANS_DECODE, 0, (long long)batch * 5 * ctx->chunks.n[lv - 1],
+        PROF_LAUNCH(ctx, st, rans_decode_by_halves(batch, ctx->n_cu) ? CLS_RANS_DECODE_HALF : CLS_RANS_DECODE, 0,
+                    (long long)batch * 5 * ctx->chunks.n[lv - 1],
                     launch_rans_decode_chunk(t, ctx->chunks, lv - 1, words_dev, cap_words, batch,
                                              head ? ctx->codec_codes : nullptr, ctx->d_codes, ctx->codec_z, ctx->d,
-                                             ctx->codec_errs, st));
+                                             ctx->codec_errs, ctx->n_cu, st));
         PROF_LAUNCH(ctx, st, CLS_UNFACTOR, 0, 8LL * batch * C * h * w,
                     launch_unfactor(ctx->state[lv], batch, h, w, C, phi, last ? 0 : C / 2, ctx->codec_z, ctx->d,
                                     ctx->z_off[lv], last ? nullptr : ctx->state[lv + 1], st));

@@ -31,3 +31,47 @@ def test_containers_at_block_edges(H, W, levels, batch):
     torch.cuda.synchronize()
     assert np.array_equal(x2.cpu().numpy(), x) and flow.codec_errors() == (0, 0, 0)
     flow.close()
+
+
+# More images than two to a compute unit (256 of them): half a wave to a lane. Up to there a whole one, with the same results
+@pytest.mark.parametrize("H,W,levels,batch,kernel", [(2, 86, 1, 512, "k_rans_decode_chunk"), (2, 2, 1, 513, "k_rans_decode_half"), (2, 86, 1, 513, "k_rans_decode_half"),
+                                                     (2, 170, 1, 700, "k_rans_decode_half"), (2, 172, 1, 515, "k_rans_decode_half"), (24, 20, 2, 600, "k_rans_decode_half"),
+                                                     (32, 32, 3, 520, "k_rans_decode_half")])
+def test_many_images_decode_as_few_do(H, W, levels, batch, kernel):
+    import torch
+    cfg = FlowConfig("many", H, W, batch, levels, 1, PLAIN, 32, 0, True, image_kind="uniform", seed_id=52)
+    print("many images", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, H, W), generator=torch.Generator().manual_seed(9), dtype=torch.uint8).cuda()
+    words, sizes = flow.encode(x)
+    few = [flow.encode(x[i:i + 256].contiguous()) for i in range(0, batch, 256)]
+    assert torch.equal(words, torch.cat([w for w, _ in few])) and torch.equal(sizes, torch.cat([s for _, s in few]))
+    flow.profile_begin(4096)
+    assert torch.equal(flow.decode(words), x)
+    assert {k["name"] for k in flow.profile_end() if "decode" in k["name"]} == {kernel}
+    assert flow.codec_errors() == (0, 0, 0) and flow.range_errors() == 0
+    # damaged containers: whatever comes out, it and the lanes counted as broken are the same
+    slots = 16 * levels
+    for what in range(5):
+        bad = words.clone()
+        if what == 0:
+            bad[:, 1 + 3 * slots::3] ^= 0x5a5a5a           # payload
+        elif what == 1:
+            bad[::2, 2] += 5                               # a lane claims more words
+        elif what == 2:
+            bad[1::2, 0] = 1 << 30                         # absurd total
+        elif what == 3:
+            bad[:, 1 + slots:1 + 3 * slots] = -1           # states of all ones
+        else:
+            bad = bad[:, :1 + 3 * slots + 7].contiguous()  # cut short
+        y = flow.decode(bad)
+        counted = flow.codec_errors()[2]
+        y_few, c_few = [], 0
+        for i in range(0, batch, 256):
+            y_few.append(flow.decode(bad[i:i + 256].contiguous()))
+            c_few += flow.codec_errors()[2]
+        assert torch.equal(y, torch.cat(y_few)) and counted == c_few, what
+        assert counted > 0 or (H, W) == (2, 2)         # (too few latents for a word to be shed)
+    flow.range_errors()
+    assert torch.equal(flow.decode(words), x)
+    flow.close()
