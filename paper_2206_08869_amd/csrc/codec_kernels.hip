@@ -198,19 +198,16 @@ __global__ __launch_bounds__(kEncThreads) void k_rans_encode(const CodecTables t
     if (clamped) atomicAdd(errs, (unsigned long long)clamped);
 }
 
-// kPackParts workgroups per image, each for some of the lanes (one for all of them took 12 to 25 us a launch, its lanes' words
-// one behind the other; 5 to 11 now). Container: [0] total words; [1 .. 1 + S) words per lane slot;
+// `parts` workgroups per image, each for some of the lanes. Container: [0] total words; [1 .. 1 + S) words per lane slot;
 // then S pairs (state low, state high); then every slot's words in the order the decoder
 // reads them (the reverse of the order they were shed). S = n_chunks * 16.
-constexpr int kPackParts = 4;
-
 __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const uint32_t* __restrict__ lane_words,
                                                    long long lwpi, const uint32_t* __restrict__ lane_meta,
                                                    uint32_t* __restrict__ out, long long cap,
-                                                   uint32_t* __restrict__ sizes, unsigned long long* errs) {
+                                                   uint32_t* __restrict__ sizes, unsigned long long* errs, const int parts) {
     __shared__ long long s_off[kMaxChunks * kLanes + 1];
     static_assert(kMaxChunks * kLanes <= TPB, "a thread per slot");
-    const int b = blockIdx.x / kPackParts, part = blockIdx.x % kPackParts;
+    const int b = blockIdx.x / parts, part = blockIdx.x - b * parts;
     const int nslots = ct.n_chunks * kLanes;
     const long long header = 1 + 3LL * nslots;
     const uint32_t* mt = lane_meta + (long long)b * nslots * 4;
@@ -238,7 +235,7 @@ __global__ __launch_bounds__(TPB) void k_rans_pack(const ChunkTable ct, const ui
         if (1 + nslots + 2 * s + 1 < cap) ob[1 + nslots + 2 * s + 1] = mt[4 * s + 2];
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
-    for (int s = part * nwaves + wave; s < nslots; s += kPackParts * nwaves) {
+    for (int s = part * nwaves + wave; s < nslots; s += parts * nwaves) {
         const int c = s / kLanes, j = s % kLanes;
         const long long nw = s_off[s + 1] - s_off[s];
         const uint32_t* w = lane_words + (long long)b * lwpi + ct.lane_off[c] + (long long)j * ct.lane_cap[c];
@@ -535,8 +532,12 @@ hipError_t launch_rans_pack(const ChunkTable& ct, const uint32_t* lane_words, lo
                             unsigned long long* errs, hipStream_t st) {
     if (batch <= 0) return hipSuccess;
     if (!table_ok(ct) || !lane_words || !lane_meta || !out || !sizes || !errs || cap < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rans_pack, dim3((unsigned)batch * kPackParts), dim3(TPB), 0, st, ct, lane_words, lane_words_per_image, lane_meta, out,
-                       cap, sizes, errs);
+    // One workgroup for all lanes copies their words one lane behind the other, while few images leave the chip idle; each further one
+    // works out all lanes' offsets again. As many as give 2048 of them at most (us, one / two / four to an image: 128 images of 64x64
+    // 18.3 / 11.6 / 9.1, 1024 31.5 / 24.2 / 26.1, 2048 43.6 / 43.6 / 45.8; of 8x8, 512 7.1 / 7.3 / 6.8, 1024 7.6 / 8.2 / 9.7, 4096 13.5 / 18.2 / 24.2).
+    const int parts = batch <= 512 ? 4 : batch <= 1024 ? 2 : 1;
+    hipLaunchKernelGGL(k_rans_pack, dim3((unsigned)batch * parts), dim3(TPB), 0, st, ct, lane_words, lane_words_per_image, lane_meta, out,
+                       cap, sizes, errs, parts);
     return hipGetLastError();
 }
 

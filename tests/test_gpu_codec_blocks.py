@@ -33,9 +33,10 @@ def test_containers_at_block_edges(H, W, levels, batch):
     flow.close()
 
 
-# More images than two to a compute unit (256 of them): half a wave to a lane. Up to there a whole one, with the same results
+# More images than two to a compute unit (256 of them): half a wave to a lane, and containers packed by two workgroups or one (past
+# 1024) instead of four. Up to there a whole wave and four, with the same results
 @pytest.mark.parametrize("H,W,levels,batch,kernel", [(2, 86, 1, 512, "k_rans_decode_chunk"), (2, 2, 1, 513, "k_rans_decode_half"), (2, 86, 1, 513, "k_rans_decode_half"),
-                                                     (2, 170, 1, 700, "k_rans_decode_half"), (2, 172, 1, 515, "k_rans_decode_half"), (24, 20, 2, 600, "k_rans_decode_half"),
+                                                     (2, 170, 1, 700, "k_rans_decode_half"), (2, 86, 1, 1025, "k_rans_decode_half"), (2, 172, 1, 515, "k_rans_decode_half"), (24, 20, 2, 600, "k_rans_decode_half"),
                                                      (32, 32, 3, 520, "k_rans_decode_half")])
 def test_many_images_decode_as_few_do(H, W, levels, batch, kernel):
     import torch
