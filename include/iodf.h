@@ -70,7 +70,8 @@ enum {
     IODF_Q_CODEC_OVERFLOWS = 14,    /* containers that needed more than cap_words (truncated, unusable) */
     IODF_Q_CODEC_BROKEN_LANES = 15, /* coder lanes that iodf_decode could not read back to their initial state
                                        (malformed or foreign container) */
-    IODF_Q_NOALLOC_MAX_BATCH = 16   /* largest batch iodf_encode_noalloc accepts for this model (<= max_batch) */
+    IODF_Q_NOALLOC_MAX_BATCH = 16,  /* largest batch iodf_encode_noalloc accepts for this model (<= max_batch) */
+    IODF_Q_GRAPHS = 17              /* call shapes whose graph the context holds */
 };
 
 /*

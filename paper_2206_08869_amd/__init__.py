@@ -11,4 +11,4 @@ from .binding import (Flow, IodfError, build_library, load_library, iodf_init, i
                       IODF_Q_MACS_INVERSE, IODF_Q_RANGE_ERRORS, IODF_Q_MAX_BATCH, IODF_Q_IMAGE_H, IODF_Q_IMAGE_W,
                       IODF_Q_CONV_LAUNCHES, IODF_Q_WIDE_MACS_FORWARD, IODF_Q_CODEC_HEADER_WORDS, IODF_Q_CODEC_MAX_WORDS,
                       IODF_Q_CODEC_CLAMPED, IODF_Q_CODEC_OVERFLOWS, IODF_Q_CODEC_BROKEN_LANES,
-                      IODF_Q_NOALLOC_MAX_BATCH)
+                      IODF_Q_NOALLOC_MAX_BATCH, IODF_Q_GRAPHS)

@@ -19,7 +19,7 @@ _LIB = None
 IODF_Q_Z_ELEMS, IODF_Q_CODE_BYTES, IODF_Q_WORKSPACE_BYTES, IODF_Q_MACS_FORWARD, IODF_Q_MACS_INVERSE, \
     IODF_Q_RANGE_ERRORS, IODF_Q_MAX_BATCH, IODF_Q_IMAGE_H, IODF_Q_IMAGE_W, IODF_Q_CONV_LAUNCHES, \
     IODF_Q_WIDE_MACS_FORWARD, IODF_Q_CODEC_HEADER_WORDS, IODF_Q_CODEC_MAX_WORDS, IODF_Q_CODEC_CLAMPED, \
-    IODF_Q_CODEC_OVERFLOWS, IODF_Q_CODEC_BROKEN_LANES, IODF_Q_NOALLOC_MAX_BATCH = range(17)
+    IODF_Q_CODEC_OVERFLOWS, IODF_Q_CODEC_BROKEN_LANES, IODF_Q_NOALLOC_MAX_BATCH, IODF_Q_GRAPHS = range(18)
 
 EXPORTS = ["iodf_init", "iodf_forward", "iodf_inverse", "iodf_query", "iodf_free", "iodf_strerror",
            "iodf_last_hip_error", "iodf_profile_begin", "iodf_profile_end", "iodf_prior_cf", "iodf_encode",

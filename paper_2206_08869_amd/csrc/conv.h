@@ -108,6 +108,8 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
 // Index of the kernel configuration launch_conv picks for `a` (-1: invalid arguments), the number of
 // configurations, and a printable name ("conv_igemm<256,256,2,4,4>").
 int conv_pick_tile(const ConvArgs& a);
+// Kernels launch_conv enqueues for `a`: one, and one more that finishes a reduction split over several workgroups.
+int conv_kernels(const ConvArgs& a);
 int conv_num_tiles();
 const char* conv_tile_name(int tile);
 // Timeline slots launch_conv uses for `a` with has_trace (see ConvArgs::trace): 8 x int64 each; 0 for invalid arguments.

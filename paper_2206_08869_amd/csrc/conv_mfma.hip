@@ -1391,6 +1391,8 @@ int conv_pick_splits(const ConvArgs& a, int tile) {
     return s < 2 ? 1 : (int)s;
 }
 
+int conv_kernels(const ConvArgs& a) { return conv_pick_splits(a, conv_pick_tile(a)) > 1 ? 2 : 1; }
+
 int conv_trace_slots(const ConvArgs& a_in) {
     ConvArgs a = a_in;
     a.has_trace = 1;

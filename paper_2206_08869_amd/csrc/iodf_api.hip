@@ -1042,6 +1042,54 @@ static void net_param_span(const iodf_ctx* ctx, const DevNet& N, int batch, cons
     *bytes = (unsigned)N.chain.in_bytes;
 }
 
+// One layer of a network that runs with a launch per layer.
+static ConvArgs conv_args(const iodf_ctx* ctx, const DevNet& N, const DevLayer& L, int batch, int mode_sign, int8_t* codes) {
+    const int lv = N.level, h = ctx->shape.H >> lv, w = ctx->shape.W >> lv, npix = batch * h * w;
+    ConvArgs a;
+    memset(&a, 0, sizeof(a));
+    a.in = ctx->buf[lv][L.in_buf];
+    a.in_plane = ctx->plane[lv];
+    a.in_chunk0 = L.in_off / 64;
+    a.cin_pad = L.cin_pad;
+    a.taps = L.taps;
+    a.h = h; a.w = w; a.npix = npix;
+    a.n_cu = ctx->n_cu;
+    a.wgt = (const int8_t*)(ctx->params + L.wgt_off);
+    a.n_pad = L.n_pad;
+    a.bias = (const int32_t*)(ctx->params + L.bias_off);
+    a.mul = (const int32_t*)(ctx->params + L.mul_off);
+    a.shift = (const int32_t*)(ctx->params + L.shift_off);
+    a.n_store = L.n_store;
+    a.rq_fast = L.rq_fast;
+    a.no_ties = L.no_ties;
+    a.out_unsigned = L.out_unsigned && L.mode == MODE_ACT;
+    a.sc_unsigned = L.sc_unsigned;
+    a.clamp_hi = L.hi_off == (size_t)-1 ? nullptr : (const int32_t*)(ctx->params + L.hi_off);
+    if (L.mode == MODE_RAW) {
+        if ((size_t)npix * L.n_pad <= ctx->raw_elems) a.partial = ctx->raw;
+    } else if (L.mode != MODE_ACT && (size_t)npix * L.n_pad <= ctx->partial_elems) {
+        a.partial = ctx->partial;
+    }
+    a.mode = L.mode;
+    a.relu = L.relu;
+    if (L.mode == MODE_ACT) {
+        a.out = ctx->buf[lv][L.out_buf];
+        a.out_plane = ctx->plane[lv];
+        a.out_chunk0 = L.out_off / 64;
+        a.shortcut = L.shortcut;
+    } else if (L.mode == MODE_COUPLE) {
+        a.state = ctx->state[lv];
+        a.state_c = N.C;
+        a.idx_b = (const int32_t*)(ctx->params + N.phi_off) + N.C_in;
+        a.sign = mode_sign;
+    } else if (L.mode == MODE_CODES) {
+        a.codes = codes;
+        a.codes_img_stride = ctx->d_codes;
+        a.codes_off = ctx->code_off[lv];
+    }
+    return a;
+}
+
 // `next`: the network that runs after this one (strips fetch its first layer's parameters ahead), or nullptr.
 int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* codes, hipStream_t st,
             const DevNet* next = nullptr) {
@@ -1065,50 +1113,8 @@ int run_net(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, int8_t* co
                                 N.cin_pad0, plane, st));
     for (size_t li = 0; li < N.layers.size(); ++li) {
         const DevLayer& L = N.layers[li];
-        ConvArgs a;
-        memset(&a, 0, sizeof(a));
-        a.in = ctx->buf[lv][L.in_buf];
-        a.in_plane = plane;
-        a.in_chunk0 = L.in_off / 64;
-        a.cin_pad = L.cin_pad;
-        a.taps = L.taps;
-        a.h = h; a.w = w; a.npix = npix;
-        a.n_cu = ctx->n_cu;
-        a.wgt = (const int8_t*)(ctx->params + L.wgt_off);
-        a.n_pad = L.n_pad;
-        a.bias = (const int32_t*)(ctx->params + L.bias_off);
-        a.mul = (const int32_t*)(ctx->params + L.mul_off);
-        a.shift = (const int32_t*)(ctx->params + L.shift_off);
-        a.n_store = L.n_store;
-        a.rq_fast = L.rq_fast;
-        a.no_ties = L.no_ties;
-        a.out_unsigned = L.out_unsigned && L.mode == MODE_ACT;
-        a.sc_unsigned = L.sc_unsigned;
-        a.clamp_hi = L.hi_off == (size_t)-1 ? nullptr : (const int32_t*)(ctx->params + L.hi_off);
-        if (L.mode == MODE_RAW) {
-            if ((size_t)npix * L.n_pad <= ctx->raw_elems) a.partial = ctx->raw;
-        } else if (L.mode != MODE_ACT && (size_t)npix * L.n_pad <= ctx->partial_elems) {
-            a.partial = ctx->partial;
-        }
-        a.mode = L.mode;
-        a.relu = L.relu;
-        if (L.mode == MODE_ACT) {
-            a.out = ctx->buf[lv][L.out_buf];
-            a.out_plane = plane;
-            a.out_chunk0 = L.out_off / 64;
-            a.shortcut = L.shortcut;
-        } else if (L.mode == MODE_COUPLE) {
-            a.state = ctx->state[lv];
-            a.state_c = N.C;
-            a.idx_b = phi + N.C_in;
-            a.sign = mode_sign;
-        } else if (L.mode == MODE_CODES) {
-            a.codes = codes;
-            a.codes_img_stride = ctx->d_codes;
-            a.codes_off = ctx->code_off[lv];
-        } else if (!a.partial) {
-            return IODF_E_NOMEM;  // cannot happen: the scratch is sized for every raw layer at init
-        }
+        const ConvArgs a = conv_args(ctx, N, L, batch, mode_sign, codes);
+        if (L.mode == MODE_RAW && !a.partial) return IODF_E_NOMEM;  // cannot happen: the scratch is sized for every raw layer at init
         const int fmode = L.mode == MODE_RAW ? L.final_mode : L.mode;
         const long long extra = fmode == MODE_COUPLE ? 8LL * N.C_out : 0;  // state read + write
         {
@@ -1408,6 +1414,17 @@ static int enqueue_inverse(iodf_ctx* ctx, const int32_t* z_dev, int batch, uint8
     return IODF_OK;
 }
 
+// Kernels of a network that runs with a launch per layer: the input's quantiser, the layers, and what finishes a last layer that
+// is split along its reduction or summed from its taps.
+static int layer_kernels(const iodf_ctx* ctx, const DevNet& N, int batch) {
+    int n = 1;
+    for (const DevLayer& L : N.layers) {
+        n += conv_kernels(conv_args(ctx, N, L, batch, 1, (int8_t*)ctx->params));  // (codes: any address; nothing runs)
+        if (L.mode == MODE_RAW) ++n;
+    }
+    return n;
+}
+
 // Whether a call is short enough to be launched kernel by kernel. A replay saves 0.8 us a launch where kernels are shorter
 // than the host takes to launch them, but costs copies into and out of the graph's own buffers and some 15 us of host work.
 // Direct against replayed: 4 launches (cfg1 at batch 1) 18.6 against 31 to 36 us, 23 (cfg2 at batch 1, 64, 512) 153 / 177 /
@@ -1424,20 +1441,22 @@ static bool launched_directly(const iodf_ctx* ctx, int dir, int batch, int codes
             if (n + nets - i > kMost) return false;
             const DevNet& N = ctx->nets[ctx->first_net[lv] + i];
             const Route r = route_of(ctx, N, batch);
-            n += r.images ? 1 : r.layers() ? 1 + (int)N.layers.size() + (N.layers.back().mode == MODE_RAW) : N.chain.blocks + 2;
+            n += r.images ? 1 : r.layers() ? layer_kernels(ctx, N, batch) : N.chain.blocks + 2;
         }
     }
     return n <= kMost;
 }
 
-// Find or capture the graph of one call shape. Returns nullptr (and *rc) when capture fails.
+// Find or capture the graph of one call shape. Returns nullptr where the call is launched directly (*rc is IODF_OK) or when capture fails.
 static iodf_ctx::GraphEntry* get_graph(iodf_ctx* ctx, int dir, int batch, int codes, int* rc) {
     *rc = IODF_OK;
+    if (!ctx->use_graphs || ctx->prof_on) return nullptr;
     for (auto& g : ctx->graphs)
         if (g.dir == dir && g.batch == batch && g.codes == codes) {
             g.last_use = ++ctx->graph_clock;
             return &g;
         }
+    if (launched_directly(ctx, dir, batch, codes)) return nullptr;
     hipError_t e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) { g_last_hip = (int)e; *rc = IODF_E_HIP; return nullptr; }
     const int erc = dir == 0 ? enqueue_forward(ctx, ctx->stage_x, batch, ctx->stage_z, codes ? ctx->stage_codes : nullptr,
@@ -1481,11 +1500,9 @@ int iodf_forward(iodf_ctx* ctx, const uint8_t* x_dev, int batch, int32_t* z_dev,
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(ctx->device));
     const int codes = (codes_dev && ctx->d_codes) ? 1 : 0;
-    if (!ctx->use_graphs || ctx->prof_on || launched_directly(ctx, 0, batch, codes))
-        return enqueue_forward(ctx, x_dev, batch, z_dev, codes_dev, st);
     int rc;
     iodf_ctx::GraphEntry* g = get_graph(ctx, 0, batch, codes, &rc);
-    if (!g) return rc;
+    if (!g) return rc == IODF_OK ? enqueue_forward(ctx, x_dev, batch, z_dev, codes_dev, st) : rc;
     HIP_TRY(hipMemcpyAsync(ctx->stage_x, x_dev, (size_t)batch * ctx->d, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipGraphLaunch(g->exec, st));
     HIP_TRY(hipEventRecord(g->done, st));
@@ -1502,10 +1519,9 @@ int iodf_inverse(iodf_ctx* ctx, const int32_t* z_dev, int batch, uint8_t* x_dev,
     if (!x_dev || !z_dev) return IODF_E_ARG;
     hipStream_t st = (hipStream_t)stream;
     HIP_TRY(hipSetDevice(ctx->device));
-    if (!ctx->use_graphs || ctx->prof_on || launched_directly(ctx, 1, batch, 0)) return enqueue_inverse(ctx, z_dev, batch, x_dev, st);
     int rc;
     iodf_ctx::GraphEntry* g = get_graph(ctx, 1, batch, 0, &rc);
-    if (!g) return rc;
+    if (!g) return rc == IODF_OK ? enqueue_inverse(ctx, z_dev, batch, x_dev, st) : rc;
     HIP_TRY(hipMemcpyAsync(ctx->stage_z, z_dev, 4 * (size_t)batch * ctx->d, hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipGraphLaunch(g->exec, st));
     HIP_TRY(hipEventRecord(g->done, st));
@@ -2002,6 +2018,7 @@ int iodf_query(iodf_ctx* ctx, int what, int64_t* out) {
             *out = (int64_t)v;
             return IODF_OK;
         }
+        case IODF_Q_GRAPHS: *out = (int64_t)ctx->graphs.size(); return IODF_OK;
         case IODF_Q_CODEC_HEADER_WORDS: *out = 1 + 3LL * ctx->shape.levels * kLanes; return IODF_OK;
         case IODF_Q_CODEC_MAX_WORDS: *out = 1 + 3LL * ctx->shape.levels * kLanes + ctx->d; return IODF_OK;
         case IODF_Q_CODEC_CLAMPED:

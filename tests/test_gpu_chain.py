@@ -258,3 +258,36 @@ def test_profile_of_strips_and_whole_networks():
     per_image = 64 * 128 * (9 * 32 + 2 * (9 + 1) * 128) + 128 * 32 * 9 * 128
     assert stats["k_chain"]["issued_macs"] == 4 * stats["k_chain"]["launches"] * per_image
     flow.close()
+
+
+# Calls of up to 32 kernels are launched directly, longer ones replayed: whole networks as one launch each, strips (ten launches a
+# network), a launch per layer with the taps of the last one summed (four a network), and with the last one split along its 32
+# k-tiles and finished by a kernel of its own (four a network too). Two more kernels take the pixels in and the latents out.
+@pytest.mark.parametrize("family,width,depth,side,couplings,kernels,split", [
+    (PLAIN, 32, 0, 8, 30, 32, False), (PLAIN, 32, 0, 8, 31, 33, False), (RESNET, 128, 8, 32, 3, 32, False), (RESNET, 128, 8, 32, 4, 42, False),
+    (PLAIN, 256, 0, 8, 7, 30, False), (PLAIN, 256, 0, 8, 8, 34, False), (PLAIN, 2048, 0, 8, 7, 30, True), (PLAIN, 2048, 0, 8, 8, 34, True)])
+def test_short_calls_are_launched_directly(family, width, depth, side, couplings, kernels, split):
+    import torch
+    from synth.model import pack_blob, parse_blob
+    cfg = FlowConfig("short", side, side, 1, 1, couplings, family, width, depth, False, seed_id=54)
+    print("short calls", cfg, flush=True)
+    blob = make_blob(cfg)
+    if split:
+        m = parse_blob(blob.copy())
+        for net in m["nets"]:
+            net["layers"][-1]["W"] = np.ascontiguousarray(net["layers"][-1]["W"][:, :, 1:2, 1:2])
+        blob = pack_blob(m)
+    flow = iodf.Flow(blob, max_batch=2, device=0)
+    x = to_gpu(make_images(cfg, batch=2))
+    flow.profile_begin(4096)
+    z = flow.forward(x[:1])[0]
+    torch.cuda.synchronize()
+    bracketed = sum(k["launches"] for k in flow.profile_end() if not k["name"].startswith("view:"))
+    assert bracketed == kernels - couplings * split   # (a split layer and what finishes it are bracketed together)
+    assert flow.query(iodf.IODF_Q_GRAPHS) == 0
+    long = int(kernels > 32)
+    for rep in range(2):
+        assert torch.equal(flow.forward(x[:1])[0], z) and flow.query(iodf.IODF_Q_GRAPHS) == long * (1 if rep == 0 else 2)
+        assert torch.equal(flow.inverse(z), x[:1]) and flow.query(iodf.IODF_Q_GRAPHS) == long * 2
+    assert torch.equal(flow.forward(x)[0][:1], z) and flow.query(iodf.IODF_Q_GRAPHS) == long * 3
+    flow.close()
