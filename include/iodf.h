@@ -208,7 +208,8 @@ int iodf_conv_probe(int device_ordinal, int c_in, int c_out, int k, int h, int w
  * output tile that ran (*n_tiles rows): [0..3] the constant 100 MHz counter when the tile's workgroup
  * started on it, when its first k-tile had landed, after its k loop and after its epilogue; [4], [5] the
  * shader-clock counter at start and end, so (row[5] - row[4]) / (row[3] - row[0]) x 100 MHz is the clock the
- * compute unit ran at; [6], [7] zero. Split launches (a last layer cut along K) are not traced.
+ * compute unit ran at; [6], [7] zero. y is what the traced launch wrote. A layer over so few pixels that a flow
+ * runs it by a kernel without stamps is run, timed and traced by the one that a flow takes for more of them.
  * Measurement support for the roofline analysis, not part of the coding path.
  */
 int iodf_conv_probe_timeline(int device_ordinal, int c_in, int c_out, int k, int h, int w, int batch, int relu,

@@ -252,8 +252,11 @@ def test_single_convolution_on_many_pixels_matches_oracle(c_in, c_out, k, b, sid
     (512, 512, 3, True, 2, 4),      # 72 k-tiles, 32 pixels: half a pixel tile
 ])
 def test_single_convolution_on_few_pixels_matches_oracle(c_in, c_out, k, relu, b, side):
-    """Hidden layers as a batch-1 call sees them: a handful of small tiles, long reductions."""
+    """Hidden layers as a batch-1 call sees them, a handful of small tiles and long reductions; with a timeline they run on 64x64
+    tiles, staged."""
     _check_single_convolution(c_in, c_out, k, relu, 36, b, side, side)
+    tiles = -(-b * side * side // 64) * (c_out // 64)
+    assert _check_single_convolution(c_in, c_out, k, relu, 36, b, side, side, timeline=True).shape[0] == tiles
 
 
 @pytest.mark.parametrize("c_in,c_out,k,relu,b,h,w,tiles", [
@@ -267,17 +270,12 @@ def test_single_convolution_on_few_pixels_matches_oracle(c_in, c_out, k, relu, b
 ])
 def test_single_convolution_on_the_small_tile_kernel_matches_oracle(c_in, c_out, k, relu, b, h, w, tiles):
     """Reduction lengths around the nine-step round of the small-tile kernel (1, 9, 10, 27 k-tiles), ragged pixel
-    tiles, both of its tile sizes; the timeline's row count (output tiles that ran = pixel blocks x channel blocks)
-    tells that the intended tiling ran."""
+    tiles, both of its tile sizes. The first four are so small that a flow runs them without staging; a launch with a timeline
+    takes the small-tile kernel, its result is compared too, and its row count (output tiles that ran = pixel blocks x channel
+    blocks) tells that the intended tiling ran."""
     _check_single_convolution(c_in, c_out, k, relu, 36, b, h, w)
-    rng = np.random.default_rng(3)
-    x = rng.integers(0, 128, (b, c_in, h, w)).astype(np.int8)
-    W = rng.integers(-128, 128, (c_out, c_in, k, k)).astype(np.int8)
-    bias = np.zeros(c_out, np.int32)
-    M = np.full(c_out, 1 << 30, np.int32)
-    shift = np.full(c_out, 40, np.uint8)
-    _, _, tl = iodf.iodf_conv_probe_timeline(x, W, bias, M, shift, relu=relu, iters=1)
-    assert tl.shape[0] == tiles
+    assert _check_single_convolution(c_in, c_out, k, relu, 36, b, h, w, timeline=True).shape[0] == tiles
+    assert _check_single_convolution(c_in, c_out, k, relu, 20, b, h, w, timeline=True).shape[0] == tiles   # general epilogue
 
 
 @pytest.mark.parametrize("c_in,c_out,k,relu,shift_lo,b,h,w", [
@@ -297,7 +295,36 @@ def test_single_convolution_on_tiles_without_staging_matches_oracle(c_in, c_out,
     _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w)
 
 
-def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w):
+@pytest.mark.parametrize("batch,hidden,last", [
+    (1, "direct<1,1,4,5>", "direct<1,1,4,5>"),     # 16 pixels: a tile of 16x16 has them all
+    (8, "direct<1,1,4,5>", "direct<1,1,4,5>"),     # 256 of 16x16
+    (9, "direct<2,1,4,5>", "direct<1,1,4,5>"),     # 288; 144 of 32x16
+    (16, "direct<2,1,4,5>", "direct<1,1,4,5>"),    # 256 of 32x16
+    (17, "direct<2,2,4,6>", "direct<1,1,4,5>"),    # 272; 144 of 32x32
+    (32, "direct<2,2,4,6>", "direct<1,1,4,5>"),    # 256 of 32x32; last layer 128 of 16x16
+    (33, "lean<64,64,2,2,2>", "direct<1,1,4,5>"),  # 272
+])
+def test_layers_over_few_pixels_choose_their_tile(batch, hidden, last):
+    """One network of 512 filters on 4x4 maps, its first layer 3x3 and its last one 54 rows of raw sums, on 256 compute units."""
+    import oracle
+    import torch
+    from synth import make_blob, make_images
+    from synth.configs import PLAIN, FlowConfig
+    cfg = FlowConfig("few", 8, 8, batch, 1, 1, PLAIN, 512, 0, False, seed_id=55)
+    blob = make_blob(cfg)
+    x = make_images(cfg, batch=batch)
+    print("few pixels", cfg, flush=True)
+    flow = iodf.Flow(blob, max_batch=batch, device=0)
+    flow.profile_begin(64)
+    z = flow.forward(to_gpu(x))[0]
+    torch.cuda.synchronize()
+    ran = {k["name"]: k["launches"] for k in flow.profile_end() if k["name"].startswith("conv_igemm")}
+    assert ran == {"conv_igemm_%s 3x3" % hidden: 1, "conv_igemm_%s 1x1" % last: 1}
+    assert np.array_equal(z.cpu().numpy(), oracle.Model(blob).forward(x)[0])
+    flow.close()
+
+
+def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w, timeline=False):
     import oracle
     rng = np.random.default_rng(c_in * 1000 + c_out)
     x = rng.integers(-128, 128, (b, c_in, h, w)).astype(np.int8)
@@ -307,11 +334,15 @@ def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w):
     bias = rng.integers(-5000, 5000, c_out).astype(np.int32)
     M = rng.integers(1 << 30, (1 << 31) - 1, c_out).astype(np.int32)
     shift = rng.integers(shift_lo, shift_lo + 6, c_out).astype(np.uint8)
-    y, us = iodf.iodf_conv_probe(x, W, bias, M, shift, relu=relu, iters=3)
+    if timeline:
+        y, us, tl = iodf.iodf_conv_probe_timeline(x, W, bias, M, shift, relu=relu, iters=1)
+    else:
+        (y, us), tl = iodf.iodf_conv_probe(x, W, bias, M, shift, relu=relu, iters=3), None
     for i in range(b):
         ref = oracle.epilogue(oracle.conv_acc(x[i], W, bias), M, shift, relu=relu)
         assert np.array_equal(y[i], ref), "image %d" % i
     assert us > 0
+    return tl
 
 
 def _edge_accumulators(M, shift, top):
@@ -331,8 +362,8 @@ def test_epilogue_at_the_saturation_edges(relu, edge, b, side, c_in):
     result changes regime: the smallest accumulator that requantises to 127 (the fast ReLU epilogue clamps
     the accumulator there BEFORE it rescales), its counterpart at -128 for layers without ReLU, and zero.
     A 1x1 layer whose only non-zero weights are +1 and -1 on two input channels adds delta in -3..3 to a
-    per-channel bias, so pixel p of channel c sees bias[c] + delta(p). Small case: the plain kernel; large
-    case (139264 pixels, 4 k-tiles): the persistent kernel."""
+    per-channel bias, so pixel p of channel c sees bias[c] + delta(p). Small case: the kernel for few pixels, and with a
+    timeline the staged 64x64 tiles; large case (139264 pixels, 4 k-tiles): the persistent kernel."""
     import oracle
     c_out = 256
     rng = np.random.default_rng(77 + b)
@@ -354,10 +385,11 @@ def test_epilogue_at_the_saturation_edges(relu, edge, b, side, c_in):
     x[:, 0] = np.maximum(delta, 0)
     x[:, 1] = np.maximum(-delta, 0)
     y, _ = iodf.iodf_conv_probe(x, W, bias, M, shift, relu=relu, iters=1)
+    yt = iodf.iodf_conv_probe_timeline(x, W, bias, M, shift, relu=relu, iters=1)[0]
     seen = set()
     for i in range(b):
         ref = oracle.epilogue(oracle.conv_acc(x[i], W, bias), M, shift, relu=relu)
-        assert np.array_equal(y[i], ref), "image %d" % i
+        assert np.array_equal(y[i], ref) and np.array_equal(yt[i], ref), "image %d" % i
         seen.update(np.unique(ref).tolist())
     # the cases straddle the edge they aim at
     if edge == "top":
@@ -390,17 +422,18 @@ def test_epilogue_without_relu_at_halves(ties, b, side, c_in):
     x[:, 0] = np.maximum(delta, 0)
     x[:, 1] = np.maximum(-delta, 0)
     y, _ = iodf.iodf_conv_probe(x, W, bias, M.astype(np.int32), shift, relu=False, iters=1)
+    yt = iodf.iodf_conv_probe_timeline(x, W, bias, M.astype(np.int32), shift, relu=False, iters=1)[0]
     for i in range(b):
         ref = oracle.epilogue(oracle.conv_acc(x[i], W, bias), M.astype(np.int32), shift, relu=False)
-        assert np.array_equal(y[i], ref), "image %d" % i
+        assert np.array_equal(y[i], ref) and np.array_equal(yt[i], ref), "image %d" % i
 
 
 @pytest.mark.parametrize("c_in,k,b,side,tiles", [(64, 3, 2, 16, 32), (256, 1, 136, 32, 544)])
 def test_conv_probe_timeline(c_in, k, b, side, tiles):
     """The per-tile timeline is measurement support: it must not change the layer's result, report one
     row per output tile that ran, and its stamps must be ordered (start <= first operands <= k loop done
-    <= epilogue done) with a plausible shader clock. Small case: plain kernel (64x64 tiles); large case: the
-    persistent kernel (256x256 tiles, 544 of them on one workgroup per CU)."""
+    <= epilogue done) with a plausible shader clock. Small case: 64x64 tiles, where without a timeline the
+    kernel for few pixels runs; large case: the persistent kernel (256x256 tiles, 544 of them on one workgroup per CU)."""
     c_out = 256
     rng = np.random.default_rng(5 + c_in)
     x = np.maximum(rng.integers(-128, 128, (b, c_in, side, side)), 0).astype(np.int8)
