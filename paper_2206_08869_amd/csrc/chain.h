@@ -8,8 +8,6 @@ namespace iodf {
 
 constexpr size_t kChainMaxLds = 160 * 1024;
 constexpr int kChainMaxTiles = 8;  // 32-pixel tiles of a workgroup
-// A workgroup requests up to this many bytes past the end of a layer's weights.
-constexpr size_t kChainOverread = 12 * 1024;
 constexpr int kChainConstBytes = 4 * 128 * (int)sizeof(int32_t);
 
 // Bytes a pixel of a tensor with 32 * nc channels takes in LDS: 16 more than its channels, so that the 16-byte

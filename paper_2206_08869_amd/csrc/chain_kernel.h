@@ -25,12 +25,14 @@ constexpr int kInvBits = 20;  // m / d = m * ceil(2^20 / d) >> 20 for m * d < 2^
 // See hold_args(const ConvArgs&).
 __device__ __forceinline__ void hold_args(const ChainArgs& a) {
     asm volatile("" ::"s"(a.params), "s"(a.state), "s"(a.idx), "s"(a.codes), "s"(a.pf_bytes), "s"(a.batch), "s"(a.mul_in));
-    const unsigned* const raw = (const unsigned*)&a;
+    const unsigned* const raw = (const unsigned*)&a;  // the bit fields
+    static_assert(offsetof(ChainArgs, mul_in) == 56 && sizeof(ChainArgs) == 80, "raw[15 .. 19]");
     asm volatile("" ::"s"(raw[15]), "s"(raw[16]), "s"(raw[17]), "s"(raw[18]), "s"(raw[19]));
 }
 __device__ __forceinline__ void hold_args(const StripArgs& a) {
     asm volatile("" ::"s"(a.params), "s"(a.in), "s"(a.out), "s"(a.state), "s"(a.idx), "s"(a.codes), "s"(a.plane), "s"(a.batch), "s"(a.mul_in));
     const unsigned* const raw = (const unsigned*)&a;
+    static_assert(offsetof(StripArgs, mul_in) == 84 && sizeof(StripArgs) == 112, "raw[22 .. 26], then padding");
     asm volatile("" ::"s"(raw[22]), "s"(raw[23]), "s"(raw[24]), "s"(raw[25]), "s"(raw[26]));
 }
 
@@ -503,12 +505,12 @@ __device__ __forceinline__ void chain_last_store(const Args& a, const v16i (&acc
     });
 }
 
-// NCX, NCT: 32-channel chunks of the stream x and of the tensor t inside a block (0: no blocks); NT2: kernel side of a
-// block's second convolution; TILES: 32-pixel tiles of the workgroup's images, rounded up to a power of two.
 // Networks of 3x3 blocks that hold their fragments in a ring (see chain_products_ring).
 template <int NCX, int NCT, int NT2, int TILES>
 constexpr bool chain_ring() { return NCX == 4 && (NCT == 2 || NCT == 4) && NT2 == 3 && TILES <= 2; }
 
+// NCX, NCT: 32-channel chunks of the stream x and of the tensor t inside a block (0: no blocks); NT2: kernel side of a
+// block's second convolution; TILES: 32-pixel tiles of the workgroup's images, rounded up to a power of two.
 // (The ring is given 256 registers: with more, the compiler keeps part of it in accumulation registers and moves it back
 // every block, behind a wait for all loads.)
 template <int NW, int NCX, int NCT, int NT2, int TILES>

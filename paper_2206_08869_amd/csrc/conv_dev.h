@@ -162,7 +162,7 @@ __device__ __forceinline__ void hold_args(const ConvArgs& a) {
 }
 
 // Pixel index m -> position of the pixel in the zero-bordered image stack, (b * PP + (i+1) * W2 + (j+1)).
-// Image sides that are powers of two (every benchmark shape) take shifts; others divide.
+// Image sides that are powers of two take shifts; others divide.
 __device__ __forceinline__ int bordered_pos(const ConvArgs& a, int m, int hw, int W2, int PP) {
     int b, i, j;
     if (a.log2_w >= 0 && a.log2_hw >= 0) {

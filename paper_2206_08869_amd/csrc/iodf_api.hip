@@ -489,7 +489,7 @@ void pack_chain(Arena& A, const HostModel& m, const HostNet& N, DevNet& D) {
         if (l == 2 && l + 1 < nl) C.block_bytes = total - C.in_bytes;
     }
     C.bytes = total;
-    C.off = A.alloc(total + kChainOverread);
+    C.off = A.alloc(total);
     uint8_t* dst = A.host.data() + C.off;
     for (int l = 0; l < nl; ++l) {
         const DevLayer& L = D.layers[l];
