@@ -113,7 +113,8 @@ class ClockSampler:
 
 def kernel_views(stats, elapsed_s):
     """Per-kernel list, per-kernel aggregates (3x3 and 1x1 launches of one kernel together, as
-    rocprofv3 names them) and the wide-layer views from iodf_profile_end's records."""
+    rocprofv3 names them) and the wide-layer views from iodf_profile_end's records. elapsed_s: of the steps
+    that the records are from, whose launches are bracketed by events and not replayed from a graph."""
     kernels, per_kernel, views = [], {}, {}
     for s in stats:
         if s["name"].startswith("view:"):      # a second sum over conv launches already listed
@@ -156,17 +157,17 @@ def profiled_pass(flow, step, steps, launches):
     return flow.profile_end(), dt
 
 
-def short_roofline(flow, step, steps, launches, elapsed_per_step):
+def short_roofline(flow, step, steps, launches):
     """Dominant kernel and wide-layer view of a secondary run."""
-    stats, _ = profiled_pass(flow, step, steps, launches)
-    _, per_kernel, views = kernel_views(stats, elapsed_per_step * steps)
+    stats, elapsed = profiled_pass(flow, step, steps, launches)
+    _, per_kernel, views = kernel_views(stats, elapsed)
     dom = dominant(per_kernel)
     if not dom:
         return None
     tops = 2.0 * dom["macs"] / (dom["total_ms"] * 1e-3) / 1e12
     out = dict(kernel=dom["name"], achieved=round(tops, 2), unit="TOP/s", frac=round(tops / INT8_PEAK_TOPS, 4),
                launches_per_step=dom["launches"] // steps, avg_launch_ms=round(dom["total_ms"] / dom["launches"], 5),
-               share_of_step=round(dom["total_ms"] / (1e3 * elapsed_per_step * steps), 4))
+               share_of_step=round(dom["total_ms"] / (1e3 * elapsed), 4))
     if "wide conv layers" in views:
         out["wide_layers_frac"] = views["wide conv layers"]["frac_of_int8_peak"]
     return out
@@ -203,7 +204,7 @@ def other_runs(iodf, main_flow, main_cfg, x, z, codes, x_out, args):
         metric="decode-inference images/sec at 3x%dx%d" % (main_cfg.H, main_cfg.W), value=round(b / t, 2),
         unit="images/s", batch=b, ms_per_step=round(1e3 * t, 3), macs_per_image=macs_inv,
         whole_path_frac_of_int8_peak=round(2.0 * macs_inv * b / t / 1e12 / INT8_PEAK_TOPS, 4),
-        round_trip_exact=exact, dominant_kernel=short_roofline(main_flow, inv_step, 2, launches, t))
+        round_trip_exact=exact, dominant_kernel=short_roofline(main_flow, inv_step, 2, launches))
 
     # cfg5: the same flow with half of the filters of every hidden convolution gated off
     cfg5 = CONFIGS["cfg5"]
@@ -239,7 +240,7 @@ def other_runs(iodf, main_flow, main_cfg, x, z, codes, x_out, args):
         p90_ms_per_image=round(ms[int(len(ms) * 0.9)], 4), min_ms=round(ms[0], 4), calls=len(ms), warmup_calls=20,
         macs_per_image=macs5, whole_path_frac_of_int8_peak=round(2.0 * macs5 / (p50 * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4),
         round_trip_exact=bool(torch.equal(xb, x1)) and flow1.range_errors() == 0,
-        dominant_kernel=short_roofline(flow1, step1, 3, flow1.query(iodf.IODF_Q_CONV_LAUNCHES), p50 * 1e-3))
+        dominant_kernel=short_roofline(flow1, step1, 3, flow1.query(iodf.IODF_Q_CONV_LAUNCHES)))
     flow1.close()
     # batch 1024: throughput
     B = cfg5.batch
@@ -260,7 +261,7 @@ def other_runs(iodf, main_flow, main_cfg, x, z, codes, x_out, args):
         batch=B, ms_per_step=round(1e3 * t, 3), steps=10, warmup=3, macs_per_image=macs5,
         whole_path_frac_of_int8_peak=round(2.0 * macs5 * B / t / 1e12 / INT8_PEAK_TOPS, 4),
         round_trip_exact=bool(torch.equal(xb, xB)) and flowB.range_errors() == 0, image0_equals_batch1_result=same,
-        dominant_kernel=short_roofline(flowB, stepB, 2, flowB.query(iodf.IODF_Q_CONV_LAUNCHES), t),
+        dominant_kernel=short_roofline(flowB, stepB, 2, flowB.query(iodf.IODF_Q_CONV_LAUNCHES)),
         setup_s=round(t_gen, 1))
     flowB.close()
     return out
@@ -456,7 +457,7 @@ def main():
     roofline = None
     kernels = []
     if stats:
-        kernels, per_kernel, views = kernel_views(stats, elapsed)
+        kernels, per_kernel, views = kernel_views(stats, prof_elapsed)
         dom = dominant(per_kernel)
         achieved = 2.0 * dom["macs"] / (dom["total_ms"] * 1e-3) / 1e12
         traffic, traffic_source = recorded_traffic("%s batch %d %s" % (cfg.name, batch, args.direction), dom["name"])
@@ -474,7 +475,7 @@ def main():
                         algorithmic_ops_per_launch=round(2.0 * dom["macs"] / dom["launches"]),
                         issued_ops_per_launch=round(2.0 * dom["issued_macs"] / dom["launches"]),
                         launches=dom["launches"], avg_launch_ms=round(dom["total_ms"] / dom["launches"], 5),
-                        share_of_step=round(dom["total_ms"] / (1e3 * elapsed), 4),
+                        share_of_step=round(dom["total_ms"] / (1e3 * prof_elapsed), 4),
                         instrumented_ms_per_step=round(1e3 * prof_elapsed / args.steps, 3),
                         wide_layers=views)
 
