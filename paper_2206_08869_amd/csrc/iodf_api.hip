@@ -664,6 +664,10 @@ struct iodf_ctx {
     std::vector<GraphEntry> graphs;   // at most kMaxGraphs, least recently used dropped
     static constexpr size_t kMaxGraphs = 8;
     unsigned long long graph_clock = 0;
+    // the last call shapes that were found to be launched directly
+    struct DirectShape { int dir, batch, codes; };
+    std::array<DirectShape, 8> direct{};  // (batch 0: none)
+    size_t direct_next = 0;
     hipStream_t cap_stream = nullptr;
     bool use_graphs = true;
     uint8_t* stage_x = nullptr;
@@ -1456,7 +1460,12 @@ static iodf_ctx::GraphEntry* get_graph(iodf_ctx* ctx, int dir, int batch, int co
             g.last_use = ++ctx->graph_clock;
             return &g;
         }
-    if (launched_directly(ctx, dir, batch, codes)) return nullptr;
+    for (const auto& d : ctx->direct)
+        if (d.dir == dir && d.batch == batch && d.codes == codes) return nullptr;
+    if (launched_directly(ctx, dir, batch, codes)) {
+        ctx->direct[ctx->direct_next++ % ctx->direct.size()] = {dir, batch, codes};
+        return nullptr;
+    }
     hipError_t e = hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) { g_last_hip = (int)e; *rc = IODF_E_HIP; return nullptr; }
     const int erc = dir == 0 ? enqueue_forward(ctx, ctx->stage_x, batch, ctx->stage_z, codes ? ctx->stage_codes : nullptr,
