@@ -111,17 +111,18 @@ class ClockSampler:
                 "source": "pp_dpm_sclk, sampled every %d ms during the timed region" % int(self.period * 1e3)}
 
 
-def kernel_views(stats, elapsed_s):
+def kernel_views(stats):
     """Per-kernel list, per-kernel aggregates (3x3 and 1x1 launches of one kernel together, as
-    rocprofv3 names them) and the wide-layer views from iodf_profile_end's records. elapsed_s: of the steps
-    that the records are from, whose launches are bracketed by events and not replayed from a graph."""
+    rocprofv3 names them) and the wide-layer views from iodf_profile_end's records. share_of_step: of the time of all
+    launches recorded: bracketed by events, they take longer than a replayed step and the host's gaps between them vary."""
     kernels, per_kernel, views = [], {}, {}
+    all_ms = sum(s["total_ms"] for s in stats if not s["name"].startswith("view:"))
     for s in stats:
         if s["name"].startswith("view:"):      # a second sum over conv launches already listed
             tops = 2.0 * s["macs"] / (s["total_ms"] * 1e-3) / 1e12
             views[s["name"][6:]] = dict(launches=s["launches"], total_ms=round(s["total_ms"], 3), tops=round(tops, 2),
                                         frac_of_int8_peak=round(tops / INT8_PEAK_TOPS, 4),
-                                        share_of_step=round(s["total_ms"] / (1e3 * elapsed_s), 4))
+                                        share_of_step=round(s["total_ms"] / all_ms, 4))
             continue
         avg_ms = s["total_ms"] / s["launches"]
         k = dict(name=s["name"], launches=s["launches"], total_ms=round(s["total_ms"], 3), avg_ms=round(avg_ms, 5))
@@ -136,6 +137,7 @@ def kernel_views(stats, elapsed_s):
         agg = per_kernel.setdefault(base, dict(name=base, launches=0, total_ms=0.0, macs=0, bytes=0, issued_macs=0))
         for f in ("launches", "total_ms", "macs", "bytes", "issued_macs"):
             agg[f] += s[f]
+        agg["share"] = round(agg["total_ms"] / all_ms, 4)
     return kernels, per_kernel, views
 
 
@@ -159,15 +161,15 @@ def profiled_pass(flow, step, steps, launches):
 
 def short_roofline(flow, step, steps, launches):
     """Dominant kernel and wide-layer view of a secondary run."""
-    stats, elapsed = profiled_pass(flow, step, steps, launches)
-    _, per_kernel, views = kernel_views(stats, elapsed)
+    stats, _ = profiled_pass(flow, step, steps, launches)
+    _, per_kernel, views = kernel_views(stats)
     dom = dominant(per_kernel)
     if not dom:
         return None
     tops = 2.0 * dom["macs"] / (dom["total_ms"] * 1e-3) / 1e12
     out = dict(kernel=dom["name"], achieved=round(tops, 2), unit="TOP/s", frac=round(tops / INT8_PEAK_TOPS, 4),
                launches_per_step=dom["launches"] // steps, avg_launch_ms=round(dom["total_ms"] / dom["launches"], 5),
-               share_of_step=round(dom["total_ms"] / (1e3 * elapsed), 4))
+               share_of_step=dom["share"])
     if "wide conv layers" in views:
         out["wide_layers_frac"] = views["wide conv layers"]["frac_of_int8_peak"]
     return out
@@ -457,7 +459,7 @@ def main():
     roofline = None
     kernels = []
     if stats:
-        kernels, per_kernel, views = kernel_views(stats, prof_elapsed)
+        kernels, per_kernel, views = kernel_views(stats)
         dom = dominant(per_kernel)
         achieved = 2.0 * dom["macs"] / (dom["total_ms"] * 1e-3) / 1e12
         traffic, traffic_source = recorded_traffic("%s batch %d %s" % (cfg.name, batch, args.direction), dom["name"])
@@ -475,7 +477,7 @@ def main():
                         algorithmic_ops_per_launch=round(2.0 * dom["macs"] / dom["launches"]),
                         issued_ops_per_launch=round(2.0 * dom["issued_macs"] / dom["launches"]),
                         launches=dom["launches"], avg_launch_ms=round(dom["total_ms"] / dom["launches"], 5),
-                        share_of_step=round(dom["total_ms"] / (1e3 * prof_elapsed), 4),
+                        share_of_step=dom["share"],
                         instrumented_ms_per_step=round(1e3 * prof_elapsed / args.steps, 3),
                         wide_layers=views)
 
