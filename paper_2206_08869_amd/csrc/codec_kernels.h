@@ -55,9 +55,11 @@ hipError_t launch_rans_pack(const ChunkTable& ct, const uint32_t* lane_words, lo
                             const uint32_t* lane_meta, int batch, uint32_t* out, long long cap, uint32_t* sizes,
                             unsigned long long* errs, hipStream_t st);
 
-// Chunk c of every container -> z[b][z_off[c] ..], with the chunk's codes (or none). Up to eight lanes a SIMD are decoded with a
-// wave each, more with half a wave each (see k_rans_decode_half).
-inline bool rans_decode_by_halves(int batch, int n_cu) { return (long long)batch * kLanes > 8LL * 4 * n_cu; }
+// Chunk c of every container -> z[b][z_off[c] ..], with the chunk's codes (or none). A wave decodes a lane; where that is more than
+// eight waves a SIMD and a lane has 32 symbols at most, half a wave does (see k_rans_decode_half).
+inline bool rans_decode_by_halves(const ChunkTable& ct, int c, int batch, int n_cu) {
+    return (long long)batch * kLanes > 8LL * 4 * n_cu && ct.n[c] <= 32 * kLanes;
+}
 hipError_t launch_rans_decode_chunk(const CodecTables& t, const ChunkTable& ct, int c, const uint32_t* cont,
                                     long long cap, int batch, const int8_t* codes, long long d_codes, int32_t* z,
                                     long long d, unsigned long long* errs, int n_cu, hipStream_t st);

@@ -392,15 +392,17 @@ __global__ __launch_bounds__(64 * kDecLanes) void k_rans_decode_chunk(const Code
     if (bad && lane == 0) atomicAdd(errs + 2, 1ULL);
 }
 
-// The same with half a wave to a lane, a workgroup eight of the sixteen lanes of one image's chunk. The 2^14 residuals are isolated
-// in three rounds (32 * 32 * 16): in each the 32 threads work out G at 32 cut points of the current interval and a ballot counts how
-// many lie at or below the slot; the last round works out G at every residual left, so the symbol's mass is two of its values. The
-// first round's G (its cut points are the same for every symbol, only the scale differs) is worked out a symbol ahead.
+// The same for chunks of at most 32 symbols a lane, with half a wave to a lane and a workgroup to eight lanes. The 2^14 residuals
+// are isolated in three rounds (32 * 32 * 16): in each the 32 threads work out G at 32 cut points of the current interval and a ballot
+// counts how many lie at or below the slot; the last round works out G at every residual left, so the symbol's mass is two of its
+// values. The first round's G (its cut points are the same for every symbol, only the scale differs) is worked out a symbol ahead.
 //
-// Its chain is longer (500 ns a symbol and more), but a wave brings two symbols on. With more images than fill the chip's wave slots
-// with a wave to a lane it is the issue of instructions that counts, and this one is ahead (us, a wave to a lane against half of one,
-// all chunks of a batch): 512 images of 8x8 20.0 against 20.0, 640 24.0 against 22.6, 2048 58.5 against 54.6; 4096 of 4x4 56 against
-// 39, of 16x16 360 against 330, of 32x32 1211 against 1192; 512 of 32x32 194 against 196, 640 of 64x64 863 against 851.
+// Its chain is longer (500 ns a symbol and more), but a wave brings two lanes on and has less to do before its first symbol. With
+// more images than fill the chip's wave slots with a wave to a lane it is the issue of instructions that counts, and for short
+// chunks this one is ahead (us, a wave to a lane against half of one): 4096 images of 12 latents 56 against 38, of 192 108 against 98, of two
+// chunks of 384 350 to 356 against 326 to 345; 2048 58 against 53 (192), 188 to 192 against 176 to 188 (384). With 48 symbols a lane and more the guess
+// pays again where it hits (4096 images of 768 latents 317 against 330, 2048 of two chunks of 1536 623 against 661) and costs little
+// where it misses (631 against 625).
 constexpr int kHalfLanes = 8, kHalfThreads = 32 * kHalfLanes;
 
 __global__ __launch_bounds__(kHalfThreads) void k_rans_decode_half(const CodecTables t, const ChunkTable ct, const int c,
@@ -422,9 +424,7 @@ __global__ __launch_bounds__(kHalfThreads) void k_rans_decode_half(const CodecTa
     const uint32_t* cb = cont + (long long)b * cap;
     const int n = ct.n[c];
     const int k = j < n ? (n - j + kLanes - 1) / kLanes : 0;
-    const int kmax = (n + kLanes - 1) / kLanes;  // the same for every thread: ballots stay convergent
-    int32_t* zc = z + (long long)b * d + ct.z_off[c];
-    const int8_t* ci = codes ? codes + (long long)b * d_codes : nullptr;
+    const int kmax = (n + kLanes - 1) / kLanes;  // the same for every thread, at most 32: ballots stay convergent
     const long long total = cb[0];
     bool bad = total > cap || total < header;
     const int slot = c * kLanes + j;
@@ -435,63 +435,49 @@ __global__ __launch_bounds__(kHalfThreads) void k_rans_decode_half(const CodecTa
     long long pos = header + before;
     unsigned nw = cb[1 + slot];
     if (bad || pos + (long long)nw > total) { bad = true; nw = 0; pos = header; }
-    const uint32_t* w = cb + pos;  // reads stay below pos + nw <= total <= cap
+    // a thread's word and codes, of the one position of the chunk that is its own (a symbol pulls in one word at most); reads stay
+    // below pos + nw <= total <= cap
+    const unsigned w_own = helper < nw ? cb[pos + helper] : 0u;
+    int m = kDefaultM, l = kDefaultL;
+    if (helper < k) codes_of(ct, c, codes ? codes + (long long)b * d_codes : nullptr, helper * kLanes + j, m, l);
+    const int ml_own = (l << 16) | (m & 0xffff);  // mean code in the low half, log-scale code above it
     unsigned used = 0;
-    auto words_at = [&](unsigned i) { return (long long)i + helper < nw ? w[i + helper] : 0u; };
-    unsigned w_cur = words_at(0), w_next = words_at(32);
     unsigned long long X = (unsigned long long)cb[1 + nslots + 2 * slot] |
                            ((unsigned long long)cb[1 + nslots + 2 * slot + 1] << 32);
-    // codes of 32 positions, one to a thread: mean code in the low half, log-scale code above it
-    auto codes_at = [&](int p) {
-        int m = kDefaultM, l = kDefaultL;
-        if (p + helper < k) codes_of(ct, c, ci, (p + helper) * kLanes + j, m, l);
-        return (l << 16) | (m & 0xffff);
-    };
-    int ml_cur = codes_at(0), ml_next = codes_at(32);
     // first round: cut points -8192 + (helper + 1) * 512; the last one is the interval's end, above every slot
     const int cut1 = -kAlphaR + (helper < 31 ? helper + 1 : 31) * 512;
-    int ml = of_half(ml_cur, 0);
+    int ml = of_half(ml_own, 0);
     unsigned inv = s_inv[(ml >> 16) + 128];
     int g1 = cdf(s_sig, cut1, inv);
-    for (int p0 = 0; p0 < kmax; p0 += 32) {
-        const int n_here = kmax - p0 < 32 ? kmax - p0 : 32;
-        int out = 0;  // this thread's latent of the 32
-        for (int i = 0; i < n_here; ++i) {
-            const int ml_after = of_half(i < 31 ? ml_cur : ml_next, (i + 1) & 31);
-            const unsigned word = (unsigned)of_half((int)w_cur, (int)(used & 31));
-            const unsigned inv_after = s_inv[(ml_after >> 16) + 128];
-            const int v = (int)(X & (unsigned long long)(kMass - 1));
-            // G(-8192) = 0 <= v < M = G(8192)
-            unsigned below = (unsigned)(__ballot(helper < 31 && g1 <= v) >> half_shift);
-            int lo = -kAlphaR + __popc(below) * 512;
-            below = (unsigned)(__ballot(helper < 31 && cdf(s_sig, lo + (helper + 1) * 16, inv) <= v) >> half_shift);
-            lo += __popc(below) * 16;
-            const int g3 = cdf(s_sig, lo + (helper < 16 ? helper : 16), inv);
-            below = (unsigned)(__ballot(helper >= 1 && helper < 16 && g3 <= v) >> half_shift);
-            const int idx = __popc(below);
-            const int C = of_half(g3, idx);
-            const int F = of_half(g3, idx + 1) - C;
-            g1 = cdf(s_sig, cut1, inv_after);
-            if (helper == i) out = lo + idx + 2 * (int)(int16_t)(ml & 0xffff);
-            if (p0 + i < k) {
-                X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
-                if (X < kStateLow) {
-                    if (used < nw) {
-                        X = (X << 32) | word;
-                        if ((++used & 31) == 0) {
-                            w_cur = w_next;
-                            w_next = words_at(used + 32);
-                        }
-                    } else { X <<= 32; bad = true; }
-                }
+    int out = 0;  // this thread's latent
+    for (int i = 0; i < kmax; ++i) {
+        const int ml_after = of_half(ml_own, (i + 1) & 31);
+        const unsigned word = (unsigned)of_half((int)w_own, (int)(used & 31));
+        const unsigned inv_after = s_inv[(ml_after >> 16) + 128];
+        const int v = (int)(X & (unsigned long long)(kMass - 1));
+        // G(-8192) = 0 <= v < M = G(8192)
+        unsigned below = (unsigned)(__ballot(helper < 31 && g1 <= v) >> half_shift);
+        int lo = -kAlphaR + __popc(below) * 512;
+        below = (unsigned)(__ballot(helper < 31 && cdf(s_sig, lo + (helper + 1) * 16, inv) <= v) >> half_shift);
+        lo += __popc(below) * 16;
+        const int g3 = cdf(s_sig, lo + (helper < 16 ? helper : 16), inv);
+        below = (unsigned)(__ballot(helper >= 1 && helper < 16 && g3 <= v) >> half_shift);
+        const int idx = __popc(below);
+        const int C = of_half(g3, idx);
+        const int F = of_half(g3, idx + 1) - C;
+        g1 = cdf(s_sig, cut1, inv_after);
+        if (helper == i) out = lo + idx + 2 * (int)(int16_t)(ml & 0xffff);
+        if (i < k) {
+            X = (unsigned long long)F * (X >> kMassBits) + (unsigned long long)(v - C);
+            if (X < kStateLow) {
+                if (used < nw) { X = (X << 32) | word; ++used; }
+                else { X <<= 32; bad = true; }
             }
-            inv = inv_after;
-            ml = ml_after;
         }
-        if (p0 + helper < k) zc[(p0 + helper) * kLanes + j] = out;
-        ml_cur = ml_next;
-        ml_next = codes_at(p0 + 64);
+        inv = inv_after;
+        ml = ml_after;
     }
+    if (helper < k) z[(long long)b * d + ct.z_off[c] + helper * kLanes + j] = out;
     if (X != kStateLow || used != nw) bad = true;
     if (bad && helper == 0) atomicAdd(errs + 2, 1ULL);
 }
@@ -548,7 +534,7 @@ hipError_t launch_rans_decode_chunk(const CodecTables& t, const ChunkTable& ct, 
     if (!table_ok(ct) || c < 0 || c >= ct.n_chunks || !cont || !z || !errs || !t.sig || !t.inv ||
         cap < 1 + 3LL * ct.n_chunks * kLanes)
         return hipErrorInvalidValue;
-    if (rans_decode_by_halves(batch, n_cu))
+    if (rans_decode_by_halves(ct, c, batch, n_cu))
         hipLaunchKernelGGL(k_rans_decode_half, dim3((unsigned)batch * (kLanes / kHalfLanes)), dim3(kHalfThreads), 0, st, t, ct, c, cont, cap,
                            batch, codes, d_codes, z, d, errs);
     else

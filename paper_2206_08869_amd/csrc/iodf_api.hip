@@ -1757,7 +1757,7 @@ int iodf_decode(iodf_ctx* ctx, const uint32_t* words_dev, int64_t cap_words, int
             rc = run_net(ctx, ctx->nets[n0 + m.couplings], batch, +1, ctx->codec_codes, st);
             if (rc != IODF_OK) return rc;
         }
-        PROF_LAUNCH(ctx, st, rans_decode_by_halves(batch, ctx->n_cu) ? CLS_RANS_DECODE_HALF : CLS_RANS_DECODE, 0,
+        PROF_LAUNCH(ctx, st, rans_decode_by_halves(ctx->chunks, lv - 1, batch, ctx->n_cu) ? CLS_RANS_DECODE_HALF : CLS_RANS_DECODE, 0,
                     (long long)batch * 5 * ctx->chunks.n[lv - 1],
                     launch_rans_decode_chunk(t, ctx->chunks, lv - 1, words_dev, cap_words, batch,
                                              head ? ctx->codec_codes : nullptr, ctx->d_codes, ctx->codec_z, ctx->d,
