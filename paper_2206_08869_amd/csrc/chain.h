@@ -89,6 +89,7 @@ struct StripArgs {
     unsigned n_a : 16, n_out : 16;
     unsigned state_c : 16, shift_in : 8, pf_blocks : 8;  // pf_blocks: workgroups per XCD behind the strips that bring pf .. pf + pf_bytes into its L2
     unsigned taps_last : 4, nc_q : 4, n_blk_last : 4, act_unsigned : 1, relu_last : 1, last_fast : 1;
+    unsigned run : 8;  // strips that a workgroup takes one below the other (blocks; see strip_max_run), else 1
     int sign : 2;
 };
 static_assert(sizeof(StripArgs) == 112, "five words of fields");
@@ -101,6 +102,7 @@ constexpr int kStripThreads = 256;
 constexpr int kStripMaxUnits = 8 * 65535;  // strips of a launch: StripArgs::chunk has 16 bits
 constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
 constexpr int kStripMaxTiles = 6;  // tiles_one of the largest block kernel
+constexpr int kStripRunLoads = 5, kStripRunCopies = 3;  // 16-byte pieces a thread moves between two strips of a run: new rows; two rows of x, of t
 constexpr int kStripSizes = 5, kStripIns = 8, kStripLasts = 4;
 extern const StripKernel kStrip433[], kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];
 extern const StripKernel kStripIn[], kStripLast[];  // (nc_t of a first layer's kernel: chunks of the quantised input)
@@ -115,6 +117,8 @@ long long chain_issued_macs(const ChainArgs& a);
 // or one of the ends (nc_t and taps_two unused).
 enum StripPart { STRIP_IN, STRIP_BLOCK, STRIP_LAST };
 const StripKernel* strip_kernel_for(StripPart part, int nc_x, int nc_t, int taps_two, int nc_q, int h, int w, int rows);
+// Strips of `rows` rows that one workgroup of this block kernel can take one below the other: those of an image, or 1.
+int strip_max_run(const StripKernel& k, int h, int w, int rows);
 hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a, hipStream_t stream);
 long long strip_issued_macs(StripPart part, const StripKernel& k, const StripArgs& a);
 hipError_t chain_setup();

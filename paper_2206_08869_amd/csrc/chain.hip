@@ -88,13 +88,26 @@ static long long layer_macs(int waves, int n_blk, int tiles, int taps, int nc) {
     return 32LL * share_tiles(waves, n_blk, tiles) * 32 * n_blk * taps * 32 * nc;
 }
 
+int strip_max_run(const StripKernel& k, int h, int w, int rows) {
+    // the largest kernels of 3x3 blocks hold the loop; it takes strips that are all alike, and rows that are kept move within LDS
+    // without overlapping
+    if (k.taps_two != 9 || k.tiles_one != kStripMaxTiles || rows < 2 || h % rows) return 1;
+    const long long fresh = 2LL * k.nc_x * (w + 2) * rows;
+    const long long kept = 2LL * chain_row_bytes(w, chain_pixel_bytes(k.nc_x)) / 16;  // (nc_t is no larger)
+    if (fresh > kStripRunLoads * kStripThreads || kept > kStripRunCopies * kStripThreads) return 1;
+    return h / rows < 255 ? h / rows : 255;
+}
+
 long long strip_issued_macs(StripPart part, const StripKernel& k, const StripArgs& a) {
     const int waves = kStripThreads / 64;
     long long per = 0;
     if (part == STRIP_IN) per = layer_macs(waves, k.nc_x, k.tiles_two, 9, a.nc_q);
     else if (part == STRIP_LAST) per = layer_macs(waves, a.n_blk_last, k.tiles_two, a.taps_last, k.nc_x);
     else per = layer_macs(waves, k.nc_t, k.tiles_one, 9, k.nc_x) + layer_macs(waves, k.nc_x, k.tiles_two, k.taps_two, k.nc_t);
-    return per * ((a.h + a.rows - 1) / a.rows) * a.batch;
+    const int strips = (a.h + a.rows - 1) / a.rows, runs = (strips + (int)a.run - 1) / (int)a.run;
+    if (a.run == 1) return per * strips * a.batch;
+    const long long more = layer_macs(waves, k.nc_t, k.tiles_two, 9, k.nc_x) + layer_macs(waves, k.nc_x, k.tiles_two, 9, k.nc_t);
+    return (per * runs + more * (strips - runs)) * a.batch;
 }
 
 long long chain_issued_macs(const ChainArgs& a) {
@@ -110,9 +123,10 @@ hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a
     if (a.batch <= 0) return hipSuccess;
     if (!k || !a.params || (part == STRIP_IN ? !a.out || !a.state || !a.idx : !a.in) || (part == STRIP_BLOCK && !a.out) ||
         (part == STRIP_LAST && (!a.state || !a.idx)) ||
-        k != strip_kernel_for(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.h, a.w, a.rows))
+        k != strip_kernel_for(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.h, a.w, a.rows) || a.run < 1 ||
+        (a.run > 1 && (part != STRIP_BLOCK || (int)a.run > strip_max_run(*k, a.h, a.w, a.rows))))
         return hipErrorInvalidValue;
-    const int units = (a.h + a.rows - 1) / a.rows * a.batch;
+    const int units = (a.h + a.rows * a.run - 1) / (a.rows * a.run) * a.batch;
     StripArgs b = a;
     b.chunk = (unsigned short)((units + 7) / 8);
     if (units > kStripMaxUnits) return hipErrorInvalidValue;

@@ -902,6 +902,23 @@ static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w
     return cost[most] >= 1.16 * cost[best] && strips <= 4LL * ctx->n_cu && 3 * best > most ? best : most;
 }
 
+// Strips of a block that a workgroup takes one below the other: the most with which the workgroups, two to a compute unit, still
+// come in rounds that are nine tenths full. Two networks of eight blocks on 32x32 maps, a strip to a workgroup against runs, in us:
+//   full rounds         128 images, runs of 2: 128 inside 763 -> 689 (at 115), 96 638 -> 619, 64 508 -> 500, 64 wide 339 -> 309
+//                       256, 4: 1473 -> 1328, 1181 -> 1086, 913 -> 868, 611 -> 553;  512, 8: 2829 -> 2464, 2256 -> 2058, 1722 -> 1569, 1126 -> 993
+//   nine tenths         232, 4: 1392 -> 1239, 1127 -> 1044, 876 -> 836, 587 -> 527
+//   eight tenths        201, 4: 1245 -> 1204, 1010 -> 990, 793 -> 825, 523 -> 512;  400, 8: 2289 -> 2219, 1804 -> 1811, 1401 -> 1499, 922 -> 921
+//   less                96, 2: 96 inside 501 -> 542, 64 inside 411 -> 454
+static int strip_run(const iodf_ctx* ctx, const StripKernel& k, int h, int w, int rows, int batch) {
+    const long long strips = (h + rows - 1) / rows, slots = 2LL * ctx->n_cu;
+    if (strips * batch <= slots) return 1;
+    for (int run = strip_max_run(k, h, w, rows); run > 1; --run) {
+        const long long groups = batch * ((strips + run - 1) / run), rounds = (groups + slots - 1) / slots;
+        if (10 * strips * batch >= 9 * run * slots * rounds) return run;
+    }
+    return 1;
+}
+
 static StripPlan strip_plan(const iodf_ctx* ctx, const DevNet& N, int batch) {
     StripPlan p = {{0, 0, 0}};
     const DevChain& C = N.chain;
@@ -958,6 +975,7 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     a.n_blk_last = (unsigned char)C.n_blk_last;
     a.taps_last = (unsigned char)C.taps_last;
     a.sign = (signed char)mode_sign;
+    a.run = 1;
     if (last.mode == MODE_CODES) {
         a.codes = codes;
         a.codes_img_stride = ctx->d_codes;
@@ -990,6 +1008,7 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     PROF_LAUNCH_CONV(ctx, st, CLS_STRIP_IN, macs(0), (4LL * N.C_in + xbytes) * px + wbytes(0), strip_issued_macs(STRIP_IN, *k, a), 0,
                      launch_strip(STRIP_IN, k, a, st));
     k = kernel(STRIP_BLOCK);
+    a.run = (unsigned)strip_run(ctx, *k, h, w, p.rows[STRIP_BLOCK], batch);
     for (int b = 0; b < C.blocks; ++b) {
         a.params = block0 + (size_t)b * C.block_bytes;
         if (b + 1 < C.blocks) ahead(a.params + C.block_bytes, C.block_bytes);
@@ -1006,6 +1025,7 @@ static int run_strips(iodf_ctx* ctx, const DevNet& N, int batch, int mode_sign, 
     a.in = ctx->buf[lv][cur];
     const int nl = (int)N.layers.size();
     k = kernel(STRIP_LAST);
+    a.run = 1;
     const int8_t* next_at = nullptr;
     unsigned next_bytes = 0;
     if (next && !next->layers.empty()) net_param_span(ctx, *next, batch, &next_at, &next_bytes);

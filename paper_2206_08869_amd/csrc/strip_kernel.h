@@ -10,6 +10,14 @@
 // 3500 + 3100. Two workgroups share a CU, so that the loads and epilogues of one run under the other's products: a pair
 // takes 39000 (87 us for the 2048 strips of 256 images; 94 us as two launches layer by layer). With a
 // strip or less per CU the length of that chain is what counts, hence strips down to a single row.
+//
+// Runs. Where strips come in several rounds a workgroup takes 2, 4, 8 .. of them one below the other: a later strip keeps the two
+// rows of t and of x that it shares with the one above, so that its first convolution runs over four rows instead of six, and its
+// new rows of x are on their way while the strip above is still multiplied. One block of 256 images of 32x32, profiler attached:
+// 89.8 -> 80.9 us (96 channels inside 73.2 -> 67.1). The matrix cores' part of a pair of strips falls from 23000 to 18400 clocks,
+// the pair from 39000 to 36000: what is left over is epilogues, weights (each fragment is loaded by two waves, 57 bytes a clock)
+// and LDS reads. Dropped: four blocks of 32 filters over four waves in one or both convolutions, half the weights and twice the pixel
+// reads (16 blocks of 256 images 1308 us; 1350 in the first, 1385 in the second, 1352 in both).
 #pragma once
 #include "chain_kernel.h"
 
@@ -19,22 +27,25 @@ namespace {
 
 struct StripGeom {
     int img, r0, r1;
+    int n;  // strips of this workgroup: rows r0 .. r1 and the n - 1 below, alike
 };
 
 __device__ __forceinline__ bool strip_of(const StripArgs& a, StripGeom& g) {
-    const int strips = (a.h + a.rows - 1) / a.rows;
+    const int each = a.rows * a.run, strips = (a.h + each - 1) / each;
     const int unit = (int)(blockIdx.x & 7) * a.chunk + (int)(blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= a.chunk || unit >= strips * a.batch) return false;
     g.img = unit / strips;
-    g.r0 = (unit - g.img * strips) * a.rows;
+    g.r0 = (unit - g.img * strips) * each;
     g.r1 = g.r0 + a.rows < a.h ? g.r0 + a.rows : a.h;
+    g.n = (a.h - g.r0 + a.rows - 1) / a.rows;
+    g.n = g.n < (int)a.run ? g.n : (int)a.run;
     return true;
 }
 
 // Workgroups behind the strips, pf_blocks to an XCD that holds strips (blocks go round the XCDs): what the next launch
 // reads first comes into the L2 while compute units would idle.
 __device__ __forceinline__ void strip_ahead(const StripArgs& a) {
-    const int slot = (int)(blockIdx.x >> 3) - a.chunk, units = (a.h + a.rows - 1) / a.rows * a.batch;
+    const int slot = (int)(blockIdx.x >> 3) - a.chunk, each = a.rows * a.run, units = (a.h + each - 1) / each * a.batch;
     if (slot < 0 || (int)(blockIdx.x & 7) * a.chunk >= units) return;
     touch_lines(a.pf, a.pf_bytes >> 7, slot * kStripThreads + threadIdx.x, a.pf_blocks * kStripThreads);
 }
@@ -53,20 +64,20 @@ __device__ __forceinline__ const int8_t* strip_source(const StripArgs& a, const 
     return a.in + ((size_t)img * (a.h + 2) * W2 + (size_t)(y0 + 1) * W2) * 64 + (size_t)pl * a.plane + (size_t)k * 16;
 }
 
-template <int NCX>
-__device__ __forceinline__ void strip_request(const StripArgs& a, v4i (&v)[kStripLoads], const int img, const int y0, const int y1,
+template <int NCX, int N>
+__device__ __forceinline__ void strip_request(const StripArgs& a, v4i (&v)[N], const int img, const int y0, const int y1,
                                               const int tid) {
     const int total = (a.w + 2) * 4 * (y1 - y0) * (NCX / 2);
 #pragma unroll
-    for (int u = 0; u < kStripLoads; ++u) {
+    for (int u = 0; u < N; ++u) {
         const int t = tid + u * kStripThreads;
         unsigned pl, k;
         v[u] = *(const v4i*)strip_source<NCX>(a, img, y0, y1, t < total ? t : 0, pl, k);
     }
 }
 
-template <int NCX>
-__device__ __forceinline__ void strip_put(const StripArgs& a, const v4i (&v)[kStripLoads], unsigned char* x, const int img,
+template <int NCX, int N>
+__device__ __forceinline__ void strip_put(const StripArgs& a, const v4i (&v)[N], unsigned char* x, const int img,
                                           const int y0, const int y1, const unsigned rp, const int tid) {
     constexpr unsigned ps = chain_pixel_bytes(NCX);
     const unsigned per_row = (a.w + 2) * 4, inv = ((1u << kInvBits) + per_row - 1) / per_row;
@@ -76,13 +87,14 @@ __device__ __forceinline__ void strip_put(const StripArgs& a, const v4i (&v)[kSt
         *(v4i*)(x + row * rp + (c >> 2) * ps + pl * 64 + (c & 3) * 16) = d;
     };
 #pragma unroll
-    for (int u = 0; u < kStripLoads; ++u) {
+    for (int u = 0; u < N; ++u) {
         const int t = tid + u * kStripThreads;
         unsigned pl, k;
         (void)strip_source<NCX>(a, img, y0, y1, t, pl, k);
         if (t < total) put(v[u], pl, k);
     }
-    for (int t = tid + kStripLoads * kStripThreads; t < total; t += kStripThreads) {
+    if constexpr (N < kStripLoads) return;  // (a run's rows: no more than that)
+    for (int t = tid + N * kStripThreads; t < total; t += kStripThreads) {
         unsigned pl, k;
         const v4i d = *(const v4i*)strip_source<NCX>(a, img, y0, y1, t, pl, k);
         put(d, pl, k);
@@ -129,6 +141,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     constexpr unsigned xb = 2 * kChainConstBytes;
     const unsigned tb = xb + rpx * (xe - xo), end = tb + rpt * (te - to);
 
+    constexpr bool RUN = NT2 == 3 && T1 == kStripMaxTiles;  // the kernels that take several strips
     using ST = Share<4, NCT, T1>;
     using SX = Share<4, NCX, T2>;
     const int tblk = wave % ST::WC * ST::TC, xblk = wave % SX::WC * SX::TC;
@@ -221,11 +234,114 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         chain_fetch<SX::TC, NCT, NT2, 0>(wf, p_two, lane16);
     }
     lds_barrier();
-    {
+    // The strip's second convolution; with MORE another strip follows, whose new rows are requested in front of it and whose
+    // first fragments behind it.
+    using SR = Share<4, NCT, T2>;  // a later strip's first convolution
+    static_assert(!RUN || (SR::TC == ST::TC && SR::WC == ST::WC), "the same weights to a wave");
+    v4i xn[kStripRunLoads];
+    auto second = [&](auto more_, const int r0) {
+        constexpr bool MORE = decltype(more_)::value;
+        // (in a run: fragments' addresses out of the lane as if anew, see below)
+        unsigned l16 = lane16;
+        Wave48 f = f48;
+        if constexpr (RUN) asm volatile("" : "+v"(l16), "+v"(f.lane));
+        if constexpr (MORE) {
+            int t = tid;
+            asm volatile("" : "+v"(t));
+            strip_request<NCX>(a, xn, g.img, r0 + a.rows + 2, r0 + 2 * a.rows + 2 < h + 1 ? r0 + 2 * a.rows + 2 : h + 1, t);
+        }
         v16i acc[SX::TC][SX::TP];
         chain_bias(acc, cst0, xblk, half);
-        chain_products<SX::TC, SX::TP, NCT, NT2, false>(acc, wf, lds, t_in, rpt, p_two, p_two, 0, lane16);
+        if constexpr (MORE && F48) {
+            chain_products_then<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, t_in, rpt, p_two, l16, [&](auto i_) {
+                constexpr int i = decltype(i_)::value;
+                wf[i] = *(gv4i)(uniform(par) + f.at[i % 3] + (i / 3) * 2048 + f.lane);
+            });
+        } else {
+            chain_products<SX::TC, SX::TP, NCT, NT2, MORE && carry>(acc, wf, lds, t_in, rpt, p_two, MORE && carry ? p_one : p_two,
+                                                                    SR::TC == 2 ? 9 * NCX * 1024 : 0, l16);
+            if constexpr (MORE) chain_fetch<SR::TC, NCX, 3, carry ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0>(wf, p_one, l16);
+        }
         chain_store<SX::TC, SX::TP, true, true>(acc, lds, x_sc, live_x, cst0, xblk * 32, half, a.act_unsigned, a.out, a.plane, go);
+    };
+    if constexpr (RUN) {
+        const int rows = a.rows, up = g.r0 - xo;  // row r of the strip at r0 lies in x at row r - r0 + up, in t at r - r0 + 1
+        int r0 = g.r0;
+#pragma unroll 1
+        for (int left = g.n; left > 1; --left) {
+            second(std::true_type{}, r0);
+            // addresses out of the lane as if anew: what is needed once a strip must not stay in registers meanwhile
+            int t = tid;
+            asm volatile("" : "+v"(t));
+            r0 += rows;
+            static_for<SX::TP>([&](auto tp_) { go[decltype(tp_)::value] += rows * W2 * 64; });
+            // The last two rows of t, and the last two of x that the next strip reads, become its first. Those of x lie where
+            // its new rows go, so they are read before any wave puts those.
+            auto keep = [&](v4i& v, unsigned at, unsigned rp, int u, auto put_) {
+                const unsigned o = (t + u * kStripThreads) * 16;
+                if (o >= 2 * rp) return;
+                if constexpr (decltype(put_)::value) *(v4i*)(lds + at + o) = v;
+                else v = *(const v4i*)(lds + at + rows * rp + o);
+            };
+            v4i cx[kStripRunCopies], ct[kStripRunCopies];
+            static_for<kStripRunCopies>([&](auto u_) { keep(cx[decltype(u_)::value], xb + up * rpx, rpx, decltype(u_)::value, std::false_type{}); });
+            lds_barrier();
+            static_for<kStripRunCopies>([&](auto u_) { keep(ct[decltype(u_)::value], tb, rpt, decltype(u_)::value, std::false_type{}); });
+            static_for<kStripRunCopies>([&](auto u_) {
+                constexpr int u = decltype(u_)::value;
+                keep(cx[u], xb + up * rpx, rpx, u, std::true_type{});
+                keep(ct[u], tb, rpt, u, std::true_type{});
+            });
+            const bool bottom = r0 + rows == h;
+            strip_put<NCX>(a, xn, lds + xb + (up + 2) * rpx, g.img, r0 + 2, bottom ? h + 1 : r0 + rows + 2, rpx, t);
+            lds_barrier();
+            if (bottom)  // the row below the image
+                for (unsigned o = tb + (rows + 1) * rpt + t * 16; o < tb + (rows + 2) * rpt; o += kStripThreads * 16)
+                    *(v4i*)(lds + o) = v4i{pad, pad, pad, pad};
+            unsigned l16 = lane16;
+            Wave48 f = f48;
+            asm volatile("" : "+v"(l16), "+v"(f.lane));
+            const int y1 = bottom ? rows : rows + 1;  // rows 1 .. y1 of t, counted from r0
+            if constexpr (F48) {
+                unsigned at[T2], out[T2];
+                int live = 0;
+                static_for<T2>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+                    int row, col;
+                    if (strip_pixel(((wave >> 1) * T2 + tp) * 16 + (t & 15), w, inv_w, 1, y1, row, col)) live |= 1 << tp;
+                    at[tp] = xb + (row - 1 + up) * rpx + col * psx + ((t & 63) >> 4) * 16;
+                    out[tp] = tb + (row + 1) * rpt + (col + 1) * pst;
+                });
+                v4i acc[3][T2];
+                const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
+                bias48(acc, cst1, ch);
+                products48<T2, NCX>(acc, wf, lds, at, rpx, uniform(par), f, [&](auto i_) {
+                    constexpr int i = decltype(i_)::value;
+                    if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
+                        wf[i] = *(gv4i)(p_two + i % SX::TC * tcs_two + (i / SX::TC) * 1024 + l16);
+                });
+                store48(acc, lds, out, live, cst1, ch, a.act_unsigned);
+            } else {
+                unsigned at[SR::TP], out[SR::TP];
+                int live = 0;
+                static_for<SR::TP>([&](auto tp_) {
+                    constexpr int tp = decltype(tp_)::value;
+                    int row, col;
+                    if (strip_pixel((wave / SR::WC * SR::TP + tp) * 32 + (t & 31), w, inv_w, 1, y1, row, col)) live |= 1 << tp;
+                    at[tp] = xb + (row - 1 + up) * rpx + col * psx + ((t & 63) >> 5) * 16;
+                    out[tp] = tb + (row + 1) * rpt + (col + 1) * pst;
+                });
+                v16i acc[SR::TC][SR::TP];
+                chain_bias(acc, cst1, tblk, half);
+                chain_products<SR::TC, SR::TP, NCX, 3, carry>(acc, wf, lds, at, rpx, p_one, p_two, tcs_two, l16);
+                chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<SR::TC, NCX, 3>() * SR::TC : 0>(wf, p_two, l16);
+                chain_store<SR::TC, SR::TP, false>(acc, lds, out, live, cst1, tblk * 32, half, a.act_unsigned);
+            }
+            lds_barrier();
+        }
+        second(std::false_type{}, r0);
+    } else {
+        second(std::false_type{}, g.r0);
     }
 }
 

@@ -150,6 +150,25 @@ def test_strip_rows_where_more_strips_pay(H, W, batch, width, keep, k2, rows):
                 batch, rows, width // 32, 2 if keep < 1 or width == 64 else 4)
 
 
+# Strips that a workgroup takes one below the other (256 compute units; full rounds of two workgroups to each): 2, 4 and all 8
+# strips of an image, rounds that are not quite full or too empty, strips of eight and three rows, 19 strips as ten and nine; the same
+# images give the same latents in batches that take a strip to a workgroup.
+@pytest.mark.parametrize("H,W,batch", [(64, 64, 128), (64, 64, 256), (64, 64, 512), (64, 64, 237), (64, 64, 201), (80, 64, 102), (128, 32, 128),
+                                       (114, 72, 256), (48, 80, 150)])
+@pytest.mark.parametrize("width,keep,unsigned", [(128, 1.0, False), (128, 0.7, True), (128, 0.4, False), (64, 1.0, True)])
+def test_runs_of_strips(H, W, batch, width, keep, unsigned):
+    import torch
+    cfg = FlowConfig("runs", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=54, block_k2=3, act_unsigned=unsigned)
+    print("runs of strips", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, H, W), generator=torch.Generator().manual_seed(9), dtype=torch.uint8).cuda()
+    z = flow.forward(x)[0]
+    for i in range(0, batch, 16):
+        assert torch.equal(z[i:i + 16], flow.forward(x[i:i + 16].contiguous())[0])
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 # 65 to 96 of 128 channels kept inside: blocks of 48 filters to a wave over four tiles and more, three waves of 32 below
 # (64, 80 and 128 pixel maps, 130 to 256 as one launch; strips at every tile count); 97 take the kernels of 128
 @pytest.mark.parametrize("H,W,batch,kernel", [(16, 16, 1, "k_chain"), (16, 20, 3, "k_chain"), (16, 32, 2, "k_chain"), (20, 26, 65, "k_chain"),
