@@ -1215,10 +1215,13 @@ const TileCfg kTiles[] = {
     TileCfg{128, 128, (size_t)9 * (128 + 128) * KT + 2048,
             {conv_igemm_lean<128, 128, 4, 2, 1, EPI_ANY>, conv_igemm_lean<128, 128, 4, 2, 1, EPI_FAST>, conv_igemm_lean<128, 128, 4, 2, 1, EPI_FAST_RELU>},
             512, "conv_igemm_lean<128,128,4,2,1>"},
+    // twice the 128x128 tile, one to a CU (see conv_pick_tile)
+    IODF_TILE(128, 256, 2, 4, 6),
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 constexpr int kPair256 = 5, kPair128 = 6;  // the two-workgroups-per-CU halves of tiles 0 and 1
 constexpr int kSmall = 4, kSmallLean = 7, kMid = 2, kMidLean = 8;  // the 64x64 and 128x128 tiles and their lean forms
+constexpr int kMidTwice = 9;
 
 // Persistent form of tile 0 (see conv_igemm_persist), by fast epilogue, and its LDS bytes.
 void (*const kPersist[3])(const ConvArgs) = {nullptr, conv_igemm_persist<256, 256, 2, 4, 4, EPI_FAST>,
@@ -1369,11 +1372,28 @@ int conv_pick_tile(const ConvArgs& a) {
     const long long nkt = (long long)a.taps * (a.cin_pad / KT);
     const bool fits = nkt * a.n_pad * KT < (1LL << 32) && (long long)(a.cin_pad / KT) * a.in_plane < (1LL << 32);
     if (!fits || (t != kSmall && t != kMid) || conv_pick_splits(a, t) != 1) return t;
-    if (t == kSmall) return kSmallLean;
+    // Tiles of the fullest compute unit (whole pixel blocks go to an XCD, see conv_igemm).
+    auto fullest = [&](int bc, int bp) {
+        const long long per_xcd = ((a.npix + bp - 1) / bp + 7) / 8 * ((a.n_store + bc - 1) / bc), cus = std::max(1, a.n_cu / 8);
+        return (per_xcd + cus - 1) / cus;
+    };
+    // A compute unit with three or four 64x64 tiles takes longer than one with a 128x128 tile, which fetches half the bytes for a
+    // product; with two of them it is the shorter one. 128 to 2048 input channels, 128 to 512 filters, 1x1 and 3x3, time of the
+    // 128x128 tile over that of the 64x64 ones: 0.76 to 0.82 with three, 0.67 to 0.72 with four, 1.04 to 1.13 with two.
+    if (t == kSmall) return a.n_pad % 128 == 0 && fullest(64, 64) > 2 && fullest(128, 128) == 1 ? kMidLean : kSmallLean;
     // the lean 128x128 form fills the LDS of a CU; with more tiles than CUs the four-stage form, two to a CU, is
     // the better one (a second workgroup's loads and epilogue run under the first one's matrix work)
     const long long blocks = (long long)((a.npix + 127) / 128) * ((a.n_store + 127) / 128);
-    return blocks <= a.n_cu ? kMidLean : t;
+    if (blocks <= a.n_cu) return kMidLean;
+    // and twice the tile is better still where it halves a compute unit's number of tiles: four as two 128x256 tiles side by side 0.81 to
+    // 0.91 of the time (64 to 2304 input channels, 128 to 512 filters); two as one, on eight waves, 0.90 to 0.93 for 3x3 layers of
+    // 256 channels on (0.96 to 1.01 below). 1x1 layers: 0.95 to 1.04 launched back to back, from eight k-tiles on ahead within whole
+    // calls (cfg3 inverse at batch 50 with them 6770 us, with the 3x3 layers alone 6855, with neither 7045); with one block of
+    // filters 0.90 to 1.10. Whole calls, both rules: cfg3 at batch 28 5472 -> 4725 us, at 100 11436 -> 9719, cfg4 at 28 12556 -> 10906,
+    // mid_dense at 200 913 -> 794, wide_resnet at 50 585 -> 499.
+    const long long twice = fullest(128, 256);
+    if (2 * twice > fullest(128, 128)) return t;
+    return twice > 1 ? kPair128 : (a.taps == 9 ? nkt > 18 : nkt >= 8 && a.n_store > 128) ? kMidTwice : t;
 }
 
 // K splits for a layer whose tiles alone cannot fill the chip (only the general epilogue

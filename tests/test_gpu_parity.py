@@ -324,6 +324,37 @@ def test_layers_over_few_pixels_choose_their_tile(batch, hidden, last):
     flow.close()
 
 
+# Dense layers of 256 filters on 16x16 maps (256 compute units): tiles of the fullest compute unit decide between 64x64 and 128x128
+# pixels, and between the latter and twice its pixels; the same images give the same latents in batches on smaller tiles.
+@pytest.mark.parametrize("batch,tile", [
+    (32, "lean<64,64,2,2,2>"),       # two of 64x64
+    (33, "lean<128,128,4,2,1>"),     # three; one of 128x128
+    (63, "lean<128,128,4,2,1>"),     # four
+    (65, "<128,256,2,4,6>"),         # two of 128x128, one of 128x256
+    (128, "<128,256,2,4,6>"),
+    (129, "<128,128,4,2,4>"),        # three; two of 128x256
+    (200, "<128,256,2,2,3>"),        # four; two of 128x256
+])
+def test_dense_layers_choose_their_tile(batch, tile):
+    import torch
+    from synth import make_blob
+    from synth.configs import DENSE, FlowConfig
+    cfg = FlowConfig("tiles", 32, 32, batch, 1, 1, DENSE, 256, 3, False, seed_id=56)
+    print("tiles", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, 32, 32), generator=torch.Generator().manual_seed(3), dtype=torch.uint8).cuda()
+    flow.profile_begin(64)
+    z = flow.forward(x)[0]
+    torch.cuda.synchronize()
+    ran = {k["name"] for k in flow.profile_end()}
+    sep = "_" if tile.startswith("lean") else ""
+    assert {"conv_igemm%s%s %s" % (sep, tile, k) for k in ("1x1", "3x3")} <= ran, ran
+    for i in range(0, batch, 7):
+        assert torch.equal(z[i:i + 7], flow.forward(x[i:i + 7].contiguous())[0])
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w, timeline=False):
     import oracle
     rng = np.random.default_rng(c_in * 1000 + c_out)
