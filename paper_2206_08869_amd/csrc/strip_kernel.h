@@ -120,6 +120,15 @@ __device__ __forceinline__ bool strip_pixel(int m, int w, unsigned inv_w, int y0
     return live;
 }
 
+// Two workgroups share a compute unit and its waves' turns: products go before the other one's epilogue, loads and copies, which
+// fill the gaps they leave (16 blocks of 256 images of 32x32: 1358 -> 1336 us, 96 channels inside 1092 -> 1078, 64 the same; one
+// workgroup before the other throughout 1364, epilogues before products 1362. In every kernel of chain_kernel.h, whole networks
+// among them, the latter lose: cfg2 forward at batch 64 175.4 -> 176.2).
+template <bool ON, int P>
+__device__ __forceinline__ void wave_priority() {
+    if constexpr (ON) __builtin_amdgcn_s_setprio(P);
+}
+
 // One residual block. T1, T2: tiles of the first and second convolution.
 template <int NCX, int NCT, int NT2, int T1, int T2>
 __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArgs a) {
@@ -209,6 +218,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         v4i acc[3][TP48];
         const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
         bias48(acc, cst1, ch);
+        wave_priority<RUN, 1>();
         products48<TP48, NCX>(acc, wf, lds, x_48, rpx, uniform(par), f48, [&](auto i_) {
             constexpr int i = decltype(i_)::value;
             if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
@@ -223,12 +233,15 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
             if (pixel48(tp, l16, row, col)) live_48 |= 1 << tp;
             t_48[tp] = tb + (row - to) * rpt + (col + 1) * pst;
         });
+        wave_priority<RUN, 0>();
         store48(acc, lds, t_48, live_48, cst1, ch, a.act_unsigned);
     } else if (one) {
         v16i acc[ST::TC][ST::TP];
         chain_bias(acc, cst1, tblk, half);
+        wave_priority<RUN, 1>();
         chain_products<ST::TC, ST::TP, NCX, 3, carry>(acc, wf, lds, x_in, rpx, p_one, p_two, tcs_two, lane16);
         chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0>(wf, p_two, lane16);
+        wave_priority<RUN, 0>();
         chain_store<ST::TC, ST::TP, false>(acc, lds, t_out, live_t, cst1, tblk * 32, half, a.act_unsigned);
     } else {
         chain_fetch<SX::TC, NCT, NT2, 0>(wf, p_two, lane16);
@@ -253,15 +266,18 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         v16i acc[SX::TC][SX::TP];
         chain_bias(acc, cst0, xblk, half);
         if constexpr (MORE && F48) {
+            wave_priority<RUN, 1>();
             chain_products_then<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, t_in, rpt, p_two, l16, [&](auto i_) {
                 constexpr int i = decltype(i_)::value;
                 wf[i] = *(gv4i)(uniform(par) + f.at[i % 3] + (i / 3) * 2048 + f.lane);
             });
         } else {
+            wave_priority<RUN, 1>();
             chain_products<SX::TC, SX::TP, NCT, NT2, MORE && carry>(acc, wf, lds, t_in, rpt, p_two, MORE && carry ? p_one : p_two,
                                                                     SR::TC == 2 ? 9 * NCX * 1024 : 0, l16);
             if constexpr (MORE) chain_fetch<SR::TC, NCX, 3, carry ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0>(wf, p_one, l16);
         }
+        wave_priority<RUN, 0>();
         chain_store<SX::TC, SX::TP, true, true>(acc, lds, x_sc, live_x, cst0, xblk * 32, half, a.act_unsigned, a.out, a.plane, go);
     };
     if constexpr (RUN) {
@@ -315,11 +331,13 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
                 v4i acc[3][T2];
                 const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
                 bias48(acc, cst1, ch);
+                wave_priority<RUN, 1>();
                 products48<T2, NCX>(acc, wf, lds, at, rpx, uniform(par), f, [&](auto i_) {
                     constexpr int i = decltype(i_)::value;
                     if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
                         wf[i] = *(gv4i)(p_two + i % SX::TC * tcs_two + (i / SX::TC) * 1024 + l16);
                 });
+                wave_priority<RUN, 0>();
                 store48(acc, lds, out, live, cst1, ch, a.act_unsigned);
             } else {
                 unsigned at[SR::TP], out[SR::TP];
@@ -333,8 +351,10 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
                 });
                 v16i acc[SR::TC][SR::TP];
                 chain_bias(acc, cst1, tblk, half);
+                wave_priority<RUN, 1>();
                 chain_products<SR::TC, SR::TP, NCX, 3, carry>(acc, wf, lds, at, rpx, p_one, p_two, tcs_two, l16);
                 chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<SR::TC, NCX, 3>() * SR::TC : 0>(wf, p_two, l16);
+                wave_priority<RUN, 0>();
                 chain_store<SR::TC, SR::TP, false>(acc, lds, out, live, cst1, tblk * 32, half, a.act_unsigned);
             }
             lds_barrier();
