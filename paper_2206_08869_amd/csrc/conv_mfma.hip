@@ -1380,7 +1380,9 @@ int conv_pick_tile(const ConvArgs& a) {
     // A compute unit with three or four 64x64 tiles takes longer than one with a 128x128 tile, which fetches half the bytes for a
     // product; with two of them it is the shorter one. 128 to 2048 input channels, 128 to 512 filters, 1x1 and 3x3, time of the
     // 128x128 tile over that of the 64x64 ones: 0.76 to 0.82 with three, 0.67 to 0.72 with four, 1.04 to 1.13 with two.
-    if (t == kSmall) return a.n_pad % 128 == 0 && fullest(64, 64) > 2 && fullest(128, 128) == 1 ? kMidLean : kSmallLean;
+    // (No larger tile where the launch would split its reduction with it.)
+    auto unsplit = [&](int tile) { return conv_pick_splits(a, tile) == 1; };
+    if (t == kSmall) return a.n_pad % 128 == 0 && fullest(64, 64) > 2 && fullest(128, 128) == 1 && unsplit(kMidLean) ? kMidLean : kSmallLean;
     // the lean 128x128 form fills the LDS of a CU; with more tiles than CUs the four-stage form, two to a CU, is
     // the better one (a second workgroup's loads and epilogue run under the first one's matrix work)
     const long long blocks = (long long)((a.npix + 127) / 128) * ((a.n_store + 127) / 128);
@@ -1392,7 +1394,7 @@ int conv_pick_tile(const ConvArgs& a) {
     // filters 0.90 to 1.10. Whole calls, both rules: cfg3 at batch 28 5472 -> 4725 us, at 100 11436 -> 9719, cfg4 at 28 12556 -> 10906,
     // mid_dense at 200 913 -> 794, wide_resnet at 50 585 -> 499.
     const long long twice = fullest(128, 256);
-    if (2 * twice > fullest(128, 128)) return t;
+    if (2 * twice > fullest(128, 128) || !unsplit(twice > 1 ? kPair128 : kMidTwice)) return t;
     return twice > 1 ? kPair128 : (a.taps == 9 ? nkt > 18 : nkt >= 8 && a.n_store > 128) ? kMidTwice : t;
 }
 
