@@ -355,6 +355,28 @@ def test_dense_layers_choose_their_tile(batch, tile):
     flow.close()
 
 
+def test_long_last_layers_over_many_pixels():
+    """Head codes of 96 filters, 1x1 over 2048 channels (level 4, 2x2 maps): on 64x64 tiles the reduction is not split, on 128x128 ones
+    it would be, so the launch keeps the former although a compute unit gets three of them."""
+    import torch
+    from synth import make_blob
+    from synth.configs import PLAIN, FlowConfig
+    from synth.model import pack_blob, parse_blob
+    batch = 4224
+    cfg = FlowConfig("long_last", 32, 32, batch, 5, 1, PLAIN, 2048, 0, True, seed_id=57)
+    m = parse_blob(make_blob(cfg).copy())
+    for net in m["nets"]:
+        net["layers"][-1]["W"] = np.ascontiguousarray(net["layers"][-1]["W"][:, :, 1:2, 1:2])
+    flow = iodf.Flow(pack_blob(m), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, 32, 32), generator=torch.Generator().manual_seed(4), dtype=torch.uint8).cuda()
+    z, codes = flow.forward(x)
+    for part in (slice(0, 40), slice(2000, 2040), slice(batch - 40, batch)):
+        z_few, codes_few = flow.forward(x[part].contiguous())
+        assert torch.equal(z[part], z_few) and torch.equal(codes[part], codes_few)
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 def _check_single_convolution(c_in, c_out, k, relu, shift_lo, b, h, w, timeline=False):
     import oracle
     rng = np.random.default_rng(c_in * 1000 + c_out)
