@@ -120,10 +120,13 @@ __device__ __forceinline__ bool strip_pixel(int m, int w, unsigned inv_w, int y0
     return live;
 }
 
-// Two workgroups share a compute unit and its waves' turns: products go before the other one's epilogue, loads and copies, which
-// fill the gaps they leave (16 blocks of 256 images of 32x32: 1358 -> 1336 us, 96 channels inside 1092 -> 1078, 64 the same; one
-// workgroup before the other throughout 1364, epilogues before products 1362. In every kernel of chain_kernel.h, whole networks
-// among them, the latter lose: cfg2 forward at batch 64 175.4 -> 176.2).
+// Two workgroups share a compute unit and its waves' turns: the first convolution's products go before all that the other one
+// does, which fills the gaps they leave and keeps the two out of step. 16 blocks of 64, 100 and 256 images of 32x32, without
+// priorities / both convolutions' products first / the first one's only, in us: 128 inside 427, 744, 1358 / 425, 719, 1338 /
+// 406, 692, 1338; 64 inside 281, 485, 875 / 284, 488, 878 / 269, 461, 841. 64 wide, where a third workgroup fits, the second
+// one's products go first as well (205 images of 40x32 617, without 637). One workgroup before the other throughout 1364 at 256
+// images, epilogues before products 1362. In every kernel of chain_kernel.h, whole networks among them, the latter lose: cfg2
+// forward at batch 64 175.4 -> 176.2.
 template <bool ON, int P>
 __device__ __forceinline__ void wave_priority() {
     if constexpr (ON) __builtin_amdgcn_s_setprio(P);
@@ -151,6 +154,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     const unsigned tb = xb + rpx * (xe - xo), end = tb + rpt * (te - to);
 
     constexpr bool RUN = NT2 == 3 && T1 == kStripMaxTiles;  // the kernels that take several strips
+    constexpr bool BOTH = RUN && NCX == 2;  // (see wave_priority)
     using ST = Share<4, NCT, T1>;
     using SX = Share<4, NCX, T2>;
     const int tblk = wave % ST::WC * ST::TC, xblk = wave % SX::WC * SX::TC;
@@ -266,18 +270,18 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         v16i acc[SX::TC][SX::TP];
         chain_bias(acc, cst0, xblk, half);
         if constexpr (MORE && F48) {
-            wave_priority<RUN, 1>();
+            wave_priority<BOTH, 1>();
             chain_products_then<SX::TC, SX::TP, NCT, NT2>(acc, wf, lds, t_in, rpt, p_two, l16, [&](auto i_) {
                 constexpr int i = decltype(i_)::value;
                 wf[i] = *(gv4i)(uniform(par) + f.at[i % 3] + (i / 3) * 2048 + f.lane);
             });
         } else {
-            wave_priority<RUN, 1>();
+            wave_priority<BOTH, 1>();
             chain_products<SX::TC, SX::TP, NCT, NT2, MORE && carry>(acc, wf, lds, t_in, rpt, p_two, MORE && carry ? p_one : p_two,
                                                                     SR::TC == 2 ? 9 * NCX * 1024 : 0, l16);
             if constexpr (MORE) chain_fetch<SR::TC, NCX, 3, carry ? chain_depth<SX::TC, NCT, NT2>() * SX::TC : 0>(wf, p_one, l16);
         }
-        wave_priority<RUN, 0>();
+        wave_priority<BOTH, 0>();
         chain_store<SX::TC, SX::TP, true, true>(acc, lds, x_sc, live_x, cst0, xblk * 32, half, a.act_unsigned, a.out, a.plane, go);
     };
     if constexpr (RUN) {
