@@ -97,11 +97,14 @@ struct StripKernel {
     int nc_x, nc_t, taps_two;
     int tiles_one, tiles_two;  // 32-pixel tiles of the block's first and second convolution (first and last layer: the same)
     void (*kern)(const StripArgs);
+    void (*kern_run)(const StripArgs);  // blocks: the form that takes several strips, or nullptr
 };
 constexpr int kStripThreads = 256;
 constexpr int kStripMaxUnits = 8 * 65535;  // strips of a launch: StripArgs::chunk has 16 bits
 constexpr size_t kStripMaxLds = 80 * 1024;  // two workgroups to a CU
 constexpr int kStripMaxTiles = 6;  // tiles_one of the largest block kernel
+// The largest kernel of 3x3 blocks, the one that launches of several rounds of strips take.
+__host__ __device__ constexpr bool strip_largest(int taps_two, int tiles_one) { return taps_two == 9 && tiles_one == kStripMaxTiles; }
 constexpr int kStripRunLoads = 5, kStripRunCopies = 3;  // 16-byte pieces a thread moves between two strips of a run: new rows; two rows of x, of t
 constexpr int kStripSizes = 5, kStripIns = 8, kStripLasts = 4;
 extern const StripKernel kStrip433[], kStrip443[], kStrip423[], kStrip223[], kStrip441[], kStrip421[], kStrip221[];

@@ -53,10 +53,11 @@ hipError_t chain_setup() {
             if (e != hipSuccess) return e;
         }
     for (const StripKernel* t : kStrips)
-        for (int i = 0; i < kStripSizes; ++i) {
-            const hipError_t e = hipFuncSetAttribute((const void*)t[i].kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
-            if (e != hipSuccess) return e;
-        }
+        for (int i = 0; i < kStripSizes; ++i)
+            for (auto kern : {t[i].kern, t[i].kern_run}) {
+                const hipError_t e = kern ? hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds) : hipSuccess;
+                if (e != hipSuccess) return e;
+            }
     for (int i = 0; i < kStripIns + kStripLasts; ++i) {
         const StripKernel& k = i < kStripIns ? kStripIn[i] : kStripLast[i - kStripIns];
         const hipError_t e = hipFuncSetAttribute((const void*)k.kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kStripMaxLds);
@@ -89,9 +90,8 @@ static long long layer_macs(int waves, int n_blk, int tiles, int taps, int nc) {
 }
 
 int strip_max_run(const StripKernel& k, int h, int w, int rows) {
-    // the largest kernels of 3x3 blocks hold the loop; it takes strips that are all alike, and rows that are kept move within LDS
-    // without overlapping
-    if (k.taps_two != 9 || k.tiles_one != kStripMaxTiles || rows < 2 || h % rows) return 1;
+    // the loop takes strips that are all alike, and rows that are kept move within LDS without overlapping
+    if (!k.kern_run || rows < 2 || h % rows) return 1;
     const long long fresh = 2LL * k.nc_x * (w + 2) * rows;
     const long long kept = 2LL * chain_row_bytes(w, chain_pixel_bytes(k.nc_x)) / 16;  // (nc_t is no larger)
     if (fresh > kStripRunLoads * kStripThreads || kept > kStripRunCopies * kStripThreads) return 1;
@@ -130,7 +130,7 @@ hipError_t launch_strip(StripPart part, const StripKernel* k, const StripArgs& a
     StripArgs b = a;
     b.chunk = (unsigned short)((units + 7) / 8);
     if (units > kStripMaxUnits) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k->kern, dim3(8 * (b.chunk + b.pf_blocks)), dim3(kStripThreads),
+    hipLaunchKernelGGL(a.run > 1 ? k->kern_run : k->kern, dim3(8 * (b.chunk + b.pf_blocks)), dim3(kStripThreads),
                        strip_lds_bytes(part, k->nc_x, k->nc_t, k->taps_two, a.nc_q, a.w, a.rows), st, b);
     return hipGetLastError();
 }

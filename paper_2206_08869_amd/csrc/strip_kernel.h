@@ -132,8 +132,12 @@ __device__ __forceinline__ void wave_priority() {
     if constexpr (ON) __builtin_amdgcn_s_setprio(P);
 }
 
-// One residual block. T1, T2: tiles of the first and second convolution.
-template <int NCX, int NCT, int NT2, int T1, int T2>
+__device__ __forceinline__ void in_register(unsigned& v) { asm volatile("" : "+v"(v)); }
+
+// One residual block. T1, T2: tiles of the first and second convolution. RUN: a.run strips one below the other, else one. The loop
+// costs registers (64 inside 162 -> 242, 64 wide 139 -> 181), and with them the third workgroup that LDS has room for, so launches
+// of one strip to a workgroup have kernels without it: 16 blocks of 160 and 201 images of 32x32, 64 wide, 434 -> 402 and 576 -> 536 us.
+template <int NCX, int NCT, int NT2, int T1, int T2, bool RUN>
 __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -153,8 +157,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
     constexpr unsigned xb = 2 * kChainConstBytes;
     const unsigned tb = xb + rpx * (xe - xo), end = tb + rpt * (te - to);
 
-    constexpr bool RUN = NT2 == 3 && T1 == kStripMaxTiles;  // the kernels that take several strips
-    constexpr bool BOTH = RUN && NCX == 2;  // (see wave_priority)
+    constexpr bool PRIO = strip_largest(NT2 * NT2, T1), BOTH = PRIO && NCX == 2;  // (see wave_priority)
     using ST = Share<4, NCT, T1>;
     using SX = Share<4, NCX, T2>;
     const int tblk = wave % ST::WC * ST::TC, xblk = wave % SX::WC * SX::TC;
@@ -210,6 +213,17 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         x_sc[tp] = xb + (row - xo) * rpx + (col + 1) * psx;
         go[tp] = (unsigned)(((g.img * (h + 2) + row + 1) * W2 + col + 1) * 64);
     });
+    if constexpr (F48 && !RUN) {
+        // worked out here, while the rows are on their way, and not between the products, where the compiler would put them
+        // (16 blocks of 64 and 201 images of 32x32 343 -> 334 and 1043 -> 1019 us)
+        static_for<TP48>([&](auto tp_) { in_register(x_48[decltype(tp_)::value]); });
+        static_for<SX::TP>([&](auto tp_) {
+            constexpr int tp = decltype(tp_)::value;
+            in_register(t_in[tp]);
+            in_register(x_sc[tp]);
+            in_register(go[tp]);
+        });
+    }
     strip_put<NCX>(a, xv, lds + xb, g.img, xo, xe, rpx, tid);
     strip_put_consts(lds, c1, 1, tid);
     strip_put_consts(lds, c0, 0, tid);
@@ -222,7 +236,7 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
         v4i acc[3][TP48];
         const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
         bias48(acc, cst1, ch);
-        wave_priority<RUN, 1>();
+        wave_priority<PRIO, 1>();
         products48<TP48, NCX>(acc, wf, lds, x_48, rpx, uniform(par), f48, [&](auto i_) {
             constexpr int i = decltype(i_)::value;
             if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
@@ -237,15 +251,15 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
             if (pixel48(tp, l16, row, col)) live_48 |= 1 << tp;
             t_48[tp] = tb + (row - to) * rpt + (col + 1) * pst;
         });
-        wave_priority<RUN, 0>();
+        wave_priority<PRIO, 0>();
         store48(acc, lds, t_48, live_48, cst1, ch, a.act_unsigned);
     } else if (one) {
         v16i acc[ST::TC][ST::TP];
         chain_bias(acc, cst1, tblk, half);
-        wave_priority<RUN, 1>();
+        wave_priority<PRIO, 1>();
         chain_products<ST::TC, ST::TP, NCX, 3, carry>(acc, wf, lds, x_in, rpx, p_one, p_two, tcs_two, lane16);
         chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<ST::TC, NCX, 3>() * ST::TC : 0>(wf, p_two, lane16);
-        wave_priority<RUN, 0>();
+        wave_priority<PRIO, 0>();
         chain_store<ST::TC, ST::TP, false>(acc, lds, t_out, live_t, cst1, tblk * 32, half, a.act_unsigned);
     } else {
         chain_fetch<SX::TC, NCT, NT2, 0>(wf, p_two, lane16);
@@ -335,13 +349,13 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
                 v4i acc[3][T2];
                 const int ch = (wave & 1) * 48 + (lane >> 4) * 4;
                 bias48(acc, cst1, ch);
-                wave_priority<RUN, 1>();
+                wave_priority<PRIO, 1>();
                 products48<T2, NCX>(acc, wf, lds, at, rpx, uniform(par), f, [&](auto i_) {
                     constexpr int i = decltype(i_)::value;
                     if constexpr (i < chain_depth<SX::TC, NCT, NT2>() * SX::TC)
                         wf[i] = *(gv4i)(p_two + i % SX::TC * tcs_two + (i / SX::TC) * 1024 + l16);
                 });
-                wave_priority<RUN, 0>();
+                wave_priority<PRIO, 0>();
                 store48(acc, lds, out, live, cst1, ch, a.act_unsigned);
             } else {
                 unsigned at[SR::TP], out[SR::TP];
@@ -355,10 +369,10 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
                 });
                 v16i acc[SR::TC][SR::TP];
                 chain_bias(acc, cst1, tblk, half);
-                wave_priority<RUN, 1>();
+                wave_priority<PRIO, 1>();
                 chain_products<SR::TC, SR::TP, NCX, 3, carry>(acc, wf, lds, at, rpx, p_one, p_two, tcs_two, l16);
                 chain_fetch<SX::TC, NCT, NT2, carry ? chain_depth<SR::TC, NCX, 3>() * SR::TC : 0>(wf, p_two, l16);
-                wave_priority<RUN, 0>();
+                wave_priority<PRIO, 0>();
                 chain_store<SR::TC, SR::TP, false>(acc, lds, out, live, cst1, tblk * 32, half, a.act_unsigned);
             }
             lds_barrier();
@@ -480,7 +494,9 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_last(const StripArgs
 
 template <int NCX, int NCT, int NT2, int T1, int T2>
 constexpr StripKernel strip_kernel() {
-    return StripKernel{NCX, NCT, NT2 * NT2, T1, T2, k_strip_block<NCX, NCT, NT2, T1, T2>};
+    StripKernel k{NCX, NCT, NT2 * NT2, T1, T2, k_strip_block<NCX, NCT, NT2, T1, T2, false>, nullptr};
+    if constexpr (strip_largest(NT2 * NT2, T1)) k.kern_run = k_strip_block<NCX, NCT, NT2, T1, T2, true>;
+    return k;
 }
 // Every wave's work is fixed by the tiles a kernel is compiled for, so the small ones are worth their own.
 #define IODF_STRIP_TABLE(NAME, NCX, NCT, NT2)                                                                       \
