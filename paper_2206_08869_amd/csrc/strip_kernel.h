@@ -135,8 +135,9 @@ __device__ __forceinline__ void wave_priority() {
 __device__ __forceinline__ void in_register(unsigned& v) { asm volatile("" : "+v"(v)); }
 
 // One residual block. T1, T2: tiles of the first and second convolution. RUN: a.run strips one below the other, else one. The loop
-// costs registers (64 inside 162 -> 242, 64 wide 139 -> 181), and with them the third workgroup that LDS has room for, so launches
-// of one strip to a workgroup have kernels without it: 16 blocks of 160 and 201 images of 32x32, 64 wide, 434 -> 402 and 576 -> 536 us.
+// costs registers (64 inside 162 -> 218, 64 wide 139 -> 157), and 64 inside with them the third workgroup that LDS has room for on
+// 16 and 24 columns, so launches of one strip to a workgroup have kernels without it: 16 blocks of 300 images of 32x16 643 -> 600 us;
+// 64 wide, when the loop took 181, 160 and 201 images of 32x32 434 -> 402 and 576 -> 536.
 template <int NCX, int NCT, int NT2, int T1, int T2, bool RUN>
 __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArgs a) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -310,12 +311,13 @@ __global__ __launch_bounds__(kStripThreads, 2) void k_strip_block(const StripArg
             r0 += rows;
             static_for<SX::TP>([&](auto tp_) { go[decltype(tp_)::value] += rows * W2 * 64; });
             // The last two rows of t, and the last two of x that the next strip reads, become its first. Those of x lie where
-            // its new rows go, so they are read before any wave puts those.
+            // its new rows go, so they are read before any wave puts those. (Read without a branch: with one, 96 channels inside
+            // spilled 14 registers; 16 blocks of 128 and 256 images of 32x32 622 -> 601 and 1103 -> 1069 us.)
             auto keep = [&](v4i& v, unsigned at, unsigned rp, int u, auto put_) {
                 const unsigned o = (t + u * kStripThreads) * 16;
-                if (o >= 2 * rp) return;
-                if constexpr (decltype(put_)::value) *(v4i*)(lds + at + o) = v;
-                else v = *(const v4i*)(lds + at + rows * rp + o);
+                const bool in = o < 2 * rp;
+                if constexpr (!decltype(put_)::value) v = *(const v4i*)(lds + at + rows * rp + (in ? o : 0));
+                else if (in) *(v4i*)(lds + at + o) = v;
             };
             v4i cx[kStripRunCopies], ct[kStripRunCopies];
             static_for<kStripRunCopies>([&](auto u_) { keep(cx[decltype(u_)::value], xb + up * rpx, rpx, decltype(u_)::value, std::false_type{}); });

@@ -56,3 +56,9 @@ def test_one_strip_kernels_leave_room_for_a_third_workgroup():
     blocks = _strip_blocks()
     for kind in ((4, 2, 3, 6, 4, 0), (2, 2, 3, 6, 4, 0)):
         assert 512 // (-(-blocks[kind][".vgpr_count"] // 8) * 8) >= 3, blocks[kind]
+
+
+def test_strip_kernels_use_no_scratch():
+    """A register that spills goes through memory in the middle of the products' loops."""
+    for kind, k in _strip_blocks().items():
+        assert k[".private_segment_fixed_size"] == k[".vgpr_spill_count"] == k[".sgpr_spill_count"] == 0, (kind, k[".vgpr_spill_count"])
