@@ -1390,12 +1390,14 @@ int conv_pick_tile(const ConvArgs& a) {
     // and twice the tile is better still where it halves a compute unit's number of tiles: four as two 128x256 tiles side by side 0.81 to
     // 0.91 of the time (64 to 2304 input channels, 128 to 512 filters); two as one, on eight waves, 0.90 to 0.93 for 3x3 layers of
     // 256 channels on (0.96 to 1.01 below). 1x1 layers: 0.95 to 1.04 launched back to back, from eight k-tiles on ahead within whole
-    // calls (cfg3 inverse at batch 50 with them 6770 us, with the 3x3 layers alone 6855, with neither 7045); with one block of
-    // filters 0.90 to 1.10. Whole calls, both rules: cfg3 at batch 28 5472 -> 4725 us, at 100 11436 -> 9719, cfg4 at 28 12556 -> 10906,
+    // calls (cfg3 inverse at batch 50 with them 6770 us, with the 3x3 layers alone 6855, with neither 7045; at 64 7369, 7491, 7768; at
+    // 36 6645, 6604, 6703); with one block of filters 0.90 to 1.10; a last layer that leaves its 32-bit sums, four times the bytes, 1.18
+    // to 1.22 (216 filters, 100 images of 16x16, 4608 channels 35.4 -> 41.7 us, 2304 23.8 -> 29.1), though four as two side by side are
+    // 0.83 to 0.90 there too. Whole calls, both rules: cfg3 at batch 28 5472 -> 4725 us, at 100 11436 -> 9719, cfg4 at 28 12556 -> 10906,
     // mid_dense at 200 913 -> 794, wide_resnet at 50 585 -> 499.
     const long long twice = fullest(128, 256);
     if (2 * twice > fullest(128, 128) || !unsplit(twice > 1 ? kPair128 : kMidTwice)) return t;
-    return twice > 1 ? kPair128 : (a.taps == 9 ? nkt > 18 : nkt >= 8 && a.n_store > 128) ? kMidTwice : t;
+    return twice > 1 ? kPair128 : (a.taps == 9 ? nkt > 18 : nkt >= 8 && a.n_store > 128 && a.mode != MODE_RAW) ? kMidTwice : t;
 }
 
 // K splits for a layer whose tiles alone cannot fill the chip (only the general epilogue

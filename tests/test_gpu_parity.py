@@ -355,6 +355,29 @@ def test_dense_layers_choose_their_tile(batch, tile):
     flow.close()
 
 
+def test_last_layers_that_leave_sums_keep_their_tile():
+    """A head's 24 filters as 216 rows, 1x1 over 1024 channels of 400 8x8 maps (256 compute units): two 128x128 tiles to a unit, like
+    the hidden layers beside it, but not one of twice the pixels. Of a network's hidden 1x1 layers two have eight k-tiles or more."""
+    import torch
+    from synth import make_blob
+    from synth.configs import DENSE, FlowConfig
+    batch = 400
+    cfg = FlowConfig("sums", 32, 32, batch, 3, 1, DENSE, 256, 3, True, seed_id=58)
+    print("sums", cfg, flush=True)
+    flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
+    x = torch.randint(0, 256, (batch, 3, 32, 32), generator=torch.Generator().manual_seed(5), dtype=torch.uint8).cuda()
+    flow.profile_begin(256)
+    z, codes = flow.forward(x)
+    torch.cuda.synchronize()
+    launches = {k["name"]: k["launches"] for k in flow.profile_end()}
+    assert launches["conv_igemm<128,256,2,4,6> 1x1"] == 2 * 2, launches   # level 2: a coupling and the head
+    for i in (0, 200, batch - 7):
+        few, few_codes = flow.forward(x[i:i + 7].contiguous())
+        assert torch.equal(z[i:i + 7], few) and torch.equal(codes[i:i + 7], few_codes)
+    assert torch.equal(flow.inverse(z), x)
+    flow.close()
+
+
 def test_long_last_layers_over_many_pixels():
     """Head codes of 96 filters, 1x1 over 2048 channels (level 4, 2x2 maps): on 64x64 tiles the reduction is not split, on 128x128 ones
     it would be, so the launch keeps the former although a compute unit gets three of them."""
