@@ -100,16 +100,19 @@ def test_strips(H, W, batch, width, keep, k2, unsigned):
                       act_unsigned=unsigned), batch, kernel="k_strip_block")
 
 
-def _issued_macs(batch, h, w, rows, nc_x, nc_t, k2):
+def _issued_macs(batch, h, w, rows, nc_x, nc_t, k2, run=1):
     """Multiply-accumulates that the matrix cores run for a residual block of nc_x (outside) and nc_t (inside) 32-channel chunks
-    in strips of `rows` rows: whole tiles of 32 pixels, as many as the smallest kernel that holds the strip takes."""
+    in strips of `rows` rows: whole tiles of 32 pixels, as many as the smallest kernel that holds the strip takes. `run` strips to a
+    workgroup, of which those behind the first take the second convolution's tiles for both."""
     one = min(h, rows + 2 if k2 == 3 else rows)
     t1, t2 = next(t for t in ((2, 1), (3, 1), (3, 2), (4, 2), (6, 4)) if one * w <= 32 * t[0] and rows * w <= 32 * t[1])
 
     def layer(n_blk, tiles, taps, nc):
         share = 4 // (n_blk // (2 if n_blk == 4 and tiles >= 4 else 1))   # waves beside each other over the pixels
         return 32 * -(-tiles // share) * share * 32 * n_blk * taps * 32 * nc
-    return batch * -(-h // rows) * (layer(nc_t, t1, 9, nc_x) + layer(nc_x, t2, k2 * k2, nc_t))
+    strips = -(-h // rows)
+    firsts, two = -(-strips // run), layer(nc_x, t2, k2 * k2, nc_t)
+    return batch * (firsts * (layer(nc_t, t1, 9, nc_x) + two) + (strips - firsts) * (layer(nc_t, t2, 9, nc_x) + two))
 
 
 def _check_rows(cfg, batch, rows, nc_x, nc_t):
@@ -151,18 +154,37 @@ def test_strip_rows_where_more_strips_pay(H, W, batch, width, keep, k2, rows):
 
 
 # Strips that a workgroup takes one below the other (256 compute units; full rounds of two workgroups to each): 2, 4 and all 8
-# strips of an image, rounds that are not quite full or too empty, strips of eight and three rows, 19 strips as ten and nine; the same
-# images give the same latents in batches that take a strip to a workgroup.
-@pytest.mark.parametrize("H,W,batch", [(64, 64, 128), (64, 64, 256), (64, 64, 512), (64, 64, 237), (64, 64, 201), (80, 64, 102), (128, 32, 128),
-                                       (114, 72, 256), (48, 80, 150)])
-@pytest.mark.parametrize("width,keep,unsigned", [(128, 1.0, False), (128, 0.7, True), (128, 0.4, False), (64, 1.0, True)])
-def test_runs_of_strips(H, W, batch, width, keep, unsigned):
+# strips of an image; just nine tenths of a round and just less; rounds that are not quite full or too empty; strips of eight and of
+# three rows, 19 of them as ten and nine; strips of two rows, where the rows that are kept lie right behind those they replace (64 wide
+# only: 128 wide, two rows of the 33 to 40 columns that take this kernel do not pay, and two of 48 are more than a workgroup moves
+# between two strips, 768 pieces of 16 bytes). The run is told from the matrix work of a block's launch; the same images give the same
+# latents in batches that take a strip to a workgroup (16 images of 24x48 maps a launch per layer).
+RUNS = [(64, 64, 115, 4, 1), (64, 64, 116, 4, 2), (64, 64, 128, 4, 2), (64, 64, 256, 4, 4), (64, 64, 512, 4, 8), (64, 64, 237, 4, 4),
+        (64, 64, 201, 4, 1), (80, 64, 102, 4, 2), (128, 32, 128, 8, 2), (114, 72, 256, 3, 10)]
+KINDS = [(128, 1.0, False, 4, 4), (128, 0.7, True, 4, 3), (128, 0.4, False, 4, 2), (64, 1.0, True, 2, 2)]
+
+
+@pytest.mark.parametrize("H,W,batch,rows,run,width,keep,unsigned,nc_x,nc_t", [r + k for r in RUNS for k in KINDS] + [
+    (48, 80, 128, 2, 3, 64, 1.0, True, 2, 2), (48, 96, 128, 2, 1, 128, 0.4, False, 4, 2)])
+def test_runs_of_strips(H, W, batch, rows, run, width, keep, unsigned, nc_x, nc_t):
     import torch
     cfg = FlowConfig("runs", H, W, batch, 1, 1, RESNET, width, 2, False, keep=keep, seed_id=54, block_k2=3, act_unsigned=unsigned)
     print("runs of strips", cfg, flush=True)
     flow = iodf.Flow(make_blob(cfg), max_batch=batch, device=0)
     x = torch.randint(0, 256, (batch, 3, H, W), generator=torch.Generator().manual_seed(9), dtype=torch.uint8).cuda()
-    z = flow.forward(x)[0]
+
+    def blocks(part):
+        flow.profile_begin(64)
+        z = flow.forward(part)[0]
+        torch.cuda.synchronize()
+        return z, {k["name"]: k for k in flow.profile_end()}.get("k_strip_block")
+    z, many = blocks(x)
+    assert many["issued_macs"] == many["launches"] * _issued_macs(batch, H // 2, W // 2, rows, nc_x, nc_t, 3, run), (rows, run)
+    _, few = blocks(x[:16])
+    assert (W == 96) == (few is None)
+    if few:
+        per = few["issued_macs"] // few["launches"]
+        assert any(per == _issued_macs(16, H // 2, W // 2, r, nc_x, nc_t, 3) for r in range(1, rows + 1))
     for i in range(0, batch, 16):
         assert torch.equal(z[i:i + 16], flow.forward(x[i:i + 16].contiguous())[0])
     assert torch.equal(flow.inverse(z), x)
