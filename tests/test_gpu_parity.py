@@ -380,7 +380,8 @@ def test_last_layers_that_leave_sums_keep_their_tile():
 
 def test_long_last_layers_over_many_pixels():
     """Head codes of 96 filters, 1x1 over 2048 channels (level 4, 2x2 maps): on 64x64 tiles the reduction is not split, on 128x128 ones
-    it would be, so the launch keeps the former although a compute unit gets three of them."""
+    it would be, so the launch keeps the former although a compute unit (of 256) gets three of them. The level's coupling, 48 filters,
+    takes the same tile."""
     import torch
     from synth import make_blob
     from synth.configs import PLAIN, FlowConfig
@@ -392,7 +393,11 @@ def test_long_last_layers_over_many_pixels():
         net["layers"][-1]["W"] = np.ascontiguousarray(net["layers"][-1]["W"][:, :, 1:2, 1:2])
     flow = iodf.Flow(pack_blob(m), max_batch=batch, device=0)
     x = torch.randint(0, 256, (batch, 3, 32, 32), generator=torch.Generator().manual_seed(4), dtype=torch.uint8).cuda()
+    flow.profile_begin(256)
     z, codes = flow.forward(x)
+    torch.cuda.synchronize()
+    small = {k["name"]: k for k in flow.profile_end()}["conv_igemm_lean<64,64,2,2,2> 1x1"]
+    assert (small["launches"], small["macs"]) == (2, batch * 2 * 2 * 2048 * (96 + 48)), small
     for part in (slice(0, 40), slice(2000, 2040), slice(batch - 40, batch)):
         z_few, codes_few = flow.forward(x[part].contiguous())
         assert torch.equal(z[part], z_few) and torch.equal(codes[part], codes_few)
