@@ -902,13 +902,16 @@ static int strip_block_rows(const iodf_ctx* ctx, const DevChain& C, int h, int w
     return cost[most] >= 1.16 * cost[best] && strips <= 4LL * ctx->n_cu && 3 * best > most ? best : most;
 }
 
-// Strips of a block that a workgroup takes one below the other: the most with which the workgroups, two to a compute unit, still
-// come in rounds that are nine tenths full. Two networks of eight blocks on 32x32 maps, a strip to a workgroup against runs, in us:
-//   full rounds         128 images, runs of 2: 128 inside 763 -> 689 (at 115), 96 638 -> 619, 64 508 -> 500, 64 wide 339 -> 309
-//                       256, 4: 1473 -> 1328, 1181 -> 1086, 913 -> 868, 611 -> 553;  512, 8: 2829 -> 2464, 2256 -> 2058, 1722 -> 1569, 1126 -> 993
-//   nine tenths         232, 4: 1392 -> 1239, 1127 -> 1044, 876 -> 836, 587 -> 527
-//   eight tenths        201, 4: 1245 -> 1204, 1010 -> 990, 793 -> 825, 523 -> 512;  400, 8: 2289 -> 2219, 1804 -> 1811, 1401 -> 1499, 922 -> 921
-//   less                96, 2: 96 inside 501 -> 542, 64 inside 411 -> 454
+// Strips of a block that a workgroup takes one below the other: the most with which the workgroups, two to a compute unit (64 wide, a
+// third fits, which the rule leaves out), still come in rounds that are nine tenths full. Two networks of eight blocks on 32x32
+// maps, 128, 96 and 64 channels inside and 64 wide; a strip to a workgroup, in the kernel that takes no more, against runs, in us:
+//   full rounds   128 images, runs of 2: 809 -> 761, 615 -> 601, 511 -> 494, 345 -> 314;  256, 4: 1556 -> 1374, 1160 -> 1069, 963 -> 862, 608 -> 565
+//                 512, 8: 3013 -> 2600, 2286 -> 2022, 1826 -> 1558, 1122 -> 1036
+//   0.91 full     232, 4: 1424 -> 1295, 1109 -> 1013, 903 -> 828, 573 -> 539
+//   0.78          201, 4: 1297 -> 1215, 1017 -> 959, 836 -> 793, 526 -> 531;  300, 2: 1788 -> 1748, 1391 -> 1362, 1109 -> 1074, 725 -> 683
+//                 400, 8: 2352 -> 2241, 1827 -> 1759, 1463 -> 1414, 917 -> 964
+//   0.75, 0.70    96, 2: 628 -> 657, 508 -> 526, 414 -> 433, 253 -> 283;  180, 2: 1111 -> 1103, 868 -> 879, 708 -> 719, 462 -> 442
+// (At 0.78 the 128 wide kinds gain 2 to 6 % and 64 wide lose up to 5; the rule takes no runs there for any.)
 static int strip_run(const iodf_ctx* ctx, const StripKernel& k, int h, int w, int rows, int batch) {
     const long long strips = (h + rows - 1) / rows, slots = 2LL * ctx->n_cu;
     if (strips * batch <= slots) return 1;

@@ -11,13 +11,15 @@
 // takes 39000 (87 us for the 2048 strips of 256 images; 94 us as two launches layer by layer). With a
 // strip or less per CU the length of that chain is what counts, hence strips down to a single row.
 //
-// Runs. Where strips come in several rounds a workgroup takes 2, 4, 8 .. of them one below the other: a later strip keeps the two
-// rows of t and of x that it shares with the one above, so that its first convolution runs over four rows instead of six, and its
-// new rows of x are on their way while the strip above is still multiplied. One block of 256 images of 32x32, profiler attached:
-// 89.8 -> 80.9 us (96 channels inside 73.2 -> 67.1). The matrix cores' part of a pair of strips falls from 23000 to 18400 clocks,
-// the pair from 39000 to 36000: what is left over is epilogues, weights (each fragment is loaded by two waves, 57 bytes a clock)
-// and LDS reads. Dropped: four blocks of 32 filters over four waves in one or both convolutions, half the weights and twice the pixel
-// reads (16 blocks of 256 images 1308 us; 1350 in the first, 1385 in the second, 1352 in both).
+// Runs. Where strips come in several rounds a workgroup takes any number of them up to all of an image, one below the other (the
+// last workgroup of an image may take fewer): a later strip keeps the two rows of t and of x that it shares with the one above, so
+// that its first convolution runs over four rows instead of six, and its new rows of x are on their way while the strip above is
+// still multiplied. One block of 256 images of 32x32, profiler attached, medians: 82.7 -> 72.8 us (96 channels inside 66.0 -> 56.7),
+// of which the priorities below are 1 to 2. The matrix cores' part of a pair of strips falls from 23000 clocks to 18400, in runs of
+// four, whose first strip still has six rows, to 19550, and is half of the time (0.49; 96 inside 0.43). A pair's weights, each fragment
+// loaded by two waves, are 1.18 MB, 20700 clocks at the 57 bytes a clock that a CU gets: no shorter than the products. The rest is
+// epilogues and LDS reads. Dropped: four blocks of 32 filters over four waves in one or both convolutions, half the weights and twice
+// the pixel reads (16 blocks of 256 images 1308 us; 1350 in the first, 1385 in the second, 1352 in both).
 #pragma once
 #include "chain_kernel.h"
 
